@@ -14,8 +14,6 @@
 
 namespace shifter {
 
-typedef uint32_t uint4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // dword-aligned
-
 // pos[k] = number of variants whose cut is smaller than variant k's (ties by index).
 __device__ __forceinline__ void load_cuts(const shifter_threshold* __restrict__ thr, uint32_t k_var,
                                           uint64_t* s_cut, uint32_t* s_pos) {
@@ -77,9 +75,7 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
 
     // w_out == nullptr: the sparse arenas are not wanted (the rebuild can mask the dense
     // arena on the way), only masks and levels are produced
-    const bool vec_ok = n == TILE && (T.offset & 3u) == 0 && (!w_out || (w_stride & 3u) == 0) &&
-                        (!want_mask || ((T.gbase & 3u) == 0 && (mask_stride & 3u) == 0));
-    if (vec_ok) {
+    if (n == TILE) {
         // wavefront w owns the w-th quarter of the tile: quad 256 w + 64 u + lane in step u,
         // so every load and store covers 1 KB and the wavefront's mask bytes are one
         // contiguous KB - written with one 16-byte store per lane after a wavefront-local
@@ -88,10 +84,9 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
         constexpr uint32_t U = TILE / BLOCK / 4;
         const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
         const uint32_t q0 = wid * (64u * U) + lane;      // quad of step 0
-        const uint4* s4 = reinterpret_cast<const uint4*>(src);
         uint4 v[U];
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(s4 + q0 + 64u * u);
+        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(src + 4u * q0 + 256u * u);
         uint32_t lvl[U][4];
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) lvl[u][0] = lvl[u][1] = lvl[u][2] = lvl[u][3] = 0;
@@ -113,7 +108,7 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
                     lvl[u][q] += keep[q];
                 }
                 if (w_out)
-                    store_u4<NT>(reinterpret_cast<uint4*>(dst) + q0 + 64u * u,
+                    store_u4<NT>(dst + 4u * q0 + 256u * u,
                                  make_uint4(o[0], o[1], o[2], o[3]));
                 if (mdst) xm[64u * u + lane] = keep[0] | (keep[1] << 8) | (keep[2] << 16) | (keep[3] << 24);
             }
@@ -122,10 +117,7 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                const uint4 mm = *reinterpret_cast<const uint4*>(xm + 4u * lane);
-                uint4_a4 out;
-                out.x = mm.x; out.y = mm.y; out.z = mm.z; out.w = mm.w;
-                *reinterpret_cast<uint4_a4*>(mdst + wid * (256u * U) + 16u * lane) = out;
+                store_mask16(mdst + wid * (256u * U) + 16u * lane, *reinterpret_cast<const uint4*>(xm + 4u * lane));
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

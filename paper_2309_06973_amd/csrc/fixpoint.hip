@@ -45,12 +45,11 @@ __global__ __launch_bounds__(BLOCK) void kernel_scan_kernel(
     auto mark = [&](uint32_t j, uint32_t bits) {
         if (bits & 0x7fffffffu) flag[div_small(c0 + j, T.khw, T.magic_khw)] = 1;
     };
-    if (n == TILE && (T.offset & 3u) == 0) {
+    if (n == TILE) {
         constexpr uint32_t U = TILE / BLOCK / 4;
-        const uint4* s4 = reinterpret_cast<const uint4*>(src);
         uint4 v[U];
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<false>(s4 + threadIdx.x + BLOCK * u);
+        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<false>(src + 4u * threadIdx.x + 4u * BLOCK * u);
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
             const uint32_t j = (threadIdx.x + BLOCK * u) * 4;

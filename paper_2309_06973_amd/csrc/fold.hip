@@ -49,13 +49,12 @@ __global__ __launch_bounds__(BLOCK) void fold_apply_kernel(
     for (uint32_t r = threadIdx.x; r < n_rows; r += BLOCK) s_scale[r] = sc[r];
     const float* src = w + T.offset + e0;
     float* dst = w_out + T.offset + e0;
-    if (n == TILE && (T.offset & 3u) == 0) {
+    if (n == TILE) {
         constexpr uint32_t U = TILE / BLOCK / 4;
-        const uint4* s4 = reinterpret_cast<const uint4*>(src);
-        uint4* d4 = reinterpret_cast<uint4*>(dst);
+        const float* src4 = src + 4u * threadIdx.x;
         uint4 v[U];
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(s4 + threadIdx.x + BLOCK * u);
+        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(src4 + 4u * BLOCK * u);
         __syncthreads();
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
@@ -66,7 +65,7 @@ __global__ __launch_bounds__(BLOCK) void fold_apply_kernel(
             };
             const uint4 r = make_uint4(mul(v[u].x, j), mul(v[u].y, j + 1), mul(v[u].z, j + 2),
                                        mul(v[u].w, j + 3));
-            store_u4<NT>(d4 + threadIdx.x + BLOCK * u, r);
+            store_u4<NT>(dst + 4u * threadIdx.x + 4u * BLOCK * u, r);
         }
     } else {
         __syncthreads();

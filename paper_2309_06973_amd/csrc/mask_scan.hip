@@ -65,13 +65,12 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_kernel(
         return out;
     };
 
-    const bool vec_ok = n == TILE && (T.offset & 3u) == 0 && (!mdst || (T.gbase & 3u) == 0);
-    if (vec_ok) {
+    if (n == TILE) {
         constexpr uint32_t U = TILE / BLOCK / 4;
-        const uint4* s4 = reinterpret_cast<const uint4*>(src);
+        const float* src4 = src + 4u * threadIdx.x;
         uint4 v[U];
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(s4 + threadIdx.x + BLOCK * u);
+        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(src4 + 4u * BLOCK * u);
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
             const uint32_t j = (threadIdx.x + BLOCK * u) * 4;
@@ -82,10 +81,8 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_kernel(
             o.z = one(j + 2, v[u].z, k2);
             o.w = one(j + 3, v[u].w, k3);
             if (DO_MASK) {
-                store_u4<NT>(reinterpret_cast<uint4*>(dst) + threadIdx.x + BLOCK * u, o);
-                if (mdst)
-                    store_u1<NT>(reinterpret_cast<uint32_t*>(mdst) + threadIdx.x + BLOCK * u,
-                                 k0 | (k1 << 8) | (k2 << 16) | (k3 << 24));
+                store_u4<NT>(dst + 4u * threadIdx.x + 4u * BLOCK * u, o);
+                if (mdst) store_mask4<NT>(mdst + 4u * threadIdx.x + 4u * BLOCK * u, k0 | (k1 << 8) | (k2 << 16) | (k3 << 24));
             }
         }
     } else {

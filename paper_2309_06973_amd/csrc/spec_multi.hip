@@ -319,13 +319,12 @@ __global__ __launch_bounds__(BLOCK) void ms_pass_kernel(
     const uint32_t sb = blockIdx.x & (SPEC_SUB - 1);
     // the tile's loads go out first: the set-up below runs while they are in flight
     const float* src = w + T.offset + e0;
-    const bool whole = n == TILE && (T.offset & 3u) == 0;
+    const bool whole = n == TILE;
     constexpr uint32_t U = TILE / BLOCK / 4;
     uint4 v[U];
     if (whole) {
-        const uint4* s4 = reinterpret_cast<const uint4*>(src);
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(s4 + threadIdx.x + BLOCK * u);
+        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(src + 4u * threadIdx.x + 4u * BLOCK * u);
     }
     const uint32_t k_var = ms->k;
     if (threadIdx.x <= MAXK) {
@@ -392,7 +391,7 @@ __global__ __launch_bounds__(BLOCK) void ms_pass_kernel(
                                  }
                              });
     } else {
-        // ragged or unaligned tile (a few per tensor): one global atomic per candidate
+        // the tensor's last, ragged tile: one global atomic per candidate
         for (uint32_t j0 = 0; j0 < n; j0 += BLOCK) {
             const uint32_t j = j0 + threadIdx.x;
             if (j < n) {
@@ -703,8 +702,6 @@ struct VariantRanks {
     int32_t r[MAXK];
 };
 
-typedef uint32_t ms_uint4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // dword-aligned
-
 template <bool NT>
 __global__ __launch_bounds__(BLOCK) void ms_fused_kernel(
     const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix, uint32_t n_t,
@@ -781,15 +778,12 @@ __global__ __launch_bounds__(BLOCK) void ms_fused_kernel(
 
     const float* src = w + T.offset + e0;
     const bool want_mask = ranked && mask != nullptr;
-    const bool vec_ok = n == TILE && (T.offset & 3u) == 0 && (!w_out || (w_stride & 3u) == 0) &&
-                        (!want_mask || ((T.gbase & 3u) == 0 && (mask_stride & 3u) == 0));
-    if (vec_ok) {
+    if (n == TILE) {
         constexpr uint32_t U = TILE / BLOCK / 4;
         const uint32_t q0 = wid * (64u * U) + lane;      // quad of step 0 (see the batched mask pass)
-        const uint4* s4 = reinterpret_cast<const uint4*>(src);
         uint4 v[U];
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(s4 + q0 + 64u * u);
+        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(src + 4u * q0 + 256u * u);
         uint32_t jj[U], cmask = 0, bmask = 0, lvl[U][4];
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
@@ -817,7 +811,7 @@ __global__ __launch_bounds__(BLOCK) void ms_fused_kernel(
                     lvl[u][q] += keep[q];
                 }
                 if (w_out)
-                    store_u4<NT>(reinterpret_cast<uint4*>(dst) + q0 + 64u * u,
+                    store_u4<NT>(dst + 4u * q0 + 256u * u,
                                  make_uint4(o[0], o[1], o[2], o[3]));
                 if (mdst) xm[64u * u + lane] = keep[0] | (keep[1] << 8) | (keep[2] << 16) | (keep[3] << 24);
             }
@@ -825,10 +819,7 @@ __global__ __launch_bounds__(BLOCK) void ms_fused_kernel(
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                const uint4 mm = *reinterpret_cast<const uint4*>(xm + 4u * lane);
-                ms_uint4_a4 out;
-                out.x = mm.x; out.y = mm.y; out.z = mm.z; out.w = mm.w;
-                *reinterpret_cast<ms_uint4_a4*>(mdst + wid * (256u * U) + 16u * lane) = out;
+                store_mask16(mdst + wid * (256u * U) + 16u * lane, *reinterpret_cast<const uint4*>(xm + 4u * lane));
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

@@ -293,13 +293,12 @@ __global__ __launch_bounds__(BLOCK) void spec_pass_kernel(
         return removed ? 0u : bits;
     };
 
-    const bool vec_ok = n == TILE && (T.offset & 3u) == 0 && (!mdst || (T.gbase & 3u) == 0);
-    if (vec_ok) {
+    if (n == TILE) {
         constexpr uint32_t U = TILE / BLOCK / 4;
-        const uint4* s4 = reinterpret_cast<const uint4*>(src);
+        const float* src4 = src + 4u * threadIdx.x;
         uint4 v[U];
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(s4 + threadIdx.x + BLOCK * u);
+        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(src4 + 4u * BLOCK * u);
         uint32_t cmask = 0;
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
@@ -313,10 +312,8 @@ __global__ __launch_bounds__(BLOCK) void spec_pass_kernel(
             o.w = one(j + 3, v[u].w, k3, q3);
             cmask |= ((q0 ? 1u : 0u) | (q1 ? 2u : 0u) | (q2 ? 4u : 0u) | (q3 ? 8u : 0u)) << (4 * u);
             if (FUSED) {
-                store_u4<NT>(reinterpret_cast<uint4*>(dst) + threadIdx.x + BLOCK * u, o);
-                if (mdst)
-                    store_u1<NT>(reinterpret_cast<uint32_t*>(mdst) + threadIdx.x + BLOCK * u,
-                                 k0 | (k1 << 8) | (k2 << 16) | (k3 << 24));
+                store_u4<NT>(dst + 4u * threadIdx.x + 4u * BLOCK * u, o);
+                if (mdst) store_mask4<NT>(mdst + 4u * threadIdx.x + 4u * BLOCK * u, k0 | (k1 << 8) | (k2 << 16) | (k3 << 24));
             }
         }
         // append the block's candidates with one global atomic: scan the per-thread
@@ -357,7 +354,7 @@ __global__ __launch_bounds__(BLOCK) void spec_pass_kernel(
             }
         }
     } else {
-        // ragged or unaligned tile (at most a few per tensor): one atomic per candidate
+        // the tensor's last, ragged tile: one atomic per candidate
         for (uint32_t j = threadIdx.x; j < n; j += BLOCK) {
             uint32_t k;
             bool q;
