@@ -184,8 +184,8 @@ int shifter_global_threshold(shifter_ctx* ctx, const shifter_model* model,
  * single tensor's weights, or an arena without gaps), with no model and no allocation.  It
  * calls no hipMalloc / hipFree and no allocating routine, puts only kernels on the
  * context's stream (no wait, no copy, no memset) and keeps its tables, histograms and
- * per-tile counts in a device array that is part of the library's code object: about
- * 4.7 MB that every GPU the library runs on holds until the process ends.
+ * lists in a device array that is part of the library's code object: about
+ * 4.8 MB that every GPU the library runs on holds until the process ends.
  *   d_w        device, n floats, 16-byte aligned, read only (may be NULL when n = 0)
  *   h_n_prune  host, K prune counts, each <= n; 1 <= K <= SHIFTER_MAX_VARIANTS
  *   d_thr      device, K records, written (same records as shifter_global_threshold's
@@ -220,7 +220,7 @@ int shifter_set_select_path(shifter_ctx* ctx, int path);
 int shifter_set_margin_sigmas(shifter_ctx* ctx, double sigmas);
 
 /* Blocks of the multi-pass select's histogram kernels, which walk the tiles with a stride
- * of the grid (default eight per compute unit; 1 .. 65536).  A launch shape only: the
+ * of the grid (default one per compute unit; 1 .. 65536).  A launch shape only: the
  * records, and everything computed from them, are the same bytes for every value. */
 int shifter_set_select_grid(shifter_ctx* ctx, uint32_t blocks);
 

@@ -15,7 +15,7 @@ using namespace shifter;
 
 namespace shifter {
 const char* const kKernelNames[K_COUNT] = {
-    "sel_init", "hist_round0", "hist_round1", "hist_round2", "select", "tie_count", "tie_final",
+    "sel_init", "hist_round0", "sel_stage", "sel_final",
     "zero_flags", "mask_scan", "scan", "propagate", "plan", "gather",
     "copy", "kernel_scan", "fix_round", "fold_scale", "fold_apply",
     "deflate_chunk", "codec_scan", "codec_pack", "inflate_chunk",
@@ -43,7 +43,7 @@ ProfileScope::~ProfileScope() {
 
 static thread_local std::string g_err;
 
-// Scratch of shifter_global_threshold_static: the tables, histograms and per-tile counts of
+// Scratch of shifter_global_threshold_static: the tables, histograms and lists of
 // the multi-pass select for one flat run of weights, in a file-scope device array instead
 // of allocated memory.  Every device the library runs on holds its own copy at its own
 // address; the name below is only a host-side handle for hipGetSymbolAddress, never a
@@ -119,7 +119,7 @@ extern "C" int shifter_create(shifter_ctx** out, int device, void* hip_stream) {
     }
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0)
-        c->hist_grid = (uint32_t)prop.multiProcessorCount * 8u;
+        c->hist_grid = (uint32_t)prop.multiProcessorCount;
     // result words of the codec calls (stream size, status): on the device, and a pinned
     // mirror the last kernel of a call writes
     void* mirror_dev = nullptr;
@@ -143,7 +143,7 @@ static void unbind(shifter_model* m) {
     if (!b.ctx) return;
     (void)hipSetDevice(b.device);
     void* ptrs[] = {b.tens, b.groups, b.vecs, b.producers, b.tile_prefix, b.tile_tensor, b.sel,
-                    b.ghist, b.tile_cnt, b.plan_t, b.plan_v, b.plan_h,
+                    b.ghist, b.plan_t, b.plan_v, b.plan_h,
                     b.out_tile_prefix, b.rect_prefix, b.rowtab_prefix, b.coltab_prefix, b.rowtab,
                     b.coltab, b.kernel_off, b.fix_prefix, b.cons_prefix, b.consumers, b.fix_alive,
                     b.fix_produced, b.fix_read, b.fix_out_flags, b.fix_removed, b.fold,
@@ -481,9 +481,7 @@ static int bind_tables(shifter_ctx* ctx, shifter_model* m) {
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.coltab),
                            sizeof(uint32_t) * MAXK * std::max<size_t>(m->coltab_prefix.back(), 1)));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.sel), sizeof(SelState)));
-    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.ghist), sizeof(uint32_t) * MAXK * HIST_BINS));
-    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.tile_cnt),
-                           sizeof(uint32_t) * (size_t)MAXK * std::max<uint32_t>(m->n_tiles, 1)));
+    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.ghist), sizeof(uint32_t) * SEL_STAGES * SEL_BINS));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.plan_t), sizeof(PlanTensor) * n_t * MAXK));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.plan_v), sizeof(PlanVec) * std::max<size_t>(n_v, 1) * MAXK));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.plan_h), sizeof(PlanHeader) * MAXK));
@@ -728,11 +726,10 @@ extern "C" int shifter_global_threshold_static(shifter_ctx* ctx, const float* d_
     uint8_t* base = ctx->static_scratch;   // the array's device address, never its name
     DevTensor* tens = reinterpret_cast<DevTensor*>(base + STATIC_OFF_TENSOR);
     uint32_t* prefix = reinterpret_cast<uint32_t*>(base + STATIC_OFF_PREFIX);
-    launch_flat_tables(ctx, tens, prefix, n);
-    const SelectTables tb{tens, prefix, 1u, (uint32_t)n_tiles,
+    const SelectTables tb{tens, prefix, 1u, (uint32_t)n_tiles, n,
                           reinterpret_cast<SelState*>(base + STATIC_OFF_SEL),
                           reinterpret_cast<uint32_t*>(base + STATIC_OFF_GHIST),
-                          reinterpret_cast<uint32_t*>(base + STATIC_OFF_TILE_CNT)};
+                          reinterpret_cast<uint2*>(base + STATIC_OFF_LISTS), STATIC_LIST_PAIRS, tens, prefix};
     launch_select_tables(ctx, tb, d_w, pc, K, d_thr);
     return after_launch(ctx, "global_threshold_static");
 }

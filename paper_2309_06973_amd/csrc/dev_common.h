@@ -119,4 +119,126 @@ __device__ __forceinline__ uint64_t block_excl_scan_u64(uint64_t v, uint64_t* sm
     return woff + x - v;
 }
 
+// Adds one to h[bin] for every lane with `want`.  Ties make lanes meet at one bin, where an LDS
+// atomic takes a turn per lane: the lanes that share the first one's bin go as one addition.
+__device__ __forceinline__ void lds_count(uint32_t* h, uint32_t bin, bool want) {
+    const uint64_t todo = __ballot(want);
+    if (todo == 0ull) return;
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)bin, (int)__ffsll((unsigned long long)todo) - 1);
+    const bool same = want && bin == first;
+    const uint64_t peers = __ballot(same);
+    if (want && !same) atomicAdd(&h[bin], 1u);
+    if (same && (peers & ((1ull << (threadIdx.x & 63u)) - 1ull)) == 0ull) atomicAdd(&h[first], (uint32_t)__popcll(peers));
+}
+
+// f(valid, pair) for the n pairs at src, DEPTH loads per thread in flight; every thread of
+// the block makes the same calls.
+template <uint32_t THREADS, uint32_t DEPTH, typename F>
+__device__ __forceinline__ void walk_pairs(const uint2* __restrict__ src, uint32_t n, F&& f) {
+    for (uint32_t i0 = 0; i0 < n; i0 += THREADS * DEPTH) {
+        uint2 c[DEPTH];
+#pragma unroll
+        for (uint32_t u = 0; u < DEPTH; ++u) {
+            const uint32_t i = i0 + u * THREADS + threadIdx.x;
+            c[u] = i < n ? src[i] : make_uint2(0, 0);
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < DEPTH; ++u)
+            if (i0 + u * THREADS < n) f(i0 + u * THREADS + threadIdx.x < n, c[u]);
+    }
+}
+
+// The r-th smallest (1-based) of n distinct pairs (bits, global index) in the order (|bits|,
+// index), by one block.  All n lie in the window of 2^width composites (|bits| << 32 | index)
+// from c_lo on, width <= 63.  4096-bin histograms of the composite narrow the window, first over
+// the key, then, where that many weights share it, over the index; a window of at most
+// RANK_DIRECT pairs is ranked by counting.  Afterwards sh.sel is the pair, sh.lt and sh.eq
+// the numbers of pairs in the list with a smaller and with the same key.  Returns false if
+// the list does not hold r pairs of the window.
+constexpr uint32_t RANK_BINS = 4096, RANK_DIRECT = 96;
+template <uint32_t THREADS>
+struct RankShared {
+    uint32_t h[RANK_BINS];
+    uint64_t comp[RANK_DIRECT];
+    uint64_t smem[THREADS / 64 + 1];
+    uint64_t sel, base;
+    uint32_t bin, cnt, nb, lt, eq;
+};
+template <uint32_t THREADS, uint32_t DEPTH>
+__device__ bool rank_in_list(const uint2* __restrict__ src, uint32_t n, uint64_t c_lo, uint32_t width,
+                             uint64_t r, RankShared<THREADS>& sh) {
+    auto composite = [](uint2 c) { return ((uint64_t)(c.x & 0x7fffffffu) << 32) | c.y; };
+    uint32_t in_window = n, below = 0;          // pairs in the window, pairs of the list below it
+    if (threadIdx.x == 0) { sh.sel = 0; sh.nb = 0; sh.lt = 0; sh.eq = 0; }
+    while (in_window > RANK_DIRECT) {
+        if (width == 0) return false;           // composites are distinct: cannot happen
+        const uint32_t shift = width >= 44u ? width - 12u : (width > 32u ? 32u : (width > 12u ? width - 12u : 0u));
+        for (uint32_t i = threadIdx.x; i < RANK_BINS; i += THREADS) sh.h[i] = 0;
+        __syncthreads();
+        walk_pairs<THREADS, DEPTH>(src, n, [&](bool valid, uint2 c) {
+            const uint64_t d = composite(c) - c_lo;               // wraps for pairs below the window
+            lds_count(sh.h, (uint32_t)(d >> shift) & (RANK_BINS - 1u), valid && (d >> width) == 0);
+        });
+        __syncthreads();
+        constexpr uint32_t PER = RANK_BINS / THREADS;
+        uint32_t c[PER];
+        uint64_t sum = 0, tot;
+#pragma unroll
+        for (uint32_t i = 0; i < PER; ++i) { c[i] = sh.h[threadIdx.x * PER + i]; sum += c[i]; }
+        uint64_t base = block_excl_scan_u64<THREADS>(sum, sh.smem, &tot);
+        if (tot < r) return false;
+#pragma unroll
+        for (uint32_t i = 0; i < PER; ++i) {
+            if (base < r && r <= base + c[i]) { sh.bin = threadIdx.x * PER + i; sh.cnt = c[i]; sh.base = base; }
+            base += c[i];
+        }
+        __syncthreads();
+        r -= sh.base;
+        below += (uint32_t)sh.base;
+        c_lo += (uint64_t)sh.bin << shift;
+        width = shift;
+        in_window = sh.cnt;
+        __syncthreads();
+    }
+    __syncthreads();
+    walk_pairs<THREADS, DEPTH>(src, n, [&](bool valid, uint2 c) {
+        const uint64_t comp = composite(c);
+        if (valid && ((comp - c_lo) >> width) == 0) {
+            const uint32_t pos = atomicAdd(&sh.nb, 1u);
+            if (pos < RANK_DIRECT) sh.comp[pos] = comp;
+        }
+    });
+    __syncthreads();
+    if (sh.nb != in_window || r == 0 || r > in_window) return false;
+    for (uint32_t i = threadIdx.x; i < in_window; i += THREADS) {
+        const uint64_t c = sh.comp[i];
+        uint32_t rank = 0;
+        for (uint32_t f = 0; f < in_window; ++f) rank += sh.comp[f] < c;
+        if (rank == r - 1) sh.sel = c;          // composites are distinct: exactly one hit
+    }
+    __syncthreads();
+    const uint32_t key = (uint32_t)(sh.sel >> 32);
+    uint32_t lt = 0, eq = 0;
+    if (width >= 32u) {                         // the window holds whole keys
+        for (uint32_t i = threadIdx.x; i < in_window; i += THREADS) {
+            const uint32_t k = (uint32_t)(sh.comp[i] >> 32);
+            lt += k < key;
+            eq += k == key;
+        }
+        if (threadIdx.x == 0) lt += below;
+    } else {                                    // it is a part of one key's indices
+        walk_pairs<THREADS, DEPTH>(src, n, [&](bool valid, uint2 c) {
+            const uint32_t k = c.x & 0x7fffffffu;
+            lt += valid && k < key;
+            eq += valid && k == key;
+        });
+        for (uint32_t d = 32; d > 0; d >>= 1) { lt += __shfl_down(lt, d, 64); eq += __shfl_down(eq, d, 64); }
+        if ((threadIdx.x & 63u) != 0) lt = eq = 0;
+    }
+    if (lt) atomicAdd(&sh.lt, lt);
+    if (eq) atomicAdd(&sh.eq, eq);
+    __syncthreads();
+    return true;
+}
+
 }  // namespace shifter

@@ -13,9 +13,7 @@ namespace shifter {
 
 constexpr uint32_t TILE = 4096;      // elements per tile of the streaming kernels
 constexpr uint32_t BLOCK = 256;      // threads per block (4 wavefronts of 64)
-constexpr uint32_t HIST_BINS = 2048; // stride of one histogram slot
 constexpr uint32_t MAXK = SHIFTER_MAX_VARIANTS;
-constexpr uint32_t SLOTS_PER_PASS = 8;
 constexpr uint32_t GATHER_CHUNK = 1024;  // columns of a gather work unit (16 per lane)
 constexpr uint32_t GATHER_ROWS = 16;
 constexpr uint32_t RECT_ELEMS = 8192;    // floats of a source rectangle staged in LDS by the portfolio rebuild
@@ -54,22 +52,29 @@ struct DevVec {
     int32_t group;
 };
 
-// State of the multi-rank radix select, one entry per requested prune count.
-struct SelRank {
-    uint64_t rank;     // remaining 1-based rank inside the current prefix; 0: P == 0
-    uint64_t n_less;   // weights known to be smaller than every key with this prefix
-    uint64_t n_equal;  // weights sharing the prefix
-    uint32_t prefix;   // decided high bits of the key, right aligned
-    uint32_t slot;     // histogram slot of this prefix in the next round
-};
-
-struct SelState {
-    SelRank r[MAXK];
-    uint32_t slot_prefix[MAXK];
-    uint32_t n_slots;
-    uint32_t k;
-    uint32_t nan_seen;
+// State of the multi-pass select (select.hip), ranks sorted by prune count.
+constexpr uint32_t SEL_BINS = 16384;      // counters of one histogram: the top bins, or all windows' of a stage
+constexpr uint32_t SEL_STAGES = 8;        // at most this many stages for any N < 2^32 and K <= MAXK
+enum : uint32_t { SEL_IDLE = 0, SEL_SPLIT = 1, SEL_LISTED = 2 };
+struct SelWindow {
+    uint64_t c_lo;             // first composite of the window, which spans 2^width
+    uint64_t r;                // 1-based rank of the pair inside it
+    uint64_t less;             // weights below it
+    uint64_t key_less, key_eq; // once it lies within one key: weights below that key, weights with it
+    uint64_t cnt;              // weights inside it
+    uint32_t width;
+    uint32_t leader;           // first rank with the same window: owner of its histogram and list
+    uint32_t mode;             // of this stage: split by a histogram, listed, or nothing to do
     uint32_t pad;
+};
+struct SelState {
+    SelWindow win[SEL_STAGES + 1][MAXK];   // by stage; the first is unused
+    SelWindow fin[MAXK];                   // the windows that were listed
+    uint64_t p[MAXK];
+    uint32_t perm[MAXK];                   // caller's position of a rank
+    uint32_t list_cnt[MAXK];
+    uint32_t done[SEL_STAGES + 1];         // every rank is listed after this stage
+    uint32_t nan_seen;
 };
 
 // State of the single-pass (sample, predict, one pass, finish) selection.
@@ -159,7 +164,7 @@ struct PlanHeader {
 };
 
 enum KernelId {
-    K_SEL_INIT = 0, K_HIST0, K_HIST1, K_HIST2, K_SELECT, K_TIE_COUNT, K_TIE_FINAL,
+    K_SEL_INIT = 0, K_HIST0, K_SEL_STAGE, K_SEL_FINAL,
     K_ZERO_FLAGS, K_MASK_SCAN, K_SCAN, K_PROPAGATE, K_PLAN, K_GATHER,
     K_COPY, K_KERNEL_SCAN, K_FIX_ROUND, K_FOLD_SCALE, K_FOLD_APPLY,
     K_DEFLATE_CHUNK, K_CODEC_SCAN, K_CODEC_PACK, K_INFLATE_CHUNK,
@@ -225,8 +230,7 @@ struct shifter_model {
         uint32_t* tile_prefix = nullptr;
         uint16_t* tile_tensor = nullptr;      // n_tiles: tensor of every tile
         shifter::SelState* sel = nullptr;
-        uint32_t* ghist = nullptr;       // MAXK * HIST_BINS
-        uint32_t* tile_cnt = nullptr;    // MAXK * n_tiles
+        uint32_t* ghist = nullptr;       // SEL_STAGES * SEL_BINS
         shifter::PlanTensor* plan_t = nullptr;
         shifter::PlanVec* plan_v = nullptr;
         shifter::PlanHeader* plan_h = nullptr;
@@ -295,7 +299,7 @@ struct shifter_ctx {
     struct Rec { int id; hipEvent_t a, b; };
     std::vector<Rec> recs;
     std::vector<hipEvent_t> pool;
-    uint32_t hist_grid = 2048;
+    uint32_t hist_grid = 256;
     int select_path = 0;   // 0: single-pass where it applies; 1: multi-pass radix only
     double margin_sigmas = 4.0;   // half-width of the predicted interval, in binomial sigmas
     uint64_t fused_min_bytes = 192ull << 20;   // portfolio_begin: arenas above this take the fused pass
@@ -352,9 +356,13 @@ struct SelectTables {
     const DevTensor* tens;
     const uint32_t* tile_prefix;
     uint32_t n_t, n_tiles;
+    uint64_t n_weights;   // prunable weights
     SelState* sel;
-    uint32_t* ghist;      // MAXK * HIST_BINS
-    uint32_t* tile_cnt;   // k * n_tiles
+    uint32_t* ghist;      // SEL_STAGES * SEL_BINS
+    uint2* lists;         // list_pairs pairs, shared out among the k ranks
+    uint64_t list_pairs;
+    DevTensor* flat_tens;     // a flat run: where its one-tensor tables (tens, tile_prefix) are to be written
+    uint32_t* flat_prefix;
 };
 void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float* d_w,
                           const PruneCounts& pc, uint32_t k, shifter_threshold* d_thr);
@@ -366,11 +374,10 @@ constexpr size_t STATIC_OFF_TENSOR = 0;
 constexpr size_t STATIC_OFF_PREFIX = 256;
 constexpr size_t STATIC_OFF_SEL = 512;
 constexpr size_t STATIC_OFF_GHIST = STATIC_OFF_SEL + ((sizeof(SelState) + 255) / 256) * 256;
-constexpr size_t STATIC_OFF_TILE_CNT = STATIC_OFF_GHIST + sizeof(uint32_t) * MAXK * HIST_BINS;
-constexpr size_t STATIC_SCRATCH_BYTES = STATIC_OFF_TILE_CNT + sizeof(uint32_t) * STATIC_MAX_TILE_COUNTS;
+constexpr size_t STATIC_OFF_LISTS = STATIC_OFF_GHIST + sizeof(uint32_t) * SEL_STAGES * SEL_BINS;
+constexpr uint64_t STATIC_LIST_PAIRS = 1ull << 19;
+constexpr size_t STATIC_SCRATCH_BYTES = STATIC_OFF_LISTS + sizeof(uint2) * STATIC_LIST_PAIRS;
 static_assert(sizeof(DevTensor) <= 256, "the one-tensor table fits its slot");
-// Writes the one-tensor table of a flat run of n weights (one prunable tensor at offset 0).
-void launch_flat_tables(shifter_ctx* ctx, DevTensor* tens, uint32_t* tile_prefix, uint64_t n);
 // host_mirror: device address of the pinned SpecState the last kernel leaves the outcome in.
 void launch_spec_select(shifter_ctx* ctx, const shifter_model* m, const float* d_w, uint64_t p,
                         shifter_threshold* d_thr, float* d_w_out, uint8_t* d_mask,
