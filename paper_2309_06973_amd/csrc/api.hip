@@ -1601,6 +1601,8 @@ extern "C" int shifter_deflate(shifter_ctx* ctx, const void* d_in, uint64_t n_by
     if (!h_stream_bytes) return SHIFTER_OK;
     uint64_t total, status;
     if ((rc = codec_result(ctx, &total, &status))) return rc;
+    if (status & CODEC_CHAIN)
+        return fail(ctx, SHIFTER_ERR_INTERNAL, "deflate: a segment's offset never arrived");
     *h_stream_bytes = total;
     if (status)
         return fail(ctx, SHIFTER_ERR_CAPACITY,

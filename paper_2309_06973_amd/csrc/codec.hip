@@ -19,8 +19,8 @@
 //     quarters of 128 bytes, the token bits of the quarter before (11 bits) and how far past
 //     the quarter's start its first literal lies (9 bits); a run's matches go with the
 //     literal that starts the run, so a lane never needs another lane's bytes.
-// Any inflater reads the stream; the encoder and the decoder here work with one block of
-// 256 threads per chunk, four lanes per sub-chunk.
+// Any inflater reads the stream; the encoder works with one block of 512 threads per chunk and
+// 32 lanes per sub-chunk, the decoder with 256 and four.
 #include <string>
 
 #include "dev_common.h"
@@ -34,24 +34,13 @@ constexpr uint32_t CODEC_SUBW = CODEC_SUB / 4;                // dwords per sub-
 constexpr uint32_t CODEC_SLOT = CODEC_CHUNK + 8;              // bytes of a chunk's slot in the workspace
 constexpr uint32_t CODEC_MARGIN = 48;                         // bits a stored sub-chunk must save
 constexpr uint32_t CODEC_STORED = 0xFFFFu;                    // side information of a stored sub-chunk
-constexpr uint32_t CODEC_MASKW = CODEC_SUB / 32 + 1;          // run-start mask words per lane, padded
 static_assert(CODEC_NSUB == 64, "one lane per sub-chunk");
-
-enum : uint32_t { CODEC_BAD_STREAM = 1u, CODEC_CAPACITY = 2u };
 
 // Sub-chunk l, dword j of the chunk staged in LDS: every row is rotated by l 16-byte
 // vectors, so that the lanes of a wave, each walking its own sub-chunk at the same pace,
 // spread over the banks while a vector stays whole.
 __device__ __forceinline__ uint32_t sub_word(uint32_t l, uint32_t j) {
     return l * CODEC_SUBW + ((j + 4u * l) & (CODEC_SUBW - 1));
-}
-
-// Fixed literal code of RFC 1951 section 3.2.6, bit-reversed so that it can be appended
-// from the least significant bit; returns the number of bits.
-__device__ __forceinline__ uint32_t literal_code(uint32_t v, uint32_t* code) {
-    const bool nine = v >= 144u;                  // 0x30 + v in 8 bits, or 0x190 + (v - 144) in 9
-    *code = __brev(nine ? 0x100u + v : 0x30u + v) >> (nine ? 23u : 24u);
-    return nine ? 9u : 8u;
 }
 
 // A match of `len` (3..258) at distance 1: length code, extra bits, 5-bit distance code 0.
@@ -73,11 +62,6 @@ __device__ __forceinline__ uint32_t match_code(uint32_t len, uint32_t* code) {
     *code = c | (extra << n);
     return n + e + 5u;
 }
-
-struct BitCounter {
-    uint32_t bits = 0;
-    __device__ __forceinline__ void put(uint32_t, uint32_t n) { bits += n; }
-};
 
 // Appends bits to the chunk's bit buffer in LDS, which starts zeroed: every dword is OR-ed
 // in, so neighbouring lanes may share the dwords at the ends of their ranges.  At most 32
@@ -103,32 +87,16 @@ struct BitWriter {
     }
 };
 
-// Bits of the distance-1 matches that cover the `rest` >= 3 bytes after a run's first byte.
-template <class Sink>
-__device__ __forceinline__ void put_matches(uint32_t rest, Sink& sink) {
-    uint32_t code, nb;
-    while (rest > 260u) {
-        nb = match_code(258u, &code);
-        sink.put(code, nb);
-        rest -= 258u;
-    }
-    if (rest <= 258u) {
-        nb = match_code(rest, &code);
-        sink.put(code, nb);
-    } else {
-        nb = match_code(rest - 3u, &code);
-        sink.put(code, nb);
-        nb = match_code(3u, &code);
-        sink.put(code, nb);
-    }
-}
-
-// First set bit of the mask row `mk` at a position after p (the row ends with a set bit).
-__device__ __forceinline__ uint32_t next_bit(const uint32_t* mk, uint32_t p) {
-    uint32_t a = (p + 1u) >> 5;
-    uint32_t mw = mk[a] & (~0u << ((p + 1u) & 31u));
-    while (mw == 0u && a + 1u < CODEC_MASKW) mw = mk[++a];
-    return mw ? a * 32u + (uint32_t)__ffs((int)mw) - 1u : CODEC_SUB;
+// The matches that cover the rest (15..511) bytes behind a run's first one: one of 258 where
+// more than 260 remain, then one, or the pieces (rest - 3, 3) of 259 and 260.  At most 31 bits.
+__device__ __forceinline__ uint32_t far_matches(uint32_t rest, uint32_t* code) {
+    uint32_t c, c258, c3, n3;
+    const bool two = rest > 260u, split = rest > 258u && !two;
+    const uint32_t n = match_code(two ? rest - 258u : (split ? rest - 3u : rest), &c);
+    const uint32_t n258 = match_code(258u, &c258);                      // constants
+    n3 = match_code(3u, &c3);
+    *code = two ? c258 | (c << n258) : (split ? c | (c3 << n) : c);
+    return n + (two ? n258 : (split ? n3 : 0u));
 }
 
 __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t lane, uint32_t* total) {
@@ -141,378 +109,456 @@ __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t lane, ui
     return x - v;
 }
 
-// Where every sub-chunk's part of a segment starts, from the side information (s_side:
-// token bits, or CODEC_STORED) and the chunk's size.  start: bit position of the first bit
-// this lane's sub-chunk is responsible for (a coded one: the block header if it opens a
-// block, then its tokens; a stored one: the end-of-block of the block it closes, then its
-// own header); in_block: whether a Huffman block is open at that point.  tail_*: the same
-// for what follows the last sub-chunk.  Returns the segment's size in bytes.
-__device__ __forceinline__ uint32_t place_subs(const uint32_t* s_side, uint32_t m, uint32_t lane,
-                                               bool any_stored, uint32_t* start, bool* in_block,
-                                               uint32_t* tail_start, bool* tail_in_block) {
-    uint32_t pos = 0;
-    bool open = false;
-    if (!any_stored) {
-        // one Huffman block: positions are prefix sums of the token bits
-        uint32_t total;
-        const uint32_t ex = wave_excl_scan(s_side[lane], lane, &total);
-        *start = lane == 0 ? 0u : 3u + ex;
-        *in_block = lane != 0;
-        pos = 3u + total;
-        open = true;
-    } else {
-        *start = 0;
-        *in_block = false;
-        for (uint32_t s = 0; s < CODEC_NSUB; ++s) {
-            const uint32_t n_s = min(CODEC_SUB, m - min(m, s * CODEC_SUB));
-            if (s == lane) { *start = pos; *in_block = open; }
-            if (n_s == 0u) continue;
-            const uint32_t v = s_side[s];
-            if (v == CODEC_STORED) {
-                pos += (open ? 7u : 0u) + 3u;
-                pos = ((pos + 7u) & ~7u) + 32u + 8u * n_s;
-                open = false;
-            } else {
-                pos += (open ? 0u : 3u) + v;
-                open = true;
-            }
-        }
-    }
+// Where every sub-chunk's part of a segment starts, one lane per sub-chunk: v its side
+// information (token bits, or CODEC_STORED; 0 where nothing is left of the chunk), n its
+// bytes.  start: bit position of the first bit this lane's sub-chunk is responsible for (a
+// coded one: the block header if it opens a block, then its tokens; a stored one: the
+// end-of-block of the block it closes, then its own header); in_block: whether a Huffman
+// block is open at that point.  tail_*: the same for what follows the last sub-chunk.
+// Returns the segment's size in bytes.
+// A stored sub-chunk ends on a byte, so a run of coded ones always starts on one: two prefix
+// sums, of the token bits and of the bytes up to the end of each stored sub-chunk, place
+// all of them at once (a walk over the 64 sub-chunks, which any stored one needed before,
+// took about 4 us of a chunk's life).
+__device__ __forceinline__ uint32_t place_subs(uint32_t v, uint32_t n, uint32_t lane, uint32_t* start,
+                                               bool* in_block, uint32_t* tail_start, bool* tail_in_block) {
+    const bool stored = n != 0u && v == CODEC_STORED;
+    uint32_t bits_total;
+    const uint32_t bits = wave_excl_scan(n != 0u && !stored ? v : 0u, lane, &bits_total);   // coded bits before this lane
+    const uint64_t st = __ballot(stored);
+    const uint64_t before = st & ((1ull << lane) - 1ull);
+    // coded bits since the last stored sub-chunk (or the start)
+    const uint32_t at_stored = __shfl(bits, before ? 63 - __clzll((long long)before) : 0, 64);
+    const uint32_t run = bits - (before ? at_stored : 0u);
+    const uint32_t head = run ? 3u + run : 0u;                        // with the block's header
+    const uint32_t bytes = stored ? ((head + (run ? 7u : 0u) + 3u + 7u) >> 3) + 4u + n : 0u;
+    uint32_t bytes_total;
+    const uint32_t byte0 = wave_excl_scan(bytes, lane, &bytes_total);
+    *start = 8u * byte0 + head;
+    *in_block = run != 0u;
+    const uint32_t last_bits = __shfl(bits, st ? 63 - __clzll((long long)st) : 0, 64);
+    const uint32_t tail_run = bits_total - (st ? last_bits : 0u);
+    const uint32_t pos = 8u * bytes_total + (tail_run ? 3u + tail_run : 0u);
     *tail_start = pos;
-    *tail_in_block = open;
-    pos += (open ? 7u : 0u) + 3u;
-    return ((pos + 7u) >> 3) + 4u;
+    *tail_in_block = tail_run != 0u;
+    return ((pos + (tail_run ? 7u : 0u) + 3u + 7u) >> 3) + 4u;
 }
 
 constexpr uint32_t CODEC_Q = 4;                               // lanes per sub-chunk
 constexpr uint32_t CODEC_QB = CODEC_SUB / CODEC_Q;            // 128 bytes of a sub-chunk per lane
-constexpr uint32_t CODEC_QW = CODEC_QB / 32;                  // 4 mask words per lane
 constexpr uint32_t CODEC_THREADS = CODEC_NSUB * CODEC_Q;      // 256: one block per chunk
 constexpr uint32_t CODEC_LOOP_GRID = 1536;                    // blocks of an instance that walks a list
 
-// Run-start bits (bit i: byte 32 a + i of sub-chunk l differs from the byte before it;
-// byte 0 always starts a run) and the bits of the bytes >= 144 (their literal code has 9
-// bits) of mask word a.
-__device__ __forceinline__ void mask_word(const uint32_t* s_in, uint32_t l, uint32_t a, uint32_t* s_out,
-                                          uint32_t* g_out) {
-    uint32_t carry = a ? s_in[sub_word(l, a * 8u - 1u)] >> 24 : 0u;
-    uint32_t sw = 0, gw = 0;
-    uint4 q4[2];
-    q4[0] = *reinterpret_cast<const uint4*>(&s_in[sub_word(l, a * 8u)]);
-    q4[1] = *reinterpret_cast<const uint4*>(&s_in[sub_word(l, a * 8u + 4u)]);
-    const uint32_t ws[8] = {q4[0].x, q4[0].y, q4[0].z, q4[0].w, q4[1].x, q4[1].y, q4[1].z, q4[1].w};
+// --- the encoder -------------------------------------------------------------------------
+// One block of 512 threads per chunk.  A lane holds 16 consecutive bytes of a sub-chunk (32
+// lanes a sub-chunk, so a wavefront takes 1 KiB at a time and four of those in turn); the
+// chunk stays in registers and only the segment being built is in LDS, so that four blocks
+// fit a compute unit whatever their segments' sizes.  First every piece finds its literals,
+// the runs they start and its token bits, and prefix sums over the lanes place the pieces in
+// their sub-chunk; then, with the sub-chunks placed in the segment, every lane appends its
+// own piece's tokens.
+// Bound by vector instructions (about 600 per KiB and wavefront), and in small inputs by the
+// life of one block.  Ten rebuilt variants of a 14.7 M weight network (3/10 to all of the
+// weights not zero), one after the other: 2780 us with four lanes walking a sub-chunk's tokens
+// one by one, a second instance for the chunks with long segments and a pack pass; 845 with 256
+// threads of this form, 690 with 512, 625 without loops for the matches.  1.3 GB of a sparse
+// model: 4840 us before, 1200 now (5 % of uniformly spread weights kept: 1473, 1101).
+
+// Bits 0-15 of a piece: which bytes differ from the byte before them, and which are >= 144
+// (9-bit literals).  prev: the byte before the piece.
+__device__ __forceinline__ uint32_t nibbles(const uint32_t (&t)[4]) {   // bit 7 of the bytes of t -> 16 bits
+    const uint32_t a = __builtin_amdgcn_udot4(t[1], 0x80402010u, __builtin_amdgcn_udot4(t[0], 0x08040201u, 0u, false), false);
+    const uint32_t b = __builtin_amdgcn_udot4(t[3], 0x80402010u, __builtin_amdgcn_udot4(t[2], 0x08040201u, 0u, false), false);
+    return (a >> 7) | (b >> 7 << 8);
+}
+__device__ __forceinline__ uint32_t not_low144(uint32_t w) {            // bit 7 of every byte >= 0x90
+    return w & ((w & 0x70707070u) + 0x70707070u) & 0x80808080u;
+}
+__device__ __forceinline__ uint32_t changes16(const uint4& v, uint32_t prev) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    uint32_t ne[4];
 #pragma unroll
-    for (uint32_t b = 0; b < 8u; ++b) {
-        const uint32_t w = ws[b];
-        const uint32_t x = w ^ ((w << 8) | carry);
-        // bit 7 of every byte: the byte of x is not 0; the byte of w is >= 0x90
-        uint32_t ne = ((((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u) >> 7;
-        uint32_t ge = (w & (((w & 0x70707070u) + 0x70707070u)) & 0x80808080u) >> 7;
-        ne = (ne | (ne >> 7) | (ne >> 14) | (ne >> 21)) & 0xfu;
-        ge = (ge | (ge >> 7) | (ge >> 14) | (ge >> 21)) & 0xfu;
-        carry = w >> 24;
-        sw |= ne << (4u * b);
-        gw |= ge << (4u * b);
+    for (uint32_t d = 0; d < 4u; ++d) {
+        const uint32_t x = w[d] ^ ((w[d] << 8) | (d ? w[d - 1u] >> 24 : prev));
+        ne[d] = (((x & 0x7f7f7f7fu) + 0x7f7f7f7fu) | x) & 0x80808080u;
     }
-    if (a == 0) sw |= 1u;
-    *s_out = sw;
-    *g_out = gw;
+    return nibbles(ne);
+}
+__device__ __forceinline__ uint32_t nines16(const uint4& v) {
+    const uint32_t ge[4] = {not_low144(v.x), not_low144(v.y), not_low144(v.z), not_low144(v.w)};
+    return nibbles(ge);
 }
 
-// Tokens of sub-chunk l whose literal lies in [p, p_end): every literal there, and the
-// matches of the run it starts (which may reach past p_end).  mk: one bit per byte sent as
-// a literal, and a set bit at the sub-chunk's length.  p must be a literal's position.
-template <class Sink>
-__device__ __forceinline__ void encode_range(const uint32_t* s_in, const uint32_t* mk, uint32_t l,
-                                             uint32_t p, uint32_t p_end, Sink& sink) {
-    while (p < p_end) {
-        const uint32_t q = next_bit(mk, p);
-        const uint32_t b = (s_in[sub_word(l, p >> 2)] >> ((p & 3u) * 8u)) & 0xffu;
-        uint32_t code;
-        const uint32_t nb = literal_code(b, &code);
-        sink.put(code, nb);
-        if (q - p >= 4u) put_matches(q - p - 1u, sink);
-        p = q;
-    }
-}
-
-// One block of 256 threads per chunk, four lanes per sub-chunk (one per 128 bytes): stages
-// the chunk in LDS, marks the bytes sent as literals, counts the token bits of every
-// quarter (a run's matches count with the literal that starts it), chooses coded or stored
-// per sub-chunk and for the chunk, builds the segment in LDS - every lane appends the tokens
-// of its quarter at the bit position the counts give it - and writes it to the chunk's slot
-// of the workspace together with its size.  The same counts are the decoder's marks.
-// Two instances: OUT_DW = CODEC_OUT_SMALL (12 KiB of LDS for the segment) takes every chunk
-// first and passes those with a longer segment on to a list, which the instance with room
-// for any segment walks (LISTED: a fixed grid, block b takes entries b, b + grid, ...).
-constexpr uint32_t CODEC_OUT_SMALL = 3072;
-constexpr uint32_t CODEC_OUT_FULL = CODEC_CHUNK / 4 + 8;
-
-struct DeflateShared {
-    uint32_t* in;       // CODEC_CHUNK / 4
-    uint32_t* out;      // OUT_DW
-    uint32_t* mask;     // CODEC_NSUB * CODEC_MASKW
-    uint32_t* side;     // CODEC_NSUB
-    uint32_t* start;    // CODEC_NSUB: bit 31 = a block is open there
-    uint32_t* misc;     // segment bytes, tail start, tail in block
+// What a lane keeps of a piece between the two passes.
+struct Piece {
+    uint4 v;          // the bytes
+    uint32_t lit;     // bits 0-15 the bytes sent as literals, 16-31 those among all that take 9 bits
+    uint32_t place;   // bits 0-15 token bits of the sub-chunk before this piece; 16-25 the first
+                      //   literal behind the piece (offset in the sub-chunk; its length if none)
 };
 
-template <uint32_t OUT_DW>
-__device__ __forceinline__ void deflate_chunk(
-    const DeflateShared& sh, uint32_t c, const uint8_t* __restrict__ in, uint64_t n_bytes, uint32_t n_chunks,
-    uint8_t* __restrict__ slots, uint32_t* __restrict__ seg_size, uint16_t* __restrict__ side,
-    uint64_t* __restrict__ marks, uint32_t* __restrict__ long_list, uint32_t* __restrict__ long_count) {
-    uint32_t* s_in = sh.in;
-    const uint32_t tid = threadIdx.x, l = tid >> 2, q = tid & 3u;
+// The runs of 4 or more that start in a piece.  lit: its literals; end: the sub-chunk's end, where
+// that lies inside the piece; next: the first literal behind it, relative to its start.
+struct Runs {
+    uint32_t ends;    // where a run in the piece can end: literals, the end, and `next` if below 32
+    uint32_t near;    // literals that start a run whose other 3 to 14 bytes one match covers
+    uint32_t far;     // the other bytes of a longer run, which only the last literal can start; or 0
+};
+__device__ __forceinline__ Runs find_runs(uint32_t lit, uint32_t end, uint32_t next) {
+    Runs r;
+    r.ends = lit | end | (next < 32u ? 1u << next : 0u);
+    r.near = lit & ~(r.ends >> 1);                  // the next byte is neither a literal nor the end
+    const uint32_t p = 31u - (uint32_t)__clz((int)(lit | 1u));
+    const uint32_t rest = next - p - 1u;            // (the end inside the piece is `next` too)
+    r.far = ((r.near >> p) & 1u) != 0u && rest >= 15u ? rest : 0u;
+    if (r.far) r.near &= ~(1u << p);
+    return r;
+}
+
+// Appends the tokens of a piece at bit position `bit` of the (zeroed) buffer.
+__device__ __forceinline__ void emit_tokens(uint32_t* out, uint32_t bit, const uint4& v, uint32_t lit, uint32_t nine,
+                                            const Runs& r) {
+    const uint32_t dw[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (uint32_t d = 0; d < 4u; ++d) {
+        if (__ballot((lit >> (4u * d)) & 15u) == 0ull) continue;
+        // the 8-bit codes of four bytes at once: 0x30 + v below 144, v (behind a 1) from there,
+        // reversed; byte j of dw[d] ends up in byte 3 - j of rev
+        const uint32_t low = ~not_low144(dw[d]) & 0x80808080u;
+        const uint32_t rev = __brev(dw[d] + ((low >> 2) | (low >> 3)));
+#pragma unroll
+        for (uint32_t h = 0; h < 2u; ++h) {
+            // two bytes and at most one match behind them: up to 31 bits
+            const uint32_t j = 4u * d + 2u * h;
+            const uint32_t g0 = (nine >> j) & 1u, g1 = (nine >> (j + 1u)) & 1u;
+            const uint32_t l0 = 0u - ((lit >> j) & 1u), l1 = 0u - ((lit >> (j + 1u)) & 1u);
+            const uint32_t c0 = ((((rev >> (24u - 16u * h)) & 0xffu) << g0) | g0) & l0;
+            const uint32_t c1 = ((((rev >> (16u - 16u * h)) & 0xffu) << g1) | g1) & l1;
+            const uint32_t n0 = (8u + g0) & l0, n01 = n0 + ((8u + g1) & l1);
+            const uint32_t run = (r.near >> j) & 3u;           // neither, the first or the second byte starts one
+            uint32_t mc = 0, mn = 0;
+            if (__ballot(run != 0u) != 0ull) {
+                // x = rest - 3 of 0..11: symbols 257..264, then two lengths per symbol and an extra bit
+                // (of no matter where no run starts)
+                const uint32_t x = (uint32_t)__builtin_ctz((r.ends >> (j + 1u) >> (run >> 1)) | 0x80000000u) - 3u;
+                const uint32_t big = (x >> 3) & 1u, on = run ? ~0u : 0u;
+                mc = ((__brev((x >> big) + 1u + 4u * big) >> 25) | ((x & big) << 7)) & on;
+                mn = (12u + big) & on;
+            }
+            const uint64_t code = (uint64_t)(c0 | (c1 << n0) | (mc << n01)) << (bit & 31u);
+            atomicOr(&out[bit >> 5], (uint32_t)code);
+            atomicOr(&out[(bit >> 5) + 1u], (uint32_t)(code >> 32));
+            bit += n01 + mn;
+        }
+    }
+    if (r.far) {
+        uint32_t c;
+        far_matches(r.far, &c);
+        const uint64_t code = (uint64_t)c << (bit & 31u);
+        atomicOr(&out[bit >> 5], (uint32_t)code);
+        atomicOr(&out[(bit >> 5) + 1u], (uint32_t)(code >> 32));
+    }
+}
+
+// Chained offsets of the segments.  status[c]: 0 nothing yet, bits 62-63 = 1 the size of segment c
+// alone, 2 the size of all segments up to and including c, 3 the chain broke.
+constexpr uint64_t CHAIN_VALUE = (1ull << 62) - 1ull;
+constexpr uint32_t CHAIN_POLLS = 1u << 22;     // seconds: far beyond any wait that ends
+__device__ __forceinline__ void chain_store(uint64_t* p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Sum of the sizes before chunk c, by one wavefront: 64 predecessors at a time, back to the
+// nearest one whose sum is known.  Chunks are numbered by a ticket that a block draws when it
+// starts, and a block stores its size before it waits for anything: every predecessor is
+// running or done and its size arrives without it waiting for this block.
+__device__ __forceinline__ uint64_t chain_before(const uint64_t* status, uint32_t c, uint32_t lane, bool* broken) {
+    uint64_t sum = 0;
+    uint32_t polls = 0;
+    for (int64_t last = (int64_t)c - 1; last >= 0;) {
+        const int64_t i = last - (int64_t)lane;
+        const uint64_t x = i >= 0 ? __hip_atomic_load(status + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 2ull << 62;
+        const uint32_t kind = (uint32_t)(x >> 62);
+        if (__ballot(kind == 3u) != 0ull || ++polls > CHAIN_POLLS) { *broken = true; return 0; }
+        const uint64_t known = __ballot(kind == 2u), here = __ballot(kind != 0u);
+        const uint32_t upto = known ? (uint32_t)__ffsll((unsigned long long)known) - 1u : 63u;   // last lane needed
+        const uint64_t need = ~0ull >> (63u - upto);
+        if ((here & need) != need) { __builtin_amdgcn_s_sleep(4); continue; }
+        uint64_t part = lane <= upto ? x & CHAIN_VALUE : 0ull;
+        for (uint32_t d = 32; d > 0; d >>= 1) part += __shfl_xor((unsigned long long)part, d, 64);
+        sum += part;
+        if (known) break;
+        last -= 64;
+    }
+    return sum;
+}
+
+// A whole sub-chunk of zeros: the literal 0 (00110000) and the matches 258 (symbol 285: 11000101)
+// and 253 (symbol 284: 11000100, extra bits 253 - 227 = 26), each with the distance code 00000.
+// All codes start from their first bit in bit 0.  Its quarters' marks: all token bits before the
+// second one, and no further literal before the end.
+constexpr uint32_t ZERO_SUB_BITS = 8u + 13u + 18u;
+constexpr uint32_t ZERO_SUB_LOW = 0x0Cu | (0xA3u << 8);                    // the literal and the first match, 21 bits
+constexpr uint32_t ZERO_SUB_HIGH = 0x23u | (26u << 8);
+constexpr uint64_t ZERO_SUB_MARK = (uint64_t)(ZERO_SUB_BITS | (384u << 11)) | (uint64_t)(256u << 11) << 20 |
+                                   (uint64_t)(128u << 11) << 40;
+static_assert(CODEC_SUB == 512u, "258 + 253 + 1");
+
+// DIRECT: the segments go straight to their place in the stream, which cannot overflow (the
+// host checked that it holds the largest possible one).  Otherwise every segment goes to its
+// slot of the workspace, and the two kernels behind this one add up the sizes and, if the
+// stream is large enough, move the segments.
+constexpr uint32_t CODEC_OUT_DW = CODEC_CHUNK / 4 + 8;
+constexpr uint32_t DEF_THREADS = 512;
+template <bool DIRECT>
+__global__ __launch_bounds__(DEF_THREADS, 6) void deflate_kernel(
+    const uint8_t* __restrict__ in, uint64_t n_bytes, uint32_t n_chunks, uint16_t* __restrict__ side,
+    uint64_t* __restrict__ marks, uint8_t* __restrict__ slots, uint32_t* __restrict__ seg_size,
+    uint64_t* __restrict__ status, uint32_t* __restrict__ ticket, uint64_t* __restrict__ seg_off,
+    uint8_t* __restrict__ stream, uint64_t* __restrict__ mirror) {
+    __shared__ __align__(16) uint32_t s_out[CODEC_OUT_DW];
+    __shared__ uint64_t s_mark[CODEC_NSUB];
+    __shared__ uint32_t s_side[CODEC_NSUB];
+    __shared__ uint64_t s_off;
+    __shared__ uint32_t s_c;
+    constexpr uint32_t STEPS = CODEC_CHUNK / 1024u / (DEF_THREADS / 64u);     // KiB per wavefront
+    const uint32_t lane = threadIdx.x & 63u, wid = uniform_u32(threadIdx.x >> 6), half = lane >> 5, hl = lane & 31u;
+    uint32_t c = blockIdx.x;
+    if (DIRECT) {
+        if (threadIdx.x == 0) s_c = atomicAdd(ticket, 1u);
+        __syncthreads();
+        c = uniform_u32(s_c);
+        if (c >= n_chunks) return;
+    }
     const uint64_t base = (uint64_t)c * CODEC_CHUNK;
     const uint32_t m = (uint32_t)min((uint64_t)CODEC_CHUNK, n_bytes - min(n_bytes, base));
     const uint32_t last = c + 1u == n_chunks ? 1u : 0u;
-    // stage: whole dwords coalesced, the ragged tail byte by byte, the rest zero
-    uint32_t any_bits = m == CODEC_CHUNK ? 0u : 1u;    // stays 0 only for a full chunk of zeros
-    if (m == CODEC_CHUNK) {
-        // 8 loads of 16 bytes per thread, all in flight together
-        const uint4* in128 = reinterpret_cast<const uint4*>(in + base);
-        uint4 v[8];
+    const uint32_t p0 = hl * 16u;                       // this lane's pieces start here in their sub-chunks
+    Piece P[STEPS];
+    uint32_t zero_kib = 0;                              // bit i: piece i is part of 1 KiB of zeros
 #pragma unroll
-        for (uint32_t u = 0; u < 8u; ++u) v[u] = in128[u * CODEC_THREADS + tid];
+    for (uint32_t i = 0; i < STEPS; ++i) {
+        const uint32_t at = (i * (DEF_THREADS / 64u) + wid) * 1024u + lane * 16u;
+        P[i].v = make_uint4(0, 0, 0, 0);
+        if (at + 16u <= m) {
+            P[i].v = *reinterpret_cast<const uint4*>(in + base + at);
+        } else if (at < m) {
+            uint32_t w[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (uint32_t u = 0; u < 8u; ++u) {
-            any_bits |= v[u].x | v[u].y | v[u].z | v[u].w;
-            const uint32_t g = (u * CODEC_THREADS + tid) * 4u;
-            *reinterpret_cast<uint4*>(&s_in[sub_word(g / CODEC_SUBW, g % CODEC_SUBW)]) = v[u];
-        }
-    } else {
-        const uint32_t* in32 = reinterpret_cast<const uint32_t*>(in + base);
-        for (uint32_t g = tid; g < CODEC_CHUNK / 4; g += CODEC_THREADS) {
-            uint32_t v = 0;
-            if (g * 4u + 4u <= m) {
-                v = in32[g];
-            } else {
-                for (uint32_t k = 0; k < 4u; ++k)
-                    if (g * 4u + k < m) v |= (uint32_t)in[base + g * 4u + k] << (8u * k);
-            }
-            s_in[sub_word(g / CODEC_SUBW, g % CODEC_SUBW)] = v;
+            for (uint32_t k = 0; k < 16u; ++k)
+                if (at + k < m) w[k >> 2] |= (uint32_t)in[base + at + k] << (8u * (k & 3u));
+            P[i].v = make_uint4(w[0], w[1], w[2], w[3]);
         }
     }
-    const bool zero_chunk = __syncthreads_or(any_bits != 0u) == 0;
-    const uint32_t n_l = min(CODEC_SUB, m - min(m, l * CODEC_SUB));      // bytes of this sub-chunk
-    const uint32_t p_lo = min(q * CODEC_QB, n_l), p_hi = min(p_lo + CODEC_QB, n_l);   // this lane's quarter
-    // Bit masks over the bytes of this lane's quarter, 4 words: S, byte i starts a run (it
-    // differs from byte i - 1; position n_l counts as a start); G, byte i >= 144.  From S:
-    // the bytes sent as literals (starts, and the second and third byte of runs shorter
-    // than 4); a literal not followed by a literal starts a run of 4 or more.
-    uint32_t* mk = sh.mask + l * CODEC_MASKW;
-    const uint32_t a0 = q * CODEC_QW;
-    uint32_t tok_bits = 0;
-    if (zero_chunk) {
-        // a chunk of zeros (common in sparse models): every sub-chunk is one literal and the
-        // matches 258 + 253
+    for (uint32_t k = threadIdx.x; k < CODEC_OUT_DW / 4u; k += DEF_THREADS)
+        reinterpret_cast<uint4*>(s_out)[k] = make_uint4(0, 0, 0, 0);
+    // --- first pass: literals, token bits, side information and marks
 #pragma unroll
-        for (uint32_t j = 0; j < CODEC_QW; ++j) mk[a0 + j] = (a0 + j == 0u) ? 1u : 0u;
-        if (q == CODEC_Q - 1u) mk[CODEC_SUB / 32] = 1u;
-        tok_bits = q == 0u ? 8u : 0u;
-    } else {
-        constexpr uint32_t NW = CODEC_SUB / 32;
-        // S[1 .. 4], G[1 .. 4]: this lane's words; S[0] and S[5]: the words next to them, from
-        // the neighbouring lanes of the sub-chunk (the lanes of a sub-chunk are neighbours in
-        // the wavefront); position 512 ends the last run
-        uint32_t S[CODEC_QW + 2], G[CODEC_QW + 2];
-#pragma unroll
-        for (uint32_t k = 1; k <= CODEC_QW; ++k) {
-            const uint32_t a = a0 + k - 1u;
-            mask_word(s_in, l, a, &S[k], &G[k]);
-            if (n_l < CODEC_SUB && (n_l >> 5) == a) S[k] |= 1u << (n_l & 31u);
+    for (uint32_t i = 0; i < STEPS; ++i) {
+        const uint32_t sub = (i * (DEF_THREADS / 64u) + wid) * 2u + half;
+        const uint32_t n_l = min(CODEC_SUB, m - min(m, sub * CODEC_SUB));
+        const uint4 v = P[i].v;
+        uint32_t lit, nine = 0, end = 0;                // end: the sub-chunk's end, where it lies inside the piece
+        if (m == CODEC_CHUNK && __ballot((v.x | v.y | v.z | v.w) != 0u) == 0ull) {
+            // 1 KiB of zeros (common in sparse models): both sub-chunks are one run
+            if (hl == 0u) {
+                s_side[sub] = ZERO_SUB_BITS;
+                s_mark[sub] = ZERO_SUB_MARK;
+            }
+            zero_kib |= 1u << i;
+            continue;
         }
         {
-            const uint32_t from_left = __shfl_up(S[CODEC_QW], 1, CODEC_Q);
-            const uint32_t from_right = __shfl_down(S[1], 1, CODEC_Q);
-            S[0] = q == 0u ? 0u : from_left;
-            S[CODEC_QW + 1] = q == CODEC_Q - 1u ? 1u : from_right;
-            G[0] = G[CODEC_QW + 1] = 0;
+            uint32_t s = changes16(v, __shfl_up(v.w >> 24, 1, 64));
+            if (hl == 0u) s |= 1u;
+            nine = nines16(v);
+            // the end counts as a change
+            const uint32_t left = n_l > p0 ? n_l - p0 : 0u;
+            if (n_l >= p0 && left < 16u) end = 1u << left;
+            const uint32_t valid = left >= 16u ? 0xffffu : (1u << left) - 1u;
+            s = (s & valid) | end;
+            const uint32_t before = __shfl_up(s, 1, 32), after = __shfl_down(s, 1, 32);
+            // bits 2-17 the piece, two bits of the neighbours on either side
+            const uint32_t S = (hl ? before >> 14 : 0u) | (s << 2) | ((hl == 31u ? 1u : after & 3u) << 18);
+            const uint32_t Z = ~S & (hl ? ~0u : ~3u);
+            lit = ((S >> 2) | ((Z >> 2) & (((S >> 1) & (S >> 3)) | ((S >> 1) & (Z >> 3) & (S >> 4)) |
+                                           ((Z >> 1) & S & (S >> 3))))) & valid;
         }
-        uint32_t n_lit = 0, n_nine = 0;
-#pragma unroll
-        for (uint32_t j = 0; j < CODEC_QW; ++j) {
-            const uint32_t a = a0 + j;
-            const uint32_t s0 = S[j + 1], sp = a ? S[j] : 0u, sn = S[j + 2];
-            const uint32_t z0 = ~s0, zp = a ? ~S[j] : 0u, zn = ~S[j + 2];
-            const uint32_t s_b1 = (s0 << 1) | (sp >> 31), s_b2 = (s0 << 2) | (sp >> 30);   // bit p: S at p - 1, p - 2
-            const uint32_t z_b1 = (z0 << 1) | (zp >> 31);
-            const uint32_t s_f1 = (s0 >> 1) | (sn << 31), s_f2 = (s0 >> 2) | (sn << 30);   // bit p: S at p + 1, p + 2
-            const uint32_t z_f1 = (z0 >> 1) | (zn << 31);
-            const uint32_t valid = n_l >= 32u * (a + 1u) ? ~0u : (n_l <= 32u * a ? 0u : (1u << (n_l - 32u * a)) - 1u);
-            const uint32_t lit = (s0 | (z0 & s_b1 & s_f1) | (z0 & s_b1 & z_f1 & s_f2) |
-                                  (z0 & z_b1 & s_b2 & s_f1)) & valid;
-            n_lit += (uint32_t)__popc(lit);
-            n_nine += (uint32_t)__popc(lit & G[j + 1]);
-            const uint32_t end_bit = (n_l < CODEC_SUB && (n_l >> 5) == a) ? 1u << (n_l & 31u) : 0u;
-            mk[a] = lit | end_bit;
-        }
-        if (q == CODEC_Q - 1u) mk[NW] = 1u;
-        tok_bits = 8u * n_lit + n_nine;
-    }
-    __syncthreads();
-    // the matches of the runs of 4 or more that start in this quarter: a literal whose next
-    // byte is not a literal starts one (every byte of a shorter run is a literal)
-    {
-        BitCounter cnt;
-        for (uint32_t j = 0; j < CODEC_QW; ++j) {
-            const uint32_t a = a0 + j;
-            uint32_t mw = mk[a] & ~((mk[a] >> 1) | (mk[a + 1u] << 31));
-            while (mw) {
-                const uint32_t p = a * 32u + (uint32_t)__ffs((int)mw) - 1u;
-                mw &= mw - 1u;
-                if (p < n_l) put_matches(next_bit(mk, p) - p - 1u, cnt);
+        const uint64_t any = __ballot(lit != 0u);
+        const uint32_t later = (uint32_t)(any >> (32u * half)) & (hl == 31u ? 0u : ~0u << (hl + 1u));
+        const uint32_t first = lit ? p0 + (uint32_t)__ffs((int)lit) - 1u : 0u;
+        const uint32_t behind = __shfl(first, later ? (int)(32u * half + (uint32_t)__ffs((int)later) - 1u) : 0, 64);
+        const uint32_t next = later ? behind : n_l;     // first literal behind the piece
+        uint32_t bits = 8u * (uint32_t)__popc(lit) + (uint32_t)__popc(lit & nine);
+        {
+            const Runs r = find_runs(lit, end, next - p0);
+            // 12 bits a match, one more where none of the eleven bytes behind its literal ends the run
+            uint32_t e = r.ends | (r.ends >> 1);
+            e |= e >> 2;
+            e |= e >> 4;
+            e |= e >> 3;
+            bits += 12u * (uint32_t)__popc(r.near) + (uint32_t)__popc(r.near & ~(e >> 1));
+            if (r.far) {
+                uint32_t code;
+                bits += far_matches(r.far, &code);
             }
         }
-        tok_bits += cnt.bits;
-    }
-    // bits before this quarter's tokens (the lanes of a sub-chunk are neighbours), and the
-    // sub-chunk's total
-    uint32_t before = 0, total = tok_bits;
-    {
-        const uint32_t t1 = __shfl_up(tok_bits, 1, CODEC_Q), t2 = __shfl_up(tok_bits, 2, CODEC_Q),
-                       t3 = __shfl_up(tok_bits, 3, CODEC_Q);
-        if (q >= 1u) before += t1;
-        if (q >= 2u) before += t2;
-        if (q >= 3u) before += t3;
-        total = __shfl(before + tok_bits, CODEC_Q - 1u, CODEC_Q);
-    }
-    // first literal at or after the quarter's start (the sub-chunk's length if there is none)
-    uint32_t first = p_lo;
-    if (q > 0u && p_lo < n_l && !((mk[p_lo >> 5] >> (p_lo & 31u)) & 1u)) first = next_bit(mk, p_lo);
-    const bool stored_sub = n_l > 0u && total > 8u * n_l + CODEC_MARGIN;
-    const uint32_t my_side = stored_sub ? CODEC_STORED : total;
-    // the decoder's mark: per later quarter the bits of the quarter before it and how far
-    // past its start its first literal lies
-    uint64_t mark = 0;
-    {
-        const uint32_t prev_bits = __shfl_up(tok_bits, 1, CODEC_Q);
-        const uint64_t field = q ? (uint64_t)(prev_bits | ((first - p_lo) << 11)) << (20u * (q - 1u)) : 0ull;
-        const uint64_t f1 = __shfl_down(field, 1, CODEC_Q), f2 = __shfl_down(field, 2, CODEC_Q),
-                       f3 = __shfl_down(field, 3, CODEC_Q);
-        mark = (n_l > 0u && !stored_sub) ? (f1 | f2 | f3) : 0ull;          // meaningful in lane q = 0
-    }
-    if (q == 0u) sh.side[l] = my_side;
-    const bool any_stored = __syncthreads_or(stored_sub) != 0;
-    if (tid < CODEC_NSUB) {
-        uint32_t start, tail_start;
-        bool in_block, tail_in_block;
-        const uint32_t sb = place_subs(sh.side, m, tid, any_stored, &start, &in_block, &tail_start,
-                                       &tail_in_block);
-        sh.start[tid] = start | (in_block ? 0x80000000u : 0u);
-        if (tid == 0) {
-            sh.misc[0] = sb;
-            sh.misc[1] = tail_start;
-            sh.misc[2] = tail_in_block ? 1u : 0u;
+        uint32_t incl = bits;
+        for (uint32_t d = 1; d < 32u; d <<= 1) {
+            const uint32_t y = __shfl_up(incl, d, 32);
+            if (hl >= d) incl += y;
         }
+        const uint32_t before = incl - bits, total = __shfl(incl, 31, 32);
+        const bool stored = n_l > 0u && total > 8u * n_l + CODEC_MARGIN;
+        // a quarter starts at every eighth lane: the token bits before it and how far past its
+        // start its first literal lies
+        const uint32_t q_at = min(p0, n_l);
+        const uint32_t quarter = before | (((lit ? first : next) - q_at) << 16);
+        uint64_t mark = 0;
+        uint32_t b_prev = 0;
+#pragma unroll
+        for (uint32_t q = 1; q < CODEC_Q; ++q) {
+            const uint32_t x = __shfl(quarter, 8 * (int)q, 32), b_q = x & 0xffffu;
+            mark |= (uint64_t)((b_q - b_prev) | ((x >> 16) << 11)) << (20u * (q - 1u));
+            b_prev = b_q;
+        }
+        if (hl == 0u) {
+            s_side[sub] = stored ? CODEC_STORED : total;
+            s_mark[sub] = n_l > 0u && !stored ? mark : 0ull;
+        }
+        P[i].lit = lit | (nine << 16);
+        P[i].place = before | (next << 16);
     }
     __syncthreads();
-    const uint32_t seg_bytes = sh.misc[0];
-    uint32_t* slot32 = reinterpret_cast<uint32_t*>(slots + (uint64_t)c * CODEC_SLOT);
-    if (m + 5u <= seg_bytes) {
-        // one stored block: header byte, LEN, NLEN, then the chunk, shifted by five bytes
-        if (q == 0u) {
-            side[(uint64_t)c * CODEC_NSUB + l] = 0;
-            marks[(uint64_t)c * CODEC_NSUB + l] = 0;
+    // --- every wavefront places the sub-chunks for itself, lane = sub-chunk
+    uint32_t start, tail_start;
+    bool in_block, tail_in_block;
+    const uint32_t side_l = s_side[lane];
+    const uint32_t coded_bytes = place_subs(side_l, min(CODEC_SUB, m - min(m, lane * CODEC_SUB)), lane, &start, &in_block,
+                                            &tail_start, &tail_in_block);
+    const bool whole = m + 5u <= coded_bytes;           // not shorter than one stored block
+    const uint32_t seg_bytes = whole ? m + 5u : coded_bytes;
+    if (threadIdx.x == 0) {
+        if (DIRECT) chain_store(status + c, ((c == 0u ? 2ull : 1ull) << 62) | seg_bytes);
+        else seg_size[c] = seg_bytes;
+    }
+    if (wid == 0u) {
+        side[(uint64_t)c * CODEC_NSUB + lane] = whole ? 0 : (uint16_t)side_l;
+        marks[(uint64_t)c * CODEC_NSUB + lane] = whole ? 0ull : s_mark[lane];
+    }
+    // --- second pass: the segment
+#pragma unroll
+    for (uint32_t i = 0; i < STEPS; ++i) {
+        const uint32_t kib = i * (DEF_THREADS / 64u) + wid, sub = kib * 2u + half;
+        const uint32_t n_l = min(CODEC_SUB, m - min(m, sub * CODEC_SUB));
+        const uint32_t left = min(16u, n_l > p0 ? n_l - p0 : 0u);
+        const uint32_t st = __shfl(start, (int)sub, 64);
+        const bool open = __shfl(in_block ? 1u : 0u, (int)sub, 64) != 0u;
+        const uint32_t sd = __shfl(side_l, (int)sub, 64);
+        const uint4 v = P[i].v;
+        if (whole || sd == CODEC_STORED) {
+            // bytes as they are: behind the header of the one block, or of the sub-chunk's own
+            uint32_t data_bit = 40u + 8u * (sub * CODEC_SUB);
+            if (!whole) {
+                const uint32_t at = st + (open ? 10u : 3u);
+                data_bit = ((at + 7u) & ~7u) + 32u;
+                if (hl == 0u && n_l > 0u) {
+                    BitWriter w(s_out, st);
+                    if (open) w.put(0u, 7u);              // end of the open block
+                    w.put(0u, 3u);                        // BFINAL = 0, BTYPE = 00
+                    w.put(0u, (8u - (at & 7u)) & 7u);
+                    w.put(n_l, 16u);
+                    w.put(n_l ^ 0xffffu, 16u);
+                    w.finish();
+                }
+            }
+            if (left) {                                   // bytes past the end are zero and change nothing
+                const uint32_t at = data_bit + 8u * p0, sh = at & 31u;
+                uint32_t* o = &s_out[at >> 5];
+                auto high = [&](uint32_t hi, uint32_t lo) { return (uint32_t)((((uint64_t)hi << 32 | lo) << sh) >> 32); };
+                atomicOr(&o[0], v.x << sh);
+                atomicOr(&o[1], high(v.y, v.x));
+                atomicOr(&o[2], high(v.z, v.y));
+                atomicOr(&o[3], high(v.w, v.z));
+                if (sh) atomicOr(&o[4], high(0u, v.w));
+            }
+        } else if ((zero_kib >> i) & 1u) {
+            if (hl == 0u) {
+                BitWriter w(s_out, st);
+                if (!open) w.put(2u, 3u);                     // BFINAL = 0, BTYPE = 01
+                w.put(ZERO_SUB_LOW, 21u);
+                w.put(ZERO_SUB_HIGH, ZERO_SUB_BITS - 21u);
+                w.finish();
+            }
+        } else {
+            const uint32_t lit = P[i].lit & 0xffffu, next = P[i].place >> 16;
+            if (lit) {
+                const uint32_t end = n_l >= p0 && n_l - p0 < 16u ? 1u << (n_l - p0) : 0u;
+                if (hl == 0u && !open) atomicOr(&s_out[st >> 5], 2u << (st & 31u));       // BFINAL = 0, BTYPE = 01 ...
+                if (hl == 0u && !open && (st & 31u) == 31u) atomicOr(&s_out[(st >> 5) + 1u], 1u);
+                emit_tokens(s_out, st + (open ? 0u : 3u) + (P[i].place & 0xffffu), v, lit, P[i].lit >> 16,
+                            find_runs(lit, end, next - p0));
+            }
         }
-        if (tid == 0) seg_size[c] = m + 5u;
-        const uint32_t n_w = (m + 5u + 3u) / 4u;
-        auto src = [&](uint32_t g) {               // dword g of the chunk (0 beyond it)
-            return g < CODEC_CHUNK / 4 ? s_in[sub_word(g / CODEC_SUBW, g % CODEC_SUBW)] : 0u;
-        };
-        for (uint32_t k = tid; k < n_w; k += CODEC_THREADS) {
-            uint32_t v;
-            if (k == 0) v = last | (m << 8) | ((m ^ 0xffffu) << 24);
-            else if (k == 1) v = ((m ^ 0xffffu) >> 8) | (src(0) << 8);
-            else v = (src(k - 2) >> 24) | (src(k - 1) << 8);
-            slot32[k] = v;
-        }
-        return;
     }
-    if (OUT_DW < CODEC_OUT_FULL && (seg_bytes + 3u) / 4u > OUT_DW) {
-        if (tid == 0) long_list[atomicAdd(long_count, 1u)] = c;   // for the other instance
-        return;
-    }
-    if (q == 0u) {
-        side[(uint64_t)c * CODEC_NSUB + l] = (uint16_t)my_side;
-        marks[(uint64_t)c * CODEC_NSUB + l] = mark;
-    }
-    if (tid == 0) seg_size[c] = seg_bytes;
-    const uint32_t n_w = (seg_bytes + 3u) / 4u;
-    for (uint32_t k = tid; k < n_w; k += CODEC_THREADS) sh.out[k] = 0;
-    __syncthreads();
-    const uint32_t start = sh.start[l] & 0x7fffffffu;
-    const bool in_block = (sh.start[l] >> 31) != 0u;
-    if (n_l > 0u && !stored_sub) {
-        // lane 0 opens the block if none is open; every lane appends its quarter's tokens
-        const uint32_t tok0 = start + (in_block ? 0u : 3u);
-        BitWriter w(sh.out, q == 0u ? start : tok0 + before);
-        if (q == 0u && !in_block) w.put(2u, 3u);          // BFINAL = 0, BTYPE = 01
-        encode_range(s_in, mk, l, first, p_hi, w);
-        w.finish();
-    } else if (n_l > 0u) {
-        // stored: lane 0 closes the open block and writes the header, every lane its bytes
-        const uint32_t at = start + (in_block ? 10u : 3u);
-        const uint32_t data_bit = ((at + 7u) & ~7u) + 32u;
-        if (q == 0u) {
-            BitWriter w(sh.out, start);
-            if (in_block) w.put(0u, 7u);                  // end of the open block
-            w.put(0u, 3u);                                // BFINAL = 0, BTYPE = 00
+    if (threadIdx.x == DEF_THREADS - 1u) {
+        if (whole) {
+            BitWriter w(s_out, 0);
+            w.put(last, 8u);                              // BFINAL, BTYPE = 00
+            w.put(m, 16u);
+            w.put(m ^ 0xffffu, 16u);
+            w.finish();
+        } else {
+            BitWriter w(s_out, tail_start);
+            if (tail_in_block) w.put(0u, 7u);             // end of block
+            w.put(last, 3u);                              // empty stored block: BFINAL, BTYPE = 00
+            const uint32_t at = tail_start + (tail_in_block ? 10u : 3u);
             w.put(0u, (8u - (at & 7u)) & 7u);
-            w.put(n_l, 16u);
-            w.put(n_l ^ 0xffffu, 16u);
-            w.finish();
-        }
-        if (p_hi > p_lo) {
-            BitWriter w(sh.out, data_bit + 8u * p_lo);
-            const uint32_t nq = p_hi - p_lo;
-            for (uint32_t j = 0; j < nq / 4u; ++j) w.put(s_in[sub_word(l, p_lo / 4u + j)], 32u);
-            for (uint32_t i = p_lo + (nq & ~3u); i < p_hi; ++i)
-                w.put((s_in[sub_word(l, i >> 2)] >> ((i & 3u) * 8u)) & 0xffu, 8u);
+            w.put(0x0000u, 16u);
+            w.put(0xffffu, 16u);
             w.finish();
         }
     }
-    if (tid == CODEC_THREADS - 1u) {
-        const uint32_t tail_start = sh.misc[1];
-        const bool tail_in_block = sh.misc[2] != 0u;
-        BitWriter w(sh.out, tail_start);
-        if (tail_in_block) w.put(0u, 7u);                 // end of block
-        w.put(last, 3u);                                  // empty stored block: BFINAL, BTYPE = 00
-        const uint32_t at = tail_start + (tail_in_block ? 10u : 3u);
-        w.put(0u, (8u - (at & 7u)) & 7u);
-        w.put(0x0000u, 16u);
-        w.put(0xffffu, 16u);
-        w.finish();
+    uint8_t* dst = slots + (uint64_t)c * CODEC_SLOT;
+    if (DIRECT) {
+        if (wid == 0u) {
+            bool broken = false;
+            const uint64_t off = chain_before(status, c, lane, &broken);
+            if (lane == 0u) {
+                if (broken) chain_store(status + c, 3ull << 62);
+                else if (c) chain_store(status + c, (2ull << 62) | (off + seg_bytes));
+                s_off = broken ? ~0ull : off;
+                seg_off[c] = off;
+                if (last) {
+                    seg_off[n_chunks] = off + seg_bytes;
+                    mirror[0] = off + seg_bytes;
+                    mirror[1] = broken ? CODEC_CHAIN : 0u;
+                }
+            }
+        }
+        __syncthreads();
+        const uint64_t off = s_off;
+        if (off == ~0ull) return;
+        dst = stream + off;
+    } else {
+        __syncthreads();
     }
-    __syncthreads();
-    for (uint32_t k = tid; k < n_w; k += CODEC_THREADS) slot32[k] = sh.out[k];
+    // --- to memory: the first bytes up to a dword, whole dwords put together from two, the rest
+    const uint32_t head = min(seg_bytes, (uint32_t)((4u - (reinterpret_cast<uintptr_t>(dst) & 3u)) & 3u));
+    const uint32_t n_w = (seg_bytes - head) / 4u, sh = head * 8u;
+    const uint8_t* out8 = reinterpret_cast<const uint8_t*>(s_out);
+    if (threadIdx.x < head) dst[threadIdx.x] = out8[threadIdx.x];
+    uint32_t* dst32 = reinterpret_cast<uint32_t*>(dst + head);
+#pragma unroll 4
+    for (uint32_t k = threadIdx.x; k < n_w; k += DEF_THREADS)
+        dst32[k] = __builtin_amdgcn_alignbit(s_out[k + 1u], s_out[k], sh);
+    const uint32_t done = head + n_w * 4u;
+    if (threadIdx.x < seg_bytes - done) dst[done + threadIdx.x] = out8[done + threadIdx.x];
 }
 
-template <uint32_t OUT_DW, bool LISTED>
-__global__ __launch_bounds__(CODEC_THREADS) void deflate_chunk_kernel(
-    const uint8_t* __restrict__ in, uint64_t n_bytes, uint32_t n_chunks,
-    uint8_t* __restrict__ slots, uint32_t* __restrict__ seg_size, uint16_t* __restrict__ side,
-    uint64_t* __restrict__ marks, const uint32_t* __restrict__ list, uint32_t* __restrict__ long_list,
-    uint32_t* __restrict__ long_count) {
-    __shared__ __align__(16) uint32_t s_in[CODEC_CHUNK / 4];
-    __shared__ uint32_t s_out[OUT_DW];
-    __shared__ uint32_t s_mask[CODEC_NSUB * CODEC_MASKW];
-    __shared__ uint32_t s_side[CODEC_NSUB];
-    __shared__ uint32_t s_start[CODEC_NSUB];
-    __shared__ uint32_t s_misc[4];
-    const DeflateShared sh{s_in, s_out, s_mask, s_side, s_start, s_misc};
-    if (!LISTED) {
-        deflate_chunk<OUT_DW>(sh, blockIdx.x, in, n_bytes, n_chunks, slots, seg_size, side, marks, long_list,
-                              long_count);
-    } else {
-        const uint32_t n_list = *long_count;               // written by the instance before this one
-        for (uint32_t it = blockIdx.x; it < n_list; it += gridDim.x) {
-            deflate_chunk<OUT_DW>(sh, list[it], in, n_bytes, n_chunks, slots, seg_size, side, marks, nullptr,
-                                  nullptr);
-            __syncthreads();
-        }
-    }
+// Clears the chain of a call: the status words of its chunks and the ticket behind them.
+__global__ __launch_bounds__(BLOCK) void chain_clear_kernel(uint64_t* status, uint32_t n) {
+    const uint32_t i = blockIdx.x * BLOCK + threadIdx.x;
+    if (i < n) status[i] = 0;
 }
 
 // Byte offsets of the segments: exclusive prefix sums of their sizes (one block).  A row is
@@ -701,7 +747,6 @@ struct InflateShared {
     uint32_t* img;      // CODEC_CHUNK / 4: the chunk being produced
     uint32_t* seg;      // SEG_DW: the segment
     uint32_t* tab;      // 512: token table
-    uint32_t* side;     // CODEC_NSUB
     uint32_t* start;    // CODEC_NSUB: bit 31 = a block is open there
     uint32_t* misc;     // segment bytes, tail start, tail in block
 };
@@ -797,17 +842,10 @@ __device__ __forceinline__ void inflate_chunk(
         const uint32_t v = side[(uint64_t)c * CODEC_NSUB + tid];
         const bool st = v == CODEC_STORED;
         const bool ok_s = st ? n_s > 0u : (n_s > 0u ? v != 0u && v <= 8u * n_s + CODEC_MARGIN : v == 0u);
-        sh.side[tid] = ok_s ? v : 0u;
-        // the lanes exchange within their own wavefront only: order the LDS accesses
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const bool any_stored = __ballot(st) != 0ull;
         const bool all_ok = __ballot(!ok_s) == 0ull;
         uint32_t start, tail_start;
         bool in_block, tail_in_block;
-        const uint32_t sb = place_subs(sh.side, m, tid, any_stored, &start, &in_block, &tail_start,
-                                       &tail_in_block);
+        const uint32_t sb = place_subs(ok_s ? v : 0u, n_s, tid, &start, &in_block, &tail_start, &tail_in_block);
         sh.start[tid] = start | (in_block ? 0x80000000u : 0u);
         if (tid == 0) {
             sh.misc[0] = all_ok ? sb : 0xffffffffu;      // never a segment's size
@@ -1008,10 +1046,9 @@ void inflate_chunk_kernel(
     __shared__ __align__(16) uint32_t s_img[SEG_DW == CODEC_SEG_SMALL ? 4 : CODEC_CHUNK / 4];   // none for the short segments
     __shared__ uint32_t s_seg[SEG_DW];
     __shared__ uint32_t s_tab[512];
-    __shared__ uint32_t s_side[CODEC_NSUB];
     __shared__ uint32_t s_start[CODEC_NSUB];
     __shared__ uint32_t s_misc[4];
-    const InflateShared sh{s_img, s_seg, s_tab, s_side, s_start, s_misc};
+    const InflateShared sh{s_img, s_seg, s_tab, s_start, s_misc};
     if (!list) {
         inflate_chunk<SEG_DW, SEG_MIN>(sh, blockIdx.x, stream, stream_bytes, seg_off, side, marks, n_bytes,
                                        n_chunks, out, result);
@@ -1074,23 +1111,32 @@ static hipError_t codec_ensure_list(shifter_ctx* ctx, uint64_t entries) {
 int launch_deflate(shifter_ctx* ctx, const uint8_t* d_in, uint64_t n_bytes, uint32_t n_chunks,
                    uint8_t* d_work, uint8_t* d_stream, uint64_t stream_cap, uint64_t* d_seg_off,
                    uint16_t* d_sub_bits, uint64_t* d_sub_marks) {
-    hipError_t e = codec_ensure_list(ctx, 2ull * n_chunks);
+    // the decoder's lists: a call of either kind makes room for both, so that either may be
+    // recorded into a graph behind it
+    const hipError_t e = codec_ensure_list(ctx, 2ull * n_chunks);
     if (e != hipSuccess) return (int)e;
+    if (stream_cap >= n_bytes + 5ull * n_chunks) {
+        // the stream holds every segment stored: it cannot overflow, so the segments go straight
+        // to their places (the workspace holds the chain)
+        uint64_t* status = reinterpret_cast<uint64_t*>(d_work);
+        {
+            ProfileScope ps(ctx, K_CODEC_SCAN);
+            chain_clear_kernel<<<(n_chunks + BLOCK) / BLOCK, BLOCK, 0, ctx->stream>>>(status, n_chunks + 1u);
+        }
+        ProfileScope ps(ctx, K_DEFLATE_CHUNK);
+        deflate_kernel<true><<<n_chunks, DEF_THREADS, 0, ctx->stream>>>(
+            d_in, n_bytes, n_chunks, d_sub_bits, d_sub_marks, nullptr, nullptr, status,
+            reinterpret_cast<uint32_t*>(status + n_chunks), d_seg_off, d_stream, ctx->dev_codec_mirror);
+        return 0;
+    }
     uint32_t* seg_size = reinterpret_cast<uint32_t*>(d_work);
     uint8_t* slots = d_work + codec_slots_offset(n_chunks);
-    uint32_t* long_count = reinterpret_cast<uint32_t*>(ctx->d_codec + 2);
     codec_begin(ctx);
     {
         ProfileScope ps(ctx, K_DEFLATE_CHUNK);
-        deflate_chunk_kernel<CODEC_OUT_SMALL, false><<<n_chunks, CODEC_THREADS, 0, ctx->stream>>>(
-            d_in, n_bytes, n_chunks, slots, seg_size, d_sub_bits, d_sub_marks, nullptr, ctx->d_codec_list,
-            long_count);
-        // the chunks whose segment did not fit the first instance's LDS: a fixed grid walks
-        // the list the first instance left, however long it is
-        deflate_chunk_kernel<CODEC_OUT_FULL, true>
-            <<<std::min(n_chunks, CODEC_LOOP_GRID), CODEC_THREADS, 0, ctx->stream>>>(
-                d_in, n_bytes, n_chunks, slots, seg_size, d_sub_bits, d_sub_marks, ctx->d_codec_list, nullptr,
-                long_count);
+        deflate_kernel<false><<<n_chunks, DEF_THREADS, 0, ctx->stream>>>(
+            d_in, n_bytes, n_chunks, d_sub_bits, d_sub_marks, slots, seg_size, nullptr, nullptr, nullptr, nullptr,
+            nullptr);
     }
     {
         ProfileScope ps(ctx, K_CODEC_SCAN);

@@ -464,6 +464,9 @@ void launch_kernel_scan(shifter_ctx* ctx, const shifter_model* m, const float* d
 void launch_fix_begin(shifter_ctx* ctx, const shifter_model* m);
 void launch_fix_batch(shifter_ctx* ctx, const shifter_model* m, const uint8_t* d_nz, uint32_t flags);
 void launch_fix_widths(shifter_ctx* ctx, const shifter_model* m, const uint32_t* d_new_width);
+// Status bits of a codec call: the stream is not what the side information says; it does not fit
+// its buffer; a segment's offset did not arrive within the poll limit.
+enum : uint32_t { CODEC_BAD_STREAM = 1u, CODEC_CAPACITY = 2u, CODEC_CHAIN = 4u };
 // Codec workspace: segment sizes (u32 per chunk) first, then one slot per chunk.
 inline uint64_t codec_slots_offset(uint64_t n_chunks) { return (n_chunks * 4u + 255u) & ~(uint64_t)255u; }
 int launch_deflate(shifter_ctx* ctx, const uint8_t* d_in, uint64_t n_bytes, uint32_t n_chunks,
