@@ -1204,10 +1204,12 @@ extern "C" int shifter_fold_bn(shifter_ctx* ctx, const shifter_model* model,
     std::vector<std::pair<uint64_t, uint64_t>> spans;
     for (uint32_t i = 0; i < n_fold; ++i) {
         const shifter_fold_desc& f = h_fold[i];
-        const std::string at = "fold_bn: entry " + std::to_string(i) + ": ";
-        if (f.tensor >= n_t) return fail(ctx, SHIFTER_ERR_INVALID_ARG, at + "tensor index out of range");
+        auto bad = [&](const char* what) {
+            return fail(ctx, SHIFTER_ERR_INVALID_ARG, "fold_bn: entry " + std::to_string(i) + ": " + what);
+        };
+        if (f.tensor >= n_t) return bad("tensor index out of range");
         if (tab[f.tensor].out_offset >= 0)
-            return fail(ctx, SHIFTER_ERR_INVALID_ARG, at + "tensor listed twice");
+            return bad("tensor listed twice");
         const uint32_t out_ch = model->t[f.tensor].out_ch;
         const int32_t bn[4] = {f.gamma, f.beta, f.mean, f.var};
         const bool has_bn = f.gamma >= 0;
@@ -1215,17 +1217,17 @@ extern "C" int shifter_fold_bn(shifter_ctx* ctx, const shifter_model* model,
         const int32_t ids[5] = {f.gamma, f.beta, f.mean, f.var, f.bias};
         for (int j = 0; j < 4; ++j)
             if ((bn[j] >= 0) != has_bn)
-                return fail(ctx, SHIFTER_ERR_INVALID_ARG, at + "gamma, beta, mean and var go together");
+                return bad("gamma, beta, mean and var go together");
         for (int j = 0; j < 5; ++j) {
             off[j] = -1;
             if (ids[j] < 0) continue;
-            if ((size_t)ids[j] >= n_v) return fail(ctx, SHIFTER_ERR_INVALID_ARG, at + "vector index out of range");
+            if ((size_t)ids[j] >= n_v) return bad("vector index out of range");
             if (model->v[ids[j]].len != out_ch)
-                return fail(ctx, SHIFTER_ERR_INVALID_ARG, at + "vector length differs from the tensor's out_ch");
+                return bad("vector length differs from the tensor's out_ch");
             off[j] = (int64_t)model->v[ids[j]].offset;
         }
         if (f.out_offset > cap_bias || out_ch > cap_bias - f.out_offset)
-            return fail(ctx, SHIFTER_ERR_INVALID_ARG, at + "bias range exceeds cap_bias");
+            return bad("bias range exceeds cap_bias");
         spans.push_back({f.out_offset, f.out_offset + out_ch});
         tab[f.tensor] = FoldTensor{off[0], off[1], off[2], off[3], off[4], (int64_t)f.out_offset};
     }

@@ -88,8 +88,9 @@ void launch_fold(shifter_ctx* ctx, const shifter_model* m, const float* d_w, con
     }
     if (m->n_tiles == 0) return;
     ProfileScope ps(ctx, K_FOLD_APPLY);
-    // arenas that fit the last-level cache are re-read by the steps that follow
-    if (m->info.w_extent * 4 > (192ull << 20))
+    // beyond the chip's L2 the streaming hint pays, also where the arena would fit the last-level
+    // cache (102 MB in and out: 41.6 us a call without it, 36.3 with)
+    if (m->info.w_extent * 4 > (32ull << 20))
         fold_apply_kernel<true><<<m->n_tiles, BLOCK, 0, ctx->stream>>>(
             b.tens, b.tile_prefix, b.tile_tensor, b.fold_scale, d_w, d_w_out);
     else

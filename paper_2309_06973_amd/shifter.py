@@ -5,7 +5,9 @@ library is missing or no GPU is visible, calls raise."""
 from __future__ import annotations
 
 import ctypes as C
+import operator
 import os
+import struct
 from typing import List, Optional, Sequence
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libshifter.so")
@@ -67,6 +69,10 @@ class PortfolioArgs(C.Structure):
                 ("d_index_map", C.c_void_p), ("d_keep", C.c_void_p), ("d_new_width", C.c_void_p),
                 ("d_w_out", C.c_void_p), ("cap_w", C.c_uint64), ("d_vecs_out", C.c_void_p),
                 ("cap_v", C.c_uint64)]
+
+
+_fold_fields = operator.attrgetter("tensor", "gamma", "beta", "mean", "var", "bias", "out_offset")
+_fold_row = struct.Struct("=IiiiiiQ").pack      # a FoldDesc
 
 
 class FoldDesc(C.Structure):
@@ -368,9 +374,15 @@ def shifter_fold_bn(ctx: Context, model: Model, folds, eps: float, d_w, d_vecs, 
                     d_bias_out) -> None:
     """folds: objects with tensor, gamma, beta, mean, var, bias, out_offset (-1: absent).
     The capacity of the bias arena is the length of d_bias_out."""
-    arr = (FoldDesc * max(len(folds), 1))()
-    for i, f in enumerate(folds):
-        arr[i] = FoldDesc(f.tensor, f.gamma, f.beta, f.mean, f.var, f.bias, f.out_offset)
+    try:
+        # one packed row per layer: a structure object each takes 0.8 us of host time, for the 54
+        # layers of a residual network more than the fold itself takes on the device
+        rows = b"".join([_fold_row(*_fold_fields(f)) for f in folds])
+        arr = (FoldDesc * max(len(folds), 1)).from_buffer_copy(rows or bytes(C.sizeof(FoldDesc)))
+    except struct.error:            # a value that wraps around in its field: the library judges it
+        arr = (FoldDesc * len(folds))()
+        for i, f in enumerate(folds):
+            arr[i] = FoldDesc(*_fold_fields(f))
     cap = d_bias_out.numel() if d_bias_out is not None else 0
     _check(load_library().shifter_fold_bn(ctx.handle, model.handle, arr, len(folds), eps,
                                           _ptr(d_w), _ptr(d_vecs), _ptr(d_w_out),
