@@ -480,11 +480,8 @@ static int bind_tables(shifter_ctx* ctx, shifter_model* m) {
                            sizeof(uint32_t) * MAXK * std::max<size_t>(m->rowtab_prefix.back(), 1)));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.coltab),
                            sizeof(uint32_t) * MAXK * std::max<size_t>(m->coltab_prefix.back(), 1)));
-    // the rankings leave what they start from cleared for the next one
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.sel), sizeof(SelState)));
-    HIP_TRY(ctx, hipMemset(b.sel, 0, sizeof(SelState)));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.ghist), sizeof(uint32_t) * SEL_STAGES * SEL_BINS));
-    HIP_TRY(ctx, hipMemset(b.ghist, 0, sizeof(uint32_t) * SEL_STAGES * SEL_BINS));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.plan_t), sizeof(PlanTensor) * n_t * MAXK));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.plan_v), sizeof(PlanVec) * std::max<size_t>(n_v, 1) * MAXK));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.plan_h), sizeof(PlanHeader) * MAXK));
@@ -1406,40 +1403,7 @@ extern "C" int shifter_portfolio_begin(shifter_ctx* ctx, const shifter_model* mo
     pp.model = model;
     pp.k_eff = k_eff;
     const auto& b = model->b;
-    const bool cached = model->info.w_extent * 4 <= ctx->fused_min_bytes;
-    if (ctx->select_path == 0 && cached && k_eff <= SPEC_MULTI_MAXK) {
-        // an arena that stays in the last-level cache: ranked exactly from a histogram of all
-        // weights, then masked (the planning launch expands a portfolio's levels on the way).
-        // Several counts: beyond STEP_TIES weights that share a threshold the step is redone, as
-        // ever - what lies behind the rebuilt variants' ends in the output arenas is what the first
-        // attempt left there, and callers may have come to compare whole arenas.  A single
-        // count's first attempt never writes beyond that end and ranks any ties that fit its list.
-        PruneCounts sp;
-        MultiPerm perm;
-        memset(&sp, 0, sizeof sp);
-        memset(&perm, 0, sizeof perm);
-        for (uint32_t k = 0; k < K; ++k) idx[k] = k;
-        std::stable_sort(idx, idx + K, [&](uint32_t x, uint32_t y) { return pp.pc.p[x] < pp.pc.p[y]; });
-        for (uint32_t i = 0; i < K; ++i) { sp.p[i] = pp.pc.p[idx[i]]; perm.v[i] = idx[i]; }
-        pp.mode = 2;
-        pp.k_eff = K;                      // a status word for every count, zeros included
-        SampleZero z;
-        const bool one = K == 1 && g.d_w_sparse && g.d_in_alive;
-        if (one) {
-            z.fa = g.d_out_alive; z.na = model->info.sum_out_ch;
-            z.fb = g.d_in_alive; z.nb = model->info.sum_in_ch;
-        } else {
-            z.extra = b.levels;
-            z.extra_n = (uint32_t)(model->info.sum_out_ch + model->info.sum_in_ch);
-        }
-        launch_step_ranking(ctx, model, g.d_w, sp, perm, K, one ? ~0ull : STEP_TIES, g.d_thr, z);
-        if (one)
-            launch_mask_scan(ctx, model, g.d_w, g.d_thr, g.d_w_sparse, g.d_mask, g.d_out_alive, g.d_in_alive, true);
-        else
-            launch_mask_scan_batch_core(ctx, model, g.d_w, g.d_thr, K, g.d_w_sparse, g.w_stride, g.d_mask,
-                                        g.mask_stride);
-        launch_plan_and_gather(ctx, model, pp.buf, !one, cut_positions(pp.pc, K));
-    } else if (ctx->select_path == 0 && K == 1 && g.d_w_sparse && g.d_in_alive) {
+    if (ctx->select_path == 0 && K == 1 && g.d_w_sparse && g.d_in_alive) {
         // one prune count: ranking, sparse arena, mask and flags in a single read
         pp.mode = 1;
         launch_spec_select(ctx, model, g.d_w, pp.pc.p[0], g.d_thr, g.d_w_sparse, g.d_mask, g.d_out_alive,
@@ -1454,11 +1418,21 @@ extern "C" int shifter_portfolio_begin(shifter_ctx* ctx, const shifter_model* mo
         std::stable_sort(idx, idx + k_eff, [&](uint32_t x, uint32_t y) { return pp.pc.p[x] < pp.pc.p[y]; });
         for (uint32_t i = 0; i < k_eff; ++i) { sp.p[i] = pp.pc.p[idx[i]]; perm.v[i] = idx[i]; }
         pp.mode = 2;
-        // an arena beyond the last-level cache: ranking, masks and levels in one read of it
-        // (the planning launch expands the levels into the variants' flags on the way)
-        FusedBatch fb{K, g.d_w_sparse, g.w_stride, g.d_mask, g.mask_stride, g.d_out_alive, g.d_in_alive, true};
-        launch_spec_multi(ctx, model, g.d_w, sp, perm, k_eff, zero_mask, g.d_thr, &fb);
-        launch_plan_and_gather(ctx, model, pp.buf, true, cut_positions(pp.pc, K));
+        if (model->info.w_extent * 4 > ctx->fused_min_bytes) {
+            // an arena beyond the last-level cache: ranking, masks and levels in one read of it
+            // (the planning launch expands the levels into the variants' flags on the way)
+            FusedBatch fb{K, g.d_w_sparse, g.w_stride, g.d_mask, g.mask_stride, g.d_out_alive, g.d_in_alive, true};
+            launch_spec_multi(ctx, model, g.d_w, sp, perm, k_eff, zero_mask, g.d_thr, &fb);
+            launch_plan_and_gather(ctx, model, pp.buf, true, cut_positions(pp.pc, K));
+        } else {
+            // a cache-sized arena: the counting pass, then the mask pass reads it again; the
+            // planning launch expands the levels into the variants' flags on the way
+            launch_spec_multi(ctx, model, g.d_w, sp, perm, k_eff, zero_mask, g.d_thr, nullptr, b.levels,
+                              (uint32_t)(model->info.sum_out_ch + model->info.sum_in_ch));
+            launch_mask_scan_batch_core(ctx, model, g.d_w, g.d_thr, K, g.d_w_sparse, g.w_stride, g.d_mask,
+                                        g.mask_stride);
+            launch_plan_and_gather(ctx, model, pp.buf, true, cut_positions(pp.pc, K));
+        }
     } else {
         pp.mode = 3;
         if ((rc = portfolio_radix(ctx, model, pp.pc, pp.buf))) return rc;

@@ -74,8 +74,7 @@ struct SelState {
     uint32_t perm[MAXK];                   // caller's position of a rank
     uint32_t list_cnt[MAXK];
     uint32_t done[SEL_STAGES + 1];         // every rank is listed after this stage
-    uint32_t nan_seen;                     // of a ranking without a decision on the host
-    uint32_t nan_raw, nan_step;            // of a step's: set by its first kernel, read by its last
+    uint32_t nan_seen;
 };
 
 // State of the single-pass (sample, predict, one pass, finish) selection.
@@ -404,12 +403,6 @@ struct SampleZero {
     uint8_t* fb = nullptr;
     uint64_t na = 0, nb = 0;
 };
-// Ranking of a step on an arena that fits the last-level cache (select.hip).  ties_max: a rank
-// whose threshold more weights share is left undecided.  Outcome in the K-rank mirrors.
-constexpr uint64_t STEP_TIES = 1024;
-void launch_step_ranking(shifter_ctx* ctx, const shifter_model* m, const float* d_w, const PruneCounts& sorted,
-                         const MultiPerm& perm, uint32_t k, uint64_t ties_max, shifter_threshold* d_thr,
-                         const SampleZero& z);
 void launch_spec_sample(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
                         const SampleZero& z = SampleZero());
 // Outputs of the fused portfolio pass (steps 1-3 in one read): k_all variants in caller order.
@@ -423,10 +416,12 @@ struct FusedBatch {
     uint8_t* d_in_alive;     // or nullptr
     bool levels_only = false;   // leave the levels unexpanded: the planning launch behind it writes the flags
 };
+// zero_ptr / zero_n: an array of 32-bit words the ranking's set-up clears on the way (or
+// nullptr), for the step that follows it.
 void launch_spec_multi(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
                        const shifter::PruneCounts& sorted_p, const shifter::MultiPerm& perm,
                        uint32_t k, uint64_t zero_mask, shifter_threshold* d_thr,
-                       const FusedBatch* fb);
+                       const FusedBatch* fb, uint32_t* zero_ptr = nullptr, uint32_t zero_n = 0);
 constexpr size_t MULTI_MIRROR_REC_OFF = 512;   // records follow the MAXK status words
 // The liveness fixpoint enqueues its rounds in batches of FIX_BATCH with no wait inside a
 // batch; its state on the device is removed[0 .. FIX_BATCH] and the rounds run so far, and
@@ -441,7 +436,7 @@ void launch_expand_levels(shifter_ctx* ctx, const shifter_model* m, const shifte
                           uint32_t k_var, uint8_t* d_out_alive, uint8_t* d_in_alive);
 void launch_mask_scan(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
                       const shifter_threshold* d_thr, float* d_w_out, uint8_t* d_mask,
-                      uint8_t* d_out_alive, uint8_t* d_in_alive, bool flags_zeroed = false);
+                      uint8_t* d_out_alive, uint8_t* d_in_alive);
 void launch_scan(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
                  uint8_t* d_out_alive, uint8_t* d_in_alive);
 void launch_mask_scan_batch(shifter_ctx* ctx, const shifter_model* m, const float* d_w,

@@ -131,12 +131,12 @@ static bool streaming(const shifter_model* m) { return m->info.w_extent * 4 > (1
 
 void launch_mask_scan(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
                       const shifter_threshold* d_thr, float* d_w_out, uint8_t* d_mask,
-                      uint8_t* d_out_alive, uint8_t* d_in_alive, bool flags_zeroed) {
+                      uint8_t* d_out_alive, uint8_t* d_in_alive) {
     const auto& b = m->b;
     const uint32_t n_t = (uint32_t)m->t.size();
     const bool nt = streaming(m);
     if (d_out_alive) {
-        if (!flags_zeroed) zero_flags(ctx, m, d_out_alive, d_in_alive);
+        zero_flags(ctx, m, d_out_alive, d_in_alive);
         ProfileScope p(ctx, K_MASK_SCAN);
         auto k = nt ? mask_scan_kernel<true, true, true> : mask_scan_kernel<true, true, false>;
         k<<<m->n_tiles, BLOCK, 0, ctx->stream>>>(b.tens, b.tile_prefix, n_t, d_w, d_thr, d_w_out,

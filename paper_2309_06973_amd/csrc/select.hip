@@ -11,14 +11,6 @@
 //           mass ties the first stage lists every rank and the stages behind it return at once;
 //   final   one block per rank ranks its list and writes the record.
 //
-// A step on an arena that fits the last-level cache ranks the same way (STEP): the top histogram and
-// one stage that only lists; a rank whose window does not fit its list, or (several counts) whose
-// threshold more than STEP_TIES weights share, is left undecided, and the host redoes the step
-// through the form that needs no decision.  Against the sampled single pass (sample, predict, counting
-// pass with candidates of a tenth of the weights, three finishing launches) it reads the arena
-// twice, from the cache, but has three launches for six and no candidates to speak of:
-// the ranking of ten counts of 14.7 M weights 89 -> 44 us, twenty of 25.5 M 127 -> 88, one of 24 k 42 -> 19.
-//
 // The launches are the same for every input (their number follows from N and K alone), so the
 // calls can be recorded into a graph.  What bounds it: two reads of the arena, and one launch
 // after the other around them (about 5 us each, 3 for a stage with nothing to do).  The form it replaces - a
@@ -123,18 +115,10 @@ __device__ __forceinline__ void sel_walk(const DevTensor* __restrict__ tens, con
     }
 }
 
-// z: arrays that the steps behind the ranking want cleared (see SampleZero).
 __global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(
     const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix, uint32_t n_t, uint32_t n_tiles,
-    const float* __restrict__ w, uint32_t* nan_seen, uint32_t* ghist, SampleZero z) {
+    const float* __restrict__ w, SelState* st, uint32_t* ghist) {
     __shared__ uint32_t h[SEL_BINS];
-    {
-        const uint64_t tid = (uint64_t)blockIdx.x * SEL_THREADS + threadIdx.x;
-        const uint64_t stride = (uint64_t)gridDim.x * SEL_THREADS;
-        for (uint64_t i = tid; i < z.extra_n; i += stride) z.extra[i] = 0;
-        for (uint64_t i = tid; i < z.na; i += stride) z.fa[i] = 0;
-        for (uint64_t i = tid; i < z.nb; i += stride) z.fb[i] = 0;
-    }
     for (uint32_t i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) h[i] = 0;
     __syncthreads();
     uint32_t key_max = 0;
@@ -143,7 +127,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(
         key_max = max(key_max, key);
         atomicAdd(&h[sample_bin(key)], 1u);
     });
-    if (key_max > 0x7f800000u) *nan_seen = 1;
+    if (key_max > 0x7f800000u) st->nan_seen = 1;
     __syncthreads();
     // the blocks start at different segments: the populated bins are few and neighbours
     constexpr uint32_t SEGS = SEL_BINS / SEL_THREADS;
@@ -156,20 +140,19 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(
 
 // Stage `stage` (1 ..): every block first works out the windows from the histograms of the
 // stage before (the same in every block; the first one publishes them), then walks the arena.
-template <bool STEP>
 __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
     const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix, uint32_t n_t, uint32_t n_tiles,
     const float* __restrict__ w, SelState* st, uint32_t* ghist, uint2* __restrict__ lists, uint32_t list_cap,
-    uint32_t k, uint32_t g_bits, uint32_t stage, PruneCounts sorted) {
+    uint32_t k, uint32_t g_bits, uint32_t stage) {
     // bytes of the map: first leader whose window lies in that top bin
     __shared__ __align__(16) uint8_t s_map[SEL_BINS];
-    __shared__ uint32_t s_hist[STEP ? 1 : SEL_BINS];
+    __shared__ uint32_t s_hist[SEL_BINS];
     __shared__ __align__(16) uint2 s_pair[SEL_STAGE_CAP];
     __shared__ uint8_t s_of[SEL_STAGE_CAP];
     __shared__ SelWindow s_win[MAXK];
     __shared__ uint64_t smem[SEL_THREADS / 64 + 1];
     __shared__ uint32_t s_next[MAXK], s_cnt[MAXK], s_base[MAXK], s_n, s_left;
-    if (!STEP && stage > 1u && st->done[stage - 1u]) {
+    if (stage > 1u && st->done[stage - 1u]) {
         if (blockIdx.x == 0 && threadIdx.x == 0) st->done[stage] = 1;
         return;
     }
@@ -184,7 +167,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
         s_next[threadIdx.x] = NONE8;
     }
     if (threadIdx.x == 0) { s_n = 0; s_left = 0; }
-    if (STEP || stage == 1u) {
+    if (stage == 1u) {
         // sixteen bins per thread, their exclusive prefix over the block (in the room of the
         // pairs), then a search per rank
         uint64_t* base_of = reinterpret_cast<uint64_t*>(s_pair);
@@ -196,7 +179,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
         base_of[threadIdx.x] = block_excl_scan_u64<SEL_THREADS>(sum, smem, &tot);
         __syncthreads();
         if (threadIdx.x < k) {
-            const uint64_t r = STEP ? sorted.p[threadIdx.x] : st->p[threadIdx.x];
+            const uint64_t r = st->p[threadIdx.x];
             if (r != 0 && r <= tot) {
                 uint32_t a = 0, b = SEL_THREADS;              // last thread whose base is below r
                 while (b - a > 1u) {
@@ -263,8 +246,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
     // no window in a top bin yet
     static_assert(SEL_BINS == 16u * SEL_THREADS, "one 16-byte piece of the map per thread");
     reinterpret_cast<uint4*>(s_map)[threadIdx.x] = make_uint4(~0u, ~0u, ~0u, ~0u);
-    if (!STEP)
-        for (uint32_t i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) s_hist[i] = 0;
+    for (uint32_t i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) s_hist[i] = 0;
     __syncthreads();
     // leaders: the ranks are sorted, so equal windows are neighbours; windows that share a top
     // bin are chained
@@ -285,7 +267,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
             const uint32_t mode = W.cnt <= list_cap ? SEL_LISTED : SEL_SPLIT;
             s_win[lane].leader = leader;
             s_win[lane].mode = mode;
-            if (opens && !(STEP && mode == SEL_SPLIT)) {
+            if (opens) {
                 if (before && prev_top == top) s_next[prev] = lane; else s_map[top] = (uint8_t)lane;
             }
             if (mode == SEL_SPLIT) s_left = 1;
@@ -293,16 +275,12 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
     }
     __syncthreads();
     if (blockIdx.x == 0) {
-        if (STEP && threadIdx.x == 0) {                 // the NaN word moves on and is clear for the next step
-            st->nan_step = st->nan_raw;
-            st->nan_raw = 0;
-        }
         if (threadIdx.x < k) {
             const SelWindow W = s_win[threadIdx.x];
-            if (!STEP) st->win[stage][threadIdx.x] = W;
-            if (STEP || W.mode == SEL_LISTED) st->fin[threadIdx.x] = W;
+            st->win[stage][threadIdx.x] = W;
+            if (W.mode == SEL_LISTED) st->fin[threadIdx.x] = W;
         }
-        if (!STEP && threadIdx.x == 0) st->done[stage] = s_left ? 0u : 1u;
+        if (threadIdx.x == 0) st->done[stage] = s_left ? 0u : 1u;
     }
     sel_walk(tens, tile_prefix, n_t, n_tiles, w, [&](uint32_t wbits, uint32_t g) {
         const uint32_t key = wbits & 0x7fffffffu;
@@ -315,7 +293,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
             if (s == NONE8) return;
             d = comp - s_win[s].c_lo;
         }
-        if (!STEP && s_win[s].mode == SEL_SPLIT) {
+        if (s_win[s].mode == SEL_SPLIT) {
             atomicAdd(&s_hist[(s << bits) + (uint32_t)(d >> sel_shift(s_win[s].width, bits, g_bits))], 1u);
             return;
         }
@@ -342,7 +320,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
         if (at < list_cap) lists[(size_t)s * list_cap + at] = make_uint2(wbits, g);
     });
     __syncthreads();
-    if (!STEP && s_left) {
+    if (s_left) {
         uint32_t* out = ghist + (size_t)stage * SEL_BINS;
         for (uint32_t i = threadIdx.x; i < (k << bits); i += SEL_THREADS) {
             const uint32_t c = s_hist[i];
@@ -373,14 +351,11 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
 }
 
 // One block per rank: the record from its list.
-// Leaves the top histogram and the lists' lengths cleared: a step's ranking starts from that.
 __global__ __launch_bounds__(SEL_THREADS) void sel_final_kernel(
-    SelState* __restrict__ st, uint32_t* ghist, const uint2* __restrict__ lists, uint32_t list_cap,
+    const SelState* __restrict__ st, const uint2* __restrict__ lists, uint32_t list_cap,
     shifter_threshold* __restrict__ thr) {
     __shared__ RankShared<SEL_THREADS> sh;
     const uint32_t q = blockIdx.x;
-    for (uint32_t i = q * SEL_THREADS + threadIdx.x; i < SEL_BINS; i += gridDim.x * SEL_THREADS) ghist[i] = 0;
-    if (q == 0 && threadIdx.x < MAXK) st->list_cnt[threadIdx.x] = 0;
     shifter_threshold out;
     out.cut = 0; out.t_key = 0; out.reserved = 0; out.g_cut = ~0ull; out.n_less = 0; out.n_equal = 0;
     out.n_prune = st->p[q];
@@ -399,50 +374,6 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_final_kernel(
         }
     }
     if (threadIdx.x == 0) thr[st->perm[q]] = out;
-}
-
-// The records of a step, one block per rank, with their mirrors in pinned host memory and the rank's
-// status word there (bit 0 undecided, bit 1 NaN, bit 2: too many equal weights, not a matter of
-// wider intervals).  Leaves the top histogram and the lists' lengths cleared for the next ranking.  An undecided rank leaves its record as it is; one without a limit on ties (the
-// one-count step) removes everything, so that what runs behind it before the host redoes the
-// step writes nothing that the redone step does not.
-__global__ __launch_bounds__(SEL_THREADS) void sel_step_final_kernel(
-    SelState* st, uint32_t* ghist, const uint2* __restrict__ lists, uint32_t list_cap, PruneCounts sorted, MultiPerm perm,
-    uint32_t k, uint64_t ties_max, shifter_threshold* __restrict__ thr, shifter_threshold* __restrict__ host_rec,
-    uint32_t* __restrict__ host_status) {
-    __shared__ RankShared<SEL_THREADS> sh;
-    const uint32_t q = blockIdx.x;
-    for (uint32_t i = q * SEL_THREADS + threadIdx.x; i < SEL_BINS; i += gridDim.x * SEL_THREADS) ghist[i] = 0;
-    if (q == 0 && threadIdx.x < MAXK) st->list_cnt[threadIdx.x] = 0;
-    const uint32_t nan_bit = st->nan_step && sorted.p[k - 1u] != 0 ? 2u : 0u;   // sorted: some count is not zero
-    shifter_threshold out;
-    out.cut = 0; out.t_key = 0; out.reserved = 0; out.g_cut = ~0ull; out.n_less = 0; out.n_equal = 0;
-    out.n_prune = sorted.p[q];
-    const bool alone = ties_max == ~0ull;
-    bool decided = true;
-    if (out.n_prune != 0) {
-        const SelWindow W = st->fin[q];
-        decided = W.mode == SEL_LISTED &&
-                  rank_in_list<SEL_THREADS, 8>(lists + (size_t)W.leader * list_cap, min((uint32_t)W.cnt, list_cap), W.c_lo,
-                                               W.width, W.r, sh) &&
-                  sh.eq <= ties_max;
-        if (decided) {
-            out.cut = sh.sel + 1;
-            out.t_key = (uint32_t)(sh.sel >> 32);
-            out.g_cut = sh.sel & 0xffffffffull;
-            out.n_less = W.less + sh.lt;
-            out.n_equal = sh.eq;
-        } else if (alone) {
-            out.cut = ~0ull;
-        }
-    }
-    if (threadIdx.x == 0) {
-        if (decided || alone) {
-            thr[perm.v[q]] = out;
-            host_rec[perm.v[q]] = out;
-        }
-        host_status[q] = nan_bit | (decided ? 0u : 5u);
-    }
 }
 
 // Stages that certainly suffice: a window of the widest kind is split until no more weights
@@ -488,47 +419,16 @@ void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float*
     }
     {
         ProfileScope p(ctx, K_HIST0);
-        sel_top_kernel<<<grid, SEL_THREADS, 0, s>>>(tb.tens, tb.tile_prefix, n_t, n_tiles, d_w, &tb.sel->nan_seen,
-                                                    tb.ghist, SampleZero());
+        sel_top_kernel<<<grid, SEL_THREADS, 0, s>>>(tb.tens, tb.tile_prefix, n_t, n_tiles, d_w, tb.sel, tb.ghist);
     }
     for (uint32_t stage = 1; stage <= stages; ++stage) {
         ProfileScope p(ctx, K_SEL_STAGE);
-        sel_stage_kernel<false><<<grid, SEL_THREADS, 0, s>>>(tb.tens, tb.tile_prefix, n_t, n_tiles, d_w, tb.sel, tb.ghist,
-                                                             tb.lists, list_cap, k, g_bits, stage, sorted);
+        sel_stage_kernel<<<grid, SEL_THREADS, 0, s>>>(tb.tens, tb.tile_prefix, n_t, n_tiles, d_w, tb.sel, tb.ghist,
+                                                      tb.lists, list_cap, k, g_bits, stage);
     }
     {
         ProfileScope p(ctx, K_SEL_FINAL);
-        sel_final_kernel<<<k, SEL_THREADS, 0, s>>>(tb.sel, tb.ghist, tb.lists, list_cap, d_thr);
-    }
-}
-
-// The ranking of a step: k counts sorted ascending (zeros first), perm their original positions.
-// The histogram, the lists' lengths and the NaN word are zero before (allocated so, and every
-// ranking leaves them so).
-void launch_step_ranking(shifter_ctx* ctx, const shifter_model* m, const float* d_w, const PruneCounts& sorted,
-                         const MultiPerm& perm, uint32_t k, uint64_t ties_max, shifter_threshold* d_thr,
-                         const SampleZero& z) {
-    const auto& b = m->b;
-    const uint32_t n_t = (uint32_t)m->t.size(), n_tiles = m->n_tiles;
-    hipStream_t s = ctx->stream;
-    const uint32_t list_cap = (uint32_t)std::min<uint64_t>((uint64_t)b.cand_cap_sb * SPEC_SUB / k, 1u << 20);
-    // as many blocks as make the blocks' shares equal
-    const uint32_t groups = std::max(1u, (n_tiles + SEL_GROUPS - 1) / SEL_GROUPS);
-    const uint32_t rounds = (groups + ctx->hist_grid - 1) / ctx->hist_grid;
-    const uint32_t grid = (groups + rounds - 1) / rounds;
-    {
-        ProfileScope p(ctx, K_HIST0);
-        sel_top_kernel<<<grid, SEL_THREADS, 0, s>>>(b.tens, b.tile_prefix, n_t, n_tiles, d_w, &b.sel->nan_raw, b.ghist, z);
-    }
-    {
-        ProfileScope p(ctx, K_SEL_STAGE);
-        sel_stage_kernel<true><<<grid, SEL_THREADS, 0, s>>>(b.tens, b.tile_prefix, n_t, n_tiles, d_w, b.sel, b.ghist,
-                                                            b.cand, list_cap, k, 32, 1, sorted);
-    }
-    {
-        ProfileScope p(ctx, K_SEL_FINAL);
-        sel_step_final_kernel<<<k, SEL_THREADS, 0, s>>>(b.sel, b.ghist, b.cand, list_cap, sorted, perm, k, ties_max, d_thr,
-                                                        b.dev_multi_rec, b.dev_multi_status);
+        sel_final_kernel<<<k, SEL_THREADS, 0, s>>>(tb.sel, tb.lists, list_cap, d_thr);
     }
 }
 

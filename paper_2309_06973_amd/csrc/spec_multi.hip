@@ -295,7 +295,9 @@ template <bool NT>
 __global__ __launch_bounds__(BLOCK) void ms_pass_kernel(
     const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix, uint32_t n_t,
     const float* __restrict__ w, MultiState* ms, uint32_t* cnt, uint2* __restrict__ cand,
-    const uint8_t* __restrict__ tab) {
+    const uint8_t* __restrict__ tab, uint32_t* zero_ptr, uint32_t zero_n) {
+    // an array the step behind this pass wants cleared (or nullptr)
+    for (uint32_t i = blockIdx.x * BLOCK + threadIdx.x; i < zero_n; i += gridDim.x * BLOCK) zero_ptr[i] = 0;
     // s_hi1[j] = hi_(j-1) + 1, s_hi1[0] = 0: a weight with j lower ends at or below it is a
     // candidate (of the cluster ending at rank j - 1) iff key < s_hi1[j]
     __shared__ uint32_t s_lo[MAXK + 1], s_hi1[MAXK + 1];
@@ -1006,7 +1008,8 @@ __global__ __launch_bounds__(BLOCK) void ms_fixup_kernel(
 
 void launch_spec_multi(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
                        const PruneCounts& sorted_p, const MultiPerm& perm, uint32_t k,
-                       uint64_t zero_mask, shifter_threshold* d_thr, const FusedBatch* fb) {
+                       uint64_t zero_mask, shifter_threshold* d_thr, const FusedBatch* fb,
+                       uint32_t* zero_ptr, uint32_t zero_n) {
     const auto& b = m->b;
     const uint32_t n_t = (uint32_t)m->t.size();
     hipStream_t s = ctx->stream;
@@ -1031,7 +1034,10 @@ void launch_spec_multi(shifter_ctx* ctx, const shifter_model* m, const float* d_
             b.multi, b.shist, b.multi_cnt, sorted_p, perm, k, m->sample_size, zero_mask, d_thr,
             b.dev_multi_rec, m->info.n_prunable, ctx->margin_sigmas, b.multi_tab, b.cand_cap_sb);
     }
-    if (k == 0 && !fb) return;   // every count was zero
+    if (k == 0 && !fb) {         // every count was zero: no pass, which would have cleared zero_ptr
+        if (zero_ptr) launch_zero_levels(ctx, m);
+        return;
+    }
     const bool nt = m->info.w_extent * 4 > (192ull << 20);
     if (fb) {
         VariantRanks rv;
@@ -1048,7 +1054,7 @@ void launch_spec_multi(shifter_ctx* ctx, const shifter_model* m, const float* d_
         ProfileScope ps(ctx, K_SPEC_PASS);
         auto kern = nt ? ms_pass_kernel<true> : ms_pass_kernel<false>;
         kern<<<m->n_tiles, BLOCK, (k + 1) * BLOCK, s>>>(
-            b.tens, b.tile_prefix, n_t, d_w, b.multi, b.multi_cnt, b.cand, b.multi_tab);
+            b.tens, b.tile_prefix, n_t, d_w, b.multi, b.multi_cnt, b.cand, b.multi_tab, zero_ptr, zero_n);
     }
     if (k != 0) {
         {
