@@ -332,7 +332,7 @@ extern "C" int shifter_model_create(const shifter_tensor_desc* tensors, uint32_t
         if (tensors[i].prunable) m->ranked_ids.push_back(i);
     m->n_ranked = (uint32_t)m->ranked_ids.size();
     // the single-pass selection samples one 16-weight sector per 1024 weights of every
-    // sample_tile_stride-th tile (see spec_sample_kernel); its size is fixed by the
+    // sample_tile_stride-th tile (see spec_sample.h); its size is fixed by the
     // descriptors.  N / 64 samples for models up to 164 M weights; beyond that 40000
     // tiles (2.6 M samples), and from 1.3 G weights on every 8th tile: the candidate
     // interval is about N / sqrt(samples) weights wide, and the finishing passes hold a
@@ -506,7 +506,7 @@ static int bind_tables(shifter_ctx* ctx, shifter_model* m) {
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.shist), sizeof(uint32_t) * 65536));
     HIP_TRY(ctx, hipMemset(b.shist, 0, sizeof(uint32_t) * 65536));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.spec_cnt), sizeof(uint32_t) * 2 * SPEC_SUB * 32));
-    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.partial), sizeof(uint32_t) * SPEC_FIN_BLOCKS * 256));
+    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.partial), sizeof(uint32_t) * 4 * 256));
     // candidate pairs: 1/4 of N in total (a 20-variant portfolio on a mid-size model makes
     // candidates of about a tenth of the weights), at least two tiles per sub-buffer
     b.cand_cap_sb = (uint32_t)std::max<uint64_t>(m->info.n_prunable / 4 / SPEC_SUB, 2 * TILE);
@@ -518,7 +518,7 @@ static int bind_tables(shifter_ctx* ctx, shifter_model* m) {
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.multi_hist), sizeof(uint32_t) * MAXK * 256));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.multi_list),
                            sizeof(uint2) * (size_t)SPEC_MULTI_MAXK * SPEC_LIST_CAP));
-    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.multi_list_cnt), sizeof(uint32_t) * MAXK));
+    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.multi_list_cnt), sizeof(uint32_t) * 3 * MAXK));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.multi_rowsum), sizeof(uint64_t) * (MAXK + 1)));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.below),
                            sizeof(uint32_t) * MAXK * (m->info.sum_group_width + m->g.size())));

@@ -95,26 +95,20 @@ struct SpecState {
     uint32_t status;     // bit 0: not decided, use the multi-pass select; bit 1: NaN seen
     uint32_t bin, bin_cnt;
     uint32_t list_cnt;
-    uint32_t pad;
+    uint32_t ticket;     // blocks of the finish that are done with the list
     shifter_threshold rec;   // copy of the record written to the caller's d_thr (one read-back)
 };
 
 // State of the single-pass selection for all prune counts of a portfolio (ranks sorted by
 // prune count, zero counts left out).
 constexpr uint32_t SPEC_MULTI_MAXK = 32;   // LDS of the fused pass's private counters: 256 B per rank
-// What the finish of one rank reads (written by the predict kernel) and what its filter step
-// leaves for its last step: one cache line each instead of a line per field.
+// What the finish of one rank reads (written by the prediction): one cache line instead of a
+// line per field.
 struct RankIn {
     uint64_t p;
     uint32_t lo, sh;                       // its cluster's interval start; the first histogram's shift (256 bins)
     uint32_t clast, cand_off, cand_cap;    // its cluster's last rank and candidate region
     uint32_t perm;                         // original position of this rank
-};
-struct RankOut {
-    uint64_t r2, less;     // rank of the P-th pair inside the selected bin; weights below that bin
-    uint32_t bin, bin_cnt;
-    uint32_t fail;         // why the finish gave up (0: it has not)
-    uint32_t pad;
 };
 struct MultiState {
     uint64_t p[MAXK];
@@ -124,7 +118,6 @@ struct MultiState {
     uint32_t clast[MAXK];  // last rank of rank k's cluster: the owner of the cluster's candidate region
     uint32_t cand_off[MAXK], cand_cap[MAXK];   // region of the cluster ending at rank k: first pair, pairs per part
     RankIn rin[MAXK];
-    RankOut rout[MAXK];
     uint32_t k, m_valid, status, pad;
 };
 struct MultiPerm {
@@ -256,7 +249,7 @@ struct shifter_model {
         shifter::SpecState* spec = nullptr;
         uint32_t* shist = nullptr;            // 65536 sample bins
         uint32_t* spec_cnt = nullptr;         // 2 * SPEC_SUB counters, one 128-byte line each
-        uint32_t* partial = nullptr;          // SPEC_FIN_BLOCKS * 256 partial histograms
+        uint32_t* partial = nullptr;          // 4 * 256: copies of the candidates' histogram
         uint2* cand = nullptr;                // SPEC_SUB sub-buffers of (key, g) pairs
         uint32_t cand_cap_sb = 0;             // pairs per sub-buffer
         uint2* list = nullptr;                // SPEC_LIST_CAP pairs
@@ -267,7 +260,7 @@ struct shifter_model {
         uint32_t* multi_hist = nullptr;       // MAXK * 256: the clusters' first histograms
         uint64_t* multi_rowsum = nullptr;     // MAXK + 1: totals of the split counters' rows
         uint2* multi_list = nullptr;          // SPEC_MULTI_MAXK * SPEC_LIST_CAP pairs: the ranks' selected bins
-        uint32_t* multi_list_cnt = nullptr;   // MAXK
+        uint32_t* multi_list_cnt = nullptr;   // 3 * MAXK: the lists' lengths, the finish's tickets, why it gave up
         uint32_t* below = nullptr;            // MAXK * (sum_group_width + n_groups): survivors below a channel
         uint8_t* host_stage = nullptr;        // pinned, for small read-backs
         // pinned mirrors of the one-count selection's state, written by its last kernel: one
@@ -382,29 +375,6 @@ static_assert(sizeof(DevTensor) <= 256, "the one-tensor table fits its slot");
 void launch_spec_select(shifter_ctx* ctx, const shifter_model* m, const float* d_w, uint64_t p,
                         shifter_threshold* d_thr, float* d_w_out, uint8_t* d_mask,
                         uint8_t* d_out_alive, uint8_t* d_in_alive, SpecState* host_mirror);
-// Scratch of the K-rank ranking that the sample kernel clears on the way (cnt == nullptr:
-// nothing): the split counters' rows in use, the clusters' histograms, the list lengths
-// and the finish's per-rank outcome.
-struct SampleZero {
-    uint32_t* cnt = nullptr;
-    uint32_t k = 0;
-    uint32_t* ghist = nullptr;
-    uint32_t* list_cnt = nullptr;
-    RankOut* rout = nullptr;
-    uint32_t* extra = nullptr;     // one more array of extra_n words to clear
-    uint32_t extra_n = 0;
-    // the one-count selection: its state to set up, its split counters and the caller's
-    // flag arrays to clear (ss == nullptr: not this call)
-    shifter::SpecState* ss = nullptr;
-    uint32_t* cnt1 = nullptr;
-    uint64_t p = 0;
-    uint32_t m_valid = 0;
-    uint8_t* fa = nullptr;
-    uint8_t* fb = nullptr;
-    uint64_t na = 0, nb = 0;
-};
-void launch_spec_sample(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
-                        const SampleZero& z = SampleZero());
 // Outputs of the fused portfolio pass (steps 1-3 in one read): k_all variants in caller order.
 struct FusedBatch {
     uint32_t k_all;

@@ -10,13 +10,11 @@
 //   x is a candidate  <=>  j >= 1 and x <= hi_{j-1}; it belongs to the cluster whose last
 //                          rank is j - 1
 // so one search per weight replaces K interval tests.  The pass appends a candidate to the
-// region of its cluster (split 256 ways by block, one reservation per block and cluster);
-// the finish is one launch, one block per rank, which walks its cluster's region.
-#include "dev_common.h"
+// region of its cluster (split CAND_SUB ways by block, one reservation per block and cluster).
+#include "spec_sample.h"
 
 namespace shifter {
 
-constexpr uint32_t MS_BINS = SAMPLE_BINS;   // sample histogram bins (sample_bin)
 constexpr uint32_t TAB_SHIFT = 19;       // the pass's bucket table: 4096 buckets of 2^19 keys
 constexpr uint32_t TAB_SIZE = 1u << (31 - TAB_SHIFT);
 // The counters all blocks add to are split CAND_SUB ways by block (one 128-byte line per
@@ -51,37 +49,37 @@ __device__ __forceinline__ uint32_t count_lower_ends(const uint32_t* s_lo, uint3
     return j + (s_lo[j] <= key ? 1u : 0u);
 }
 
-// One block.  First the set-up of a ranking (the state, the zero-count records; the sample
-// histogram is read into registers and cleared for the next call), then the
-// inclusive prefix of the sample histogram in LDS, for every rank the interval from the
-// sample's order statistics at P/N -/+ margin, monotone ends, clusters, and each cluster's
-// share of the candidate buffer.
+// Sample and prediction in one launch.  On the way the scratch of the kernels behind it is cleared: the
+// split counters' rows in use, the clusters' histograms, the finish's per-rank words and one
+// more array of the caller's.
+// The block that ends last sets up the ranking (the state, the zero-count records) and works out,
+// for every rank, the interval from the sample's order statistics at P/N -/+ margin, monotone
+// ends, clusters, and each cluster's share of the candidate buffer.
 // sorted_p / perm: the k prune counts > 0 in ascending order and their original positions;
 // zero_mask: bit i set = original position i asked for P = 0 and gets its record here.
-constexpr uint32_t PREDICT_THREADS = 1024;
-
-__global__ __launch_bounds__(PREDICT_THREADS) void ms_predict_kernel(
-    MultiState* ms, uint32_t* shist, uint32_t* cnt, PruneCounts sorted_p, MultiPerm perm,
-    uint32_t k_var, uint32_t m, uint64_t zero_mask, shifter_threshold* thr,
+__global__ __launch_bounds__(SAMPLE_THREADS) void ms_front_kernel(
+    SampleIn sample, MultiState* ms, uint32_t* __restrict__ cnt, uint32_t* __restrict__ ghist,
+    uint32_t* __restrict__ rank_words, uint32_t* __restrict__ extra, uint32_t extra_n, PruneCounts sorted_p,
+    MultiPerm perm, uint32_t k_var, uint32_t m, uint64_t zero_mask, shifter_threshold* thr,
     shifter_threshold* host_rec, uint64_t n_prunable, double margin_sigmas,
     uint8_t* __restrict__ tab, uint32_t cap_sb_total) {
-    constexpr uint32_t SEG = 256, NSEG = MS_BINS / SEG, WAVES = PREDICT_THREADS / 64;
-    static_assert(NSEG == 64, "one segment per lane in the scan of the segment sums");
-    __shared__ uint32_t prefix[MS_BINS];          // 64 KB
-    __shared__ uint32_t seg_sum[NSEG];
-    __shared__ uint32_t s_total;
-    __shared__ uint32_t s_lo[MAXK];
+    __shared__ __align__(16) uint32_t prefix[SAMPLE_BINS];          // 64 KB
+    __shared__ uint32_t s_lo[MAXK], s_bins[3][64];
+    {
+        // rows 0 .. k and MAXK + 1 .. MAXK + k of the split counters (the first word of each
+        // 128-byte line)
+        const uint32_t tid = blockIdx.x * SAMPLE_THREADS + threadIdx.x, nthr = gridDim.x * SAMPLE_THREADS;
+        for (uint32_t i = tid; i < (2u * k_var + 1u) * SPEC_SUB; i += nthr) {
+            const uint32_t row = i / SPEC_SUB, sb = i % SPEC_SUB;
+            const uint32_t r = row <= k_var ? row : MAXK + 1u + (row - (k_var + 1u));
+            cnt[((size_t)r * SPEC_SUB + sb) * 32u] = 0;
+        }
+        for (uint32_t i = tid; i < k_var * 256u; i += nthr) ghist[i] = 0;
+        for (uint32_t i = tid; i < extra_n; i += nthr) extra[i] = 0;
+        if (tid < 3u * MAXK) rank_words[tid] = 0;
+    }
+    if (k_var != 0 && !sample_prefix(sample, prefix)) return;     // no rank: one block, no sample
     const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
-    constexpr uint32_t PER_WAVE = NSEG / WAVES;   // segments per wavefront
-    // each wavefront's segments are loaded once, all loads in flight together; the bins
-    // are then cleared: the next ranking's sample adds to them
-    uint4 x[PER_WAVE];
-#pragma unroll
-    for (uint32_t i = 0; i < PER_WAVE; ++i)
-        x[i] = reinterpret_cast<const uint4*>(shist + (wid + i * WAVES) * SEG)[lane];
-#pragma unroll
-    for (uint32_t i = 0; i < PER_WAVE; ++i)
-        reinterpret_cast<uint4*>(shist + (wid + i * WAVES) * SEG)[lane] = make_uint4(0, 0, 0, 0);
     if (threadIdx.x < MAXK) {
         const uint32_t t = threadIdx.x;
         ms->p[t] = t < k_var ? sorted_p.p[t] : 0;
@@ -108,65 +106,27 @@ __global__ __launch_bounds__(PREDICT_THREADS) void ms_predict_kernel(
         ms->status = 0;
     }
     if (k_var == 0) return;
-    const uint64_t p = threadIdx.x < k_var ? sorted_p.p[threadIdx.x] : 0;
-    // phase 1: segment sums, then their exclusive scan by the first wavefront
-#pragma unroll
-    for (uint32_t i = 0; i < PER_WAVE; ++i) {
-        uint32_t v = x[i].x + x[i].y + x[i].z + x[i].w;
-        for (uint32_t d = 32; d > 0; d >>= 1) v += __shfl_down(v, d, 64);
-        if (lane == 0) seg_sum[wid + i * WAVES] = v;
+    // rank k in lane k (k_var <= 64); the low end, the high end and the centre by a wavefront each
+    const uint32_t total = prefix[SAMPLE_BINS - 1u];
+    const uint64_t p = lane < k_var ? sorted_p.p[lane] : 0;
+    const bool use = lane < k_var && p > 0 && m >= 256 && n_prunable > 0 && total == m;
+    double r_lo = 0, r_hi = 0;
+    if (wid < 3 && use) {
+        const double frac = (double)p / (double)n_prunable;
+        const double centre = frac * (double)m;
+        const double delta = margin_sigmas * sqrt((double)m * frac * (1.0 - frac)) + 16.0;
+        r_lo = centre - delta;
+        r_hi = centre + delta;
+        const double r = wid == 0 ? r_lo : wid == 1 ? r_hi : min(max(centre, 0.0), (double)(m - 1));
+        s_bins[wid][lane] = sample_bin_of_rank(prefix, r > 0.0 ? (uint32_t)min(r, (double)(m - 1)) : 0u);
     }
     __syncthreads();
-    if (wid == 0) {
-        const uint32_t v = seg_sum[lane];
-        uint32_t incl = v;
-        for (uint32_t d = 1; d < 64; d <<= 1) {
-            const uint32_t y = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += y;
-        }
-        seg_sum[lane] = incl - v;                 // exclusive segment base
-        if (lane == 63) s_total = incl;
-    }
-    __syncthreads();
-    const uint64_t total = s_total;
-    // phase 2: inclusive prefix per bin
-#pragma unroll
-    for (uint32_t i = 0; i < PER_WAVE; ++i) {
-        const uint32_t sg = wid + i * WAVES;
-        const uint32_t mine4 = x[i].x + x[i].y + x[i].z + x[i].w;
-        uint32_t incl = mine4;
-        for (uint32_t d = 1; d < 64; d <<= 1) {
-            const uint32_t y = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += y;
-        }
-        uint32_t run = seg_sum[sg] + incl - mine4;
-        uint32_t* out = prefix + sg * SEG + lane * 4;
-        run += x[i].x; out[0] = run;
-        run += x[i].y; out[1] = run;
-        run += x[i].z; out[2] = run;
-        run += x[i].w; out[3] = run;
-    }
-    __syncthreads();
-    // the first wavefront: lane k takes rank k (k_var <= 64)
     if (wid == 0) {
         uint32_t lo = 0, hi = 0x7fffffffu, mid = 0;
-        if (lane < k_var && p > 0 && m >= 256 && n_prunable > 0 && total == m) {
-            const double frac = (double)p / (double)n_prunable;
-            const double centre = frac * (double)m;
-            const double delta = margin_sigmas * sqrt((double)m * frac * (1.0 - frac)) + 16.0;
-            auto bin_of = [&](double r) -> uint32_t {   // first bin with prefix > r
-                const uint32_t target = (uint32_t)r;
-                uint32_t a = 0, b = MS_BINS - 1;
-                while (a < b) {
-                    const uint32_t mid = (a + b) >> 1;
-                    if (prefix[mid] > target) b = mid; else a = mid + 1;
-                }
-                return a;
-            };
-            const double r_lo = centre - delta, r_hi = centre + delta;
-            if (r_lo > 0.0) lo = sample_bin_first_key(bin_of(r_lo));
-            if (r_hi < (double)(m - 1)) hi = sample_bin_last_key(bin_of(r_hi));
-            mid = sample_bin_first_key(bin_of(min(max(centre, 0.0), (double)(m - 1))));
+        if (use) {
+            if (r_lo > 0.0) lo = sample_bin_first_key(s_bins[0][lane]);
+            if (r_hi < (double)(m - 1)) hi = sample_bin_last_key(s_bins[1][lane]);
+            mid = sample_bin_first_key(s_bins[2][lane]);
         }
         // widen so that both ends are non-decreasing in k (ranks are sorted by P): a running
         // maximum of hi from the left, a running minimum of lo from the right; lanes past
@@ -245,7 +205,7 @@ __global__ __launch_bounds__(PREDICT_THREADS) void ms_predict_kernel(
     // above that inside the bucket (3: three or more).  With a few dozen ranks almost every
     // bucket holds none, and a weight's j is then the entry itself.
     __syncthreads();
-    constexpr uint32_t PER_THREAD = TAB_SIZE / PREDICT_THREADS;
+    constexpr uint32_t PER_THREAD = TAB_SIZE / SAMPLE_THREADS;
     uint32_t j0[PER_THREAD], inside[PER_THREAD];
 #pragma unroll
     for (uint32_t i = 0; i < PER_THREAD; ++i) j0[i] = inside[i] = 0;
@@ -253,7 +213,7 @@ __global__ __launch_bounds__(PREDICT_THREADS) void ms_predict_kernel(
         const uint32_t lo = s_lo[k];
 #pragma unroll
         for (uint32_t i = 0; i < PER_THREAD; ++i) {
-            const uint32_t first = (threadIdx.x + i * PREDICT_THREADS) << TAB_SHIFT;
+            const uint32_t first = (threadIdx.x + i * SAMPLE_THREADS) << TAB_SHIFT;
             const uint32_t last = first + ((1u << TAB_SHIFT) - 1u);
             j0[i] += lo <= first ? 1u : 0u;
             inside[i] += (lo > first && lo <= last) ? 1u : 0u;
@@ -261,7 +221,7 @@ __global__ __launch_bounds__(PREDICT_THREADS) void ms_predict_kernel(
     }
 #pragma unroll
     for (uint32_t i = 0; i < PER_THREAD; ++i)
-        tab[threadIdx.x + i * PREDICT_THREADS] = (uint8_t)(j0[i] | (min(inside[i], 3u) << 6));
+        tab[threadIdx.x + i * SAMPLE_THREADS] = (uint8_t)(j0[i] | (min(inside[i], 3u) << 6));
 }
 
 // Appends the candidates a block found to the regions of their clusters: count per cluster
@@ -426,18 +386,22 @@ __global__ __launch_bounds__(BLOCK) void ms_pass_kernel(
     if (threadIdx.x == 0 && s_nan) atomicOr(&ms->status, 2u);
 }
 
-// The finish, three launches over the candidates.
+// The finish, two launches over the candidates.
 //   hist    grid (part, rank): a 256-bin histogram of (key - lo) >> sh over one part of a
 //           cluster's region, added to the cluster's histogram in global memory;
-//   filter  grid (part, rank): every block first locates its rank - totals of the split
+//   finish  grid (part, rank): every block first locates its rank - totals of the split
 //           counters, the check that makes the result exact (below < P <= below + candidates
 //           of the cluster), the bin holding the P-th pair - and then moves its part's pairs
-//           of that bin to the rank's list (one reservation per block);
-//   rank    one block per rank: refines the list with 4096-bin histograms until a bin holds
+//           of that bin to the rank's list (one reservation per block).  The rank's block that
+//           ends last refines the list with 4096-bin histograms until a bin holds
 //           at most FIN_LIST pairs, ranks those exactly by counting and writes the record,
 //           to d_thr and to its mirror in pinned host memory, with the rank's status word
 //           (bit 0: could not decide; bit 1: NaN; bit 2: a buffer was full or too many
 //           weights share the threshold's key - wider intervals would not help).
+// What bounds it is the chain of latencies: the counters, the histogram and the part's first
+// candidates are loaded before the first of them is used, the sums are taken side by side by
+// different wavefronts, and the ranking costs no launch of its own (filter + rank of fifteen ranks
+// on 0.86 M weights 11.9 + 6.6 us, 18.1 as one; of eight on 10 M 9.3 + 6.7 and 11.9).
 constexpr uint32_t MF_THREADS = 1024, MF_DEPTH = 8;
 constexpr uint32_t MF_BINS1 = 256;
 constexpr uint32_t MF_STAGE = 2048;      // pairs of the selected bin one filter block may hold
@@ -487,7 +451,7 @@ __global__ __launch_bounds__(MF_THREADS) void ms_hist_kernel(
     __syncthreads();
     const uint32_t lo = R.lo, sh = R.sh;
     ms_walk(cand + (size_t)R.cand_off + (size_t)part * cap, n,
-            [&](uint2 c) { atomicAdd(&h[((c.x & 0x7fffffffu) - lo) >> sh], 1u); });
+            [&](uint2 c) { lds_count(h, ((c.x & 0x7fffffffu) - lo) >> sh, true); });
     __syncthreads();
     if (threadIdx.x < MF_BINS1) {
         const uint32_t c = h[threadIdx.x];
@@ -495,115 +459,142 @@ __global__ __launch_bounds__(MF_THREADS) void ms_hist_kernel(
     }
 }
 
-__global__ __launch_bounds__(MF_THREADS) void ms_filter_kernel(
+__global__ __launch_bounds__(MF_THREADS) void ms_finish_kernel(
     MultiState* ms, const uint32_t* __restrict__ cnt, const uint2* __restrict__ cand,
-    const uint32_t* __restrict__ ghist, const uint64_t* __restrict__ rowsum, uint2* __restrict__ list,
-    uint32_t* list_cnt) {
-    __shared__ uint64_t smem[MF_THREADS / 64 + 1];
-    __shared__ uint2 stage[MF_STAGE];
-    __shared__ uint32_t s_over, s_bin, s_found, s_n, s_base;
-    const uint32_t part = blockIdx.x, k = blockIdx.y;
-    const RankIn R = ms->rin[k];
-    const uint32_t cl = R.clast;
-    const uint64_t p = R.p;
-    const uint32_t cap = R.cand_cap;
-    const bool publish = part == 0;
-    if (threadIdx.x == 0) { s_over = 0; s_found = 0; s_n = 0; s_bin = 0; }
-    __syncthreads();
-    // weights below the cluster's interval: rows 0 .. k of the split counters
-    uint64_t below, inside;
-    {
-        const uint64_t b = threadIdx.x <= k ? rowsum[threadIdx.x] : 0;     // k < MAXK <= MF_THREADS
-        uint32_t c = 0;
-        if (threadIdx.x < CAND_SUB) {
-            c = cnt[((size_t)(MAXK + 1u + cl) * SPEC_SUB + threadIdx.x) * 32u];
-            if (c > cap) s_over = 1;
-        }
-        block_excl_scan_u64<MF_THREADS>(b, smem, &below);
-        block_excl_scan_u64<MF_THREADS>(c, smem, &inside);
-    }
-    __syncthreads();
-    uint32_t why = 0;
-    if (s_over) why = 5u;
-    else if (!(below < p && p <= below + inside)) why = 1u;
-    uint64_t r = 0, base = 0;
-    uint32_t c = 0;
-    if (!why) {
-        r = p - below;
-        c = threadIdx.x < MF_BINS1 ? ghist[cl * MF_BINS1 + threadIdx.x] : 0u;
-        uint64_t tot;
-        base = block_excl_scan_u64<MF_THREADS>(c, smem, &tot);
-        if (threadIdx.x < MF_BINS1 && base < r && r <= base + c) {
-            s_bin = threadIdx.x;
-            s_found = 1;
-            if (publish) {
-                RankOut* o = &ms->rout[k];
-                o->bin = threadIdx.x;
-                o->bin_cnt = c;
-                o->r2 = r - base;
-                o->less = below + base;
-                if (c > SPEC_LIST_CAP) atomicOr(&o->fail, 5u);
-            }
-        }
-        __syncthreads();
-        if (!s_found) why = 1u;       // cannot happen unless the buffers were disturbed
-    }
-    if (why) {
-        if (publish && threadIdx.x == 0) atomicOr(&ms->rout[k].fail, why);
-        return;
-    }
-    // this part's pairs of the selected bin -> the rank's list
-    const uint32_t n = min(cnt[((size_t)(MAXK + 1u + cl) * SPEC_SUB + part) * 32u], cap);
-    const uint32_t lo = R.lo, sh = R.sh, bin = s_bin;
-    ms_walk(cand + (size_t)R.cand_off + (size_t)part * cap, n, [&](uint2 x) {
-        if ((((x.x & 0x7fffffffu) - lo) >> sh) == bin) {
-            const uint32_t pos = atomicAdd(&s_n, 1u);
-            if (pos < MF_STAGE) stage[pos] = x;
-        }
-    });
-    __syncthreads();
-    const uint32_t m = s_n;
-    if (m > MF_STAGE) {
-        if (threadIdx.x == 0) atomicOr(&ms->rout[k].fail, 5u);
-        return;
-    }
-    if (m == 0) return;
-    if (threadIdx.x == 0) s_base = atomicAdd(&list_cnt[k], m);
-    __syncthreads();
-    uint2* dst = list + (size_t)k * SPEC_LIST_CAP;
-    for (uint32_t i = threadIdx.x; i < m; i += MF_THREADS)
-        if (s_base + i < SPEC_LIST_CAP) dst[s_base + i] = stage[i];
-}
-
-__global__ __launch_bounds__(FIN_THREADS) void ms_rank_kernel(
-    MultiState* ms, const uint2* __restrict__ list, const uint32_t* __restrict__ list_cnt,
+    const uint32_t* __restrict__ ghist, const uint64_t* __restrict__ rowsum, uint2* list, uint32_t* rank_words,
     shifter_threshold* thr, shifter_threshold* host_rec, uint32_t* host_status) {
+    static_assert(MF_THREADS == FIN_THREADS && MF_BINS1 == 4u * 64u && CAND_SUB <= 64u, "a wavefront for each sum");
+    __shared__ uint2 stage[MF_STAGE];
     __shared__ uint32_t h[FIN_BINS];
     __shared__ uint64_t comp[FIN_LIST];
     __shared__ uint64_t smem[FIN_THREADS / 64 + 1];
-    __shared__ uint64_t s_sel, s_base;
-    __shared__ uint32_t s_bin, s_cnt, s_lt, s_eq, s_nb;
-    const uint32_t k = blockIdx.x;
-    // everything this block needs from the state, fetched side by side
+    __shared__ uint64_t s_below, s_inside, s_r2, s_less, s_sel, s_base2;
+    __shared__ uint32_t s_over, s_n, s_base, s_bin, s_cnt, s_last, s_why, s_lt, s_eq, s_nb;
+    const uint32_t part = blockIdx.x, k = blockIdx.y;
+    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
     const RankIn R = ms->rin[k];
-    const RankOut O = ms->rout[k];
-    const uint32_t n = list_cnt[k];
     const uint32_t nan_bit = ms->status & 2u;      // the pass has ended
+    const uint32_t cl = R.clast, cap = R.cand_cap, lo = R.lo;
     const uint64_t p = R.p;
-    auto give_up = [&](uint32_t why) {
+    uint32_t *list_cnt = rank_words + k, *ticket = rank_words + MAXK + k, *fail = rank_words + 2u * MAXK + k;
+    const uint32_t* parts = cnt + (size_t)(MAXK + 1u + cl) * SPEC_SUB * 32u;
+    // this part's first candidates, on their way while the rank is located
+    const uint32_t n_part = min(parts[part * 32u], cap);
+    const uint2* src1 = cand + (size_t)R.cand_off + (size_t)part * cap;
+    uint2 ahead[MF_DEPTH];
+#pragma unroll
+    for (uint32_t u = 0; u < MF_DEPTH; ++u) {
+        const uint32_t i = u * MF_THREADS + threadIdx.x;
+        ahead[u] = i < n_part ? src1[i] : make_uint2(0u, 0u);
+    }
+    uint4 hc = make_uint4(0, 0, 0, 0);
+    uint32_t incl = 0;
+    if (wid == 0) {
+        // weights below the cluster's interval: rows 0 .. k of the split counters
+        uint64_t v = lane <= k ? rowsum[lane] : 0;     // k < MAXK = 64
+        for (uint32_t d = 32; d > 0; d >>= 1) v += __shfl_down((unsigned long long)v, d, 64);
+        if (lane == 0) { s_below = v; s_n = 0; s_bin = 0xffffffffu; }
+    } else if (wid == 1) {
+        const uint32_t c = lane < CAND_SUB ? parts[lane * 32u] : 0u;
+        const bool over = __ballot(c > cap) != 0ull;
+        uint64_t v = c;
+        for (uint32_t d = 32; d > 0; d >>= 1) v += __shfl_down((unsigned long long)v, d, 64);
+        if (lane == 0) { s_inside = v; s_over = over; }
+    } else if (wid == 2) {
+        hc = reinterpret_cast<const uint4*>(ghist + cl * MF_BINS1)[lane];
+        incl = hc.x + hc.y + hc.z + hc.w;
+        for (uint32_t d = 1; d < 64; d <<= 1) {
+            const uint32_t y = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += y;
+        }
+    }
+    __syncthreads();
+    const uint64_t below = s_below, inside = s_inside;
+    const bool reached = !s_over && below < p && p <= below + inside;
+    if (wid == 2 && reached) {
+        const uint64_t r = p - below;
+        const uint32_t c4[4] = {hc.x, hc.y, hc.z, hc.w};
+        uint64_t base = incl - (hc.x + hc.y + hc.z + hc.w);
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+            if (base < r && r <= base + c4[i]) {
+                s_bin = lane * 4u + i;
+                s_cnt = c4[i];
+                s_r2 = r - base;
+                s_less = below + base;
+            }
+            base += c4[i];
+        }
+    }
+    __syncthreads();
+    auto give_up = [&](uint32_t why) {             // by one block of the rank
         if (threadIdx.x == 0) {
             atomicOr(&ms->status, 1u);
             host_status[k] = why | 1u | nan_bit;
         }
     };
-    if (O.fail) { give_up(O.fail); return; }
-    if (n != O.bin_cnt || n > SPEC_LIST_CAP) { give_up(5u); return; }
+    const uint32_t bin = s_bin;
+    {
+        // the same in every block of the rank (no bin: cannot happen unless the buffers were disturbed)
+        uint32_t why = 0;
+        if (s_over) why = 5u;
+        else if (!reached || bin == 0xffffffffu) why = 1u;
+        else if (s_cnt > SPEC_LIST_CAP) why = 5u;
+        if (why) {
+            if (part == 0) give_up(why);
+            return;
+        }
+    }
+    // this part's pairs of the selected bin -> the rank's list
+    {
+        const uint32_t sh = R.sh;
+        auto take = [&](uint2 x) {
+            if ((((x.x & 0x7fffffffu) - lo) >> sh) == bin) {
+                const uint32_t pos = atomicAdd(&s_n, 1u);
+                if (pos < MF_STAGE) stage[pos] = x;
+            }
+        };
+#pragma unroll
+        for (uint32_t u = 0; u < MF_DEPTH; ++u)
+            if (u * MF_THREADS + threadIdx.x < n_part) take(ahead[u]);
+        if (n_part > MF_DEPTH * MF_THREADS) ms_walk(src1 + MF_DEPTH * MF_THREADS, n_part - MF_DEPTH * MF_THREADS, take);
+        __syncthreads();
+        const uint32_t m = s_n;
+        if (m > MF_STAGE) {
+            if (threadIdx.x == 0) atomicOr(fail, 5u);
+        } else if (m != 0) {
+            if (threadIdx.x == 0) s_base = atomicAdd(list_cnt, m);
+            __syncthreads();
+            uint2* dst = list + (size_t)k * SPEC_LIST_CAP;
+            for (uint32_t i = threadIdx.x; i < m; i += MF_THREADS)
+                if (s_base + i < SPEC_LIST_CAP) store_device(&dst[s_base + i], stage[i]);
+        }
+    }
+    // the list is complete when the rank's last ticket is drawn
+    if (!last_block(ticket, gridDim.x, &s_last)) return;
+    if (threadIdx.x == 0) {
+        s_n = atomicAdd(list_cnt, 0u);
+        s_why = atomicOr(fail, 0u);
+    }
+    __syncthreads();
+    const uint32_t n = s_n;
+    if (s_why) { give_up(s_why); return; }
+    if (n != s_cnt || n > SPEC_LIST_CAP) { give_up(5u); return; }
+    // a list that fits stays in LDS
     const uint2* src = list + (size_t)k * SPEC_LIST_CAP;
+    const bool staged = n <= MF_STAGE;
+    if (staged) {
+        for (uint32_t i = threadIdx.x; i < n; i += FIN_THREADS) stage[i] = load_device(&src[i]);
+        __syncthreads();
+    }
+    auto walk = [&](auto&& f) {
+        for (uint32_t i = threadIdx.x; i < n; i += FIN_THREADS) f(staged ? stage[i] : load_device(&src[i]));
+    };
     if (threadIdx.x == 0) { s_sel = 0; s_nb = 0; s_lt = 0; s_eq = 0; }
-    uint64_t r = O.r2;               // 1-based rank among the pairs still in play
-    uint64_t less = O.less;          // weights below them
+    uint64_t r = s_r2;               // 1-based rank among the pairs still in play
+    uint64_t less = s_less;          // weights below them
     uint32_t width_sh = R.sh;        // the pairs in play have (key - lo_cur) >> width_sh == 0
-    uint32_t lo_cur = R.lo + (O.bin << width_sh);
+    uint32_t lo_cur = R.lo + (bin << width_sh);
     uint32_t cnt_sel = n;
     // refine while it pays: ranking by counting is quadratic; a bin of equal keys cannot be
     // refined and must fit the list
@@ -615,9 +606,9 @@ __global__ __launch_bounds__(FIN_THREADS) void ms_rank_kernel(
         const uint32_t sh = width_sh > 12u ? width_sh - 12u : 0u;
         for (uint32_t i = threadIdx.x; i < FIN_BINS; i += FIN_THREADS) h[i] = 0;
         __syncthreads();
-        ms_walk(src, n, [&](uint2 c) {
+        walk([&](uint2 c) {
             const uint32_t d = (c.x & 0x7fffffffu) - lo_cur;      // wraps for keys below lo_cur
-            if ((d >> width_sh) == 0) atomicAdd(&h[d >> sh], 1u);
+            if ((d >> width_sh) == 0) lds_count(h, d >> sh, true);
         });
         __syncthreads();
         constexpr uint32_t PER = FIN_BINS / FIN_THREADS;
@@ -630,14 +621,14 @@ __global__ __launch_bounds__(FIN_THREADS) void ms_rank_kernel(
         if (base < r && r <= base + sum) {
 #pragma unroll
             for (uint32_t i = 0; i < PER; ++i) {
-                if (base < r && r <= base + c4[i]) { s_bin = b0 + i; s_cnt = c4[i]; s_base = base; }
+                if (base < r && r <= base + c4[i]) { s_bin = b0 + i; s_cnt = c4[i]; s_base2 = base; }
                 base += c4[i];
             }
         }
         __syncthreads();
         if (tot < r) { give_up(1u); return; }    // cannot happen unless the buffers were disturbed
-        less += s_base;
-        r -= s_base;
+        less += s_base2;
+        r -= s_base2;
         lo_cur += s_bin << sh;
         width_sh = sh;
         cnt_sel = s_cnt;
@@ -645,7 +636,7 @@ __global__ __launch_bounds__(FIN_THREADS) void ms_rank_kernel(
     }
     __syncthreads();
     // the pairs of the last bin, then the r-th of them by counting
-    ms_walk(src, n, [&](uint2 c) {
+    walk([&](uint2 c) {
         const uint32_t key = c.x & 0x7fffffffu, d = key - lo_cur;
         if ((d >> width_sh) == 0) {
             const uint32_t pos = atomicAdd(&s_nb, 1u);
@@ -1013,26 +1004,14 @@ void launch_spec_multi(shifter_ctx* ctx, const shifter_model* m, const float* d_
     const auto& b = m->b;
     const uint32_t n_t = (uint32_t)m->t.size();
     hipStream_t s = ctx->stream;
-    if (k != 0) {
-        ProfileScope ps(ctx, K_SPEC_SAMPLE);
-        // adds to the sample histogram, which every ranking leaves cleared; clears this
-        // ranking's counters on the way
-        SampleZero z;
-        z.cnt = b.multi_cnt; z.k = k; z.ghist = b.multi_hist; z.list_cnt = b.multi_list_cnt;
-        z.rout = b.multi->rout;
-        if (fb) {       // the fused pass adds to the level arrays
-            z.extra = b.levels;
-            z.extra_n = (uint32_t)(m->info.sum_out_ch + m->info.sum_in_ch);
-        }
-        launch_spec_sample(ctx, m, d_w, z);
-    } else if (fb) {
-        launch_zero_levels(ctx, m);
-    }
+    if (k == 0 && fb) launch_zero_levels(ctx, m);
     {
-        ProfileScope ps(ctx, K_SPEC_PREDICT);
-        ms_predict_kernel<<<1, PREDICT_THREADS, 0, s>>>(
-            b.multi, b.shist, b.multi_cnt, sorted_p, perm, k, m->sample_size, zero_mask, d_thr,
-            b.dev_multi_rec, m->info.n_prunable, ctx->margin_sigmas, b.multi_tab, b.cand_cap_sb);
+        // the fused pass adds to the level arrays: cleared on the way
+        ProfileScope ps(ctx, K_SPEC_SAMPLE);
+        ms_front_kernel<<<k ? sample_grid(m) : 1u, SAMPLE_THREADS, 0, s>>>(
+            sample_in(m, d_w), b.multi, b.multi_cnt, b.multi_hist, b.multi_list_cnt, fb && k ? b.levels : nullptr,
+            fb && k ? (uint32_t)(m->info.sum_out_ch + m->info.sum_in_ch) : 0u, sorted_p, perm, k, m->sample_size,
+            zero_mask, d_thr, b.dev_multi_rec, m->info.n_prunable, ctx->margin_sigmas, b.multi_tab, b.cand_cap_sb);
     }
     if (k == 0 && !fb) {         // every count was zero: no pass, which would have cleared zero_ptr
         if (zero_ptr) launch_zero_levels(ctx, m);
@@ -1066,14 +1045,9 @@ void launch_spec_multi(shifter_ctx* ctx, const shifter_model* m, const float* d_
         }
         {
             ProfileScope ps(ctx, K_SPEC_FINISH2);
-            ms_filter_kernel<<<dim3(CAND_SUB, k), MF_THREADS, 0, s>>>(b.multi, b.multi_cnt, b.cand, b.multi_hist,
-                                                                     b.multi_rowsum, b.multi_list,
-                                                                     b.multi_list_cnt);
-        }
-        {
-            ProfileScope ps(ctx, K_SPEC_RANK);
-            ms_rank_kernel<<<k, FIN_THREADS, 0, s>>>(b.multi, b.multi_list, b.multi_list_cnt, d_thr,
-                                                     b.dev_multi_rec, b.dev_multi_status);
+            ms_finish_kernel<<<dim3(CAND_SUB, k), MF_THREADS, 0, s>>>(b.multi, b.multi_cnt, b.cand, b.multi_hist,
+                                                                     b.multi_rowsum, b.multi_list, b.multi_list_cnt,
+                                                                     d_thr, b.dev_multi_rec, b.dev_multi_status);
         }
     }
     if (fb) {

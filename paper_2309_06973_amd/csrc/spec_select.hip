@@ -17,15 +17,15 @@
 //
 // The result is exact whenever step 4's check holds; otherwise (a sample that misled,
 // an interval with too many ties, a full buffer) a status bit is raised and the host
-// runs the multi-pass radix select instead.
+// runs the multi-pass select instead.
 #include <algorithm>
 
-#include "dev_common.h"
+#include "spec_sample.h"
 
 namespace shifter {
 
-constexpr uint32_t SBINS = SAMPLE_BINS;  // sample histogram bins (sample_bin)
 constexpr uint32_t FBINS1 = 256;        // round-1 finishing histogram: one bin per thread
+constexpr uint32_t FHIST_COPIES = 4;    // of it in global memory: blocks that meet at one bin take their turns
 constexpr uint32_t FBINS = 4096;        // round-2 finishing histogram (one block, LDS)
 constexpr uint32_t FIN_BLOCKS = SPEC_FIN_BLOCKS;  // blocks of the passes over candidates
 
@@ -37,197 +37,58 @@ __device__ __forceinline__ uint32_t* sub_counter(uint32_t* cnt, uint32_t which, 
     return cnt + (which * SPEC_SUB + sb) * 32u;
 }
 
-// The sample: from every quarter (1024 weights) of every sample_tile_stride-th tile one
-// 64-byte sector of 16 weights, at a position that rotates with the tile and the quarter.
-// Every filter of 1024 or more weights is thus sampled in proportion to its size - the
-// sample is stratified by filter, which matters because filters differ in scale by
-// orders of magnitude and a sample clustered on few filters misjudges the quantiles.
-// A wavefront takes four tiles per step (16 lanes per tile, 4 lanes per sector, one
-// float4 each).  The samples go to a per-block LDS histogram first: a global atomic
-// costs about 11 ns per lane on one address, and the bins around the mode are hot.
-__host__ __device__ __forceinline__ uint32_t sample_sector(uint32_t tile, uint32_t quarter) {
-    return (tile * 37u + quarter * 11u) & 63u;
-}
-
-constexpr uint32_t SAMPLE_THREADS = 1024;   // sixteen wavefronts on the block's CU keep its loads in flight
-
-__global__ __launch_bounds__(SAMPLE_THREADS) void spec_sample_kernel(
-    const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix,
-    const uint16_t* __restrict__ tile_tensor, uint32_t n_tiles, uint32_t tile_stride,
-    const float* __restrict__ w, uint32_t* shist, SampleZero z) {
-    __shared__ uint32_t h[SBINS];
-    if (z.cnt) {
-        // scratch of the K-rank ranking, idle until its pass: rows 0 .. k and
-        // MAXK + 1 .. MAXK + k of the split counters (the first word of each 128-byte line)
-        const uint32_t tid = blockIdx.x * SAMPLE_THREADS + threadIdx.x, nthr = gridDim.x * SAMPLE_THREADS;
-        for (uint32_t i = tid; i < (2u * z.k + 1u) * SPEC_SUB; i += nthr) {
-            const uint32_t row = i / SPEC_SUB, sb = i % SPEC_SUB;
-            const uint32_t r = row <= z.k ? row : MAXK + 1u + (row - (z.k + 1u));
-            z.cnt[((size_t)r * SPEC_SUB + sb) * 32u] = 0;
-        }
-        for (uint32_t i = tid; i < z.k * 256u; i += nthr) z.ghist[i] = 0;
-        for (uint32_t i = tid; i < z.extra_n; i += nthr) z.extra[i] = 0;
-        if (tid < MAXK) {
-            z.list_cnt[tid] = 0;
-            z.rout[tid].fail = 0;
-        }
-    }
-    if (z.ss) {
-        // set-up of the one-count selection, idle until the kernels behind this one: its
-        // split counters and the caller's flag arrays cleared, its state initialised (every
-        // ranking leaves the sample histogram cleared, see the predict kernels)
+// Sample and prediction in one launch.  On the way the scratch of the kernels behind it is cleared: the
+// split counters, the candidates' histogram, the caller's flag arrays.
+// The block that ends last takes the sample's order statistics around P/N for the candidate
+// interval [lo, hi] and a provisional threshold mid (the fused pass writes candidates below mid as
+// removed, the others as kept; few of them then need correcting).
+__global__ __launch_bounds__(SAMPLE_THREADS) void spec_front_kernel(
+    SampleIn in, SpecState* __restrict__ ss, uint32_t* __restrict__ cnt, uint32_t* __restrict__ hist,
+    uint8_t* __restrict__ fa, uint64_t na, uint8_t* __restrict__ fb, uint64_t nb, uint64_t p, uint32_t m,
+    uint64_t n_prunable, double margin_sigmas) {
+    __shared__ __align__(16) uint32_t h[SAMPLE_BINS];
+    {
         const uint64_t tid = (uint64_t)blockIdx.x * SAMPLE_THREADS + threadIdx.x;
         const uint64_t stride = (uint64_t)gridDim.x * SAMPLE_THREADS;
-        for (uint64_t i = tid; i < 2u * SPEC_SUB * 32u; i += stride) z.cnt1[i] = 0;
-        for (uint64_t i = tid; i < z.na; i += stride) z.fa[i] = 0;
-        for (uint64_t i = tid; i < z.nb; i += stride) z.fb[i] = 0;
-        if (tid == 0) {
-            SpecState* ss = z.ss;
-            ss->p = z.p;
-            ss->n_below = 0;
-            ss->n_inside = 0;
-            ss->m_valid = z.m_valid;
-            ss->status = 0;
-            ss->list_cnt = 0;
-            ss->lo = 0;
-            ss->hi = 0x7fffffffu;
-            ss->mid = 0;
-            ss->sh = 19;
-        }
+        for (uint64_t i = tid; i < 2u * SPEC_SUB; i += stride) cnt[i * 32u] = 0;
+        for (uint64_t i = tid; i < FHIST_COPIES * FBINS1; i += stride) hist[i] = 0;
+        for (uint64_t i = tid; i < na; i += stride) fa[i] = 0;
+        for (uint64_t i = tid; i < nb; i += stride) fb[i] = 0;
     }
-    for (uint32_t i = threadIdx.x; i < SBINS; i += SAMPLE_THREADS) h[i] = 0;
-    __syncthreads();
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = blockIdx.x * (SAMPLE_THREADS / 64) + (threadIdx.x >> 6);
-    const uint32_t n_waves = gridDim.x * (SAMPLE_THREADS / 64);
-    const uint32_t quarter = (lane >> 2) & 3u, part = lane & 3u;
-    // address of this lane's four samples of sampled tile s, or nullptr; the tensor of a
-    // tile comes from a table (one load instead of a search per lane)
-    auto locate = [&](uint64_t s) -> const float* {
-        if (s * tile_stride >= n_tiles) return nullptr;
-        const uint32_t tile = (uint32_t)(s * tile_stride);
-        const uint32_t t = tile_tensor[tile];
-        if (!tens[t].prunable) return nullptr;
-        const uint32_t e0 = (tile - tile_prefix[t]) * TILE;
-        const uint32_t n = min(TILE, tens[t].numel - e0);
-        const uint32_t j = quarter * 1024u + sample_sector(tile, quarter) * 16u + part * 4u;
-        return j + 3 < n ? w + tens[t].offset + e0 + j : nullptr;
-    };
-    auto fetch = [&](const float* p) -> float4 {
-        float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (p) {
-            if ((reinterpret_cast<uintptr_t>(p) & 15u) == 0) {
-                x = *reinterpret_cast<const float4*>(p);
-            } else {
-                x.x = p[0]; x.y = p[1]; x.z = p[2]; x.w = p[3];
-            }
-        }
-        return x;
-    };
-    auto count = [&](const float* p, const float4& x) {
-        if (!p) return;
-        atomicAdd(&h[sample_bin(key_of(x.x))], 1u);
-        atomicAdd(&h[sample_bin(key_of(x.y))], 1u);
-        atomicAdd(&h[sample_bin(key_of(x.z))], 1u);
-        atomicAdd(&h[sample_bin(key_of(x.w))], 1u);
-    };
-    // two sampled tiles per lane group and step, their loads in flight together
-    const uint64_t step = (uint64_t)n_waves * 4;
-    for (uint64_t s = (uint64_t)wave * 4 + (lane >> 4); s * tile_stride < n_tiles; s += 2 * step) {
-        const float* pa = locate(s);
-        const float* pb = locate(s + step);
-        const float4 xa = fetch(pa);
-        const float4 xb = fetch(pb);
-        count(pa, xa);
-        count(pb, xb);
-    }
-    __syncthreads();
-    // the blocks start at different segments of the histogram: the populated bins are few
-    // and neighbours, and atomics that meet at one address take their turns
-    constexpr uint32_t SEGS = SBINS / SAMPLE_THREADS;
-    for (uint32_t it = 0; it < SEGS; ++it) {
-        const uint32_t i = ((it + blockIdx.x) % SEGS) * SAMPLE_THREADS + threadIdx.x;
-        const uint32_t c = h[i];
-        if (c) atomicAdd(&shist[i], c);
-    }
-}
-
-// One block: the sample's order statistics around P/N give the candidate interval
-// [lo, hi] and a provisional threshold mid (the fused pass writes candidates below mid as
-// removed, the others as kept; few of them then need correcting).
-// The histogram is read as 64 segments of 256 bins, one coalesced load per wavefront.
-__global__ __launch_bounds__(BLOCK) void spec_predict_kernel(SpecState* ss, uint32_t* shist,
-                                                             uint64_t n_prunable,
-                                                             double margin_sigmas) {
-    constexpr uint32_t SEG = 256, NSEG = SBINS / SEG;   // 64 segments
-    static_assert(NSEG == 64, "one segment per lane, one segment sum per thread");
-    __shared__ uint64_t smem[BLOCK / 64 + 1];
-    __shared__ uint32_t seg_sum[NSEG];
-    __shared__ uint64_t s_base[NSEG];
-    __shared__ uint32_t s_bin[3];
-    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
-    for (uint32_t sg = wid; sg < NSEG; sg += BLOCK / 64) {
-        const uint4 x = reinterpret_cast<const uint4*>(shist + sg * SEG)[lane];
-        uint32_t v = x.x + x.y + x.z + x.w;
-        for (uint32_t d = 32; d > 0; d >>= 1) v += __shfl_down(v, d, 64);
-        if (lane == 0) seg_sum[sg] = v;
-    }
-    if (threadIdx.x < 3) s_bin[threadIdx.x] = 0xffffffffu;
-    __syncthreads();
-    const uint64_t mine = threadIdx.x < NSEG ? seg_sum[threadIdx.x] : 0;
-    uint64_t total;
-    const uint64_t base = block_excl_scan_u64(mine, smem, &total);
-    const uint64_t p = ss->p;
-    const uint32_t m = ss->m_valid;
-    const bool use = p > 0 && m >= 256 && n_prunable > 0 && total == m;
-    double r[3] = {0, 0, 0};   // 0-based sample ranks: low end, high end, centre
+    if (!sample_prefix(in, h)) return;
+    if (threadIdx.x >= 64u) return;
+    // lanes 0, 1, 2: low end, high end, centre
+    const uint32_t lane = threadIdx.x;
+    const bool use = p > 0 && m >= 256 && n_prunable > 0 && h[SAMPLE_BINS - 1u] == m;
+    uint32_t bin = 0xffffffffu;
+    double r_hi = 0;
     if (use) {
         const double frac = (double)p / (double)n_prunable;
         const double centre = frac * (double)m;
         // a multiple of the binomial deviation of a simple random sample of this size
         const double delta = margin_sigmas * sqrt((double)m * frac * (1.0 - frac)) + 16.0;
-        r[0] = centre - delta;
-        r[1] = centre + delta;
-        r[2] = centre;
+        r_hi = centre + delta;
+        const double r = lane == 0 ? centre - delta : lane == 1 ? r_hi : centre;     // 0-based sample rank
+        if (r >= 0.0 && r < (double)m) bin = sample_bin_of_rank(h, (uint32_t)r);
     }
-    // bin holding the r-th sample, one wavefront per rank: the segment from the segment
-    // bases (one per lane), then a scan over the segment's 256 bins (four per lane)
-    if (threadIdx.x < NSEG) s_base[threadIdx.x] = base;
-    __syncthreads();
-    if (wid < 3 && use && r[wid] >= 0.0 && r[wid] < (double)m) {
-        const uint64_t target = (uint64_t)r[wid];
-        const uint32_t sg = (uint32_t)__popcll(__ballot(s_base[lane] <= target)) - 1u;   // bases ascend from 0
-        const uint4 x = reinterpret_cast<const uint4*>(shist + sg * SEG)[lane];
-        const uint32_t mine4 = x.x + x.y + x.z + x.w;
-        uint32_t incl = mine4;
-        for (uint32_t d = 1; d < 64; d <<= 1) {
-            const uint32_t y = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += y;
-        }
-        const uint64_t seg_base = s_base[sg];
-        const unsigned long long over = __ballot(seg_base + incl > target);
-        if (over != 0 && lane == (uint32_t)__ffsll(over) - 1u) {
-            uint64_t run = seg_base + incl - mine4;
-            const uint32_t v[4] = {x.x, x.y, x.z, x.w};
-            for (uint32_t i = 0; i < 4; ++i) {
-                run += v[i];
-                if (run > target) { s_bin[wid] = sg * SEG + lane * 4 + i; break; }
-            }
-        }
-    }
-    __syncthreads();
-    // the sample has been read: cleared for the next ranking, which adds to it
-    for (uint32_t i = threadIdx.x; i < SBINS; i += BLOCK) shist[i] = 0;
-    if (threadIdx.x != 0) return;
+    const uint32_t bin_lo = __shfl(bin, 0, 64), bin_hi = __shfl(bin, 1, 64), bin_mid = __shfl(bin, 2, 64);
+    if (lane != 0) return;
     uint32_t lo = 0, hi = 0x7fffffffu;
-    if (s_bin[0] != 0xffffffffu) lo = sample_bin_first_key(s_bin[0]);
-    if (s_bin[1] != 0xffffffffu && r[1] < (double)(m - 1)) hi = sample_bin_last_key(s_bin[1]);
+    if (bin_lo != 0xffffffffu) lo = sample_bin_first_key(bin_lo);
+    if (bin_hi != 0xffffffffu && r_hi < (double)(m - 1)) hi = sample_bin_last_key(bin_hi);
     uint32_t mid = lo;
-    if (s_bin[2] != 0xffffffffu)      // the middle of the bin
-        mid = sample_bin_first_key(s_bin[2]) + (sample_bin_last_key(s_bin[2]) - sample_bin_first_key(s_bin[2])) / 2u;
+    if (bin_mid != 0xffffffffu)      // the middle of the bin
+        mid = sample_bin_first_key(bin_mid) + (sample_bin_last_key(bin_mid) - sample_bin_first_key(bin_mid)) / 2u;
     mid = max(lo, min(mid, hi));
     uint32_t sh = 0;
     while (((hi - lo) >> sh) >= FBINS1) ++sh;
+    ss->p = p;
+    ss->n_below = 0;
+    ss->n_inside = 0;
+    ss->m_valid = m;
+    ss->status = 0;
+    ss->list_cnt = 0;
+    ss->ticket = 0;
     ss->lo = lo;
     ss->hi = hi;
     ss->mid = mid;
@@ -430,156 +291,172 @@ __device__ __forceinline__ void for_each_candidate(const uint32_t* cnt, const ui
     }
 }
 
-// Totals of the split counters, the check that makes the result exact, then the round-1
-// bin holding the P-th pair.  Every block of the filter kernel runs this on the same
-// inputs (64 KB of partial histograms from L2) and gets the same answer, which is cheaper
-// than a kernel of its own or a fenced rendezvous; `publish` is set for one block, which
-// records the outcome.  Returns false when the single pass cannot decide.
-__device__ bool spec_locate(SpecState* ss, const uint32_t* __restrict__ cnt,
-                            const uint32_t* __restrict__ partial, uint32_t cap_sb,
-                            uint64_t* smem, bool publish, uint32_t* bin_out) {
-    __shared__ uint32_t s_over;
-    const uint64_t p = ss->p;
-    if (threadIdx.x == 0) s_over = 0;
-    __syncthreads();
-    uint64_t below = 0, inside = 0, tot;
-    static_assert(SPEC_SUB == BLOCK, "one split counter per thread");
-    {
-        const uint32_t c = cnt[(CNT_CAND * SPEC_SUB + threadIdx.x) * 32u];
-        const uint32_t b = cnt[(CNT_BELOW * SPEC_SUB + threadIdx.x) * 32u];
-        block_excl_scan_u64(c, smem, &inside);
-        block_excl_scan_u64(b, smem, &below);
-        if (c > cap_sb) s_over = 1;
-    }
-    __syncthreads();
-    if (publish && threadIdx.x == 0) { ss->n_below = below; ss->n_inside = inside; }
-    if (s_over || !(below < p && p <= below + inside)) {
-        if (publish && threadIdx.x == 0) atomicOr(&ss->status, 1u);
-        return false;
-    }
-    const uint64_t r = p - below;
-    static_assert(FBINS1 == BLOCK, "one round-1 bin per thread");
-    // sum the FIN_BLOCKS partial histograms: thread t reads the uint4s t, t + 256, ...;
-    // each covers the same four bins (4t mod 256 ...), so it keeps four sums and four
-    // threads then meet in LDS.  All loads are independent of each other.
-    __shared__ uint32_t s_bins[FBINS1];
-    s_bins[threadIdx.x] = 0;
-    __syncthreads();
-    {
-        const uint4* p4 = reinterpret_cast<const uint4*>(partial);
-        uint4 acc = make_uint4(0, 0, 0, 0);
-        constexpr uint32_t N4 = FIN_BLOCKS * FBINS1 / 4 / BLOCK;
-#pragma unroll 16
-        for (uint32_t i = 0; i < N4; ++i) {
-            const uint4 x = p4[threadIdx.x + BLOCK * i];
-            acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
-        }
-        const uint32_t b4 = (4u * threadIdx.x) & (FBINS1 - 1);
-        atomicAdd(&s_bins[b4], acc.x);
-        atomicAdd(&s_bins[b4 + 1], acc.y);
-        atomicAdd(&s_bins[b4 + 2], acc.z);
-        atomicAdd(&s_bins[b4 + 3], acc.w);
-    }
-    __syncthreads();
-    const uint32_t c = s_bins[threadIdx.x];
-    const uint64_t base = block_excl_scan_u64(c, smem, &tot);
-    __shared__ uint32_t s_bin, s_ok;
-    if (base < r && r <= base + c) {
-        s_bin = threadIdx.x;
-        s_ok = c <= SPEC_LIST_CAP ? 1u : 0u;
-        if (publish) {
-            ss->bin = threadIdx.x;
-            ss->bin_cnt = c;
-            ss->r2 = r - base;
-            ss->less = below + base;
-            if (c > SPEC_LIST_CAP) atomicOr(&ss->status, 1u);
-        }
-    }
-    __syncthreads();
-    *bin_out = s_bin;
-    return s_ok != 0;
-}
-
-// Round 1: per-block LDS histogram of (key - lo) >> sh (256 bins) over the candidates; the
-// partial histograms go to global memory side by side (no atomics).
+// Round 1: a 256-bin histogram of (key - lo) >> sh over the candidates.
 __global__ __launch_bounds__(BLOCK) void spec_hist_kernel(const SpecState* __restrict__ ss,
                                                           const uint32_t* __restrict__ cnt,
                                                           const uint2* __restrict__ cand,
-                                                          uint32_t cap_sb,
-                                                          uint32_t* __restrict__ partial) {
+                                                          uint32_t cap_sb, uint32_t* __restrict__ hist) {
     __shared__ uint32_t h[FBINS1];
+    static_assert(FBINS1 == BLOCK, "one round-1 bin per thread");
     h[threadIdx.x] = 0;
     __syncthreads();
     const uint32_t lo = ss->lo, sh = ss->sh;
     for_each_candidate(cnt, cand, cap_sb, [&](uint2 c, bool valid) {
-        if (valid) atomicAdd(&h[((c.x & 0x7fffffffu) - lo) >> sh], 1u);
+        lds_count(h, ((c.x & 0x7fffffffu) - lo) >> sh, valid);
     });
     __syncthreads();
-    partial[blockIdx.x * FBINS1 + threadIdx.x] = h[threadIdx.x];
+    const uint32_t c = h[threadIdx.x];
+    if (c) atomicAdd(&hist[(blockIdx.x % FHIST_COPIES) * FBINS1 + threadIdx.x], c);
 }
 
-// One block: round-2 histogram over the list, then an exact rank (by counting) among the
-// pairs of the selected round-2 bin, then the record.
-// Whatever the outcome, the state (status, counts, the record) is left in its mirror in
-// pinned host memory as the last thing: the host reads it after waiting for the stream,
-// with no copy on the stream.
-__global__ __launch_bounds__(BLOCK) void spec_rank_kernel(SpecState* ss,
-                                                          const uint2* __restrict__ list,
-                                                          shifter_threshold* thr, SpecState* host_mirror) {
-    // only thread 0 writes the state in this kernel, so it reads back its own writes
-    auto publish = [&]() {
-        if (threadIdx.x == 0) *host_mirror = *ss;
-    };
+// The rest of the finish in one launch.  Every block first locates the P-th pair from the same
+// counters and histogram and gets the same answer: totals of the split counters, the check that
+// makes the result exact, the round-1 bin.  Then it moves its share of the bin's candidates to the
+// list (staged in LDS, one reservation), and the block that ends last ranks the list: a
+// round-2 histogram, an exact rank by counting among the pairs of the selected bin, the record.
+// Whatever the outcome, the state (status, counts, the record) is left in its mirror in pinned
+// host memory as the last thing: the host reads it after waiting for the stream, with no copy
+// on the stream.
+// What bounds it is the chain of latencies, so the counters, the histogram and the first
+// candidates are all loaded before the first of them is used, and the ranking costs no launch of
+// its own (filter + rank of one count of 77 M weights 10.0 + 6.0 us, 13.7 as one).
+__global__ __launch_bounds__(BLOCK) void spec_finish_kernel(
+    SpecState* ss, const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ hist,
+    const uint2* __restrict__ cand, uint32_t cap_sb, uint2* list, shifter_threshold* thr, SpecState* host_mirror) {
+    constexpr uint32_t STAGE = 2048, WAVES = BLOCK / 64;
+    __shared__ uint2 stage[STAGE];
     __shared__ uint32_t h[FBINS];
     __shared__ uint64_t comp[SPEC_SMALL_CAP];
-    __shared__ uint64_t smem[BLOCK / 64 + 1];
+    __shared__ uint64_t smem[WAVES + 1];
     __shared__ uint64_t s_sel, s_less2, s_r3;
+    __shared__ uint32_t s_below[WAVES], s_inside[WAVES], s_hist[WAVES], s_over[WAVES];
+    __shared__ uint32_t s_n, s_base, s_bin, s_cnt1, s_last, s_status;
+    __shared__ uint64_t s_r2, s_less;
     __shared__ uint32_t s_lt, s_eq, s_bin2, s_cnt2, s_nb;
-    shifter_threshold out;
-    out.reserved = 0;
-    out.n_prune = ss->p;
-    if (ss->p == 0) {
-        if (threadIdx.x == 0) {
-            out.cut = 0; out.t_key = 0; out.g_cut = ~0ull; out.n_less = 0; out.n_equal = 0;
+    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+    static_assert(SPEC_SUB == BLOCK && FBINS1 == BLOCK, "one split counter and one round-1 bin per thread");
+    const uint32_t n_cand = cnt[(CNT_CAND * SPEC_SUB + threadIdx.x) * 32u];
+    const uint32_t n_less = cnt[(CNT_BELOW * SPEC_SUB + threadIdx.x) * 32u];
+    uint32_t in_bin = 0;
+#pragma unroll
+    for (uint32_t i = 0; i < FHIST_COPIES; ++i) in_bin += hist[i * FBINS1 + threadIdx.x];
+    const uint64_t p = ss->p;
+    const uint32_t lo = ss->lo, sh = ss->sh;
+    shifter_threshold out;                 // nothing removed
+    out.reserved = 0; out.n_prune = p;
+    out.cut = 0; out.t_key = 0; out.g_cut = ~0ull; out.n_less = 0; out.n_equal = 0;
+    if (p == 0) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
             *thr = out;
             ss->rec = out;
+            *host_mirror = *ss;
         }
-        publish();
         return;
     }
+    if (threadIdx.x == 0) {
+        s_n = 0; s_bin = 0xffffffffu;
+        s_lt = 0; s_eq = 0; s_sel = 0; s_nb = 0; s_cnt2 = 0; s_bin2 = 0;
+    }
+    uint32_t sum_c = n_cand, sum_b = n_less, incl = in_bin;    // N < 2^32: the sums fit 32 bits
+    for (uint32_t d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(incl, d, 64), yc = __shfl_up(sum_c, d, 64), yb = __shfl_up(sum_b, d, 64);
+        if (lane >= d) { incl += y; sum_c += yc; sum_b += yb; }
+    }
+    const bool over = __ballot(n_cand > cap_sb) != 0ull;
+    if (lane == 63) { s_below[wid] = sum_b; s_inside[wid] = sum_c; s_hist[wid] = incl; s_over[wid] = over; }
+    __syncthreads();
+    uint64_t below = 0, inside = 0, base = incl - in_bin;
+    bool any_over = false;
+#pragma unroll
+    for (uint32_t i = 0; i < WAVES; ++i) {
+        below += s_below[i];
+        inside += s_inside[i];
+        if (i < wid) base += s_hist[i];
+        any_over = any_over || s_over[i] != 0;
+    }
+    const bool reached = !any_over && below < p && p <= below + inside;
+    if (reached) {
+        const uint64_t r = p - below;
+        if (base < r && r <= base + in_bin) {
+            s_bin = threadIdx.x;
+            s_cnt1 = in_bin;
+            s_r2 = r - base;
+            s_less = below + base;
+        }
+    }
+    __syncthreads();
+    const uint32_t bin = s_bin;
     // Undecided: the host redoes the ranking and every step behind it.  What is enqueued
     // behind this kernel still runs once on the record it finds, so leave a harmless one
-    // (nothing removed) rather than the record of some earlier call.
-    auto undecided = [&]() {
-        if (threadIdx.x == 0) {
-            out.cut = 0; out.t_key = 0; out.g_cut = ~0ull; out.n_less = 0; out.n_equal = 0;
-            *thr = out;
-        }
-        publish();
+    // (nothing removed) rather than the record of some earlier call.  By one block's first thread.
+    auto publish = [&](bool decided) {
+        ss->n_below = below;
+        ss->n_inside = inside;
+        if (bin != 0xffffffffu) { ss->bin = bin; ss->bin_cnt = s_cnt1; ss->r2 = s_r2; ss->less = s_less; }
+        if (decided) ss->rec = out;
+        *thr = out;
+        const uint32_t undecided = decided ? 0u : 1u;
+        const uint32_t status = atomicOr(&ss->status, undecided) | undecided;
+        SpecState mirror = *ss;
+        mirror.status = status;
+        *host_mirror = mirror;
     };
-    if (ss->status & 1u) { undecided(); return; }
-    const uint32_t n = min(ss->list_cnt, SPEC_LIST_CAP);
-    if (n != ss->bin_cnt) {   // cannot happen unless the buffers were disturbed
-        if (threadIdx.x == 0) atomicOr(&ss->status, 1u);
-        undecided();
+    if (!reached || bin == 0xffffffffu || s_cnt1 > SPEC_LIST_CAP) {      // the same in every block
+        if (blockIdx.x == 0 && threadIdx.x == 0) publish(false);
         return;
     }
-    // round 2: the list's keys span 2^sh values starting at lo + (bin << sh)
-    const uint32_t sh = ss->sh;
-    const uint32_t sh2 = sh > 12 ? sh - 12 : 0;   // 2^sh keys over FBINS = 2^12 bins
-    const uint32_t lo1 = ss->lo + (ss->bin << sh);
-    for (uint32_t i = threadIdx.x; i < FBINS; i += BLOCK) h[i] = 0;
-    if (threadIdx.x == 0) { s_lt = 0; s_eq = 0; s_sel = 0; s_nb = 0; s_cnt2 = 0; s_bin2 = 0; }
+    for_each_candidate(cnt, cand, cap_sb, [&](uint2 c, bool valid) {
+        if (valid && (((c.x & 0x7fffffffu) - lo) >> sh) == bin) {
+            const uint32_t pos = atomicAdd(&s_n, 1u);
+            if (pos < STAGE) stage[pos] = c;
+        }
+    });
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < n; i += BLOCK)
-        atomicAdd(&h[((list[i].x & 0x7fffffffu) - lo1) >> sh2], 1u);
+    {
+        const uint32_t n = s_n;
+        if (n > STAGE) {         // far more ties than the stage holds: leave it to the multi-pass select
+            if (threadIdx.x == 0) atomicOr(&ss->status, 1u);
+        } else if (n != 0) {
+            if (threadIdx.x == 0) s_base = atomicAdd(&ss->list_cnt, n);
+            __syncthreads();
+            for (uint32_t i = threadIdx.x; i < n; i += BLOCK)
+                if (s_base + i < SPEC_LIST_CAP) store_device(&list[s_base + i], stage[i]);
+        }
+    }
+    // the list is complete when the last ticket is drawn
+    if (!last_block(&ss->ticket, gridDim.x, &s_last)) return;
+    if (threadIdx.x == 0) {
+        s_n = atomicAdd(&ss->list_cnt, 0u);
+        s_status = atomicOr(&ss->status, 0u);
+    }
+    for (uint32_t i = threadIdx.x; i < FBINS; i += BLOCK) h[i] = 0;
+    __syncthreads();
+    const uint32_t n = s_n;
+    // the second cannot happen unless the buffers were disturbed
+    if ((s_status & 1u) || n != s_cnt1) {
+        if (threadIdx.x == 0) publish(false);
+        return;
+    }
+    // a list that fits stays in LDS
+    const bool staged = n <= STAGE;
+    if (staged) {
+        for (uint32_t i = threadIdx.x; i < n; i += BLOCK) stage[i] = load_device(&list[i]);
+        __syncthreads();
+    }
+    auto walk = [&](auto&& f) {
+        for (uint32_t i = threadIdx.x; i < n; i += BLOCK) f(staged ? stage[i] : load_device(&list[i]));
+    };
+    // round 2: the list's keys span 2^sh values starting at lo + (bin << sh)
+    const uint32_t sh2 = sh > 12 ? sh - 12 : 0;   // 2^sh keys over FBINS = 2^12 bins
+    const uint32_t lo1 = lo + (bin << sh);
+    walk([&](uint2 c) { lds_count(h, ((c.x & 0x7fffffffu) - lo1) >> sh2, true); });
     __syncthreads();
     constexpr uint32_t PER = FBINS / BLOCK;
     const uint32_t b0 = threadIdx.x * PER;
     uint64_t sum = 0, tot;
     for (uint32_t i = 0; i < PER; ++i) sum += h[b0 + i];
-    uint64_t base = block_excl_scan_u64(sum, smem, &tot);
-    const uint64_t r = ss->r2;
+    base = block_excl_scan_u64(sum, smem, &tot);
+    const uint64_t r = s_r2;
     if (base < r && r <= base + sum) {
         for (uint32_t i = 0; i < PER; ++i) {
             const uint32_t c = h[b0 + i];
@@ -596,18 +473,16 @@ __global__ __launch_bounds__(BLOCK) void spec_rank_kernel(SpecState* ss,
     __syncthreads();
     const uint32_t bin2 = s_bin2, cnt2 = s_cnt2;
     if (cnt2 == 0 || cnt2 > SPEC_SMALL_CAP) {
-        if (threadIdx.x == 0) atomicOr(&ss->status, 1u);
-        undecided();
+        if (threadIdx.x == 0) publish(false);
         return;
     }
-    for (uint32_t i = threadIdx.x; i < n; i += BLOCK) {
-        const uint2 c = list[i];
+    walk([&](uint2 c) {
         const uint32_t key = c.x & 0x7fffffffu;
         if (((key - lo1) >> sh2) == bin2) {
             const uint32_t pos = atomicAdd(&s_nb, 1u);
             comp[pos] = ((uint64_t)key << 32) | c.y;   // pos < cnt2 <= SPEC_SMALL_CAP
         }
-    }
+    });
     __syncthreads();
     const uint64_t want = s_r3 - 1;   // 0-based rank inside the bin
     for (uint32_t i = threadIdx.x; i < cnt2; i += BLOCK) {
@@ -632,47 +507,10 @@ __global__ __launch_bounds__(BLOCK) void spec_rank_kernel(SpecState* ss,
         out.t_key = key;
         out.g_cut = sel & 0xffffffffull;
         out.cut = sel + 1;
-        out.n_less = ss->less + s_less2 + s_lt;
+        out.n_less = s_less + s_less2 + s_lt;
         out.n_equal = s_eq;
-        *thr = out;
-        ss->rec = out;
+        publish(true);
     }
-    publish();
-}
-
-// Candidates of the selected round-1 bin -> list.  Each block stages its hits in LDS and
-// reserves its range of the list with one global atomic.
-__global__ __launch_bounds__(BLOCK) void spec_filter_kernel(SpecState* ss,
-                                                            const uint32_t* __restrict__ cnt,
-                                                            const uint32_t* __restrict__ partial,
-                                                            const uint2* __restrict__ cand,
-                                                            uint32_t cap_sb, uint2* list) {
-    constexpr uint32_t STAGE = 2048;
-    __shared__ uint2 stage[STAGE];
-    __shared__ uint64_t smem[BLOCK / 64 + 1];
-    __shared__ uint32_t s_n, s_base;
-    if (ss->p == 0) return;
-    uint32_t bin;
-    if (threadIdx.x == 0) s_n = 0;
-    if (!spec_locate(ss, cnt, partial, cap_sb, smem, blockIdx.x == 0, &bin)) return;
-    const uint32_t lo = ss->lo, sh = ss->sh;
-    for_each_candidate(cnt, cand, cap_sb, [&](uint2 c, bool valid) {
-        if (valid && (((c.x & 0x7fffffffu) - lo) >> sh) == bin) {
-            const uint32_t pos = atomicAdd(&s_n, 1u);
-            if (pos < STAGE) stage[pos] = c;
-        }
-    });
-    __syncthreads();
-    const uint32_t n = s_n;
-    if (n > STAGE) {   // far more ties than the stage holds: leave it to the radix select
-        if (threadIdx.x == 0) atomicOr(&ss->status, 1u);
-        return;
-    }
-    if (n == 0) return;
-    if (threadIdx.x == 0) s_base = atomicAdd(&ss->list_cnt, n);
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < n; i += BLOCK)
-        if (s_base + i < SPEC_LIST_CAP) list[s_base + i] = stage[i];
 }
 
 // Fused form only: settle the candidates.  The pass wrote those below mid as removed and
@@ -722,18 +560,6 @@ __global__ __launch_bounds__(BLOCK) void spec_fixup_kernel(
     });
 }
 
-void launch_spec_sample(shifter_ctx* ctx, const shifter_model* m, const float* d_w, const SampleZero& z) {
-    const auto& b = m->b;
-    const uint32_t sampled = (m->n_tiles + m->sample_tile_stride - 1) / m->sample_tile_stride;
-    // one block per CU: more blocks shorten the loop but every block flushes its LDS
-    // histogram with global atomics (measured with 256-thread blocks: 22 us at 256 blocks,
-    // 24 at 512, 34 at 128 or 1024; 1024-thread blocks brought the 256 to 15 us)
-    const uint32_t grid = std::min(256u, (sampled + 63) / 64);   // 64 tiles per block and step
-    spec_sample_kernel<<<grid, SAMPLE_THREADS, 0, ctx->stream>>>(b.tens, b.tile_prefix, b.tile_tensor,
-                                                        m->n_tiles, m->sample_tile_stride, d_w,
-                                                        b.shist, z);
-}
-
 void launch_spec_select(shifter_ctx* ctx, const shifter_model* m, const float* d_w, uint64_t p,
                         shifter_threshold* d_thr, float* d_w_out, uint8_t* d_mask,
                         uint8_t* d_out_alive, uint8_t* d_in_alive, SpecState* host_mirror) {
@@ -742,23 +568,10 @@ void launch_spec_select(shifter_ctx* ctx, const shifter_model* m, const float* d
     const bool fused = d_w_out != nullptr;
     hipStream_t s = ctx->stream;
     {
-        // the set-up rides on the sample kernel
         ProfileScope ps(ctx, K_SPEC_SAMPLE);
-        SampleZero z;
-        z.ss = b.spec;
-        z.cnt1 = b.spec_cnt;
-        z.p = p;
-        z.m_valid = m->sample_size;
-        z.fa = d_out_alive;
-        z.na = fused ? m->info.sum_out_ch : 0;
-        z.fb = d_in_alive;
-        z.nb = fused ? m->info.sum_in_ch : 0;
-        launch_spec_sample(ctx, m, d_w, z);
-    }
-    {
-        ProfileScope ps(ctx, K_SPEC_PREDICT);
-        spec_predict_kernel<<<1, BLOCK, 0, s>>>(b.spec, b.shist, m->info.n_prunable,
-                                                ctx->margin_sigmas);
+        spec_front_kernel<<<sample_grid(m), SAMPLE_THREADS, 0, s>>>(
+            sample_in(m, d_w), b.spec, b.spec_cnt, b.partial, d_out_alive, fused ? m->info.sum_out_ch : 0, d_in_alive,
+            fused ? m->info.sum_in_ch : 0, p, m->sample_size, m->info.n_prunable, ctx->margin_sigmas);
     }
     {
         ProfileScope ps(ctx, K_SPEC_PASS);
@@ -775,9 +588,8 @@ void launch_spec_select(shifter_ctx* ctx, const shifter_model* m, const float* d
     }
     {
         ProfileScope ps(ctx, K_SPEC_FINISH2);
-        spec_filter_kernel<<<FIN_BLOCKS, BLOCK, 0, s>>>(b.spec, b.spec_cnt, b.partial, b.cand,
-                                                        b.cand_cap_sb, b.list);
-        spec_rank_kernel<<<1, BLOCK, 0, s>>>(b.spec, b.list, d_thr, host_mirror);
+        spec_finish_kernel<<<FIN_BLOCKS, BLOCK, 0, s>>>(b.spec, b.spec_cnt, b.partial, b.cand, b.cand_cap_sb, b.list,
+                                                        d_thr, host_mirror);
     }
     if (fused) {
         ProfileScope ps(ctx, K_SPEC_FIXUP);
