@@ -755,7 +755,8 @@ struct InflateShared {
 // is copied.  Otherwise the segment is staged in LDS, every sub-chunk's place follows from
 // the side information and every lane's from the sub-chunk's mark: lane q decodes the tokens
 // from bit b_q on (or copies its 128 stored bytes) into a zeroed LDS image of the chunk,
-// which is then written out as whole lines.  Three instances share the chunks by segment
+// which is then written out as whole lines.  Few chunks are all taken by one instance (SEG_MIN 0,
+// room for the longest segment).  Of more, three instances share the chunks by segment
 // size (SEG_DW dwords of LDS for the segment); the smallest visits every chunk and also
 // takes those stored as one block, the other two walk lists.  The segment's size must be
 // what the side information implies, every lane must end exactly where the next one
@@ -1194,6 +1195,15 @@ __global__ __launch_bounds__(CLASSIFY_THREADS) void codec_classify_kernel(
     }
 }
 
+// Up to this many chunks - two rounds of two blocks on each of 256 compute units - one instance with
+// room for the longest segment takes them all.  An instance's time is then the latency of a
+// chunk or two, and three instances one behind the other cost three; beyond it the room that
+// short segments leave unused costs more than the launches.  Three instances against one, us a
+// call, chunks of one density / of densities from 0 to 1: 128 chunks 26-44 / 74 and 19-37 / 40;
+// 855 29-77 / 87 and 25-70 / 68; 1024 30-79 / 108 and 27-71 / 76; 1280 31-100 / 114 and 31-91 / 89, but at
+// density 0.3 67 and 73; 8192 at density 0.3 285 and 372.
+constexpr uint32_t INFLATE_ONE_LAUNCH = 1024;
+
 // Kernels only, nothing waited for: the lists of the two larger instances are made on the
 // device and walked by fixed grids.  Returns a HIP error code (0: fine).
 int launch_inflate(shifter_ctx* ctx, const uint8_t* d_stream, uint64_t stream_bytes,
@@ -1206,7 +1216,12 @@ int launch_inflate(shifter_ctx* ctx, const uint8_t* d_stream, uint64_t stream_by
     const uint32_t* n_medium = reinterpret_cast<const uint32_t*>(ctx->d_codec + 2);
     const uint32_t* n_large = reinterpret_cast<const uint32_t*>(ctx->d_codec + 3);
     codec_begin(ctx);
-    {
+    if (n_chunks <= INFLATE_ONE_LAUNCH) {
+        ProfileScope ps(ctx, K_INFLATE_CHUNK);
+        inflate_chunk_kernel<CODEC_SEG_LARGE, 0><<<n_chunks, CODEC_THREADS, 0, ctx->stream>>>(
+            d_stream, stream_bytes, d_seg_off, d_sub_bits, d_sub_marks, n_bytes, n_chunks, d_out, ctx->d_codec,
+            nullptr, nullptr);
+    } else {
         ProfileScope ps(ctx, K_INFLATE_CHUNK);
         codec_classify_kernel<<<(n_chunks + CLASSIFY_THREADS - 1) / CLASSIFY_THREADS, CLASSIFY_THREADS, 0, ctx->stream>>>(
             stream_bytes, d_seg_off, d_sub_bits, n_chunks, list_medium, list_large, ctx->d_codec);
