@@ -1006,9 +1006,11 @@ void launch_spec_multi(shifter_ctx* ctx, const shifter_model* m, const float* d_
     hipStream_t s = ctx->stream;
     if (k == 0 && fb) launch_zero_levels(ctx, m);
     {
-        // the fused pass adds to the level arrays: cleared on the way
+        // the fused pass adds to the level arrays: cleared on the way.  At least a block per rank: the
+        // ranks' counters lie on 512 lines each, too many for one block to clear (fifteen ranks, 264
+        // tiles: 22.2 us with one block, 16.7 with fifteen)
         ProfileScope ps(ctx, K_SPEC_SAMPLE);
-        ms_front_kernel<<<k ? sample_grid(m) : 1u, SAMPLE_THREADS, 0, s>>>(
+        ms_front_kernel<<<k ? std::max(sample_grid(m), k) : 1u, SAMPLE_THREADS, 0, s>>>(
             sample_in(m, d_w), b.multi, b.multi_cnt, b.multi_hist, b.multi_list_cnt, fb && k ? b.levels : nullptr,
             fb && k ? (uint32_t)(m->info.sum_out_ch + m->info.sum_in_ch) : 0u, sorted_p, perm, k, m->sample_size,
             zero_mask, d_thr, b.dev_multi_rec, m->info.n_prunable, ctx->margin_sigmas, b.multi_tab, b.cand_cap_sb);

@@ -51,7 +51,7 @@ inline SampleIn sample_in(const shifter_model* m, const float* d_w) {
 // What bounds it is a chain of latencies: table, tensor and weights behind one another, then the
 // prediction on one block.  In the last block of this launch the prediction costs no launch of its own
 // (kernel times: one count of 24 k weights 3 + 11 us apart, 6.7 here; of 295 M 13.6 + 11.7 and 19.1;
-// a portfolio's on 10 M 7.2 + 11.4 and 16.2, on 0.86 M 7.4 + 12.4 and 21.9, less a launch's gap).
+// a portfolio's on 10 M 7.2 + 11.4 and 16.2, on 0.86 M 7.4 + 12.4 and 16.7, less a launch's gap).
 __device__ __forceinline__ bool sample_prefix(const SampleIn& in, uint32_t* h) {
     const DevTensor* __restrict__ tens = in.tens;
     const uint32_t* __restrict__ tile_prefix = in.tile_prefix;
