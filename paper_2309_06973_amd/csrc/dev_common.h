@@ -155,20 +155,27 @@ __device__ __forceinline__ void lds_count(uint32_t* h, uint32_t bin, bool want) 
     if (same && (peers & ((1ull << (threadIdx.x & 63u)) - 1ull)) == 0ull) atomicAdd(&h[first], (uint32_t)__popcll(peers));
 }
 
-// f(valid, pair) for the n pairs at src, DEPTH loads per thread in flight; every thread of
-// the block makes the same calls.
+// f(valid, pair) for the n pairs at src, which starts on 16 bytes and has room for an even number
+// of them; DEPTH loads of two pairs per thread in flight; every thread of the block makes the same
+// calls.
 template <uint32_t THREADS, uint32_t DEPTH, typename F>
 __device__ __forceinline__ void walk_pairs(const uint2* __restrict__ src, uint32_t n, F&& f) {
-    for (uint32_t i0 = 0; i0 < n; i0 += THREADS * DEPTH) {
-        uint2 c[DEPTH];
+    const uint4* __restrict__ src4 = reinterpret_cast<const uint4*>(src);
+    for (uint32_t i0 = 0; i0 < n; i0 += 2u * THREADS * DEPTH) {
+        uint4 c[DEPTH];
 #pragma unroll
         for (uint32_t u = 0; u < DEPTH; ++u) {
-            const uint32_t i = i0 + u * THREADS + threadIdx.x;
-            c[u] = i < n ? src[i] : make_uint2(0, 0);
+            const uint32_t i = i0 + 2u * (u * THREADS + threadIdx.x);
+            c[u] = i < n ? src4[i / 2u] : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
-        for (uint32_t u = 0; u < DEPTH; ++u)
-            if (i0 + u * THREADS < n) f(i0 + u * THREADS + threadIdx.x < n, c[u]);
+        for (uint32_t u = 0; u < DEPTH; ++u) {
+            const uint32_t i = i0 + 2u * (u * THREADS + threadIdx.x);
+            if (i0 + 2u * u * THREADS < n) {
+                f(i < n, make_uint2(c[u].x, c[u].y));
+                f(i + 1u < n, make_uint2(c[u].z, c[u].w));
+            }
+        }
     }
 }
 
@@ -176,9 +183,9 @@ __device__ __forceinline__ void walk_pairs(const uint2* __restrict__ src, uint32
 // index), by one block.  All n lie in the window of 2^width composites (|bits| << 32 | index)
 // from c_lo on, width <= 63.  4096-bin histograms of the composite narrow the window, first over
 // the key, then, where that many weights share it, over the index; a window of at most
-// RANK_DIRECT pairs is ranked by counting.  Afterwards sh.sel is the pair, sh.lt and sh.eq
-// the numbers of pairs in the list with a smaller and with the same key.  Returns false if
-// the list does not hold r pairs of the window.
+// RANK_DIRECT pairs is ranked by counting.  Afterwards sh.sel is the pair and, if count, sh.lt
+// and sh.eq are the numbers of pairs in the list with a smaller and with the same key.  Returns
+// false if the list does not hold r pairs of the window.
 constexpr uint32_t RANK_BINS = 4096, RANK_DIRECT = 96;
 template <uint32_t THREADS>
 struct RankShared {
@@ -190,7 +197,7 @@ struct RankShared {
 };
 template <uint32_t THREADS, uint32_t DEPTH>
 __device__ bool rank_in_list(const uint2* __restrict__ src, uint32_t n, uint64_t c_lo, uint32_t width,
-                             uint64_t r, RankShared<THREADS>& sh) {
+                             uint64_t r, bool count, RankShared<THREADS>& sh) {
     auto composite = [](uint2 c) { return ((uint64_t)(c.x & 0x7fffffffu) << 32) | c.y; };
     uint32_t in_window = n, below = 0;          // pairs in the window, pairs of the list below it
     if (threadIdx.x == 0) { sh.sel = 0; sh.nb = 0; sh.lt = 0; sh.eq = 0; }
@@ -241,6 +248,7 @@ __device__ bool rank_in_list(const uint2* __restrict__ src, uint32_t n, uint64_t
         if (rank == r - 1) sh.sel = c;          // composites are distinct: exactly one hit
     }
     __syncthreads();
+    if (!count) return true;
     const uint32_t key = (uint32_t)(sh.sel >> 32);
     uint32_t lt = 0, eq = 0;
     if (width >= 32u) {                         // the window holds whole keys

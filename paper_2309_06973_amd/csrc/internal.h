@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "sel_plan.h"
 #include "shifter.h"
 
 namespace shifter {
@@ -53,8 +54,6 @@ struct DevVec {
 };
 
 // State of the multi-pass select (select.hip), ranks sorted by prune count.
-constexpr uint32_t SEL_BINS = 16384;      // counters of one histogram: the top bins, or all windows' of a stage
-constexpr uint32_t SEL_STAGES = 8;        // at most this many stages for any N < 2^32 and K <= MAXK
 enum : uint32_t { SEL_IDLE = 0, SEL_SPLIT = 1, SEL_LISTED = 2 };
 struct SelWindow {
     uint64_t c_lo;             // first composite of the window, which spans 2^width
@@ -65,7 +64,7 @@ struct SelWindow {
     uint32_t width;
     uint32_t leader;           // first rank with the same window: owner of its histogram and list
     uint32_t mode;             // of this stage: split by a histogram, listed, or nothing to do
-    uint32_t pad;
+    uint32_t stage;            // whose key_lo, key_hi say what keys it holds; 0: not known
 };
 struct SelState {
     SelWindow win[SEL_STAGES + 1][MAXK];   // by stage; the first is unused
@@ -73,8 +72,11 @@ struct SelState {
     uint64_t p[MAXK];
     uint32_t perm[MAXK];                   // caller's position of a rank
     uint32_t list_cnt[MAXK];
+    uint32_t key_lo[SEL_STAGES + 1][MAXK]; // smallest and largest key met in a window, by stage
+    uint32_t key_hi[SEL_STAGES + 1][MAXK];
     uint32_t done[SEL_STAGES + 1];         // every rank is listed after this stage
     uint32_t nan_seen;
+    uint32_t n_zero;                       // prunable weights that are zero
 };
 
 // State of the single-pass (sample, predict, one pass, finish) selection.
