@@ -1047,9 +1047,13 @@ void launch_spec_multi(shifter_ctx* ctx, const shifter_model* m, const float* d_
         }
         {
             ProfileScope ps(ctx, K_SPEC_FINISH2);
-            ms_finish_kernel<<<dim3(CAND_SUB, k), MF_THREADS, 0, s>>>(b.multi, b.multi_cnt, b.cand, b.multi_hist,
-                                                                     b.multi_rowsum, b.multi_list, b.multi_list_cnt,
-                                                                     d_thr, b.dev_multi_rec, b.dev_multi_status);
+            // a block for each part that a pass over this many tiles can have filled: two blocks fit a
+            // compute unit, so with 32 to a rank those of seventeen and more ranks take two rounds (twenty
+            // ranks of a 24 k weight network, 9 tiles: 34 us with 32 blocks a rank, 14 with 9; few distinct
+            // weights 64 and 29)
+            ms_finish_kernel<<<dim3(std::min(CAND_SUB, m->n_tiles), k), MF_THREADS, 0, s>>>(
+                b.multi, b.multi_cnt, b.cand, b.multi_hist, b.multi_rowsum, b.multi_list, b.multi_list_cnt, d_thr,
+                b.dev_multi_rec, b.dev_multi_status);
         }
     }
     if (fb) {
