@@ -119,7 +119,9 @@ __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t lane, ui
 // A stored sub-chunk ends on a byte, so a run of coded ones always starts on one: two prefix
 // sums, of the token bits and of the bytes up to the end of each stored sub-chunk, place
 // all of them at once (a walk over the 64 sub-chunks, which any stored one needed before,
-// took about 4 us of a chunk's life).
+// took about 4 us of a chunk's life).  Without a stored one the first sum does (with
+// both, 12288 chunks of half-full weights inflated in 805 us, with the first alone in 792, as with the walk; 39347
+// sparse ones deflated in 1198 and 1172).
 __device__ __forceinline__ uint32_t place_subs(uint32_t v, uint32_t n, uint32_t lane, uint32_t* start,
                                                bool* in_block, uint32_t* tail_start, bool* tail_in_block) {
     const bool stored = n != 0u && v == CODEC_STORED;
@@ -127,17 +129,20 @@ __device__ __forceinline__ uint32_t place_subs(uint32_t v, uint32_t n, uint32_t 
     const uint32_t bits = wave_excl_scan(n != 0u && !stored ? v : 0u, lane, &bits_total);   // coded bits before this lane
     const uint64_t st = __ballot(stored);
     const uint64_t before = st & ((1ull << lane) - 1ull);
-    // coded bits since the last stored sub-chunk (or the start)
-    const uint32_t at_stored = __shfl(bits, before ? 63 - __clzll((long long)before) : 0, 64);
-    const uint32_t run = bits - (before ? at_stored : 0u);
-    const uint32_t head = run ? 3u + run : 0u;                        // with the block's header
-    const uint32_t bytes = stored ? ((head + (run ? 7u : 0u) + 3u + 7u) >> 3) + 4u + n : 0u;
-    uint32_t bytes_total;
-    const uint32_t byte0 = wave_excl_scan(bytes, lane, &bytes_total);
-    *start = 8u * byte0 + head;
+    uint32_t run = bits, tail_run = bits_total;         // coded bits since the last stored sub-chunk (or the start)
+    uint32_t byte0 = 0, bytes_total = 0;
+    if (st == 0ull) {                                   // most chunks: one Huffman block
+        *start = run ? 3u + run : 0u;
+    } else {
+        const uint32_t at_stored = __shfl(bits, before ? 63 - __clzll((long long)before) : 0, 64);
+        run = bits - (before ? at_stored : 0u);
+        const uint32_t head = run ? 3u + run : 0u;                    // with the block's header
+        const uint32_t bytes = stored ? ((head + (run ? 7u : 0u) + 3u + 7u) >> 3) + 4u + n : 0u;
+        byte0 = wave_excl_scan(bytes, lane, &bytes_total);
+        *start = 8u * byte0 + head;
+        tail_run = bits_total - __shfl(bits, 63 - __clzll((long long)st), 64);
+    }
     *in_block = run != 0u;
-    const uint32_t last_bits = __shfl(bits, st ? 63 - __clzll((long long)st) : 0, 64);
-    const uint32_t tail_run = bits_total - (st ? last_bits : 0u);
     const uint32_t pos = 8u * bytes_total + (tail_run ? 3u + tail_run : 0u);
     *tail_start = pos;
     *tail_in_block = tail_run != 0u;
