@@ -9,6 +9,7 @@
 #include <mutex>
 #include <new>
 
+#include "chain.h"
 #include "internal.h"
 
 using namespace shifter;
@@ -1573,8 +1574,8 @@ static int codec_enter(shifter_ctx* ctx, const char* fn) {
 static int codec_result(shifter_ctx* ctx, uint64_t* total, uint64_t* status) {
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     const volatile uint64_t* mirror = ctx->h_codec;
-    *total = mirror[0];
-    *status = mirror[1];
+    *total = mirror[CHAIN_BYTES];
+    *status = mirror[CHAIN_STATUS] | (mirror[CHAIN_BROKE] ? CODEC_CHAIN : 0u);
     return SHIFTER_OK;
 }
 
@@ -1643,8 +1644,8 @@ extern "C" int shifter_inflate(shifter_ctx* ctx, const uint8_t* d_stream, uint64
 extern "C" int shifter_codec_status(shifter_ctx* ctx, uint64_t* h_stream_bytes, uint32_t* h_bad) {
     if (!ctx) return fail(nullptr, SHIFTER_ERR_INVALID_ARG, "codec_status: ctx is NULL");
     const volatile uint64_t* mirror = ctx->h_codec;
-    if (h_stream_bytes) *h_stream_bytes = mirror[0];
-    if (h_bad) *h_bad = mirror[1] != 0;
+    if (h_stream_bytes) *h_stream_bytes = mirror[CHAIN_BYTES];
+    if (h_bad) *h_bad = (mirror[CHAIN_STATUS] | mirror[CHAIN_BROKE]) != 0;
     return SHIFTER_OK;
 }
 

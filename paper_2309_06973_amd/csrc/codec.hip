@@ -23,6 +23,7 @@
 // 32 lanes per sub-chunk, the decoder with 256 and four.
 #include <string>
 
+#include "chain.h"
 #include "dev_common.h"
 
 namespace shifter {
@@ -265,36 +266,28 @@ __device__ __forceinline__ void emit_tokens(uint32_t* out, uint32_t bit, const u
     }
 }
 
-// Chained offsets of the segments.  status[c]: 0 nothing yet, bits 62-63 = 1 the size of segment c
-// alone, 2 the size of all segments up to and including c, 3 the chain broke.
-constexpr uint64_t CHAIN_VALUE = (1ull << 62) - 1ull;
+// Chained offsets of the segments (the decoupled look-back of Merrill and Garland's single-pass
+// scan; chain.h has its rules).
 constexpr uint32_t CHAIN_POLLS = 1u << 22;     // seconds: far beyond any wait that ends
 __device__ __forceinline__ void chain_store(uint64_t* p, uint64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Sum of the sizes before chunk c, by one wavefront: 64 predecessors at a time, back to the
-// nearest one whose sum is known.  Chunks are numbered by a ticket that a block draws when it
-// starts, and a block stores its size before it waits for anything: every predecessor is
-// running or done and its size arrives without it waiting for this block.
-__device__ __forceinline__ uint64_t chain_before(const uint64_t* status, uint32_t c, uint32_t lane, bool* broken) {
-    uint64_t sum = 0;
-    uint32_t polls = 0;
-    for (int64_t last = (int64_t)c - 1; last >= 0;) {
-        const int64_t i = last - (int64_t)lane;
+// Sum of the sizes before chunk c, by one wavefront.  Chunks are numbered by a ticket that a block
+// draws when it starts, and a block stores its size before it waits for anything: every predecessor
+// is running or done and its size arrives without it waiting for this block.
+__device__ __forceinline__ ChainWalk chain_before(const uint64_t* status, uint32_t c, uint32_t lane) {
+    ChainWalk walk(c);
+    while (walk.waits()) {
+        const int64_t i = walk.last - (int64_t)lane;
         const uint64_t x = i >= 0 ? __hip_atomic_load(status + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 2ull << 62;
         const uint32_t kind = (uint32_t)(x >> 62);
-        if (__ballot(kind == 3u) != 0ull || ++polls > CHAIN_POLLS) { *broken = true; return 0; }
-        const uint64_t known = __ballot(kind == 2u), here = __ballot(kind != 0u);
-        const uint32_t upto = known ? (uint32_t)__ffsll((unsigned long long)known) - 1u : 63u;   // last lane needed
-        const uint64_t need = ~0ull >> (63u - upto);
-        if ((here & need) != need) { __builtin_amdgcn_s_sleep(4); continue; }
-        uint64_t part = lane <= upto ? x & CHAIN_VALUE : 0ull;
+        const uint64_t need = walk.look(__ballot(kind == 2u), __ballot(kind != 0u), __ballot(kind == 3u), CHAIN_POLLS);
+        if (need == 0ull) { __builtin_amdgcn_s_sleep(4); continue; }
+        uint64_t part = (need >> lane) & 1ull ? x & CHAIN_VALUE : 0ull;
         for (uint32_t d = 32; d > 0; d >>= 1) part += __shfl_xor((unsigned long long)part, d, 64);
-        sum += part;
-        if (known) break;
-        last -= 64;
+        walk.sum += part;
     }
-    return sum;
+    return walk;
 }
 
 // A whole sub-chunk of zeros: the literal 0 (00110000) and the matches 258 (symbol 285: 11000101)
@@ -443,7 +436,7 @@ __global__ __launch_bounds__(DEF_THREADS, 6) void deflate_kernel(
     const bool whole = m + 5u <= coded_bytes;           // not shorter than one stored block
     const uint32_t seg_bytes = whole ? m + 5u : coded_bytes;
     if (threadIdx.x == 0) {
-        if (DIRECT) chain_store(status + c, ((c == 0u ? 2ull : 1ull) << 62) | seg_bytes);
+        if (DIRECT) chain_store(status + c, chain_size(c, seg_bytes));
         else seg_size[c] = seg_bytes;
     }
     if (wid == 0u) {
@@ -526,18 +519,12 @@ __global__ __launch_bounds__(DEF_THREADS, 6) void deflate_kernel(
     uint8_t* dst = slots + (uint64_t)c * CODEC_SLOT;
     if (DIRECT) {
         if (wid == 0u) {
-            bool broken = false;
-            const uint64_t off = chain_before(status, c, lane, &broken);
+            const ChainWalk walk = chain_before(status, c, lane);
             if (lane == 0u) {
-                if (broken) chain_store(status + c, 3ull << 62);
-                else if (c) chain_store(status + c, (2ull << 62) | (off + seg_bytes));
-                s_off = broken ? ~0ull : off;
-                seg_off[c] = off;
-                if (last) {
-                    seg_off[n_chunks] = off + seg_bytes;
-                    mirror[0] = off + seg_bytes;
-                    mirror[1] = broken ? CODEC_CHAIN : 0u;
-                }
+                chain_leave(walk, c, last != 0u, seg_bytes, status + c, mirror, chain_store);
+                s_off = walk.broken ? ~0ull : walk.sum;
+                seg_off[c] = walk.sum;
+                if (last) seg_off[n_chunks] = walk.sum + seg_bytes;
             }
         }
         __syncthreads();
@@ -560,10 +547,12 @@ __global__ __launch_bounds__(DEF_THREADS, 6) void deflate_kernel(
     if (threadIdx.x < seg_bytes - done) dst[done + threadIdx.x] = out8[done + threadIdx.x];
 }
 
-// Clears the chain of a call: the status words of its chunks and the ticket behind them.
-__global__ __launch_bounds__(BLOCK) void chain_clear_kernel(uint64_t* status, uint32_t n) {
+// Clears the chain of a call: the status words of its chunks, the ticket behind them and the word
+// that says that a wait ran out.
+__global__ __launch_bounds__(BLOCK) void chain_clear_kernel(uint64_t* status, uint32_t n, uint64_t* mirror) {
     const uint32_t i = blockIdx.x * BLOCK + threadIdx.x;
     if (i < n) status[i] = 0;
+    if (i == 0) mirror[CHAIN_BROKE] = 0;
 }
 
 // Byte offsets of the segments: exclusive prefix sums of their sizes (one block).  A row is
@@ -1079,8 +1068,9 @@ __global__ void codec_clear_kernel(uint64_t* result) {
 // its wait; the result words are then cleared for the next call (zero after use: the next
 // call needs no clearing launch of its own).
 __global__ void codec_publish_kernel(uint64_t* __restrict__ result, uint64_t* __restrict__ mirror) {
-    mirror[0] = result[0];
-    mirror[1] = result[1];
+    mirror[CHAIN_BYTES] = result[0];
+    mirror[CHAIN_STATUS] = result[1];
+    mirror[CHAIN_BROKE] = 0;
     result[0] = 0;
     result[1] = 0;
     result[2] = 0;
@@ -1127,7 +1117,7 @@ int launch_deflate(shifter_ctx* ctx, const uint8_t* d_in, uint64_t n_bytes, uint
         uint64_t* status = reinterpret_cast<uint64_t*>(d_work);
         {
             ProfileScope ps(ctx, K_CODEC_SCAN);
-            chain_clear_kernel<<<(n_chunks + BLOCK) / BLOCK, BLOCK, 0, ctx->stream>>>(status, n_chunks + 1u);
+            chain_clear_kernel<<<(n_chunks + BLOCK) / BLOCK, BLOCK, 0, ctx->stream>>>(status, n_chunks + 1u, ctx->dev_codec_mirror);
         }
         ProfileScope ps(ctx, K_DEFLATE_CHUNK);
         deflate_kernel<true><<<n_chunks, DEF_THREADS, 0, ctx->stream>>>(
