@@ -88,9 +88,16 @@ void launch_fold(shifter_ctx* ctx, const shifter_model* m, const float* d_w, con
     }
     if (m->n_tiles == 0) return;
     ProfileScope ps(ctx, K_FOLD_APPLY);
-    // beyond the chip's L2 the streaming hint pays, also where the arena would fit the last-level
-    // cache (102 MB in and out: 41.6 us a call without it, 36.3 with)
-    if (m->info.w_extent * 4 > (32ull << 20))
+    // Where input and output together exceed the last-level cache (256 MiB) the streaming hint pays.
+    // Below, what of them the cache holds is worth more than the hint gives an arena that comes from
+    // memory.  us a call without / with it, the same arenas again and again, arenas that come from memory, and
+    // input made just before and output read behind (all three steps):
+    //    34 MB  16.3 / 15.2   22.2 / 18.5    38.6 /  44.8        119 MB  39.3 / 44.0   51.0 / 46.4   134.6 / 132.7
+    //    56 MB  21.0 / 21.1   28.4 / 23.4    55.9 /  59.5        138 MB  46.6 / 46.6   54.2 / 48.3   155.5 / 140.5
+    //    81 MB  29.0 / 30.8   37.7 / 33.3    84.7 /  85.1        162 MB  62.0 / 58.9   65.2 / 60.6   183.8 / 180.0
+    //   102 MB  34.1 / 38.0   42.5 / 40.1   117.4 / 110.8        191 MB  73.7 / 65.8   74.4 / 67.8   211.7 / 198.4
+    // (Of sizes 3 MB apart from 136 to 201 MB one, 146, was slower with the hint: same arenas 51.8 / 53.3.)
+    if (m->info.w_extent * 8 > (256ull << 20))
         fold_apply_kernel<true><<<m->n_tiles, BLOCK, 0, ctx->stream>>>(
             b.tens, b.tile_prefix, b.tile_tensor, b.fold_scale, d_w, d_w_out);
     else
