@@ -21,8 +21,7 @@ const char* const kKernelNames[K_COUNT] = {
     "copy", "kernel_scan", "fix_round", "fold_scale", "fold_apply",
     "deflate_chunk", "codec_scan", "codec_pack", "inflate_chunk",
     "mask_scan_batch", "expand_levels",
-    "spec_init", "spec_sample", "spec_predict", "spec_pass", "spec_hist_locate", "spec_filter_rank",
-    "spec_fixup", "spec_rank"};
+    "spec_sample", "spec_pass", "spec_hist_locate", "spec_filter_rank", "spec_fixup"};
 
 ProfileScope::ProfileScope(shifter_ctx* c, int id) : ctx(c), idx(-1) {
     if (!c->profiling) return;
@@ -504,8 +503,8 @@ static int bind_tables(shifter_ctx* ctx, shifter_model* m) {
     if ((rc = upload(ctx, &b.ranked_ids, m->ranked_ids.data(), m->ranked_ids.size()))) return rc;
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.spec), sizeof(SpecState)));
     // every ranking reads the sample histogram and leaves it cleared for the next one
-    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.shist), sizeof(uint32_t) * 65536));
-    HIP_TRY(ctx, hipMemset(b.shist, 0, sizeof(uint32_t) * 65536));
+    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.shist), sizeof(uint32_t) * (SAMPLE_BINS + 1)));
+    HIP_TRY(ctx, hipMemset(b.shist, 0, sizeof(uint32_t) * (SAMPLE_BINS + 1)));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.spec_cnt), sizeof(uint32_t) * 2 * SPEC_SUB * 32));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.partial), sizeof(uint32_t) * 4 * 256));
     // candidate pairs: 1/4 of N in total (a 20-variant portfolio on a mid-size model makes
@@ -652,7 +651,7 @@ extern "C" int shifter_global_threshold(shifter_ctx* ctx, const shifter_model* m
         pc.p[k] = h_n_prune[k];
     }
     if (h_thr && K == 1 && ctx->select_path == 0) {
-        // single pass; exact when its own check holds, else fall through to the radix select
+        // single pass; exact when its own check holds, else fall through to the multi-pass select
         launch_spec_select(ctx, model, d_w, pc.p[0], d_thr, nullptr, nullptr, nullptr, nullptr,
                            model->b.dev_spec_now);
         if ((rc = after_launch(ctx, "global_threshold"))) return rc;
@@ -1347,7 +1346,7 @@ static MultiPerm cut_positions(const PruneCounts& pc, uint32_t K) {
     return pos;
 }
 
-static int portfolio_radix(shifter_ctx* ctx, const shifter_model* model, const PruneCounts& pc,
+static int portfolio_multipass(shifter_ctx* ctx, const shifter_model* model, const PruneCounts& pc,
                            const PortfolioBuffers& a) {
     int rc;
     launch_select(ctx, model, a.d_w, pc, a.k_var, a.d_thr);
@@ -1436,7 +1435,7 @@ extern "C" int shifter_portfolio_begin(shifter_ctx* ctx, const shifter_model* mo
         }
     } else {
         pp.mode = 3;
-        if ((rc = portfolio_radix(ctx, model, pp.pc, pp.buf))) return rc;
+        if ((rc = portfolio_multipass(ctx, model, pp.pc, pp.buf))) return rc;
     }
     if ((rc = after_launch(ctx, "portfolio_begin"))) return rc;
     pp.active = true;
@@ -1462,7 +1461,7 @@ extern "C" int shifter_portfolio_end(shifter_ctx* ctx, shifter_threshold* h_thr,
     if (!decided) {
         if (pp.mode != 3) {
             // the single pass could not decide: the multi-pass select, and every later step again
-            if ((rc = portfolio_radix(ctx, model, pp.pc, pp.buf))) return rc;
+            if ((rc = portfolio_multipass(ctx, model, pp.pc, pp.buf))) return rc;
         }
         ctx->last_path = 2;
         HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));

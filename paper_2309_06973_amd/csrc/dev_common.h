@@ -23,7 +23,6 @@ __device__ __forceinline__ uint32_t find_tensor(const uint32_t* __restrict__ pre
 // the keys above it the last bin.  The intervals predicted from the sample are rounded
 // outward to whole bins, so narrow bins mean few candidates; no result depends on the
 // binning (weights all outside the window only send the selection to its multi-pass form).
-constexpr uint32_t SAMPLE_BINS = 16384;
 constexpr uint32_t SAMPLE_BIN_SHIFT = 15;
 constexpr uint32_t SAMPLE_KEY0 = (127u - 50u) << 23;      // first key of the window
 static_assert(((uint64_t)SAMPLE_BINS << SAMPLE_BIN_SHIFT) == (64ull << 23), "64 binades");

@@ -17,6 +17,7 @@ constexpr uint32_t BLOCK = 256;      // threads per block (4 wavefronts of 64)
 constexpr uint32_t MAXK = SHIFTER_MAX_VARIANTS;
 constexpr uint32_t GATHER_CHUNK = 1024;  // columns of a gather work unit (16 per lane)
 constexpr uint32_t GATHER_ROWS = 16;
+constexpr uint32_t SAMPLE_BINS = 16384;  // of the sample histogram (sample_bin)
 constexpr uint32_t RECT_ELEMS = 8192;    // floats of a source rectangle staged in LDS by the portfolio rebuild
 
 // Device-side view of one weight tensor.
@@ -164,8 +165,7 @@ enum KernelId {
     K_COPY, K_KERNEL_SCAN, K_FIX_ROUND, K_FOLD_SCALE, K_FOLD_APPLY,
     K_DEFLATE_CHUNK, K_CODEC_SCAN, K_CODEC_PACK, K_INFLATE_CHUNK,
     K_MASK_SCAN_BATCH, K_EXPAND_LEVELS,
-    K_SPEC_INIT, K_SPEC_SAMPLE, K_SPEC_PREDICT, K_SPEC_PASS, K_SPEC_FINISH, K_SPEC_FINISH2,
-    K_SPEC_FIXUP, K_SPEC_RANK,
+    K_SPEC_SAMPLE, K_SPEC_PASS, K_SPEC_FINISH, K_SPEC_FINISH2, K_SPEC_FIXUP,
     K_COUNT
 };
 extern const char* const kKernelNames[K_COUNT];
@@ -249,7 +249,7 @@ struct shifter_model {
         std::vector<shifter::FoldTensor> fold_host;   // the layer table the device holds (empty: none yet)
         float* fold_scale = nullptr;          // sum_out_ch
         shifter::SpecState* spec = nullptr;
-        uint32_t* shist = nullptr;            // 65536 sample bins
+        uint32_t* shist = nullptr;            // SAMPLE_BINS counts of the sample, then the ticket
         uint32_t* spec_cnt = nullptr;         // 2 * SPEC_SUB counters, one 128-byte line each
         uint32_t* partial = nullptr;          // 4 * 256: copies of the candidates' histogram
         uint2* cand = nullptr;                // SPEC_SUB sub-buffers of (key, g) pairs
@@ -295,7 +295,7 @@ struct shifter_ctx {
     std::vector<Rec> recs;
     std::vector<hipEvent_t> pool;
     uint32_t hist_grid = 256;
-    int select_path = 0;   // 0: single-pass where it applies; 1: multi-pass radix only
+    int select_path = 0;   // 0: single-pass where it applies; 1: multi-pass select only
     double margin_sigmas = 4.0;   // half-width of the predicted interval, in binomial sigmas
     uint64_t fused_min_bytes = 192ull << 20;   // portfolio_begin: arenas above this take the fused pass
     shifter::SpecState last_spec{};  // outcome of the last single-pass selection
