@@ -192,7 +192,8 @@ int shifter_global_threshold(shifter_ctx* ctx, const shifter_model* model,
  *              multi-pass select on a model of one prunable tensor of n weights; no NaN
  *              report, as with h_thr = NULL there)
  * Limits: n <= SHIFTER_STATIC_MAX_WEIGHTS and K * ceil(n / 4096) <=
- * SHIFTER_STATIC_MAX_TILE_COUNTS, else SHIFTER_ERR_CAPACITY (nothing is enqueued).
+ * SHIFTER_STATIC_MAX_TILE_COUNTS, else SHIFTER_ERR_CAPACITY (nothing is enqueued).  (The
+ * second is a limit of the call, no longer of its scratch, whose size does not depend on K.)
  * All calls on one GPU share that GPU's array, whatever their context or stream: calls
  * that overlap in time on one GPU race; calls on one stream, or otherwise ordered, are
  * fine.  What must start at zero is cleared by the call's first kernel. */
@@ -204,10 +205,10 @@ int shifter_global_threshold_static(shifter_ctx* ctx, const float* d_w, uint64_t
 
 /* Which selection algorithm shifter_global_threshold and shifter_prune_fused may use:
  * 0 (default) the single-pass selection where it applies (waiting or two-call form,
- * at most 32 prune counts above zero), with the multi-pass radix select as its
+ * at most 32 prune counts above zero), with the multi-pass select as its
  * fall-back (taken when the pass's own check fails: a sample that misjudged a quantile,
  * tens of thousands of weights equal to a threshold, or - for several prune counts -
- * an index space beyond about 10^9 weights); 1 the multi-pass radix select only.  Both
+ * an index space beyond about 10^9 weights); 1 the multi-pass select only.  Both
  * give the same records. */
 int shifter_set_select_path(shifter_ctx* ctx, int path);
 
@@ -504,7 +505,11 @@ int shifter_codec_status(shifter_ctx* ctx, uint64_t* h_stream_bytes, uint32_t* h
  *   d_vecs_out, cap_v    device, capacity in floats (v_elems always suffices)
  *   h_out_tensors        host, n_tensors descriptors of the rebuilt tensors, or NULL
  *   h_out_vecs           host, n_vecs descriptors, or NULL
- *   h_elems_w, h_elems_v host, floats written to each output arena, or NULL
+ *   h_elems_w, h_elems_v host, floats of the rebuilt tensors and vectors in each output
+ *                        arena, or NULL.  What lies behind them, up to the capacity, is
+ *                        unspecified in every call that rebuilds variants: a portfolio step
+ *                        may leave a first attempt's values there (see
+ *                        shifter_portfolio_begin)
  * If any h_* is non-NULL the call waits for the stream and fills them.  When a
  * capacity is too small nothing is gathered; a waiting call then returns
  * SHIFTER_ERR_CAPACITY with the needed sizes in h_elems_w / h_elems_v. */
@@ -576,7 +581,8 @@ int shifter_prune_fused_batch(shifter_ctx* ctx, const shifter_model* model, cons
  * variants' descriptors.  Every output is identical to what the single steps give
  * (shifter_global_threshold, shifter_apply_mask_batch, shifter_propagate_groups_batch,
  * shifter_compact_batch).  If the single-pass ranking could not decide (rare: heavy ties),
- * _end runs the multi-pass select and repeats the later steps itself before it returns.
+ * _end runs the multi-pass select and repeats the later steps itself before it returns; the
+ * first attempt, made on whatever records d_thr held, stays behind the rebuilt variants' ends.
  *   d_w, d_vecs       device, the dense weight arena and the vector arena
  *   h_n_prune, K      host, K prune counts
  *   flags             as shifter_propagate_groups

@@ -158,8 +158,9 @@ constexpr uint32_t CODEC_LOOP_GRID = 1536;                    // blocks of an in
 // --- the encoder -------------------------------------------------------------------------
 // One block of 512 threads per chunk.  A lane holds 16 consecutive bytes of a sub-chunk (32
 // lanes a sub-chunk, so a wavefront takes 1 KiB at a time and four of those in turn); the
-// chunk stays in registers and only the segment being built is in LDS, so that four blocks
-// fit a compute unit whatever their segments' sizes.  First every piece finds its literals,
+// chunk stays in registers and only the segment being built is in LDS: 33.6 KB a block whatever
+// its size, room for four blocks a compute unit.  (The bound on registers asks for three; the 58 that
+// the compiler takes let four run.)  First every piece finds its literals,
 // the runs they start and its token bits, and prefix sums over the lanes place the pieces in
 // their sub-chunk; then, with the sub-chunks placed in the segment, every lane appends its
 // own piece's tokens.
@@ -302,7 +303,9 @@ constexpr uint64_t ZERO_SUB_MARK = (uint64_t)(ZERO_SUB_BITS | (384u << 11)) | (u
 static_assert(CODEC_SUB == 512u, "258 + 253 + 1");
 
 // DIRECT: the segments go straight to their place in the stream, which cannot overflow (the
-// host checked that it holds the largest possible one).  Otherwise every segment goes to its
+// host checked that it holds the largest possible one).  The tickets take 13.8 ns each on their one
+// address, which only chunks that hold next to nothing notice: 1.3 GB of nothing but zeros take 540 us
+// a call, with slots 345 (39347 chunks at density 0.002: 1172 and 1467).  Otherwise every segment goes to its
 // slot of the workspace, and the two kernels behind this one add up the sizes and, if the
 // stream is large enough, move the segments.
 constexpr uint32_t CODEC_OUT_DW = CODEC_CHUNK / 4 + 8;

@@ -364,7 +364,9 @@ void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float*
 // Layout of the static scratch array used by shifter_global_threshold_static (byte offsets
 // from its 256-byte aligned start) and the limits that follow from its size.
 constexpr uint64_t STATIC_MAX_WEIGHTS = 1ull << 28;       // weights of one flat run
-constexpr uint64_t STATIC_MAX_TILE_COUNTS = 1ull << 20;   // K * tiles of the run
+// K * tiles of the run.  The scratch has no array of that size any more (it held tie counts per
+// tile); kept because the interface promises the error.
+constexpr uint64_t STATIC_MAX_TILE_COUNTS = 1ull << 20;
 constexpr size_t STATIC_OFF_TENSOR = 0;
 constexpr size_t STATIC_OFF_PREFIX = 256;
 constexpr size_t STATIC_OFF_SEL = 512;

@@ -1,9 +1,10 @@
 // Single-pass exact selection of the P-th smallest (|w|, g) pair for one prune count:
 // the unstructured magnitude ranking of Sec. II-A / Sec. III-C of the paper, reached in
-// one read of the arena instead of one read per radix digit.
+// one read of the arena.
 //
-//   1. sample      a systematic sample of the prunable weights (two 128-byte lines out
-//                  of every sampled tile) is histogrammed on the top 16 key bits;
+//   1. sample      a stratified sample of the prunable weights (four 64-byte sectors out of
+//                  every sampled tile, spec_sample.h) is histogrammed on 16384 bins of 1/256 of a
+//                  binade;
 //   2. predict     from the sample's order statistics around P/N, widened by a margin,
 //                  a key interval [lo, hi] that should contain the threshold key;
 //   3. one pass    over the arena counts the weights below lo and appends the
@@ -17,7 +18,8 @@
 //
 // The result is exact whenever step 4's check holds; otherwise (a sample that misled,
 // an interval with too many ties, a full buffer) a status bit is raised and the host
-// runs the multi-pass select instead.
+// runs the multi-pass select instead.  Steps 1 and 2 are one launch, and so are the two later
+// parts of step 4 (the block that ends last goes on).
 #include <algorithm>
 
 #include "spec_sample.h"

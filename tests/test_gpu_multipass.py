@@ -1,5 +1,5 @@
-"""The multi-pass select at the sizes where its windows change kind: lists of exactly the
-capacity and beyond, runs of equal weights that only their index separates, weights outside
+"""The multi-pass select at the sizes where its windows change kind: runs of exactly a list's room
+and beyond, runs of equal weights that only their index separates, weights outside
 the binned range, weights sorted by size (one block meets a whole window), more ranks than
 windows.  Every record against the counting definition on one stable sort."""
 import numpy as np
@@ -31,7 +31,8 @@ def values(kind, n):
     raise ValueError(kind)
 
 
-# a list holds 2^19 / K pairs: one rank lists everything up to 524288 weights at once, 64 ranks 8192 each
+# a list has room for 2^19 / K pairs, 524288 of one rank and 8192 of each of 64; beyond 65536 pairs it is
+# taken only by the last stage
 @pytest.mark.parametrize("kind", ["gauss", "equal", "half_zero", "sorted", "half_precision", "far_out"])
 @pytest.mark.parametrize("n,k", [(1, 1), (4095, 3), (4097, 2), (8193, 64), (524_288, 1), (524_289, 1), (N, 1), (N, 7),
                                  (N, 64)])
