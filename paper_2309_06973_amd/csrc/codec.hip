@@ -19,8 +19,8 @@
 //     quarters of 128 bytes, the token bits of the quarter before (11 bits) and how far past
 //     the quarter's start its first literal lies (9 bits); a run's matches go with the
 //     literal that starts the run, so a lane never needs another lane's bytes.
-// Any inflater reads the stream; the encoder works with one block of 512 threads per chunk and
-// 32 lanes per sub-chunk, the decoder with 256 and four.
+// Any inflater reads the stream; the encoder works with 512 threads per chunk and 32 lanes per
+// sub-chunk, the decoder with 256 and four.
 #include <string>
 
 #include "chain.h"
@@ -156,11 +156,11 @@ constexpr uint32_t CODEC_THREADS = CODEC_NSUB * CODEC_Q;      // 256: one block 
 constexpr uint32_t CODEC_LOOP_GRID = 1536;                    // blocks of an instance that walks a list
 
 // --- the encoder -------------------------------------------------------------------------
-// One block of 512 threads per chunk.  A lane holds 16 consecutive bytes of a sub-chunk (32
+// 512 threads per chunk, one or two chunks a block.  A lane holds 16 consecutive bytes of a sub-chunk (32
 // lanes a sub-chunk, so a wavefront takes 1 KiB at a time and four of those in turn); the
-// chunk stays in registers and only the segment being built is in LDS: 33.6 KB a block whatever
-// its size, room for four blocks a compute unit.  (The bound on registers asks for three; the 58 that
-// the compiler takes let four run.)  First every piece finds its literals,
+// chunk stays in registers and only the segment being built is in LDS: 33.6 KB whatever its
+// size, room for four chunks a compute unit.  (The bound on registers asks for fewer; the 58 that the
+// compiler takes let four run.)  First every piece finds its literals,
 // the runs they start and its token bits, and prefix sums over the lanes place the pieces in
 // their sub-chunk; then, with the sub-chunks placed in the segment, every lane appends its
 // own piece's tokens.
@@ -274,7 +274,7 @@ __device__ __forceinline__ void chain_store(uint64_t* p, uint64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Sum of the sizes before chunk c, by one wavefront.  Chunks are numbered by a ticket that a block
-// draws when it starts, and a block stores its size before it waits for anything: every predecessor
+// draws when it starts, and a block stores its sizes before it waits for anything: every predecessor
 // is running or done and its size arrives without it waiting for this block.
 __device__ __forceinline__ ChainWalk chain_before(const uint64_t* status, uint32_t c, uint32_t lane) {
     ChainWalk walk(c);
@@ -304,32 +304,36 @@ static_assert(CODEC_SUB == 512u, "258 + 253 + 1");
 
 // DIRECT: the segments go straight to their place in the stream, which cannot overflow (the
 // host checked that it holds the largest possible one).  The tickets take 13.8 ns each on their one
-// address, which only chunks that hold next to nothing notice: 1.3 GB of nothing but zeros take 540 us
-// a call, with slots 345 (39347 chunks at density 0.002: 1172 and 1467).  Otherwise every segment goes to its
+// address, a bound where chunks hold next to nothing: 1.3 GB of zeros take 540 us a call with a ticket for
+// each chunk, 408 with one for two (GROUPS: 512 threads each, side by side in a block).  Otherwise every segment goes to its
 // slot of the workspace, and the two kernels behind this one add up the sizes and, if the
 // stream is large enough, move the segments.
 constexpr uint32_t CODEC_OUT_DW = CODEC_CHUNK / 4 + 8;
 constexpr uint32_t DEF_THREADS = 512;
-template <bool DIRECT>
-__global__ __launch_bounds__(DEF_THREADS, 6) void deflate_kernel(
+template <bool DIRECT, uint32_t GROUPS>
+__global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void deflate_kernel(
     const uint8_t* __restrict__ in, uint64_t n_bytes, uint32_t n_chunks, uint16_t* __restrict__ side,
     uint64_t* __restrict__ marks, uint8_t* __restrict__ slots, uint32_t* __restrict__ seg_size,
     uint64_t* __restrict__ status, uint32_t* __restrict__ ticket, uint64_t* __restrict__ seg_off,
     uint8_t* __restrict__ stream, uint64_t* __restrict__ mirror) {
-    __shared__ __align__(16) uint32_t s_out[CODEC_OUT_DW];
-    __shared__ uint64_t s_mark[CODEC_NSUB];
-    __shared__ uint32_t s_side[CODEC_NSUB];
-    __shared__ uint64_t s_off;
+    __shared__ __align__(16) uint32_t g_out[GROUPS][CODEC_OUT_DW];
+    __shared__ uint64_t g_mark[GROUPS][CODEC_NSUB];
+    __shared__ uint32_t g_side[GROUPS][CODEC_NSUB];
+    __shared__ uint64_t g_off[GROUPS];
     __shared__ uint32_t s_c;
     constexpr uint32_t STEPS = CODEC_CHUNK / 1024u / (DEF_THREADS / 64u);     // KiB per wavefront
-    const uint32_t lane = threadIdx.x & 63u, wid = uniform_u32(threadIdx.x >> 6), half = lane >> 5, hl = lane & 31u;
-    uint32_t c = blockIdx.x;
+    const uint32_t group = GROUPS == 1 ? 0u : uniform_u32(threadIdx.x / DEF_THREADS), tid = threadIdx.x % DEF_THREADS;
+    uint32_t* s_out = g_out[group];
+    uint64_t* s_mark = g_mark[group];
+    uint32_t* s_side = g_side[group];
+    const uint32_t lane = threadIdx.x & 63u, wid = uniform_u32(tid >> 6), half = lane >> 5, hl = lane & 31u;
+    uint32_t c = blockIdx.x * GROUPS + group;
     if (DIRECT) {
         if (threadIdx.x == 0) s_c = atomicAdd(ticket, 1u);
         __syncthreads();
-        c = uniform_u32(s_c);
-        if (c >= n_chunks) return;
+        c = uniform_u32(s_c) * GROUPS + group;
     }
+    const bool alive = c < n_chunks;                    // of the last block's groups maybe the first alone
     const uint64_t base = (uint64_t)c * CODEC_CHUNK;
     const uint32_t m = (uint32_t)min((uint64_t)CODEC_CHUNK, n_bytes - min(n_bytes, base));
     const uint32_t last = c + 1u == n_chunks ? 1u : 0u;
@@ -350,7 +354,7 @@ __global__ __launch_bounds__(DEF_THREADS, 6) void deflate_kernel(
             P[i].v = make_uint4(w[0], w[1], w[2], w[3]);
         }
     }
-    for (uint32_t k = threadIdx.x; k < CODEC_OUT_DW / 4u; k += DEF_THREADS)
+    for (uint32_t k = tid; k < CODEC_OUT_DW / 4u; k += DEF_THREADS)
         reinterpret_cast<uint4*>(s_out)[k] = make_uint4(0, 0, 0, 0);
     // --- first pass: literals, token bits, side information and marks
 #pragma unroll
@@ -438,11 +442,11 @@ __global__ __launch_bounds__(DEF_THREADS, 6) void deflate_kernel(
                                             &tail_start, &tail_in_block);
     const bool whole = m + 5u <= coded_bytes;           // not shorter than one stored block
     const uint32_t seg_bytes = whole ? m + 5u : coded_bytes;
-    if (threadIdx.x == 0) {
+    if (tid == 0 && alive) {
         if (DIRECT) chain_store(status + c, chain_size(c, seg_bytes));
         else seg_size[c] = seg_bytes;
     }
-    if (wid == 0u) {
+    if (wid == 0u && alive) {
         side[(uint64_t)c * CODEC_NSUB + lane] = whole ? 0 : (uint16_t)side_l;
         marks[(uint64_t)c * CODEC_NSUB + lane] = whole ? 0ull : s_mark[lane];
     }
@@ -501,7 +505,7 @@ __global__ __launch_bounds__(DEF_THREADS, 6) void deflate_kernel(
             }
         }
     }
-    if (threadIdx.x == DEF_THREADS - 1u) {
+    if (tid == DEF_THREADS - 1u) {
         if (whole) {
             BitWriter w(s_out, 0);
             w.put(last, 8u);                              // BFINAL, BTYPE = 00
@@ -521,33 +525,34 @@ __global__ __launch_bounds__(DEF_THREADS, 6) void deflate_kernel(
     }
     uint8_t* dst = slots + (uint64_t)c * CODEC_SLOT;
     if (DIRECT) {
-        if (wid == 0u) {
+        if (wid == 0u && alive) {
             const ChainWalk walk = chain_before(status, c, lane);
             if (lane == 0u) {
                 chain_leave(walk, c, last != 0u, seg_bytes, status + c, mirror, chain_store);
-                s_off = walk.broken ? ~0ull : walk.sum;
+                g_off[group] = walk.broken ? ~0ull : walk.sum;
                 seg_off[c] = walk.sum;
                 if (last) seg_off[n_chunks] = walk.sum + seg_bytes;
             }
         }
         __syncthreads();
-        const uint64_t off = s_off;
-        if (off == ~0ull) return;
+        const uint64_t off = g_off[group];
+        if (!alive || off == ~0ull) return;
         dst = stream + off;
     } else {
         __syncthreads();
+        if (!alive) return;
     }
     // --- to memory: the first bytes up to a dword, whole dwords put together from two, the rest
     const uint32_t head = min(seg_bytes, (uint32_t)((4u - (reinterpret_cast<uintptr_t>(dst) & 3u)) & 3u));
     const uint32_t n_w = (seg_bytes - head) / 4u, sh = head * 8u;
     const uint8_t* out8 = reinterpret_cast<const uint8_t*>(s_out);
-    if (threadIdx.x < head) dst[threadIdx.x] = out8[threadIdx.x];
+    if (tid < head) dst[tid] = out8[tid];
     uint32_t* dst32 = reinterpret_cast<uint32_t*>(dst + head);
 #pragma unroll 4
-    for (uint32_t k = threadIdx.x; k < n_w; k += DEF_THREADS)
+    for (uint32_t k = tid; k < n_w; k += DEF_THREADS)
         dst32[k] = __builtin_amdgcn_alignbit(s_out[k + 1u], s_out[k], sh);
     const uint32_t done = head + n_w * 4u;
-    if (threadIdx.x < seg_bytes - done) dst[done + threadIdx.x] = out8[done + threadIdx.x];
+    if (tid < seg_bytes - done) dst[done + tid] = out8[done + tid];
 }
 
 // Clears the chain of a call: the status words of its chunks, the ticket behind them and the word
@@ -1092,6 +1097,12 @@ static void codec_end(shifter_ctx* ctx) {
     if (hipPeekAtLastError() == hipSuccess) ctx->codec_dirty = false;
 }
 
+// Up to this many chunks, three to each of 256 compute units, a block takes one chunk, beyond it two: they
+// wait for each other at the barriers, which a chip that is not full notices, and share a ticket.  us a
+// call, one / two: 4 chunks 28 / 35, 256 32 / 37, 640 54 / 57 (zeros 33 / 28), 769 62 / 58 (35 / 30), 1024 69 / 63
+// (41 / 33), 4096 164 / 158 (82 / 61), 39347 1196 / 1196 (540 / 408).
+constexpr uint32_t DEFLATE_ONE_EACH = 768;
+
 // Room for chunk lists, kept by the context and grown when a longer input comes.
 static hipError_t codec_ensure_list(shifter_ctx* ctx, uint64_t entries) {
     if (ctx->codec_list_cap >= entries) return hipSuccess;
@@ -1123,7 +1134,9 @@ int launch_deflate(shifter_ctx* ctx, const uint8_t* d_in, uint64_t n_bytes, uint
             chain_clear_kernel<<<(n_chunks + BLOCK) / BLOCK, BLOCK, 0, ctx->stream>>>(status, n_chunks + 1u, ctx->dev_codec_mirror);
         }
         ProfileScope ps(ctx, K_DEFLATE_CHUNK);
-        deflate_kernel<true><<<n_chunks, DEF_THREADS, 0, ctx->stream>>>(
+        const bool two = n_chunks > DEFLATE_ONE_EACH;
+        const auto kernel = two ? deflate_kernel<true, 2> : deflate_kernel<true, 1>;
+        kernel<<<two ? (n_chunks + 1u) / 2u : n_chunks, two ? 2u * DEF_THREADS : DEF_THREADS, 0, ctx->stream>>>(
             d_in, n_bytes, n_chunks, d_sub_bits, d_sub_marks, nullptr, nullptr, status,
             reinterpret_cast<uint32_t*>(status + n_chunks), d_seg_off, d_stream, ctx->dev_codec_mirror);
         return 0;
@@ -1133,7 +1146,7 @@ int launch_deflate(shifter_ctx* ctx, const uint8_t* d_in, uint64_t n_bytes, uint
     codec_begin(ctx);
     {
         ProfileScope ps(ctx, K_DEFLATE_CHUNK);
-        deflate_kernel<false><<<n_chunks, DEF_THREADS, 0, ctx->stream>>>(
+        deflate_kernel<false, 1><<<n_chunks, DEF_THREADS, 0, ctx->stream>>>(
             d_in, n_bytes, n_chunks, d_sub_bits, d_sub_marks, slots, seg_size, nullptr, nullptr, nullptr, nullptr,
             nullptr);
     }
