@@ -168,8 +168,8 @@ constexpr uint32_t CODEC_LOOP_GRID = 1536;                    // blocks of an in
 // life of one block.  Ten rebuilt variants of a 14.7 M weight network (3/10 to all of the
 // weights not zero), one after the other: 2780 us with four lanes walking a sub-chunk's tokens
 // one by one, a second instance for the chunks with long segments and a pack pass; 845 with 256
-// threads of this form, 690 with 512, 625 without loops for the matches.  1.3 GB of a sparse
-// model: 4840 us before, 1200 now (5 % of uniformly spread weights kept: 1473, 1101).
+// threads of this form, 690 with 512, 650 without loops for the matches and with two chunks a
+// block.  1.3 GB of a sparse model: 4820 us before, 1200 now.
 
 // Bits 0-15 of a piece: which bytes differ from the byte before them, and which are >= 144
 // (9-bit literals).  prev: the byte before the piece.
