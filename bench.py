@@ -366,7 +366,7 @@ def measure(name, steps, warmup, lean_run=True, cpu_leg=True):
             cd.inflate(pkg, out=back)
         cp = S.shifter_profile_read(pl.ctx)
         S.shifter_profile_enable(pl.ctx, False)
-        # segments that go straight to their place need no scan and no packing
+        # segments that go straight to their place need no packing (codec_scan clears their chain then)
         avg = lambda kn: cp[kn][1] / cp[kn][0] if kn in cp else 0.0
         enc_ms = avg("deflate_chunk") + avg("codec_scan") + avg("codec_pack")
         dec_ms = avg("inflate_chunk")
