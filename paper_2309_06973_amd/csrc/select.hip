@@ -23,12 +23,12 @@
 // run, the radix select of 11 + 10 + 10 bits with one read per distinct key for the ties that this
 // replaces / lists of up to 2^20 pairs and none of these / now:
 //   counts of weights     normal              half of them zero     all equal             30 levels a sigma
-//    1 of   1 M           86 /   33 /   34    89 / 1331 /   54      93 /  121 /   66      89 /  90 /  53
-//   10 of   1 M          199 /   37 /   38   142 /  131 /   61     140 /  143 /   73     197 /  93 /  54
-//    1 of  14.7 M        174 /   53 /   53   201 /  274 /  106     246 /  332 /  142     182 / 683 / 123
-//   10 of  14.7 M        422 /   71 /   70   258 /  357 /  132     296 /  422 /  170     390 / 164 / 141
-//    1 of 100 M          483 /  179 /  181   725 / 1281 /  397    1213 / 1665 /  571     470 / 617 / 485
-//   10 of 100 M         1282 /  311 /  294   848 / 2295 /  662    1264 / 2790 /  870    1276 / 693 / 612
+//    1 of   1 M           85 /   35 /   33    88 / 1336 /   59      92 /  121 /   75      89 /  90 /  48
+//   10 of   1 M          197 /   38 /   35   140 /  132 /   64     140 /  143 /   82     196 /  93 /  54
+//    1 of  14.7 M        174 /   53 /   52   200 /  273 /  122     246 /  331 /  188     181 / 685 /  96
+//   10 of  14.7 M        418 /   71 /   63   258 /  359 /  146     296 /  421 /  213     390 / 165 / 138
+//    1 of 100 M          481 /  175 /  180   723 / 1279 /  508    1210 / 1662 /  857     469 / 617 / 346
+//   10 of 100 M         1276 /  312 /  268   850 / 2287 /  801    1261 / 2781 / 1236    1271 / 693 / 596
 #include <algorithm>
 
 #include "dev_common.h"
@@ -38,6 +38,7 @@ namespace shifter {
 constexpr uint32_t SEL_THREADS = 1024;
 constexpr uint32_t SEL_GROUPS = SEL_THREADS / BLOCK;   // tiles a block walks side by side
 constexpr uint32_t SEL_STAGE_CAP = 4096;               // listed pairs a block collects in LDS
+constexpr uint32_t SEL_QUADS = TILE / BLOCK / 4;        // of a full tile per thread
 constexpr uint32_t NONE8 = 0xffu;
 // What the walk of a stage has to know of a window, in one word: width | shift << 6 | these |
 // leader << 16 | windows in its top bin << 24.
@@ -94,12 +95,13 @@ __global__ __launch_bounds__(BLOCK) void sel_clear_kernel(SelState* st, uint32_t
     }
 }
 
-// quad(bits of four weights, g of the first) and one(bits, g) for the prunable weights.  Four tiles at a time per block, one per 256 threads,
+// whole(bits of a thread's sixteen weights of a full tile, g of the first) and one(bits, g) for the
+// prunable weights; the four quads of the sixteen lie 4 * BLOCK weights apart.  Four tiles at a time per block, one per 256 threads,
 // a thread's 64 bytes in flight together; no barriers, so the wavefronts drift apart and one's
 // loads overlap with another's work.
 template <typename Q, typename F>
 __device__ __forceinline__ void sel_walk(const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix,
-                                         uint32_t n_t, uint32_t n_tiles, const float* __restrict__ w, Q&& quad, F&& one) {
+                                         uint32_t n_t, uint32_t n_tiles, const float* __restrict__ w, Q&& whole, F&& one) {
     const uint32_t tid = threadIdx.x & (BLOCK - 1u);
     const uint32_t group = uniform_u32(threadIdx.x / BLOCK);
     for (uint32_t tile = blockIdx.x * SEL_GROUPS + group; tile < n_tiles; tile += gridDim.x * SEL_GROUPS) {
@@ -110,12 +112,11 @@ __device__ __forceinline__ void sel_walk(const DevTensor* __restrict__ tens, con
         const uint32_t g0 = (uint32_t)(tens[t].gbase + e0);
         const float* src = w + tens[t].offset + e0;
         if (n == TILE) {
-            constexpr uint32_t U = TILE / BLOCK / 4;
-            uint4 v[U];
+            uint4 v[SEL_QUADS];
+            constexpr uint32_t U = SEL_QUADS;
 #pragma unroll
             for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<false>(src + 4u * tid + 4u * BLOCK * u);
-#pragma unroll
-            for (uint32_t u = 0; u < U; ++u) quad(v[u], g0 + 4u * tid + 4u * BLOCK * u);
+            whole(v, g0 + 4u * tid);
         } else {
             for (uint32_t j = tid; j < n; j += BLOCK) one(__float_as_uint(src[j]), g0 + j);
         }
@@ -165,23 +166,27 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(
     bool runs = false;
     RunCount run;
     auto bin_of = [&](uint32_t key) { return key ? sample_bin(key) : SEL_BINS + lane; };
-    sel_walk(tens, tile_prefix, n_t, n_tiles, w, [&](uint4 v, uint32_t) {
-        const uint32_t k0 = v.x & 0x7fffffffu, k1 = v.y & 0x7fffffffu, k2 = v.z & 0x7fffffffu, k3 = v.w & 0x7fffffffu;
-        const uint32_t b0 = bin_of(k0), b1 = bin_of(k1), b2 = bin_of(k2), b3 = bin_of(k3);
-        key_max = max(max(key_max, max(k0, k1)), max(k2, k3));
-        // every fourth time, until some lane has met a run
-        bool same = false;
-        if (runs || (turn++ & 3u) == 0u) {
-            same = (b0 == b1) & (b1 == b2) & (b2 == b3);
-            runs = __ballot(same) != 0ull;
-        }
-        if (same) {
-            run.add(h, b0, 4u);
-        } else {
-            atomicAdd(&h[b0], 1u);
-            atomicAdd(&h[b1], 1u);
-            atomicAdd(&h[b2], 1u);
-            atomicAdd(&h[b3], 1u);
+    sel_walk(tens, tile_prefix, n_t, n_tiles, w, [&](const uint4 (&quads)[SEL_QUADS], uint32_t) {
+#pragma unroll
+        for (uint32_t u = 0; u < SEL_QUADS; ++u) {
+            const uint4 v = quads[u];
+            const uint32_t k0 = v.x & 0x7fffffffu, k1 = v.y & 0x7fffffffu, k2 = v.z & 0x7fffffffu, k3 = v.w & 0x7fffffffu;
+            const uint32_t b0 = bin_of(k0), b1 = bin_of(k1), b2 = bin_of(k2), b3 = bin_of(k3);
+            key_max = max(max(key_max, max(k0, k1)), max(k2, k3));
+            // every fourth time, until some lane has met a run
+            bool same = false;
+            if (runs || (turn++ & 3u) == 0u) {
+                same = (b0 == b1) & (b1 == b2) & (b2 == b3);
+                runs = __ballot(same) != 0ull;
+            }
+            if (same) {
+                run.add(h, b0, 4u);
+            } else {
+                atomicAdd(&h[b0], 1u);
+                atomicAdd(&h[b1], 1u);
+                atomicAdd(&h[b2], 1u);
+                atomicAdd(&h[b3], 1u);
+            }
         }
     }, [&](uint32_t bits, uint32_t) {
         const uint32_t key = bits & 0x7fffffffu;
@@ -440,8 +445,26 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
         const uint32_t at = __shfl(base, (int)__ffsll((unsigned long long)peers) - 1, 64) + rank;
         if (at < list_cap) lists[(size_t)s * list_cap + at] = make_uint2(wbits, g);
     };
-    sel_walk(tens, tile_prefix, n_t, n_tiles, w, [&](uint4 v, uint32_t g) {
-        one(v.x, g); one(v.y, g + 1u); one(v.z, g + 2u); one(v.w, g + 3u);
+    sel_walk(tens, tile_prefix, n_t, n_tiles, w, [&](const uint4 (&v)[SEL_QUADS], uint32_t g) {
+        // first which of the sixteen are met by a window, without a branch, then those one by one: few are,
+        // and the long body stands here once (in line sixteen times: 20 ranks of 14.7 M weights 34 us, 24 so; 30
+        // levels a sigma, one rank of 100 M 134 and 92; all 100 M equal 170 and 265)
+        static_assert(SEL_QUADS == 4u, "sixteen weights");
+        uint32_t met = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < 4u; ++u) {
+            const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) met |= (s_map[top_bin(x[q] & 0x7fffffffu)] != NONE8 ? 1u : 0u) << (4u * u + q);
+        }
+        while (met) {
+            const uint32_t j = (uint32_t)__builtin_ctz(met);
+            met &= met - 1u;
+            const uint32_t u = j >> 2, q = j & 3u;
+            const uint4 lo = (u & 1u) ? v[1] : v[0], hi = (u & 1u) ? v[3] : v[2], x = (u & 2u) ? hi : lo;
+            const uint32_t a = (q & 1u) ? x.y : x.x, b = (q & 1u) ? x.w : x.z;
+            one((q & 2u) ? b : a, g + 4u * BLOCK * u + q);
+        }
     }, one);
     run.flush(s_hist);
     keys.flush(s_key_lo, s_key_hi);
