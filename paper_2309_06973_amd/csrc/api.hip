@@ -514,7 +514,7 @@ static int bind_tables(shifter_ctx* ctx, shifter_model* m) {
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.list), sizeof(uint2) * SPEC_LIST_CAP));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.multi), sizeof(MultiState)));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.multi_cnt), sizeof(uint32_t) * (2 * MAXK + 1) * SPEC_SUB * 32));
-    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.multi_tab), 4096));
+    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.multi_tab), PASS_TAB + SAMPLE_BINS));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.multi_hist), sizeof(uint32_t) * MAXK * 256));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.multi_list),
                            sizeof(uint2) * (size_t)SPEC_MULTI_MAXK * SPEC_LIST_CAP));

@@ -104,6 +104,7 @@ struct SpecState {
 
 // State of the single-pass selection for all prune counts of a portfolio (ranks sorted by
 // prune count, zero counts left out).
+constexpr uint32_t PASS_TAB = 4096;         // entries of the K-rank pass's table: bins of the sample histogram, 16 binades
 constexpr uint32_t SPEC_MULTI_MAXK = 32;   // LDS of the fused pass's private counters: 256 B per rank
 // What the finish of one rank reads (written by the prediction): one cache line instead of a
 // line per field.
@@ -121,7 +122,8 @@ struct MultiState {
     uint32_t clast[MAXK];  // last rank of rank k's cluster: the owner of the cluster's candidate region
     uint32_t cand_off[MAXK], cand_cap[MAXK];   // region of the cluster ending at rank k: first pair, pairs per part
     RankIn rin[MAXK];
-    uint32_t k, m_valid, status, pad;
+    uint32_t k, m_valid, status;
+    uint32_t tab_first, tab_wide;   // of the pass's table: (key >> SAMPLE_BIN_SHIFT) of entry 0; the table of all bins is used
 };
 struct MultiPerm {
     uint32_t v[MAXK];
@@ -258,7 +260,7 @@ struct shifter_model {
         uint32_t* ranked_ids = nullptr;
         shifter::MultiState* multi = nullptr;
         uint32_t* multi_cnt = nullptr;        // (2 * MAXK + 1) * SPEC_SUB counters, 128-byte lines
-        uint8_t* multi_tab = nullptr;         // 4096 bucket entries of the K-rank pass
+        uint8_t* multi_tab = nullptr;         // classes of the K-rank pass: PASS_TAB entries, then SAMPLE_BINS
         uint32_t* multi_hist = nullptr;       // MAXK * 256: the clusters' first histograms
         uint64_t* multi_rowsum = nullptr;     // MAXK + 1: totals of the split counters' rows
         uint2* multi_list = nullptr;          // SPEC_MULTI_MAXK * SPEC_LIST_CAP pairs: the ranks' selected bins

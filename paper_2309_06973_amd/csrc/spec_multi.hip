@@ -15,8 +15,6 @@
 
 namespace shifter {
 
-constexpr uint32_t TAB_SHIFT = 19;       // the pass's bucket table: 4096 buckets of 2^19 keys
-constexpr uint32_t TAB_SIZE = 1u << (31 - TAB_SHIFT);
 // The counters all blocks add to are split CAND_SUB ways by block (one 128-byte line per
 // part), and so is a cluster's candidate region: few enough parts that each averages over
 // hundreds of tiles - filters differ in scale by orders of magnitude, so the candidates of
@@ -64,7 +62,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void ms_front_kernel(
     shifter_threshold* host_rec, uint64_t n_prunable, double margin_sigmas,
     uint8_t* __restrict__ tab, uint32_t cap_sb_total) {
     __shared__ __align__(16) uint32_t prefix[SAMPLE_BINS];          // 64 KB
-    __shared__ uint32_t s_lo[MAXK], s_bins[3][64];
+    __shared__ uint32_t s_lo_bin[MAXK], s_hi_bin[MAXK], s_bins[3][64];
     {
         // rows 0 .. k and MAXK + 1 .. MAXK + k of the split counters (the first word of each
         // 128-byte line)
@@ -182,7 +180,8 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void ms_front_kernel(
             ms->clast[lane] = last;
             ms->cand_cap[lane] = cap;
             ms->cand_off[lane] = (cinc - cap) * CAND_SUB;     // at most cap_sb_total * SPEC_SUB pairs
-            s_lo[lane] = lo;
+            s_lo_bin[lane] = sample_bin(lo);
+            s_hi_bin[lane] = sample_bin(hi);
         }
         // the finish's view of a rank: its cluster's region and first histogram
         const uint32_t cap_cl = __shfl(cap, min(last, 63u), 64);
@@ -200,28 +199,37 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void ms_front_kernel(
             ms->rin[lane] = in;
         }
     }
-    // The pass's bucket table.  Entry b covers the keys [b << TAB_SHIFT, (b + 1) << TAB_SHIFT):
-    // bits 0-5 = #{k : lo_k <= first key of the bucket}, bits 6-7 = how many lo_k lie
-    // above that inside the bucket (3: three or more).  With a few dozen ranks almost every
-    // bucket holds none, and a weight's j is then the entry itself.
+    // The pass's table: what it has to know of a weight follows from its bin of the sample histogram,
+    // because all interval ends are edges of those bins.  Bits 0-5 = #{k : lo_k <= key}, bit 7: the
+    // key lies in the interval of the last of those ranks.  Entry 0 is for the bins below the first
+    // rank's lower end, entry i for the i-th bin from there on, the last entry for all above it too; where
+    // the intervals span more bins than that, a table of all bins follows it and is used instead.
     __syncthreads();
-    constexpr uint32_t PER_THREAD = TAB_SIZE / SAMPLE_THREADS;
-    uint32_t j0[PER_THREAD], inside[PER_THREAD];
+    auto classes = [&](uint32_t bin0) {      // of four bins from bin0 on, which may start at -1 for bin 0
+        uint32_t j[4] = {0, 0, 0, 0}, four = 0;
+        for (uint32_t k = 0; k < k_var; ++k) {
+            const int32_t lo = (int32_t)s_lo_bin[k];
 #pragma unroll
-    for (uint32_t i = 0; i < PER_THREAD; ++i) j0[i] = inside[i] = 0;
-    for (uint32_t k = 0; k < k_var; ++k) {
-        const uint32_t lo = s_lo[k];
-#pragma unroll
-        for (uint32_t i = 0; i < PER_THREAD; ++i) {
-            const uint32_t first = (threadIdx.x + i * SAMPLE_THREADS) << TAB_SHIFT;
-            const uint32_t last = first + ((1u << TAB_SHIFT) - 1u);
-            j0[i] += lo <= first ? 1u : 0u;
-            inside[i] += (lo > first && lo <= last) ? 1u : 0u;
+            for (uint32_t i = 0; i < 4u; ++i) j[i] += lo <= max((int32_t)(bin0 + i), 0) ? 1u : 0u;
         }
-    }
 #pragma unroll
-    for (uint32_t i = 0; i < PER_THREAD; ++i)
-        tab[threadIdx.x + i * SAMPLE_THREADS] = (uint8_t)(j0[i] | (min(inside[i], 3u) << 6));
+        for (uint32_t i = 0; i < 4u; ++i)
+            four |= (j[i] | (j[i] != 0u && max((int32_t)(bin0 + i), 0) <= (int32_t)s_hi_bin[j[i] - 1u] ? 0x80u : 0u)) << (8u * i);
+        return four;
+    };
+    static_assert(PASS_TAB == 4u * SAMPLE_THREADS, "four entries a thread");
+    const uint32_t first = s_lo_bin[0];
+    uint32_t* tab4 = reinterpret_cast<uint32_t*>(tab);
+    tab4[threadIdx.x] = classes(first - 1u + 4u * threadIdx.x);
+    // the last bin whose class differs from the one below it
+    const uint32_t change = max(s_lo_bin[k_var - 1u], min(s_hi_bin[k_var - 1u] + 1u, SAMPLE_BINS - 1u));
+    const bool wide = change - first > PASS_TAB - 2u;
+    if (wide)
+        for (uint32_t i = threadIdx.x; i < SAMPLE_BINS / 4u; i += SAMPLE_THREADS) tab4[PASS_TAB / 4u + i] = classes(4u * i);
+    if (threadIdx.x == 0) {
+        ms->tab_first = (SAMPLE_KEY0 >> SAMPLE_BIN_SHIFT) + first - 1u;
+        ms->tab_wide = wide ? 1u : 0u;
+    }
 }
 
 // Appends the candidates a block found to the regions of their clusters: count per cluster
@@ -251,118 +259,146 @@ __device__ __forceinline__ void ms_append_candidates(
 }
 
 // The one pass over the arena: counts per j and candidate pairs.
+// What bounds it are a wavefront's vector instructions where many tiles wait (eight wavefronts a SIMD, a
+// block's life 18 us with 1650 of them) and the latencies one behind the other where few do; the arena's
+// bytes, which come from the cache, lie far behind.  So a weight's class is one look at a table on bins
+// of the sample histogram, a cluster's candidates are counted by eight counters, and a
+// tensor's last, ragged tile goes the same way as a full one, the weights it lacks counted in a row of their own.  Against
+// a 4096-entry table of 1/16 binades with compares behind it, one counter a cluster and one global
+// addition per candidate in the ragged tiles (kernel, us): fifteen ranks of 0.86 M weights, where
+// over half are candidates, 19.2 -> 8.3; eight of 10 M 27.8 -> 16.0; ten of 14.7 M 39.4 -> 28.3; twenty of
+// 25.5 M 67.4 -> 51.9.  A table of all 16384 bins in LDS (six blocks to a compute unit, not eight): 8.3, 20.3,
+// 32.0, 55.4.  Tried and dropped: four tiles a block (19.3, 35.5, 60.4 beyond the first), blocks that fetch their next
+// tile while they work on one (registers spill: twice the time).
+constexpr uint32_t PASS_COPIES = 8;      // counters of a cluster's candidates: one for eight lanes
 template <bool NT>
-__global__ __launch_bounds__(BLOCK) void ms_pass_kernel(
-    const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix, uint32_t n_t,
-    const float* __restrict__ w, MultiState* ms, uint32_t* cnt, uint2* __restrict__ cand,
+__global__ __launch_bounds__(BLOCK, 8) void ms_pass_kernel(
+    const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix, const uint16_t* __restrict__ tile_tensor,
+    const float* __restrict__ w, MultiState* ms, uint32_t k_var, uint32_t* cnt, uint2* __restrict__ cand,
     const uint8_t* __restrict__ tab, uint32_t* zero_ptr, uint32_t zero_n) {
     // an array the step behind this pass wants cleared (or nullptr)
     for (uint32_t i = blockIdx.x * BLOCK + threadIdx.x; i < zero_n; i += gridDim.x * BLOCK) zero_ptr[i] = 0;
-    // s_hi1[j] = hi_(j-1) + 1, s_hi1[0] = 0: a weight with j lower ends at or below it is a
-    // candidate (of the cluster ending at rank j - 1) iff key < s_hi1[j]
-    __shared__ uint32_t s_lo[MAXK + 1], s_hi1[MAXK + 1];
-    __shared__ uint32_t s_coff[MAXK], s_ccap[MAXK], s_rc[MAXK], s_rc2[MAXK], s_rbase[MAXK];
     // counts per j: one private byte column per thread (a thread sees 16 weights; no
-    // conflicts, no atomics), summed at the end; rows 0 .. k_var of BLOCK bytes (the launch
-    // sizes it).  Small, so that a CU holds as many blocks as it has wavefront slots: a
-    // block's life is a chain of memory latencies, which only other blocks can hide.
-    extern __shared__ uint32_t s_col[];
-    __shared__ __align__(16) uint8_t s_tab[TAB_SIZE];
+    // conflicts, no atomics), summed at the end; rows 0 .. k_var of BLOCK bytes and one for the
+    // weights that a ragged tile lacks (the launch sizes it)
+    extern __shared__ __align__(16) uint32_t s_col[];
+    __shared__ __align__(16) uint8_t s_tab[PASS_TAB];
+    // candidates by cluster and eight lanes, then their places in the block's part of the cluster's region;
+    // where that part starts and how many pairs it holds
+    __shared__ uint32_t s_cnt[SPEC_MULTI_MAXK * PASS_COPIES];
+    __shared__ uint2 s_part[SPEC_MULTI_MAXK];
     __shared__ uint32_t s_nan;
-    const uint32_t tile = blockIdx.x;
-    const uint32_t t = find_tensor(tile_prefix, n_t, tile);
-    if (!tens[t].prunable) return;
-    const DevTensor T = tens[t];
-    const uint32_t e0 = (tile - tile_prefix[t]) * TILE;
-    const uint32_t n = min(TILE, T.numel - e0);
-    const uint32_t g0 = (uint32_t)(T.gbase + e0);
-    const uint32_t sb = blockIdx.x & (SPEC_SUB - 1);
-    // the tile's loads go out first: the set-up below runs while they are in flight
-    const float* src = w + T.offset + e0;
-    const bool whole = n == TILE;
     constexpr uint32_t U = TILE / BLOCK / 4;
+    const uint32_t tile = blockIdx.x, tid = threadIdx.x;
+    const uint32_t sb = tile & (SPEC_SUB - 1), csb = tile & (CAND_SUB - 1);
+    const uint32_t t = tile_tensor[tile];
+    const uint4 piece = reinterpret_cast<const uint4*>(tab)[tid];
+    static_assert(PASS_TAB == 16u * BLOCK, "one 16-byte piece of the table per thread");
+    const uint32_t tab_first = ms->tab_first;
+    const bool wide = ms->tab_wide != 0;
+    uint32_t coff = 0, ccap = 0;
+    if (tid < k_var) {
+        coff = ms->cand_off[tid];
+        ccap = ms->cand_cap[tid];
+    }
+    if (!tens[t].prunable) return;
+    // the tile's loads: the set-up below runs while they are in flight
+    const uint32_t e0 = (tile - tile_prefix[t]) * TILE;
+    const uint32_t n = min(TILE, tens[t].numel - e0);
+    const uint32_t g0 = (uint32_t)(tens[t].gbase + e0);
+    const float* src = w + tens[t].offset + e0;
     uint4 v[U];
-    if (whole) {
+    uint32_t missing = 0;                   // bit 4 u + q: no such weight in a ragged tile
+    if (n == TILE) {
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(src + 4u * threadIdx.x + 4u * BLOCK * u);
+        for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(src + 4u * tid + 4u * BLOCK * u);
+    } else {
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t j = (tid + BLOCK * u) * 4u;
+            v[u] = make_uint4(0, 0, 0, 0);
+            if (j + 3u < n) {
+                v[u] = load_u4<NT>(src + j);
+            } else {
+                if (j < n) v[u].x = __float_as_uint(src[j]);
+                if (j + 1u < n) v[u].y = __float_as_uint(src[j + 1u]);
+                if (j + 2u < n) v[u].z = __float_as_uint(src[j + 2u]);
+                missing |= (0xfu << (j < n ? n - j : 0u) & 0xfu) << (4u * u);
+            }
+        }
     }
-    const uint32_t k_var = ms->k;
-    if (threadIdx.x <= MAXK) {
-        s_lo[threadIdx.x] = threadIdx.x < MAXK ? ms->lo[threadIdx.x] : 0xffffffffu;
-        s_hi1[threadIdx.x] = (threadIdx.x >= 1 && threadIdx.x <= k_var) ? ms->hi[threadIdx.x - 1] + 1u : 0u;
-    }
-    if (threadIdx.x < MAXK) {
-        s_coff[threadIdx.x] = ms->cand_off[threadIdx.x];
-        s_ccap[threadIdx.x] = ms->cand_cap[threadIdx.x];
-        s_rc[threadIdx.x] = 0;
-        s_rc2[threadIdx.x] = 0;
-    }
-    for (uint32_t i = threadIdx.x; i < (k_var + 1) * (BLOCK / 4); i += BLOCK) s_col[i] = 0;
-    static_assert(TAB_SIZE == BLOCK * 16, "one 16-byte piece of the table per thread");
-    reinterpret_cast<uint4*>(s_tab)[threadIdx.x] = reinterpret_cast<const uint4*>(tab)[threadIdx.x];
-    if (threadIdx.x == 0) s_nan = 0;
+    for (uint32_t i = tid; i < (k_var + 2u) * (BLOCK / 16u); i += BLOCK)
+        reinterpret_cast<uint4*>(s_col)[i] = make_uint4(0, 0, 0, 0);
+    s_cnt[tid] = 0;
+    static_assert(SPEC_MULTI_MAXK * PASS_COPIES == BLOCK, "one counter per thread");
+    if (tid < k_var) s_part[tid] = make_uint2(coff + csb * ccap, ccap);
+    if (tid == 0) s_nan = 0;
+    reinterpret_cast<uint4*>(s_tab)[tid] = piece;
     __syncthreads();
 
     uint32_t key_max = 0;   // a NaN's key is above that of +inf
-    uint8_t* my_col = reinterpret_cast<uint8_t*>(s_col) + threadIdx.x;
-    // classify one weight; returns whether it is a candidate; adds it to the count of
-    // j = #{k : lo_k <= key}: the bucket table's entry, plus a compare or two in the few
-    // buckets that hold a rank's lower end (the binary search where three or more meet)
-    auto one = [&](uint32_t bits, uint32_t& j_out) -> bool {
-        const uint32_t key = bits & 0x7fffffffu;
-        key_max = max(key_max, key);
-        const uint32_t e = s_tab[key >> TAB_SHIFT];
-        uint32_t j = e & 63u;
-        if (e >> 6) {
-            if ((e >> 6) == 3u) {
-                j = count_lower_ends(s_lo, key);    // j in [0, MAXK]; s_lo[MAXK] is padding
-            } else {
-                // the lower ends are sorted: the second one counts only if the first does
-                const uint32_t j0 = j;
-                j += s_lo[j0] <= key ? 1u : 0u;
-                j += ((e >> 6) == 2u && s_lo[j0 + 1] <= key) ? 1u : 0u;
+    // of every weight: j, and for a candidate the counter it goes by (slot << 16) and its place there
+    uint32_t cl[4 * U], cmask = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+#pragma unroll
+        for (uint32_t q = 0; q < 4u; ++q) {
+            const uint32_t key = x[q] & 0x7fffffffu;
+            key_max = max(key_max, key);
+            const uint32_t at = key >> SAMPLE_BIN_SHIFT;
+            cl[4u * u + q] = s_tab[min(at > tab_first ? at - tab_first : 0u, PASS_TAB - 1u)];
+            if (wide) cl[4u * u + q] = tab[PASS_TAB + sample_bin(key)];
+        }
+    }
+    if (n != TILE) {
+#pragma unroll
+        for (uint32_t i = 0; i < 4u * U; ++i)
+            if ((missing >> i) & 1u) cl[i] = k_var + 1u;
+    }
+    uint8_t* my_col = reinterpret_cast<uint8_t*>(s_col) + tid;
+#pragma unroll
+    for (uint32_t i = 0; i < 4u * U; ++i) {
+        cmask |= (cl[i] >> 7) << i;
+        cl[i] &= 63u;
+        my_col[cl[i] * BLOCK] += 1;          // private byte, at most 16
+    }
+    // the candidates to the regions of their clusters: counted by cluster and eight lanes in LDS (all
+    // of a wavefront's may belong to one cluster, and additions that meet take their turns), one
+    // global reservation per cluster the block met, then the writes
+    if (__syncthreads_or(cmask ? 1 : 0)) {   // uniform
+        const uint32_t copy = (tid >> 3) & (PASS_COPIES - 1u);
+#pragma unroll
+        for (uint32_t i = 0; i < 4u * U; ++i) {
+            if ((cmask >> i) & 1u) {
+                const uint32_t slot = (cl[i] - 1u) * PASS_COPIES + copy;
+                cl[i] = atomicAdd(&s_cnt[slot], 1u) | (slot << 16);
             }
         }
-        my_col[j * BLOCK] += 1;                 // private byte, at most 16
-        j_out = j;
-        return key < s_hi1[j];                  // j <= k_var <= SPEC_MULTI_MAXK
-    };
-
-    if (whole) {
-        uint32_t cmask = 0, jj[U];
+        __syncthreads();
+        {
+            const uint32_t mine = s_cnt[tid], last = PASS_COPIES - 1u;
+            uint32_t incl = mine;
+            for (uint32_t d = 1; d < PASS_COPIES; d <<= 1) {
+                const uint32_t y = __shfl_up(incl, d, PASS_COPIES);
+                if ((tid & last) >= d) incl += y;
+            }
+            uint32_t base = 0;
+            if ((tid & last) == last && incl) base = atomicAdd(mcnt_cand(cnt, tid / PASS_COPIES, csb), incl);
+            base = __shfl(base, (int)last, PASS_COPIES);
+            s_cnt[tid] = base + incl - mine;
+        }
+        __syncthreads();
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
-            uint32_t j_0, j_1, j_2, j_3;
-            cmask |= ((one(v[u].x, j_0) ? 1u : 0u) | (one(v[u].y, j_1) ? 2u : 0u) |
-                      (one(v[u].z, j_2) ? 4u : 0u) | (one(v[u].w, j_3) ? 8u : 0u)) << (4 * u);
-            jj[u] = j_0 | (j_1 << 8) | (j_2 << 16) | (j_3 << 24);
-        }
-        ms_append_candidates(cmask != 0, s_coff, s_ccap, s_rc, s_rc2, s_rbase, k_var, cnt,
-                             blockIdx.x & (CAND_SUB - 1), cand,
-                             [&](auto&& f) {
+            const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
-                                 for (uint32_t u = 0; u < U; ++u) {
-                                     const uint32_t j = (threadIdx.x + BLOCK * u) * 4;
-                                     const uint32_t vv[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-                                     for (uint32_t q = 0; q < 4; ++q)
-                                         if (cmask & (1u << (4 * u + q)))
-                                             f(vv[q], g0 + j + q, ((jj[u] >> (8 * q)) & 0xffu) - 1u);
-                                 }
-                             });
-    } else {
-        // the tensor's last, ragged tile: one global atomic per candidate
-        for (uint32_t j0 = 0; j0 < n; j0 += BLOCK) {
-            const uint32_t j = j0 + threadIdx.x;
-            if (j < n) {
-                const uint32_t bits = __float_as_uint(src[j]);
-                uint32_t jw;
-                if (one(bits, jw)) {
-                    const uint32_t cl = jw - 1u;
-                    const uint32_t csb = blockIdx.x & (CAND_SUB - 1);
-                    const uint32_t pos = atomicAdd(mcnt_cand(cnt, cl, csb), 1u);
-                    const uint32_t cap = s_ccap[cl];
-                    if (pos < cap) cand[(size_t)s_coff[cl] + (size_t)csb * cap + pos] = make_uint2(bits, g0 + j);
+            for (uint32_t q = 0; q < 4u; ++q) {
+                const uint32_t i = 4u * u + q;
+                if ((cmask >> i) & 1u) {
+                    const uint32_t at = s_cnt[cl[i] >> 16] + (cl[i] & 0xffffu);
+                    const uint2 part = s_part[(cl[i] >> 16) / PASS_COPIES];
+                    if (at < part.y) cand[part.x + at] = make_uint2(x[q], g0 + (tid + BLOCK * u) * 4u + q);
                 }
             }
         }
@@ -371,8 +407,8 @@ __global__ __launch_bounds__(BLOCK) void ms_pass_kernel(
     __syncthreads();
     // column sums: four threads per j, a quarter of the row's words each (rotated by j: the
     // rows start in the same bank); bytes are added in two 16-bit lanes per word
-    if (threadIdx.x < 4 * (k_var + 1)) {
-        const uint32_t j = threadIdx.x >> 2, q = threadIdx.x & 3u;
+    if (tid < 4 * (k_var + 1)) {
+        const uint32_t j = tid >> 2, q = tid & 3u;
         constexpr uint32_t ROW_W = BLOCK / 4;
         uint32_t even = 0, odd = 0;
         for (uint32_t i = 0; i < ROW_W / 4; ++i) {
@@ -383,7 +419,7 @@ __global__ __launch_bounds__(BLOCK) void ms_pass_kernel(
         const uint32_t c = (even & 0xffffu) + (even >> 16) + (odd & 0xffffu) + (odd >> 16);
         if (c) atomicAdd(mcnt_below(cnt, j, sb), c);
     }
-    if (threadIdx.x == 0 && s_nan) atomicOr(&ms->status, 2u);
+    if (tid == 0 && s_nan) atomicOr(&ms->status, 2u);
 }
 
 // The finish, two launches over the candidates.
@@ -1034,8 +1070,8 @@ void launch_spec_multi(shifter_ctx* ctx, const shifter_model* m, const float* d_
     } else {
         ProfileScope ps(ctx, K_SPEC_PASS);
         auto kern = nt ? ms_pass_kernel<true> : ms_pass_kernel<false>;
-        kern<<<m->n_tiles, BLOCK, (k + 1) * BLOCK, s>>>(
-            b.tens, b.tile_prefix, n_t, d_w, b.multi, b.multi_cnt, b.cand, b.multi_tab, zero_ptr, zero_n);
+        kern<<<m->n_tiles, BLOCK, (k + 2) * BLOCK, s>>>(
+            b.tens, b.tile_prefix, b.tile_tensor, d_w, b.multi, k, b.multi_cnt, b.cand, b.multi_tab, zero_ptr, zero_n);
     }
     if (k != 0) {
         {
