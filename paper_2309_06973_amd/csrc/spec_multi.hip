@@ -440,7 +440,12 @@ __global__ __launch_bounds__(BLOCK, 8) void ms_pass_kernel(
 // on 0.86 M weights 11.9 + 6.6 us, 18.1 as one; of eight on 10 M 9.3 + 6.7 and 11.9).
 constexpr uint32_t MF_THREADS = 1024, MF_DEPTH = 8;
 constexpr uint32_t MF_BINS1 = 256;
-constexpr uint32_t MF_STAGE = 2048;      // pairs of the selected bin one filter block may hold
+constexpr uint32_t MF_STAGE = 2048;      // pairs of the selected bin that one part may hold
+// Parts that one block of the finish takes at most.  Its registers let a compute unit run one block of 1024
+// threads, so with a block for each of 32 parts nine ranks and more took two rounds or three: a block
+// takes as many parts as make one round.  Kernel, us: fifteen ranks of 0.86 M weights 17.2 -> 12.3, twenty of 25.5 M
+// 20.4 -> 15.4, ten of 14.7 M with ties 33.0 -> 30.0.  (Registers cut to what two blocks need spill: 19.9, 24.2, 37.3.)
+constexpr uint32_t MF_PARTS = 4;
 
 // f(pair) for the n pairs at src, MF_DEPTH loads per thread in flight.
 template <typename F>
@@ -498,15 +503,15 @@ __global__ __launch_bounds__(MF_THREADS) void ms_hist_kernel(
 __global__ __launch_bounds__(MF_THREADS) void ms_finish_kernel(
     MultiState* ms, const uint32_t* __restrict__ cnt, const uint2* __restrict__ cand,
     const uint32_t* __restrict__ ghist, const uint64_t* __restrict__ rowsum, uint2* list, uint32_t* rank_words,
-    shifter_threshold* thr, shifter_threshold* host_rec, uint32_t* host_status) {
+    uint32_t n_parts, shifter_threshold* thr, shifter_threshold* host_rec, uint32_t* host_status) {
     static_assert(MF_THREADS == FIN_THREADS && MF_BINS1 == 4u * 64u && CAND_SUB <= 64u, "a wavefront for each sum");
-    __shared__ uint2 stage[MF_STAGE];
+    __shared__ uint2 stage[MF_STAGE * MF_PARTS];
     __shared__ uint32_t h[FIN_BINS];
     __shared__ uint64_t comp[FIN_LIST];
     __shared__ uint64_t smem[FIN_THREADS / 64 + 1];
     __shared__ uint64_t s_below, s_inside, s_r2, s_less, s_sel, s_base2;
     __shared__ uint32_t s_over, s_n, s_base, s_bin, s_cnt, s_last, s_why, s_lt, s_eq, s_nb;
-    const uint32_t part = blockIdx.x, k = blockIdx.y;
+    const uint32_t part = blockIdx.x, k = blockIdx.y;     // the block's parts: part, part + gridDim.x, ...
     const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
     const RankIn R = ms->rin[k];
     const uint32_t nan_bit = ms->status & 2u;      // the pass has ended
@@ -515,7 +520,11 @@ __global__ __launch_bounds__(MF_THREADS) void ms_finish_kernel(
     uint32_t *list_cnt = rank_words + k, *ticket = rank_words + MAXK + k, *fail = rank_words + 2u * MAXK + k;
     const uint32_t* parts = cnt + (size_t)(MAXK + 1u + cl) * SPEC_SUB * 32u;
     // this part's first candidates, on their way while the rank is located
-    const uint32_t n_part = min(parts[part * 32u], cap);
+    uint32_t n_of[MF_PARTS];
+#pragma unroll
+    for (uint32_t i = 0; i < MF_PARTS; ++i)
+        n_of[i] = part + i * gridDim.x < n_parts ? min(parts[(part + i * gridDim.x) * 32u], cap) : 0u;
+    const uint32_t n_part = n_of[0];
     const uint2* src1 = cand + (size_t)R.cand_off + (size_t)part * cap;
     uint2 ahead[MF_DEPTH];
 #pragma unroll
@@ -581,13 +590,13 @@ __global__ __launch_bounds__(MF_THREADS) void ms_finish_kernel(
             return;
         }
     }
-    // this part's pairs of the selected bin -> the rank's list
+    // the parts' pairs of the selected bin -> the rank's list
     {
         const uint32_t sh = R.sh;
         auto take = [&](uint2 x) {
             if ((((x.x & 0x7fffffffu) - lo) >> sh) == bin) {
                 const uint32_t pos = atomicAdd(&s_n, 1u);
-                if (pos < MF_STAGE) stage[pos] = x;
+                if (pos < MF_STAGE * MF_PARTS) stage[pos] = x;
             }
         };
 #pragma unroll
@@ -595,8 +604,18 @@ __global__ __launch_bounds__(MF_THREADS) void ms_finish_kernel(
             if (u * MF_THREADS + threadIdx.x < n_part) take(ahead[u]);
         if (n_part > MF_DEPTH * MF_THREADS) ms_walk(src1 + MF_DEPTH * MF_THREADS, n_part - MF_DEPTH * MF_THREADS, take);
         __syncthreads();
-        const uint32_t m = s_n;
-        if (m > MF_STAGE) {
+        uint32_t m = s_n;
+        bool over = m > MF_STAGE;
+#pragma unroll
+        for (uint32_t i = 1; i < MF_PARTS; ++i) {
+            if (part + i * gridDim.x >= n_parts) break;          // the same in every thread
+            __syncthreads();                                     // all have read s_n
+            ms_walk(src1 + (size_t)i * gridDim.x * cap, n_of[i], take);
+            __syncthreads();
+            over = over || s_n - m > MF_STAGE;
+            m = s_n;
+        }
+        if (over) {
             if (threadIdx.x == 0) atomicOr(fail, 5u);
         } else if (m != 0) {
             if (threadIdx.x == 0) s_base = atomicAdd(list_cnt, m);
@@ -618,7 +637,7 @@ __global__ __launch_bounds__(MF_THREADS) void ms_finish_kernel(
     if (n != s_cnt || n > SPEC_LIST_CAP) { give_up(5u); return; }
     // a list that fits stays in LDS
     const uint2* src = list + (size_t)k * SPEC_LIST_CAP;
-    const bool staged = n <= MF_STAGE;
+    const bool staged = n <= MF_STAGE * MF_PARTS;
     if (staged) {
         for (uint32_t i = threadIdx.x; i < n; i += FIN_THREADS) stage[i] = load_device(&src[i]);
         __syncthreads();
@@ -1083,13 +1102,13 @@ void launch_spec_multi(shifter_ctx* ctx, const shifter_model* m, const float* d_
         }
         {
             ProfileScope ps(ctx, K_SPEC_FINISH2);
-            // a block for each part that a pass over this many tiles can have filled: two blocks fit a
-            // compute unit, so with 32 to a rank those of seventeen and more ranks take two rounds (twenty
-            // ranks of a 24 k weight network, 9 tiles: 34 us with 32 blocks a rank, 14 with 9; few distinct
-            // weights 64 and 29)
-            ms_finish_kernel<<<dim3(std::min(CAND_SUB, m->n_tiles), k), MF_THREADS, 0, s>>>(
-                b.multi, b.multi_cnt, b.cand, b.multi_hist, b.multi_rowsum, b.multi_list, b.multi_list_cnt, d_thr,
-                b.dev_multi_rec, b.dev_multi_status);
+            // the parts that a pass over this many tiles can have filled (twenty ranks of a 24 k weight network, 9
+            // tiles: 34 us with 32 parts a rank, 14 with 9), shared out to no more blocks than run at a time
+            const uint32_t parts = std::min(CAND_SUB, m->n_tiles);
+            const uint32_t per = std::min(MF_PARTS, (parts * k + 255u) / 256u);
+            ms_finish_kernel<<<dim3((parts + per - 1u) / per, k), MF_THREADS, 0, s>>>(
+                b.multi, b.multi_cnt, b.cand, b.multi_hist, b.multi_rowsum, b.multi_list, b.multi_list_cnt, parts,
+                d_thr, b.dev_multi_rec, b.dev_multi_status);
         }
     }
     if (fb) {
