@@ -734,17 +734,6 @@ extern "C" int shifter_global_threshold_static(shifter_ctx* ctx, const float* d_
     return after_launch(ctx, "global_threshold_static");
 }
 
-// Enqueues the read-back of a ranking's outcome (a status word, then the K records) into
-// the model's pinned buffer.
-static int rank_result_enqueue(shifter_ctx* ctx, const shifter_model* model, const uint32_t* d_status,
-                               const shifter_threshold* d_thr, uint32_t K) {
-    uint8_t* st = model->b.host_multi;
-    HIP_TRY(ctx, hipMemcpyAsync(st, d_status, sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(ctx, hipMemcpyAsync(st + MULTI_MIRROR_REC_OFF, d_thr, sizeof(shifter_threshold) * K,
-                                hipMemcpyDeviceToHost, ctx->stream));
-    return SHIFTER_OK;
-}
-
 extern "C" int shifter_global_threshold_begin(shifter_ctx* ctx, const shifter_model* model,
                                               const float* d_w, const uint64_t* h_n_prune, uint32_t K,
                                               shifter_threshold* d_thr) {
@@ -784,9 +773,8 @@ extern "C" int shifter_global_threshold_begin(shifter_ctx* ctx, const shifter_mo
         if ((rc = after_launch(ctx, "global_threshold_begin"))) return rc;
         pr.k_eff = k_eff;
     } else {
-        launch_select(ctx, model, d_w, pr.pc, K, d_thr);
+        launch_select(ctx, model, d_w, pr.pc, K, d_thr, true);
         if ((rc = after_launch(ctx, "global_threshold_begin"))) return rc;
-        if ((rc = rank_result_enqueue(ctx, model, &model->b.sel->nan_seen, d_thr, K))) return rc;
     }
     pr.active = true;
     pr.model = model;
@@ -814,9 +802,8 @@ extern "C" int shifter_global_threshold_end(shifter_ctx* ctx, shifter_threshold*
         if (decided) return SHIFTER_OK;
         // the single pass could not decide: the multi-pass select, and the caller repeats
         // what it had enqueued behind the ranking
-        launch_select(ctx, model, pr.d_w, pr.pc, pr.k, pr.d_thr);
+        launch_select(ctx, model, pr.d_w, pr.pc, pr.k, pr.d_thr, true);
         if ((rc = after_launch(ctx, "global_threshold_end"))) return rc;
-        if ((rc = rank_result_enqueue(ctx, model, &model->b.sel->nan_seen, pr.d_thr, pr.k))) return rc;
         if (h_redone) *h_redone = 1;
     } else {
         ctx->last_path = 2;
@@ -1348,11 +1335,9 @@ static MultiPerm cut_positions(const PruneCounts& pc, uint32_t K) {
 
 static int portfolio_multipass(shifter_ctx* ctx, const shifter_model* model, const PruneCounts& pc,
                            const PortfolioBuffers& a) {
-    int rc;
-    launch_select(ctx, model, a.d_w, pc, a.k_var, a.d_thr);
-    if ((rc = after_launch(ctx, "portfolio"))) return rc;
-    if ((rc = rank_result_enqueue(ctx, model, &model->b.sel->nan_seen, a.d_thr, a.k_var))) return rc;
-    launch_zero_levels(ctx, model);
+    // the select's first launch clears the levels, its last one leaves the records in the pinned mirror
+    launch_select(ctx, model, a.d_w, pc, a.k_var, a.d_thr, true, model->b.levels,
+                  (uint32_t)(model->info.sum_out_ch + model->info.sum_in_ch));
     launch_mask_scan_batch_core(ctx, model, a.d_w, a.d_thr, a.k_var, a.d_w_sparse, a.w_stride, a.d_mask,
                                 a.mask_stride);
     launch_plan_and_gather(ctx, model, a, true, cut_positions(pc, a.k_var));
@@ -1429,8 +1414,13 @@ extern "C" int shifter_portfolio_begin(shifter_ctx* ctx, const shifter_model* mo
             // planning launch expands the levels into the variants' flags on the way
             launch_spec_multi(ctx, model, g.d_w, sp, perm, k_eff, zero_mask, g.d_thr, nullptr, b.levels,
                               (uint32_t)(model->info.sum_out_ch + model->info.sum_in_ch));
+            // Where the ranking could not decide the step is made again (portfolio_end), so this pass leaves the sparse
+            // arenas and masks to that one; the levels are what the launches behind it read.  (A rebuild
+            // from the sparse arenas has to find some of this model's.)  Ten variants of 14.7 M
+            // weights kept in half precision: this pass 132 -> 64 us, the call 727 -> 629 (with the records left in
+            // the mirror by the select's last kernel, not copied in the middle of the stream)
             launch_mask_scan_batch_core(ctx, model, g.d_w, g.d_thr, K, g.d_w_sparse, g.w_stride, g.d_mask,
-                                        g.mask_stride);
+                                        g.mask_stride, k_eff && rebuild_reads_dense(model, pp.buf) ? &b.multi->status : nullptr);
             launch_plan_and_gather(ctx, model, pp.buf, true, cut_positions(pp.pc, K));
         }
     } else {

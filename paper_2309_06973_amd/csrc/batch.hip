@@ -41,7 +41,8 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
     const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix, uint32_t n_t,
     const float* __restrict__ w, const shifter_threshold* __restrict__ thr, uint32_t k_var,
     float* __restrict__ w_out, uint64_t w_stride, uint8_t* __restrict__ mask,
-    uint64_t mask_stride, uint32_t* out_level, uint32_t* in_level) {
+    uint64_t mask_stride, uint32_t* out_level, uint32_t* in_level, const uint32_t* __restrict__ undecided) {
+    if (undecided && (*undecided & 1u)) { w_out = nullptr; mask = nullptr; }
     __shared__ uint32_t rowmax[TILE + 16];
     __shared__ uint32_t colmax[TILE + 16];
     __shared__ uint64_t s_cut[MAXK];
@@ -253,7 +254,7 @@ void launch_mask_scan_batch(shifter_ctx* ctx, const shifter_model* m, const floa
 
 void launch_mask_scan_batch_core(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
                                  const shifter_threshold* d_thr, uint32_t k_var, float* d_w_out,
-                                 uint64_t w_stride, uint8_t* d_mask, uint64_t mask_stride) {
+                                 uint64_t w_stride, uint8_t* d_mask, uint64_t mask_stride, const uint32_t* undecided) {
     const auto& b = m->b;
     const uint32_t n_t = (uint32_t)m->t.size();
     const uint64_t n_out = m->info.sum_out_ch;
@@ -267,7 +268,7 @@ void launch_mask_scan_batch_core(shifter_ctx* ctx, const shifter_model* m, const
         const bool nt = m->info.w_extent * 4 <= (192ull << 20);
         auto k = nt ? mask_scan_batch_kernel<true> : mask_scan_batch_kernel<false>;
         k<<<m->n_tiles, BLOCK, 0, s>>>(b.tens, b.tile_prefix, n_t, d_w, d_thr, k_var, d_w_out,
-                                       w_stride, d_mask, mask_stride, b.levels, b.levels + n_out);
+                                       w_stride, d_mask, mask_stride, b.levels, b.levels + n_out, undecided);
     }
 }
 

@@ -345,8 +345,12 @@ struct shifter_ctx {
 namespace shifter {
 
 // Launchers (defined next to their kernels).  All enqueue on ctx->stream.
+// mirror: the records and whether a NaN was met also go to the model's pinned mirror, written by the last
+// kernel.  zero_ptr / zero_n: an array of 32-bit words that the first launch clears on the way (or nullptr),
+// for the step that follows.
 void launch_select(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
-                   const PruneCounts& pc, uint32_t k, shifter_threshold* d_thr);
+                   const PruneCounts& pc, uint32_t k, shifter_threshold* d_thr, bool mirror = false,
+                   uint32_t* zero_ptr = nullptr, uint32_t zero_n = 0);
 // The tables and scratch the multi-pass select works on: a model's, or the ones laid out in
 // the static scratch array for one flat run of weights.
 struct SelectTables {
@@ -360,6 +364,10 @@ struct SelectTables {
     uint64_t list_pairs;
     DevTensor* flat_tens;     // a flat run: where its one-tensor tables (tens, tile_prefix) are to be written
     uint32_t* flat_prefix;
+    uint32_t* zero_ptr = nullptr;                // see launch_select
+    uint32_t zero_n = 0;
+    shifter_threshold* host_rec = nullptr;       // device addresses of the pinned mirror, or nullptr
+    uint32_t* host_nan = nullptr;
 };
 void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float* d_w,
                           const PruneCounts& pc, uint32_t k, shifter_threshold* d_thr);
@@ -430,11 +438,14 @@ void launch_compact(shifter_ctx* ctx, const shifter_model* m, const float* d_w, 
 // pos[k] = number of variants that remove fewer weights than variant k (ties by index).
 void launch_plan_and_gather(shifter_ctx* ctx, const shifter_model* m, const PortfolioBuffers& a,
                             bool from_levels, const MultiPerm& pos);
-// The batched mask pass alone: with_zero clears the level arrays first, with_expand turns
-// them into the variants' flag bytes afterwards.
+// The batched mask pass alone, on cleared level arrays.  undecided: bit 0 of that word says that the
+// records are not there yet and the caller will make the step again: levels only (or nullptr).
 void launch_mask_scan_batch_core(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
                                  const shifter_threshold* d_thr, uint32_t k_var, float* d_w_out,
-                                 uint64_t w_stride, uint8_t* d_mask, uint64_t mask_stride);
+                                 uint64_t w_stride, uint8_t* d_mask, uint64_t mask_stride,
+                                 const uint32_t* undecided = nullptr);
+// Whether the rebuild behind a portfolio step's mask pass reads the dense arena, not the sparse ones.
+bool rebuild_reads_dense(const shifter_model* m, const PortfolioBuffers& a);
 void launch_copy(shifter_ctx* ctx, const float* src, float* dst, uint64_t n);
 void launch_kernel_scan(shifter_ctx* ctx, const shifter_model* m, const float* d_w, uint8_t* d_nz);
 void launch_fix_begin(shifter_ctx* ctx, const shifter_model* m);

@@ -851,6 +851,12 @@ void launch_compact(shifter_ctx* ctx, const shifter_model* m, const float* d_w, 
     launch_gather(ctx, m, d_w, w_stride, d_vecs, d_keep, d_w_out, cap_w, d_vecs_out, cap_v, k_var, d_thr);
 }
 
+// The source of the rebuild: the dense arena masked on the way, unless only the sparse
+// arenas can serve the output-ordered gather.
+bool rebuild_reads_dense(const shifter_model* m, const PortfolioBuffers& a) {
+    return use_rect(m, a.k_var, a.d_thr) || !a.d_w_sparse;
+}
+
 // Steps 4 and 5 of a portfolio step behind its mask pass: one planning launch (groups,
 // rebuild plans, tables; with from_levels also the variants' flag bytes, expanded from the
 // level arrays the batched mask pass left) and the gather.
@@ -860,8 +866,6 @@ void launch_plan_and_gather(shifter_ctx* ctx, const shifter_model* m, const Port
     const uint32_t n_t = (uint32_t)m->t.size(), n_v = (uint32_t)m->v.size();
     const uint32_t n_g = (uint32_t)m->g.size();
     const uint64_t n_out = m->info.sum_out_ch, n_in = m->info.sum_in_ch;
-    // the source of the rebuild: the dense arena masked on the way, unless only the sparse
-    // arenas can serve the output-ordered gather
     const bool rect = use_rect(m, a.k_var, a.d_thr);
     PlanAllArgs A;
     A.groups = b.groups; A.producers = b.producers; A.tens = b.tens; A.n_t = n_t;
@@ -889,7 +893,7 @@ void launch_plan_and_gather(shifter_ctx* ctx, const shifter_model* m, const Port
                                                         a.cap_w, a.cap_v, b.plan_t, b.plan_v,
                                                         b.out_tile_prefix, b.plan_h, b.dev_plan);
     }
-    const bool dense_src = rect || !a.d_w_sparse;
+    const bool dense_src = rebuild_reads_dense(m, a);
     launch_gather(ctx, m, dense_src ? a.d_w : a.d_w_sparse, dense_src ? 0 : a.w_stride, a.d_vecs, a.d_keep,
                   a.d_w_out, a.cap_w, a.d_vecs_out, a.cap_v, a.k_var, dense_src ? a.d_thr : nullptr);
 }

@@ -51,10 +51,12 @@ __device__ __forceinline__ uint32_t top_bin(uint32_t key) { return key ? sample_
 
 __global__ __launch_bounds__(BLOCK) void sel_clear_kernel(SelState* st, uint32_t* ghist, uint32_t hists,
                                                           PruneCounts pc, MultiPerm perm, uint32_t k,
-                                                          DevTensor* flat_tens, uint32_t* flat_prefix, uint64_t flat_n) {
+                                                          DevTensor* flat_tens, uint32_t* flat_prefix, uint64_t flat_n,
+                                                          uint32_t* zero_ptr, uint32_t zero_n) {
     const uint32_t tid = blockIdx.x * BLOCK + threadIdx.x;
     uint4* g4 = reinterpret_cast<uint4*>(ghist);
     for (uint32_t i = tid; i < hists * (SEL_BINS / 4); i += gridDim.x * BLOCK) g4[i] = make_uint4(0, 0, 0, 0);
+    for (uint32_t i = tid; i < zero_n; i += gridDim.x * BLOCK) zero_ptr[i] = 0;
     if (tid < (SEL_STAGES + 1u) * MAXK) {
         (&st->key_lo[0][0])[tid] = 0xffffffffu;
         (&st->key_hi[0][0])[tid] = 0;
@@ -518,7 +520,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
 // One block per rank: the record from its list.
 __global__ __launch_bounds__(SEL_THREADS) void sel_final_kernel(
     const SelState* __restrict__ st, const uint2* __restrict__ lists, uint32_t list_cap, uint32_t g_bits,
-    shifter_threshold* __restrict__ thr) {
+    shifter_threshold* __restrict__ thr, shifter_threshold* host_rec, uint32_t* host_nan) {
     __shared__ RankShared<SEL_THREADS> sh;
     const uint32_t q = blockIdx.x;
     shifter_threshold out;
@@ -551,15 +553,21 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_final_kernel(
             }
         }
     }
-    if (threadIdx.x == 0) thr[st->perm[q]] = out;
+    if (threadIdx.x == 0) {
+        thr[st->perm[q]] = out;
+        if (host_rec) host_rec[st->perm[q]] = out;
+        if (host_nan && q == 0) *host_nan = st->nan_seen;
+    }
 }
 
 void launch_select(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
-                   const PruneCounts& pc, uint32_t k, shifter_threshold* d_thr) {
+                   const PruneCounts& pc, uint32_t k, shifter_threshold* d_thr, bool mirror, uint32_t* zero_ptr,
+                   uint32_t zero_n) {
     const auto& b = m->b;
     // the candidate buffer of the single-pass selections is idle here: it holds the lists
     const SelectTables tb{b.tens, b.tile_prefix, (uint32_t)m->t.size(), m->n_tiles, m->info.n_prunable, b.sel, b.ghist,
-                          b.cand, (uint64_t)b.cand_cap_sb * SPEC_SUB, nullptr, nullptr};
+                          b.cand, (uint64_t)b.cand_cap_sb * SPEC_SUB, nullptr, nullptr, zero_ptr, zero_n,
+                          mirror ? b.dev_multi_rec : nullptr, mirror ? b.dev_multi_status : nullptr};
     launch_select_tables(ctx, tb, d_w, pc, k, d_thr);
 }
 
@@ -579,7 +587,7 @@ void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float*
     {
         ProfileScope p(ctx, K_SEL_INIT);
         sel_clear_kernel<<<64, BLOCK, 0, s>>>(tb.sel, tb.ghist, stages, sorted, perm, k, tb.flat_tens, tb.flat_prefix,
-                                              tb.n_weights);
+                                              tb.n_weights, tb.zero_ptr, tb.zero_n);
     }
     {
         ProfileScope p(ctx, K_HIST0);
@@ -592,7 +600,7 @@ void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float*
     }
     {
         ProfileScope p(ctx, K_SEL_FINAL);
-        sel_final_kernel<<<k, SEL_THREADS, 0, s>>>(tb.sel, tb.lists, list_cap, g_bits, d_thr);
+        sel_final_kernel<<<k, SEL_THREADS, 0, s>>>(tb.sel, tb.lists, list_cap, g_bits, d_thr, tb.host_rec, tb.host_nan);
     }
 }
 
