@@ -22,6 +22,7 @@
 // Any inflater reads the stream; the encoder works with 512 threads per chunk and 32 lanes per
 // sub-chunk, the decoder with 256 and four.
 #include <string>
+#include <type_traits>
 
 #include "chain.h"
 #include "dev_common.h"
@@ -42,26 +43,6 @@ static_assert(CODEC_NSUB == 64, "one lane per sub-chunk");
 // spread over the banks while a vector stays whole.
 __device__ __forceinline__ uint32_t sub_word(uint32_t l, uint32_t j) {
     return l * CODEC_SUBW + ((j + 4u * l) & (CODEC_SUBW - 1));
-}
-
-// A match of `len` (3..258) at distance 1: length code, extra bits, 5-bit distance code 0.
-__device__ __forceinline__ uint32_t match_code(uint32_t len, uint32_t* code) {
-    uint32_t idx, e = 0, extra = 0;
-    if (len == 258u) {
-        idx = 28u;
-    } else if (len < 11u) {
-        idx = len - 3u;
-    } else {
-        const uint32_t x = len - 3u;              // 8..254
-        e = 29u - (uint32_t)__clz(x);             // floor(log2 x) - 2
-        idx = 4u * e + 4u + ((x >> e) & 3u);
-        extra = x & ((1u << e) - 1u);
-    }
-    uint32_t c, n;
-    if (idx < 23u) { c = __brev(1u + idx) >> 25; n = 7u; }         // symbols 257..279
-    else { c = __brev(0xC0u + (idx - 23u)) >> 24; n = 8u; }        // symbols 280..285
-    *code = c | (extra << n);
-    return n + e + 5u;
 }
 
 // Appends bits to the chunk's bit buffer in LDS, which starts zeroed: every dword is OR-ed
@@ -87,18 +68,6 @@ struct BitWriter {
         if (cnt) atomicOr(&buf[widx], (uint32_t)acc);
     }
 };
-
-// The matches that cover the rest (15..511) bytes behind a run's first one: one of 258 where
-// more than 260 remain, then one, or the pieces (rest - 3, 3) of 259 and 260.  At most 31 bits.
-__device__ __forceinline__ uint32_t far_matches(uint32_t rest, uint32_t* code) {
-    uint32_t c, c258, c3, n3;
-    const bool two = rest > 260u, split = rest > 258u && !two;
-    const uint32_t n = match_code(two ? rest - 258u : (split ? rest - 3u : rest), &c);
-    const uint32_t n258 = match_code(258u, &c258);                      // constants
-    n3 = match_code(3u, &c3);
-    *code = two ? c258 | (c << n258) : (split ? c | (c3 << n) : c);
-    return n + (two ? n258 : (split ? n3 : 0u));
-}
 
 __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t lane, uint32_t* total) {
     uint32_t x = v;
@@ -158,18 +127,24 @@ constexpr uint32_t CODEC_LOOP_GRID = 1536;                    // blocks of an in
 // --- the encoder -------------------------------------------------------------------------
 // 512 threads per chunk, one or two chunks a block.  A lane holds 16 consecutive bytes of a sub-chunk (32
 // lanes a sub-chunk, so a wavefront takes 1 KiB at a time and four of those in turn); the
-// chunk stays in registers and only the segment being built is in LDS: 33.6 KB whatever its
+// chunk stays in registers and only the segment being built is in LDS: 37 KB with the codes, whatever its
 // size, room for four chunks a compute unit.  (The bound on registers asks for fewer; the 58 that the
 // compiler takes let four run.)  First every piece finds its literals,
 // the runs they start and its token bits, and prefix sums over the lanes place the pieces in
 // their sub-chunk; then, with the sub-chunks placed in the segment, every lane appends its
 // own piece's tokens.
-// Bound by vector instructions (about 600 per KiB and wavefront), and in small inputs by the
-// life of one block.  Ten rebuilt variants of a 14.7 M weight network (3/10 to all of the
+// Bound by vector instructions for two thirds of its time (counters: 27 M of 41 M issue slots with 474 of them per
+// KiB and wavefront; fewer now), the rest is the latency of the ticket, of the chunk's bytes and
+// of the chain, and in small inputs the life of one block.  So the codes come from tables in LDS (literals, short
+// matches, long ones: the arithmetic took a third of the instructions), lanes exchange by DPP, a match is appended once
+// for four bytes and not for two, the marks are put together by one wavefront for all sub-chunks, and a full
+// chunk takes no care of its end.
+// Ten rebuilt variants of a 14.7 M weight network (3/10 to all of the
 // weights not zero), one after the other: 2780 us with four lanes walking a sub-chunk's tokens
 // one by one, a second instance for the chunks with long segments and a pack pass; 845 with 256
 // threads of this form, 690 with 512, 650 without loops for the matches and with two chunks a
-// block.  1.3 GB of a sparse model: 4820 us before, 1200 now.
+// block, 570 with the tables and what goes with them (the kernels alone 492 -> 409).  1.3 GB of a model with
+// 5 % of its weights: 4820 us, 1104, 853 now; with 30 % 1209 -> 945; all of its weights 725 -> 725; all zeros 409 -> 420.
 
 // Bits 0-15 of a piece: which bytes differ from the byte before them, and which are >= 144
 // (9-bit literals).  prev: the byte before the piece.
@@ -199,9 +174,10 @@ __device__ __forceinline__ uint32_t nines16(const uint4& v) {
 // What a lane keeps of a piece between the two passes.
 struct Piece {
     uint4 v;          // the bytes
-    uint32_t lit;     // bits 0-15 the bytes sent as literals, 16-31 those among all that take 9 bits
+    uint32_t lit;     // the bytes sent as literals
     uint32_t place;   // bits 0-15 token bits of the sub-chunk before this piece; 16-25 the first
                       //   literal behind the piece (offset in the sub-chunk; its length if none)
+    uint32_t runs;    // bits 0-15 Runs::near, 16-24 Runs::far
 };
 
 // The runs of 4 or more that start in a piece.  lit: its literals; end: the sub-chunk's end, where
@@ -222,49 +198,114 @@ __device__ __forceinline__ Runs find_runs(uint32_t lit, uint32_t end, uint32_t n
     return r;
 }
 
-// Appends the tokens of a piece at bit position `bit` of the (zeroed) buffer.
-__device__ __forceinline__ void emit_tokens(uint32_t* out, uint32_t bit, const uint4& v, uint32_t lit, uint32_t nine,
-                                            const Runs& r) {
+// Codes by table, in LDS: of the 256 literals, of the matches that cover 3 to 14 bytes, by that
+// number, and of those that cover up to a sub-chunk.
+struct alignas(16) CodeTable {
+    uint32_t match[32];           // code | length << 16; others: 0
+    uint32_t far[CODEC_SUB];      // by rest, from 15 on (Runs::far): the code
+    uint16_t literal[256];        // code | length << 12
+    uint8_t far_bits[CODEC_SUB];  // length of far's
+};
+constexpr uint32_t reversed(uint32_t x, uint32_t n) {
+    uint32_t y = 0;
+    for (uint32_t i = 0; i < n; ++i) y |= ((x >> i) & 1u) << (n - 1u - i);
+    return y;
+}
+// A match of `len` (3..258) at distance 1: length code, extra bits, 5-bit distance code 0.
+constexpr uint32_t match_code(uint32_t len, uint32_t* code) {
+    uint32_t idx = 28u, e = 0, extra = 0;
+    if (len < 11u) {
+        idx = len - 3u;
+    } else if (len != 258u) {
+        const uint32_t x = len - 3u;              // 8..254
+        while ((x >> (e + 3u)) != 0u) ++e;        // floor(log2 x) - 2
+        idx = 4u * e + 4u + ((x >> e) & 3u);
+        extra = x & ((1u << e) - 1u);
+    }
+    // symbols 257..279 in 7 bits, 280..285 in 8
+    const uint32_t n = idx < 23u ? 7u : 8u;
+    *code = reversed(idx < 23u ? 1u + idx : 0xC0u + (idx - 23u), n) | (extra << n);
+    return n + e + 5u;
+}
+// The matches that cover the rest (15..511) bytes behind a run's first one: one of 258 where
+// more than 260 remain, then one, or the pieces (rest - 3, 3) of 259 and 260.  At most 31 bits.
+constexpr uint32_t far_matches(uint32_t rest, uint32_t* code) {
+    uint32_t a = 0, b = 0;
+    if (rest > 258u) {
+        const uint32_t first = rest > 260u ? 258u : rest - 3u;
+        const uint32_t na = match_code(first, &a), nb = match_code(rest - first, &b);
+        *code = a | (b << na);
+        return na + nb;
+    }
+    return match_code(rest, code);
+}
+constexpr CodeTable make_code_table() {
+    CodeTable t{};
+    for (uint32_t i = 0; i < 256u; ++i)           // 0x30 + i in 8 bits below 144, 0x190 + i - 144 in 9 from there on
+        t.literal[i] = (uint16_t)(i < 144u ? reversed(0x30u + i, 8) | (8u << 12) : reversed(0x190u + i - 144u, 9) | (9u << 12));
+    for (uint32_t i = 0; i < CODEC_SUB; ++i) {
+        uint32_t c = 0;
+        if (i >= 3u && i <= 14u) t.match[i] = match_code(i, &c) << 16 | c;
+        if (i >= 15u) {
+            t.far_bits[i] = (uint8_t)far_matches(i, &c);
+            t.far[i] = c;
+        }
+    }
+    return t;
+}
+static __device__ const CodeTable kCodeTable = make_code_table();
+static_assert(sizeof(CodeTable) % 16 == 0 && sizeof(CodeTable) / 16 <= 512 - 64, "one piece a thread behind the first wavefront");
+
+// Appends the tokens of a piece at bit position `bit` of the (zeroed) buffer.  ends, near, far: see Runs.
+__device__ __forceinline__ void emit_tokens(const CodeTable& t, uint32_t* out, uint32_t bit, const uint4& v, uint32_t lit,
+                                            uint32_t ends, uint32_t near, uint32_t far) {
     const uint32_t dw[4] = {v.x, v.y, v.z, v.w};
+    auto append = [&](uint32_t bits, uint32_t n) {       // at most 32 bits
+        const uint64_t code = (uint64_t)bits << (bit & 31u);
+        atomicOr(&out[bit >> 5], (uint32_t)code);
+        atomicOr(&out[(bit >> 5) + 1u], (uint32_t)(code >> 32));
+        bit += n;
+    };
 #pragma unroll
     for (uint32_t d = 0; d < 4u; ++d) {
         if (__ballot((lit >> (4u * d)) & 15u) == 0ull) continue;
-        // the 8-bit codes of four bytes at once: 0x30 + v below 144, v (behind a 1) from there,
-        // reversed; byte j of dw[d] ends up in byte 3 - j of rev
-        const uint32_t low = ~not_low144(dw[d]) & 0x80808080u;
-        const uint32_t rev = __brev(dw[d] + ((low >> 2) | (low >> 3)));
+        uint32_t e[4];
 #pragma unroll
-        for (uint32_t h = 0; h < 2u; ++h) {
-            // two bytes and at most one match behind them: up to 31 bits
-            const uint32_t j = 4u * d + 2u * h;
-            const uint32_t g0 = (nine >> j) & 1u, g1 = (nine >> (j + 1u)) & 1u;
-            const uint32_t l0 = 0u - ((lit >> j) & 1u), l1 = 0u - ((lit >> (j + 1u)) & 1u);
-            const uint32_t c0 = ((((rev >> (24u - 16u * h)) & 0xffu) << g0) | g0) & l0;
-            const uint32_t c1 = ((((rev >> (16u - 16u * h)) & 0xffu) << g1) | g1) & l1;
-            const uint32_t n0 = (8u + g0) & l0, n01 = n0 + ((8u + g1) & l1);
-            const uint32_t run = (r.near >> j) & 3u;           // neither, the first or the second byte starts one
-            uint32_t mc = 0, mn = 0;
-            if (__ballot(run != 0u) != 0ull) {
-                // x = rest - 3 of 0..11: symbols 257..264, then two lengths per symbol and an extra bit
-                // (of no matter where no run starts)
-                const uint32_t x = (uint32_t)__builtin_ctz((r.ends >> (j + 1u) >> (run >> 1)) | 0x80000000u) - 3u;
-                const uint32_t big = (x >> 3) & 1u, on = run ? ~0u : 0u;
-                mc = ((__brev((x >> big) + 1u + 4u * big) >> 25) | ((x & big) << 7)) & on;
-                mn = (12u + big) & on;
-            }
-            const uint64_t code = (uint64_t)(c0 | (c1 << n0) | (mc << n01)) << (bit & 31u);
-            atomicOr(&out[bit >> 5], (uint32_t)code);
-            atomicOr(&out[(bit >> 5) + 1u], (uint32_t)(code >> 32));
-            bit += n01 + mn;
+        for (uint32_t q = 0; q < 4u; ++q) e[q] = t.literal[(dw[d] >> (8u * q)) & 0xffu] & (0u - ((lit >> (4u * d + q)) & 1u));
+        // two bytes: up to 18 bits
+        const uint32_t n0 = e[0] >> 12, n2 = e[2] >> 12;
+        append((e[0] & 0xfffu) | ((e[1] & 0xfffu) << n0), n0 + (e[1] >> 12));
+        uint32_t c = (e[2] & 0xfffu) | ((e[3] & 0xfffu) << n2), n = n2 + (e[3] >> 12);
+        // runs that start in a piece are at least four bytes apart: at most one starts among these four, the
+        // rest of them belong to it, and its match comes behind their literals
+        const uint32_t run = (near >> (4u * d)) & 15u;
+        if (__ballot(run != 0u) != 0ull) {
+            const uint32_t first = (uint32_t)__builtin_ctz(run | 16u);
+            const uint32_t rest = (uint32_t)__builtin_ctz((ends >> (4u * d + 1u) >> first) | 0x80000000u);
+            const uint32_t m = t.match[run ? rest : 0u];
+            c |= (m & 0xffffu) << n;
+            n += m >> 16;
         }
+        append(c, n);
     }
-    if (r.far) {
-        uint32_t c;
-        far_matches(r.far, &c);
-        const uint64_t code = (uint64_t)c << (bit & 31u);
-        atomicOr(&out[bit >> 5], (uint32_t)code);
-        atomicOr(&out[(bit >> 5) + 1u], (uint32_t)(code >> 32));
-    }
+    if (far) append(t.far[far], 0u);
+}
+
+// Lane exchanges without a trip through LDS: the value of the lane below and above in the wavefront (0
+// at its ends), and the inclusive sum over 32 lanes.
+__device__ __forceinline__ uint32_t lane_below(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x138, 0xf, 0xf, true);       // wave_shr:1
+}
+__device__ __forceinline__ uint32_t lane_above(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x130, 0xf, 0xf, true);       // wave_shl:1
+}
+__device__ __forceinline__ uint32_t incl_sum32(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);         // row_shr:1, 2, 4, 8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);
+    // lane 15 of a 32's first row to its second (row_bcast:15 into rows 1 and 3)
+    return x + (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);
 }
 
 // Chained offsets of the segments (the decoupled look-back of Merrill and Garland's single-pass
@@ -293,19 +334,18 @@ __device__ __forceinline__ ChainWalk chain_before(const uint64_t* status, uint32
 
 // A whole sub-chunk of zeros: the literal 0 (00110000) and the matches 258 (symbol 285: 11000101)
 // and 253 (symbol 284: 11000100, extra bits 253 - 227 = 26), each with the distance code 00000.
-// All codes start from their first bit in bit 0.  Its quarters' marks: all token bits before the
+// All codes start from their first bit in bit 0.  Its quarters: all token bits before the
 // second one, and no further literal before the end.
 constexpr uint32_t ZERO_SUB_BITS = 8u + 13u + 18u;
 constexpr uint32_t ZERO_SUB_LOW = 0x0Cu | (0xA3u << 8);                    // the literal and the first match, 21 bits
 constexpr uint32_t ZERO_SUB_HIGH = 0x23u | (26u << 8);
-constexpr uint64_t ZERO_SUB_MARK = (uint64_t)(ZERO_SUB_BITS | (384u << 11)) | (uint64_t)(256u << 11) << 20 |
-                                   (uint64_t)(128u << 11) << 40;
 static_assert(CODEC_SUB == 512u, "258 + 253 + 1");
 
 // DIRECT: the segments go straight to their place in the stream, which cannot overflow (the
 // host checked that it holds the largest possible one).  The tickets take 13.8 ns each on their one
 // address, a bound where chunks hold next to nothing: 1.3 GB of zeros take 540 us a call with a ticket for
-// each chunk, 408 with one for two (GROUPS: 512 threads each, side by side in a block).  Otherwise every segment goes to its
+// each chunk, 408 with one for two (GROUPS: 512 threads each, side by side in a block; they are one link of the
+// chain too: dense weights 831 -> 760 us).  Otherwise every segment goes to its
 // slot of the workspace, and the two kernels behind this one add up the sizes and, if the
 // stream is large enough, move the segments.
 constexpr uint32_t CODEC_OUT_DW = CODEC_CHUNK / 4 + 8;
@@ -317,21 +357,28 @@ __global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void def
     uint64_t* __restrict__ status, uint32_t* __restrict__ ticket, uint64_t* __restrict__ seg_off,
     uint8_t* __restrict__ stream, uint64_t* __restrict__ mirror) {
     __shared__ __align__(16) uint32_t g_out[GROUPS][CODEC_OUT_DW];
-    __shared__ uint64_t g_mark[GROUPS][CODEC_NSUB];
+    // of every sub-chunk's quarters the token bits before it (bits 0-15) and how far past its start its first
+    // literal lies
+    __shared__ __align__(16) uint32_t g_quarter[GROUPS][CODEC_NSUB * CODEC_Q];
     __shared__ uint32_t g_side[GROUPS][CODEC_NSUB];
+    __shared__ CodeTable s_codes;
     __shared__ uint64_t g_off[GROUPS];
-    __shared__ uint32_t s_c;
+    __shared__ uint32_t s_c, g_size[GROUPS];
     constexpr uint32_t STEPS = CODEC_CHUNK / 1024u / (DEF_THREADS / 64u);     // KiB per wavefront
     const uint32_t group = GROUPS == 1 ? 0u : uniform_u32(threadIdx.x / DEF_THREADS), tid = threadIdx.x % DEF_THREADS;
     uint32_t* s_out = g_out[group];
-    uint64_t* s_mark = g_mark[group];
+    uint32_t* s_quarter = g_quarter[group];
     uint32_t* s_side = g_side[group];
     const uint32_t lane = threadIdx.x & 63u, wid = uniform_u32(tid >> 6), half = lane >> 5, hl = lane & 31u;
-    uint32_t c = blockIdx.x * GROUPS + group;
+    uint32_t link = blockIdx.x, c = link * GROUPS + group;
+    if (DIRECT && threadIdx.x == 0) s_c = atomicAdd(ticket, 1u);
+    // while the first wavefront waits for the ticket
+    if (threadIdx.x - 64u < sizeof(CodeTable) / 16u)
+        reinterpret_cast<uint4*>(&s_codes)[threadIdx.x - 64u] = reinterpret_cast<const uint4*>(&kCodeTable)[threadIdx.x - 64u];
+    __syncthreads();
     if (DIRECT) {
-        if (threadIdx.x == 0) s_c = atomicAdd(ticket, 1u);
-        __syncthreads();
-        c = uniform_u32(s_c) * GROUPS + group;
+        link = uniform_u32(s_c);
+        c = link * GROUPS + group;
     }
     const bool alive = c < n_chunks;                    // of the last block's groups maybe the first alone
     const uint64_t base = (uint64_t)c * CODEC_CHUNK;
@@ -356,83 +403,65 @@ __global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void def
     }
     for (uint32_t k = tid; k < CODEC_OUT_DW / 4u; k += DEF_THREADS)
         reinterpret_cast<uint4*>(s_out)[k] = make_uint4(0, 0, 0, 0);
-    // --- first pass: literals, token bits, side information and marks
+    // --- first pass: literals, token bits, side information and the quarters.  FULL: a chunk of whole sub-chunks
+    auto first_pass = [&](auto FULL) {
+        constexpr bool full = decltype(FULL)::value;
 #pragma unroll
-    for (uint32_t i = 0; i < STEPS; ++i) {
-        const uint32_t sub = (i * (DEF_THREADS / 64u) + wid) * 2u + half;
-        const uint32_t n_l = min(CODEC_SUB, m - min(m, sub * CODEC_SUB));
-        const uint4 v = P[i].v;
-        uint32_t lit, nine = 0, end = 0;                // end: the sub-chunk's end, where it lies inside the piece
-        if (m == CODEC_CHUNK && __ballot((v.x | v.y | v.z | v.w) != 0u) == 0ull) {
-            // 1 KiB of zeros (common in sparse models): both sub-chunks are one run
-            if (hl == 0u) {
-                s_side[sub] = ZERO_SUB_BITS;
-                s_mark[sub] = ZERO_SUB_MARK;
+        for (uint32_t i = 0; i < STEPS; ++i) {
+            const uint32_t sub = (i * (DEF_THREADS / 64u) + wid) * 2u + half;
+            const uint32_t n_l = full ? CODEC_SUB : min(CODEC_SUB, m - min(m, sub * CODEC_SUB));
+            const uint4 v = P[i].v;
+            if (full && __ballot((v.x | v.y | v.z | v.w) != 0u) == 0ull) {
+                // 1 KiB of zeros (common in sparse models): both sub-chunks are one run
+                if (hl == 0u) s_side[sub] = ZERO_SUB_BITS;
+                if ((hl & 7u) == 0u) s_quarter[sub * CODEC_Q + (hl >> 3)] = ZERO_SUB_BITS | ((CODEC_SUB - p0) << 16);
+                zero_kib |= 1u << i;
+                continue;
             }
-            zero_kib |= 1u << i;
-            continue;
-        }
-        {
-            uint32_t s = changes16(v, __shfl_up(v.w >> 24, 1, 64));
+            uint32_t s = changes16(v, lane_below(v.w >> 24)), end = 0;   // end: the sub-chunk's end, where it lies inside the piece
             if (hl == 0u) s |= 1u;
-            nine = nines16(v);
-            // the end counts as a change
-            const uint32_t left = n_l > p0 ? n_l - p0 : 0u;
-            if (n_l >= p0 && left < 16u) end = 1u << left;
-            const uint32_t valid = left >= 16u ? 0xffffu : (1u << left) - 1u;
-            s = (s & valid) | end;
-            const uint32_t before = __shfl_up(s, 1, 32), after = __shfl_down(s, 1, 32);
-            // bits 2-17 the piece, two bits of the neighbours on either side
-            const uint32_t S = (hl ? before >> 14 : 0u) | (s << 2) | ((hl == 31u ? 1u : after & 3u) << 18);
-            const uint32_t Z = ~S & (hl ? ~0u : ~3u);
-            lit = ((S >> 2) | ((Z >> 2) & (((S >> 1) & (S >> 3)) | ((S >> 1) & (Z >> 3) & (S >> 4)) |
-                                           ((Z >> 1) & S & (S >> 3))))) & valid;
-        }
-        const uint64_t any = __ballot(lit != 0u);
-        const uint32_t later = (uint32_t)(any >> (32u * half)) & (hl == 31u ? 0u : ~0u << (hl + 1u));
-        const uint32_t first = lit ? p0 + (uint32_t)__ffs((int)lit) - 1u : 0u;
-        const uint32_t behind = __shfl(first, later ? (int)(32u * half + (uint32_t)__ffs((int)later) - 1u) : 0, 64);
-        const uint32_t next = later ? behind : n_l;     // first literal behind the piece
-        uint32_t bits = 8u * (uint32_t)__popc(lit) + (uint32_t)__popc(lit & nine);
-        {
-            const Runs r = find_runs(lit, end, next - p0);
-            // 12 bits a match, one more where none of the eleven bytes behind its literal ends the run
-            uint32_t e = r.ends | (r.ends >> 1);
-            e |= e >> 2;
-            e |= e >> 4;
-            e |= e >> 3;
-            bits += 12u * (uint32_t)__popc(r.near) + (uint32_t)__popc(r.near & ~(e >> 1));
-            if (r.far) {
-                uint32_t code;
-                bits += far_matches(r.far, &code);
+            const uint32_t nine = nines16(v);
+            uint32_t valid = 0xffffu;
+            if (!full) {
+                // the end counts as a change
+                const uint32_t left = n_l > p0 ? n_l - p0 : 0u;
+                if (n_l >= p0 && left < 16u) end = 1u << left;
+                valid = left >= 16u ? 0xffffu : (1u << left) - 1u;
+                s = (s & valid) | end;
             }
+            const uint32_t below = lane_below(s), above = lane_above(s);
+            // bits 2-17 the piece, two bits of the neighbours on either side
+            const uint32_t S = (hl ? below >> 14 : 0u) | (s << 2) | ((hl == 31u ? 1u : above & 3u) << 18);
+            const uint32_t Z = ~S & (hl ? ~0u : ~3u);
+            const uint32_t lit = ((S >> 2) | ((Z >> 2) & (((S >> 1) & (S >> 3)) | ((S >> 1) & (Z >> 3) & (S >> 4)) |
+                                                          ((Z >> 1) & S & (S >> 3))))) & valid;
+            const uint64_t any = __ballot(lit != 0u);
+            const uint32_t later = (uint32_t)(any >> (32u * half)) & (hl == 31u ? 0u : ~0u << (hl + 1u));
+            const uint32_t first = lit ? p0 + (uint32_t)__ffs((int)lit) - 1u : 0u;
+            const uint32_t behind = __shfl(first, later ? (int)(32u * half + (uint32_t)__ffs((int)later) - 1u) : 0, 64);
+            const uint32_t next = later ? behind : n_l;     // first literal behind the piece
+            uint32_t bits = 8u * (uint32_t)__popc(lit) + (uint32_t)__popc(lit & nine);
+            const Runs run = find_runs(lit, end, next - p0);
+            {
+                // 12 bits a match, one more where none of the eleven bytes behind its literal ends the run
+                uint32_t e = run.ends | (run.ends >> 1);
+                e |= e >> 2;
+                e |= e >> 4;
+                e |= e >> 3;
+                bits += 12u * (uint32_t)__popc(run.near) + (uint32_t)__popc(run.near & ~(e >> 1));
+                bits += s_codes.far_bits[run.far];       // [0] is 0
+            }
+            const uint32_t incl = incl_sum32(bits), before = incl - bits;
+            if (hl == 31u) s_side[sub] = n_l > 0u && incl > 8u * n_l + CODEC_MARGIN ? CODEC_STORED : incl;
+            // a quarter starts at every eighth lane
+            if ((hl & 7u) == 0u)
+                s_quarter[sub * CODEC_Q + (hl >> 3)] = before | (((lit ? first : next) - min(p0, n_l)) << 16);
+            P[i].lit = lit;
+            P[i].place = before | (next << 16);
+            P[i].runs = run.near | (run.far << 16);
         }
-        uint32_t incl = bits;
-        for (uint32_t d = 1; d < 32u; d <<= 1) {
-            const uint32_t y = __shfl_up(incl, d, 32);
-            if (hl >= d) incl += y;
-        }
-        const uint32_t before = incl - bits, total = __shfl(incl, 31, 32);
-        const bool stored = n_l > 0u && total > 8u * n_l + CODEC_MARGIN;
-        // a quarter starts at every eighth lane: the token bits before it and how far past its
-        // start its first literal lies
-        const uint32_t q_at = min(p0, n_l);
-        const uint32_t quarter = before | (((lit ? first : next) - q_at) << 16);
-        uint64_t mark = 0;
-        uint32_t b_prev = 0;
-#pragma unroll
-        for (uint32_t q = 1; q < CODEC_Q; ++q) {
-            const uint32_t x = __shfl(quarter, 8 * (int)q, 32), b_q = x & 0xffffu;
-            mark |= (uint64_t)((b_q - b_prev) | ((x >> 16) << 11)) << (20u * (q - 1u));
-            b_prev = b_q;
-        }
-        if (hl == 0u) {
-            s_side[sub] = stored ? CODEC_STORED : total;
-            s_mark[sub] = n_l > 0u && !stored ? mark : 0ull;
-        }
-        P[i].lit = lit | (nine << 16);
-        P[i].place = before | (next << 16);
-    }
+    };
+    if (m == CODEC_CHUNK) first_pass(std::true_type{}); else first_pass(std::false_type{});
     __syncthreads();
     // --- every wavefront places the sub-chunks for itself, lane = sub-chunk
     uint32_t start, tail_start;
@@ -442,69 +471,100 @@ __global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void def
                                             &tail_start, &tail_in_block);
     const bool whole = m + 5u <= coded_bytes;           // not shorter than one stored block
     const uint32_t seg_bytes = whole ? m + 5u : coded_bytes;
-    if (tid == 0 && alive) {
-        if (DIRECT) chain_store(status + c, chain_size(c, seg_bytes));
-        else seg_size[c] = seg_bytes;
+    if (DIRECT) {
+        // a block's chunks are one link of the chain
+        if (GROUPS > 1) {
+            if (tid == 0) g_size[group] = alive ? seg_bytes : 0u;
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) {
+            uint32_t size = seg_bytes;
+            if (GROUPS > 1) {
+                size = 0;
+                for (uint32_t g = 0; g < GROUPS; ++g) size += g_size[g];
+            }
+            chain_store(status + link, chain_size(link, size));
+        }
+    } else if (tid == 0 && alive) {
+        seg_size[c] = seg_bytes;
     }
     if (wid == 0u && alive) {
         side[(uint64_t)c * CODEC_NSUB + lane] = whole ? 0 : (uint16_t)side_l;
-        marks[(uint64_t)c * CODEC_NSUB + lane] = whole ? 0ull : s_mark[lane];
+        uint64_t mark = 0;
+        uint32_t b_prev = 0;
+#pragma unroll
+        for (uint32_t q = 1; q < CODEC_Q; ++q) {
+            const uint32_t x = s_quarter[lane * CODEC_Q + q], b_q = x & 0xffffu;
+            mark |= (uint64_t)((b_q - b_prev) | ((x >> 16) << 11)) << (20u * (q - 1u));
+            b_prev = b_q;
+        }
+        const bool coded = !whole && side_l != CODEC_STORED && lane * CODEC_SUB < m;
+        marks[(uint64_t)c * CODEC_NSUB + lane] = coded ? mark : 0ull;
     }
     // --- second pass: the segment
+    auto second_pass = [&](auto FULL) {
+        constexpr bool full = decltype(FULL)::value;
 #pragma unroll
-    for (uint32_t i = 0; i < STEPS; ++i) {
-        const uint32_t kib = i * (DEF_THREADS / 64u) + wid, sub = kib * 2u + half;
-        const uint32_t n_l = min(CODEC_SUB, m - min(m, sub * CODEC_SUB));
-        const uint32_t left = min(16u, n_l > p0 ? n_l - p0 : 0u);
-        const uint32_t st = __shfl(start, (int)sub, 64);
-        const bool open = __shfl(in_block ? 1u : 0u, (int)sub, 64) != 0u;
-        const uint32_t sd = __shfl(side_l, (int)sub, 64);
-        const uint4 v = P[i].v;
-        if (whole || sd == CODEC_STORED) {
-            // bytes as they are: behind the header of the one block, or of the sub-chunk's own
-            uint32_t data_bit = 40u + 8u * (sub * CODEC_SUB);
-            if (!whole) {
-                const uint32_t at = st + (open ? 10u : 3u);
-                data_bit = ((at + 7u) & ~7u) + 32u;
-                if (hl == 0u && n_l > 0u) {
+        for (uint32_t i = 0; i < STEPS; ++i) {
+            const uint32_t kib = i * (DEF_THREADS / 64u) + wid, sub = kib * 2u + half;
+            const uint32_t n_l = full ? CODEC_SUB : min(CODEC_SUB, m - min(m, sub * CODEC_SUB));
+            const uint32_t left = full ? 16u : min(16u, n_l > p0 ? n_l - p0 : 0u);
+            // two sub-chunks a wavefront: what concerns them comes by scalar reads
+            auto of_sub = [&](uint32_t x) {
+                const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)x, (int)(2u * kib));
+                const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)x, (int)(2u * kib + 1u));
+                return half ? b : a;
+            };
+            const uint32_t st = of_sub(start), sd = of_sub(side_l);
+            const bool open = of_sub(in_block ? 1u : 0u) != 0u;
+            const uint4 v = P[i].v;
+            if (whole || sd == CODEC_STORED) {
+                // bytes as they are: behind the header of the one block, or of the sub-chunk's own
+                uint32_t data_bit = 40u + 8u * (sub * CODEC_SUB);
+                if (!whole) {
+                    const uint32_t at = st + (open ? 10u : 3u);
+                    data_bit = ((at + 7u) & ~7u) + 32u;
+                    if (hl == 0u && n_l > 0u) {
+                        BitWriter w(s_out, st);
+                        if (open) w.put(0u, 7u);              // end of the open block
+                        w.put(0u, 3u);                        // BFINAL = 0, BTYPE = 00
+                        w.put(0u, (8u - (at & 7u)) & 7u);
+                        w.put(n_l, 16u);
+                        w.put(n_l ^ 0xffffu, 16u);
+                        w.finish();
+                    }
+                }
+                if (left) {                                   // bytes past the end are zero and change nothing
+                    const uint32_t at = data_bit + 8u * p0, sh = at & 31u;
+                    uint32_t* o = &s_out[at >> 5];
+                    auto high = [&](uint32_t hi, uint32_t lo) { return (uint32_t)((((uint64_t)hi << 32 | lo) << sh) >> 32); };
+                    atomicOr(&o[0], v.x << sh);
+                    atomicOr(&o[1], high(v.y, v.x));
+                    atomicOr(&o[2], high(v.z, v.y));
+                    atomicOr(&o[3], high(v.w, v.z));
+                    if (sh) atomicOr(&o[4], high(0u, v.w));
+                }
+            } else if ((zero_kib >> i) & 1u) {
+                if (hl == 0u) {
                     BitWriter w(s_out, st);
-                    if (open) w.put(0u, 7u);              // end of the open block
-                    w.put(0u, 3u);                        // BFINAL = 0, BTYPE = 00
-                    w.put(0u, (8u - (at & 7u)) & 7u);
-                    w.put(n_l, 16u);
-                    w.put(n_l ^ 0xffffu, 16u);
+                    if (!open) w.put(2u, 3u);                     // BFINAL = 0, BTYPE = 01
+                    w.put(ZERO_SUB_LOW, 21u);
+                    w.put(ZERO_SUB_HIGH, ZERO_SUB_BITS - 21u);
                     w.finish();
                 }
-            }
-            if (left) {                                   // bytes past the end are zero and change nothing
-                const uint32_t at = data_bit + 8u * p0, sh = at & 31u;
-                uint32_t* o = &s_out[at >> 5];
-                auto high = [&](uint32_t hi, uint32_t lo) { return (uint32_t)((((uint64_t)hi << 32 | lo) << sh) >> 32); };
-                atomicOr(&o[0], v.x << sh);
-                atomicOr(&o[1], high(v.y, v.x));
-                atomicOr(&o[2], high(v.z, v.y));
-                atomicOr(&o[3], high(v.w, v.z));
-                if (sh) atomicOr(&o[4], high(0u, v.w));
-            }
-        } else if ((zero_kib >> i) & 1u) {
-            if (hl == 0u) {
-                BitWriter w(s_out, st);
-                if (!open) w.put(2u, 3u);                     // BFINAL = 0, BTYPE = 01
-                w.put(ZERO_SUB_LOW, 21u);
-                w.put(ZERO_SUB_HIGH, ZERO_SUB_BITS - 21u);
-                w.finish();
-            }
-        } else {
-            const uint32_t lit = P[i].lit & 0xffffu, next = P[i].place >> 16;
-            if (lit) {
-                const uint32_t end = n_l >= p0 && n_l - p0 < 16u ? 1u << (n_l - p0) : 0u;
-                if (hl == 0u && !open) atomicOr(&s_out[st >> 5], 2u << (st & 31u));       // BFINAL = 0, BTYPE = 01 ...
-                if (hl == 0u && !open && (st & 31u) == 31u) atomicOr(&s_out[(st >> 5) + 1u], 1u);
-                emit_tokens(s_out, st + (open ? 0u : 3u) + (P[i].place & 0xffffu), v, lit, P[i].lit >> 16,
-                            find_runs(lit, end, next - p0));
+            } else {
+                const uint32_t lit = P[i].lit, next = (P[i].place >> 16) - p0;
+                if (lit) {
+                    const uint32_t end = !full && n_l >= p0 && n_l - p0 < 16u ? 1u << (n_l - p0) : 0u;
+                    if (hl == 0u && !open) atomicOr(&s_out[st >> 5], 2u << (st & 31u));       // BFINAL = 0, BTYPE = 01 ...
+                    if (hl == 0u && !open && (st & 31u) == 31u) atomicOr(&s_out[(st >> 5) + 1u], 1u);
+                    emit_tokens(s_codes, s_out, st + (open ? 0u : 3u) + (P[i].place & 0xffffu), v, lit,
+                                lit | end | (next < 32u ? 1u << next : 0u), P[i].runs & 0xffffu, P[i].runs >> 16);
+                }
             }
         }
-    }
+    };
+    if (m == CODEC_CHUNK) second_pass(std::true_type{}); else second_pass(std::false_type{});
     if (tid == DEF_THREADS - 1u) {
         if (whole) {
             BitWriter w(s_out, 0);
@@ -525,13 +585,19 @@ __global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void def
     }
     uint8_t* dst = slots + (uint64_t)c * CODEC_SLOT;
     if (DIRECT) {
-        if (wid == 0u && alive) {
-            const ChainWalk walk = chain_before(status, c, lane);
+        if (threadIdx.x < 64u) {
+            const ChainWalk walk = chain_before(status, link, lane);
             if (lane == 0u) {
-                chain_leave(walk, c, last != 0u, seg_bytes, status + c, mirror, chain_store);
-                g_off[group] = walk.broken ? ~0ull : walk.sum;
-                seg_off[c] = walk.sum;
-                if (last) seg_off[n_chunks] = walk.sum + seg_bytes;
+                uint64_t end = walk.sum;
+                for (uint32_t g = 0; g < GROUPS; ++g) {
+                    const uint32_t size = GROUPS > 1 ? g_size[g] : seg_bytes;
+                    if (c + g < n_chunks) seg_off[c + g] = end;         // c: the first group's
+                    g_off[g] = walk.broken ? ~0ull : end;
+                    end += size;
+                }
+                const bool ends = c + GROUPS >= n_chunks;
+                if (ends) seg_off[n_chunks] = end;
+                chain_leave(walk, link, ends, end - walk.sum, status + link, mirror, chain_store);
             }
         }
         __syncthreads();
@@ -1099,8 +1165,8 @@ static void codec_end(shifter_ctx* ctx) {
 
 // Up to this many chunks, three to each of 256 compute units, a block takes one chunk, beyond it two: they
 // wait for each other at the barriers, which a chip that is not full notices, and share a ticket.  us a
-// call, one / two: 4 chunks 28 / 35, 256 32 / 37, 640 54 / 57 (zeros 33 / 28), 769 62 / 58 (35 / 30), 1024 69 / 63
-// (41 / 33), 4096 164 / 158 (82 / 61), 39347 1196 / 1196 (540 / 408).
+// call, one / two, 30 % of the weights not zero (none): 4 chunks 27 / 33, 256 32 / 35 (25 / 24), 640 47 / 51 (33 / 30), 769
+// 52 / 53 (35 / 32), 1024 60 / 56 (40 / 34), 4096 123 / 127 (85 / 66), 39347 864 / 929 (539 / 420).
 constexpr uint32_t DEFLATE_ONE_EACH = 768;
 
 // Room for chunk lists, kept by the context and grown when a longer input comes.
