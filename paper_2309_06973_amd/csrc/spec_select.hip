@@ -30,6 +30,10 @@ constexpr uint32_t FBINS1 = 256;        // round-1 finishing histogram: one bin 
 constexpr uint32_t FHIST_COPIES = 4;    // of it in global memory: blocks that meet at one bin take their turns
 constexpr uint32_t FBINS = 4096;        // round-2 finishing histogram (one block, LDS)
 constexpr uint32_t FIN_BLOCKS = SPEC_FIN_BLOCKS;  // blocks of the passes over candidates
+// The last one: few blocks, because all draw a ticket of one address at its end (14 ns each), wide ones, because
+// the block that ends last ranks alone; each takes up to FIN_SUBS sub-buffers.
+constexpr uint32_t FIN_THREADS = 1024, FIN_SUBS = 4, FIN_AHEAD = 2;
+static_assert(FIN_AHEAD * FIN_THREADS <= 2 * TILE, "a sub-buffer's least capacity");
 
 // Global atomics to one address serialise (about 11 ns each on this chip), so every
 // counter that all blocks touch is split into SPEC_SUB copies, one 128-byte line each,
@@ -321,27 +325,43 @@ __global__ __launch_bounds__(BLOCK) void spec_hist_kernel(const SpecState* __res
 // on the stream.
 // What bounds it is the chain of latencies, so the counters, the histogram and the first
 // candidates are all loaded before the first of them is used, and the ranking costs no launch of
-// its own (filter + rank of one count of 77 M weights 10.0 + 6.0 us, 13.7 as one).
-__global__ __launch_bounds__(BLOCK) void spec_finish_kernel(
+// its own (filter + rank of one count of 77 M weights 10.0 + 6.0 us, 13.7 as one).  With 64 blocks of 1024 threads, not 256
+// of 256: 322 M weights 20.0 -> 13.1, 37 M 14.3 -> 11.8, 24 k 13.3 -> 12.4.
+__global__ __launch_bounds__(FIN_THREADS) void spec_finish_kernel(
     SpecState* ss, const uint32_t* __restrict__ cnt, const uint32_t* __restrict__ hist,
-    const uint2* __restrict__ cand, uint32_t cap_sb, uint2* list, shifter_threshold* thr, SpecState* host_mirror) {
-    constexpr uint32_t STAGE = 2048, WAVES = BLOCK / 64;
-    __shared__ uint2 stage[STAGE];
+    const uint2* __restrict__ cand, uint32_t cap_sb, uint32_t n_sub, uint2* list, shifter_threshold* thr,
+    SpecState* host_mirror) {
+    constexpr uint32_t STAGE = 2048, WAVES = BLOCK / 64;       // of the wavefronts that add up the counters
+    __shared__ uint2 stage[STAGE * FIN_SUBS];
     __shared__ uint32_t h[FBINS];
     __shared__ uint64_t comp[SPEC_SMALL_CAP];
-    __shared__ uint64_t smem[WAVES + 1];
+    __shared__ uint64_t smem[FIN_THREADS / 64 + 1];
     __shared__ uint64_t s_sel, s_less2, s_r3;
     __shared__ uint32_t s_below[WAVES], s_inside[WAVES], s_hist[WAVES], s_over[WAVES];
-    __shared__ uint32_t s_n, s_base, s_bin, s_cnt1, s_last, s_status;
+    __shared__ uint32_t s_n, s_base, s_bin, s_cnt1, s_last, s_status, s_sub[FIN_SUBS];
     __shared__ uint64_t s_r2, s_less;
     __shared__ uint32_t s_lt, s_eq, s_bin2, s_cnt2, s_nb;
     const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
     static_assert(SPEC_SUB == BLOCK && FBINS1 == BLOCK, "one split counter and one round-1 bin per thread");
-    const uint32_t n_cand = cnt[(CNT_CAND * SPEC_SUB + threadIdx.x) * 32u];
-    const uint32_t n_less = cnt[(CNT_BELOW * SPEC_SUB + threadIdx.x) * 32u];
-    uint32_t in_bin = 0;
+    // the first candidates of the block's sub-buffers, on their way while the P-th pair is located (a sub-buffer has
+    // room for more than these, whatever it holds)
+    uint2 ahead0[FIN_SUBS], ahead1[FIN_SUBS];
+    uint32_t n_of[FIN_SUBS];
 #pragma unroll
-    for (uint32_t i = 0; i < FHIST_COPIES; ++i) in_bin += hist[i * FBINS1 + threadIdx.x];
+    for (uint32_t i = 0; i < FIN_SUBS; ++i) {
+        const uint32_t sub = min(blockIdx.x + i * gridDim.x, n_sub - 1u);
+        n_of[i] = min(cnt[(CNT_CAND * SPEC_SUB + sub) * 32u], cap_sb);
+        ahead0[i] = cand[(size_t)sub * cap_sb + threadIdx.x];
+        ahead1[i] = cand[(size_t)sub * cap_sb + FIN_THREADS + threadIdx.x];
+    }
+    const bool counts = threadIdx.x < BLOCK;
+    uint32_t n_cand = 0, n_less = 0, in_bin = 0;
+    if (counts) {
+        n_cand = cnt[(CNT_CAND * SPEC_SUB + threadIdx.x) * 32u];
+        n_less = cnt[(CNT_BELOW * SPEC_SUB + threadIdx.x) * 32u];
+#pragma unroll
+        for (uint32_t i = 0; i < FHIST_COPIES; ++i) in_bin += hist[i * FBINS1 + threadIdx.x];
+    }
     const uint64_t p = ss->p;
     const uint32_t lo = ss->lo, sh = ss->sh;
     shifter_threshold out;                 // nothing removed
@@ -355,6 +375,7 @@ __global__ __launch_bounds__(BLOCK) void spec_finish_kernel(
         }
         return;
     }
+    if (threadIdx.x < FIN_SUBS) s_sub[threadIdx.x] = 0;
     if (threadIdx.x == 0) {
         s_n = 0; s_bin = 0xffffffffu;
         s_lt = 0; s_eq = 0; s_sel = 0; s_nb = 0; s_cnt2 = 0; s_bin2 = 0;
@@ -365,7 +386,7 @@ __global__ __launch_bounds__(BLOCK) void spec_finish_kernel(
         if (lane >= d) { incl += y; sum_c += yc; sum_b += yb; }
     }
     const bool over = __ballot(n_cand > cap_sb) != 0ull;
-    if (lane == 63) { s_below[wid] = sum_b; s_inside[wid] = sum_c; s_hist[wid] = incl; s_over[wid] = over; }
+    if (lane == 63 && counts) { s_below[wid] = sum_b; s_inside[wid] = sum_c; s_hist[wid] = incl; s_over[wid] = over; }
     __syncthreads();
     uint64_t below = 0, inside = 0, base = incl - in_bin;
     bool any_over = false;
@@ -377,7 +398,7 @@ __global__ __launch_bounds__(BLOCK) void spec_finish_kernel(
         any_over = any_over || s_over[i] != 0;
     }
     const bool reached = !any_over && below < p && p <= below + inside;
-    if (reached) {
+    if (reached && counts) {
         const uint64_t r = p - below;
         if (base < r && r <= base + in_bin) {
             s_bin = threadIdx.x;
@@ -407,21 +428,35 @@ __global__ __launch_bounds__(BLOCK) void spec_finish_kernel(
         if (blockIdx.x == 0 && threadIdx.x == 0) publish(false);
         return;
     }
-    for_each_candidate(cnt, cand, cap_sb, [&](uint2 c, bool valid) {
-        if (valid && (((c.x & 0x7fffffffu) - lo) >> sh) == bin) {
-            const uint32_t pos = atomicAdd(&s_n, 1u);
-            if (pos < STAGE) stage[pos] = c;
-        }
-    });
-    __syncthreads();
     {
+        auto take = [&](uint2 c, uint32_t i) {
+            if ((((c.x & 0x7fffffffu) - lo) >> sh) == bin) {
+                const uint32_t pos = atomicAdd(&s_n, 1u);
+                atomicAdd(&s_sub[i], 1u);
+                if (pos < STAGE * FIN_SUBS) stage[pos] = c;
+            }
+        };
+#pragma unroll
+        for (uint32_t i = 0; i < FIN_SUBS; ++i) {
+            const uint32_t sub = blockIdx.x + i * gridDim.x;
+            if (sub < n_sub) {
+                if (threadIdx.x < n_of[i]) take(ahead0[i], i);
+                if (FIN_THREADS + threadIdx.x < n_of[i]) take(ahead1[i], i);
+                for (uint32_t j = FIN_AHEAD * FIN_THREADS + threadIdx.x; j < n_of[i]; j += FIN_THREADS)
+                    take(cand[(size_t)sub * cap_sb + j], i);
+            }
+        }
+        __syncthreads();
         const uint32_t n = s_n;
-        if (n > STAGE) {         // far more ties than the stage holds: leave it to the multi-pass select
+        bool over = false;
+#pragma unroll
+        for (uint32_t i = 0; i < FIN_SUBS; ++i) over = over || s_sub[i] > STAGE;
+        if (over) {              // far more ties than the stage holds: leave it to the multi-pass select
             if (threadIdx.x == 0) atomicOr(&ss->status, 1u);
         } else if (n != 0) {
             if (threadIdx.x == 0) s_base = atomicAdd(&ss->list_cnt, n);
             __syncthreads();
-            for (uint32_t i = threadIdx.x; i < n; i += BLOCK)
+            for (uint32_t i = threadIdx.x; i < n; i += FIN_THREADS)
                 if (s_base + i < SPEC_LIST_CAP) store_device(&list[s_base + i], stage[i]);
         }
     }
@@ -431,7 +466,7 @@ __global__ __launch_bounds__(BLOCK) void spec_finish_kernel(
         s_n = atomicAdd(&ss->list_cnt, 0u);
         s_status = atomicOr(&ss->status, 0u);
     }
-    for (uint32_t i = threadIdx.x; i < FBINS; i += BLOCK) h[i] = 0;
+    for (uint32_t i = threadIdx.x; i < FBINS; i += FIN_THREADS) h[i] = 0;
     __syncthreads();
     const uint32_t n = s_n;
     // the second cannot happen unless the buffers were disturbed
@@ -440,24 +475,24 @@ __global__ __launch_bounds__(BLOCK) void spec_finish_kernel(
         return;
     }
     // a list that fits stays in LDS
-    const bool staged = n <= STAGE;
+    const bool staged = n <= STAGE * FIN_SUBS;
     if (staged) {
-        for (uint32_t i = threadIdx.x; i < n; i += BLOCK) stage[i] = load_device(&list[i]);
+        for (uint32_t i = threadIdx.x; i < n; i += FIN_THREADS) stage[i] = load_device(&list[i]);
         __syncthreads();
     }
     auto walk = [&](auto&& f) {
-        for (uint32_t i = threadIdx.x; i < n; i += BLOCK) f(staged ? stage[i] : load_device(&list[i]));
+        for (uint32_t i = threadIdx.x; i < n; i += FIN_THREADS) f(staged ? stage[i] : load_device(&list[i]));
     };
     // round 2: the list's keys span 2^sh values starting at lo + (bin << sh)
     const uint32_t sh2 = sh > 12 ? sh - 12 : 0;   // 2^sh keys over FBINS = 2^12 bins
     const uint32_t lo1 = lo + (bin << sh);
     walk([&](uint2 c) { lds_count(h, ((c.x & 0x7fffffffu) - lo1) >> sh2, true); });
     __syncthreads();
-    constexpr uint32_t PER = FBINS / BLOCK;
+    constexpr uint32_t PER = FBINS / FIN_THREADS;
     const uint32_t b0 = threadIdx.x * PER;
     uint64_t sum = 0, tot;
     for (uint32_t i = 0; i < PER; ++i) sum += h[b0 + i];
-    base = block_excl_scan_u64(sum, smem, &tot);
+    base = block_excl_scan_u64<FIN_THREADS>(sum, smem, &tot);
     const uint64_t r = s_r2;
     if (base < r && r <= base + sum) {
         for (uint32_t i = 0; i < PER; ++i) {
@@ -487,7 +522,7 @@ __global__ __launch_bounds__(BLOCK) void spec_finish_kernel(
     });
     __syncthreads();
     const uint64_t want = s_r3 - 1;   // 0-based rank inside the bin
-    for (uint32_t i = threadIdx.x; i < cnt2; i += BLOCK) {
+    for (uint32_t i = threadIdx.x; i < cnt2; i += FIN_THREADS) {
         const uint64_t c = comp[i];
         uint32_t rank = 0;
         for (uint32_t f = 0; f < cnt2; ++f) rank += comp[f] < c;
@@ -497,7 +532,7 @@ __global__ __launch_bounds__(BLOCK) void spec_finish_kernel(
     const uint64_t sel = s_sel;
     const uint32_t key = (uint32_t)(sel >> 32);
     uint32_t lt = 0, eq = 0;
-    for (uint32_t i = threadIdx.x; i < cnt2; i += BLOCK) {
+    for (uint32_t i = threadIdx.x; i < cnt2; i += FIN_THREADS) {
         const uint32_t k = (uint32_t)(comp[i] >> 32);
         lt += k < key;
         eq += k == key;
@@ -590,7 +625,8 @@ void launch_spec_select(shifter_ctx* ctx, const shifter_model* m, const float* d
     }
     {
         ProfileScope ps(ctx, K_SPEC_FINISH2);
-        spec_finish_kernel<<<FIN_BLOCKS, BLOCK, 0, s>>>(b.spec, b.spec_cnt, b.partial, b.cand, b.cand_cap_sb, b.list,
+        const uint32_t n_sub = std::min(SPEC_SUB, std::max(1u, m->n_tiles));      // sub-buffers that can hold anything
+        spec_finish_kernel<<<std::min(n_sub, SPEC_SUB / FIN_SUBS), FIN_THREADS, 0, s>>>(b.spec, b.spec_cnt, b.partial, b.cand, b.cand_cap_sb, n_sub, b.list,
                                                         d_thr, host_mirror);
     }
     if (fused) {
