@@ -18,6 +18,7 @@ constexpr uint32_t MAXK = SHIFTER_MAX_VARIANTS;
 constexpr uint32_t GATHER_CHUNK = 1024;  // columns of a gather work unit (16 per lane)
 constexpr uint32_t GATHER_ROWS = 16;
 constexpr uint32_t SAMPLE_BINS = 16384;  // of the sample histogram (sample_bin)
+constexpr uint32_t PLAN_TICKET = 32;     // words of a variant's planning ticket: a line of its own
 constexpr uint32_t RECT_ELEMS = 8192;    // floats of a source rectangle staged in LDS by the portfolio rebuild
 
 // Device-side view of one weight tensor.
@@ -231,6 +232,7 @@ struct shifter_model {
         shifter::PlanTensor* plan_t = nullptr;
         shifter::PlanVec* plan_v = nullptr;
         shifter::PlanHeader* plan_h = nullptr;
+        uint32_t* plan_ticket = nullptr;      // MAXK * PLAN_TICKET: groups planned per variant
         uint32_t* out_tile_prefix = nullptr;  // MAXK * (n_tensors + 1)
         uint32_t* rect_prefix = nullptr;      // n_tensors + 1 each
         uint32_t* rowtab_prefix = nullptr;

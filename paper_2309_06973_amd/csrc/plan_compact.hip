@@ -70,7 +70,8 @@ __device__ __forceinline__ void propagate_group(
     }
     for (uint32_t c = base + threadIdx.x; c < G.width; c += PROP_THREADS) keep[G.off + c] = 0xffffffffu;
     if (threadIdx.x == 0) {
-        *new_width_g = base;
+        // at device scope: the block that ends last may read it in the same launch (plan_all_kernel)
+        __hip_atomic_store(new_width_g, base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (below) below[G.width] = base;
     }
 }
@@ -113,13 +114,13 @@ __host__ __device__ __forceinline__ uint32_t gather_unit_rows(uint32_t lg) {
 // side (rows padded to a power of two, at least 64).  Every unit is four row steps deep.
 // The records also go, packed per variant (header, tensors, vectors), to a mirror in
 // pinned host memory, so that the host reads a plan without a copy on the stream.
-template <uint32_t THREADS>
+// width(group): the variant's new widths.
+template <uint32_t THREADS, typename Width>
 __device__ __forceinline__ void plan_variant(
     uint32_t k, const DevTensor* __restrict__ tens, uint32_t n_t, const DevVec* __restrict__ vecs,
-    uint32_t n_v, uint32_t n_g, const uint32_t* new_width, uint64_t cap_w, uint64_t cap_v,
+    uint32_t n_v, uint32_t n_g, Width&& width, uint64_t cap_w, uint64_t cap_v,
     PlanTensor* __restrict__ pt, PlanVec* __restrict__ pv, uint32_t* __restrict__ oup,
     PlanHeader* __restrict__ hdr, uint8_t* __restrict__ pack, uint64_t* smem, uint32_t* s_collapse) {
-    new_width += k * n_g;
     pt += k * n_t;
     pv += k * n_v;
     oup += k * (n_t + 1);
@@ -137,8 +138,8 @@ __device__ __forceinline__ void plan_variant(
         p.rb = GATHER_ROWS;
         uint32_t my_units = 0;
         if (t < n_t) {
-            p.o2 = new_width[tens[t].out_group];
-            p.c2 = new_width[tens[t].in_group];
+            p.o2 = width(tens[t].out_group);
+            p.c2 = width(tens[t].in_group);
             p.row2 = p.c2 * tens[t].kk;
             p.numel2 = p.o2 * p.row2;
             if (p.numel2) {
@@ -162,7 +163,7 @@ __device__ __forceinline__ void plan_variant(
     for (uint32_t v0 = 0; v0 < n_v; v0 += THREADS) {
         const uint32_t v = v0 + threadIdx.x;
         PlanVec p;
-        p.len2 = v < n_v ? new_width[vecs[v].group] : 0;
+        p.len2 = v < n_v ? width(vecs[v].group) : 0;
         p.pad = 0;
         p.out_off = voff + block_excl_scan_u64<THREADS>(p.len2, smem, &tot);
         voff += tot;
@@ -173,7 +174,7 @@ __device__ __forceinline__ void plan_variant(
     }
     __syncthreads();
     for (uint32_t g = threadIdx.x; g < n_g; g += THREADS)
-        if (new_width[g] == 0) *s_collapse = 1;
+        if (width((int32_t)g) == 0) *s_collapse = 1;
     __syncthreads();
     if (threadIdx.x == 0) {
         const uint32_t status = ((off > cap_w || voff > cap_v) ? 1u : 0u) | (*s_collapse ? 2u : 0u);
@@ -198,8 +199,9 @@ __global__ __launch_bounds__(BLOCK) void plan_kernel(
     __shared__ uint32_t s_collapse;
     (void)groups;
     // blockIdx.x = variant of a batch
-    plan_variant<BLOCK>(blockIdx.x, tens, n_t, vecs, n_v, n_g, new_width, cap_w, cap_v, pt, pv, oup, hdr,
-                        pack, smem, &s_collapse);
+    new_width += blockIdx.x * n_g;
+    plan_variant<BLOCK>(blockIdx.x, tens, n_t, vecs, n_v, n_g, [&](int32_t g) { return new_width[g]; }, cap_w, cap_v, pt,
+                        pv, oup, hdr, pack, smem, &s_collapse);
 }
 
 // x / d for any 32-bit x with the (magic, shift) pair the host derived from d >= 2.
@@ -403,10 +405,11 @@ __global__ __launch_bounds__(BLOCK) void rect_tables_kernel(
 // 0 .. n_groups - 1 each plan one group and, for the portfolio rebuild, fill the row and
 // column tables of the tensors around it.  With levels as the source of liveness the blocks
 // from n_groups on expand them into the variant's flag bytes (the outputs of the batched
-// mask pass, which nothing in this launch reads).  The rebuild plans, which need every
-// group's new width, follow in plan_kernel: a rendezvous inside this launch (the last
-// block of a variant going on after a device-wide fence) was measured at 250 us - such a
-// fence writes back the whole L2 of the block's XCD, just filled by the mask pass.
+// mask pass, which nothing in this launch reads).  The rebuild plan of a variant, which needs every
+// group's new width, is made by that of its group blocks which ends last: widths and tickets go past the L2, so
+// that no block has to write its XCD's back (with a device-wide fence 250 us).  Against a launch of its
+// own (kernels, us): one variant of 24 k weights 3.4 + 3.5 and 7.3, fifteen of 0.86 M 6.8 + 5.6 and 11.4, eight of 10 M
+// 5.1 + 4.8 and 8.8, twenty of 25.5 M 13.9 + 6.1 and 18.3, less a launch and its gap each: the steps are 3 to 7 us shorter.
 struct PlanAllArgs {
     const DevGroup* groups; const uint32_t* producers; const DevTensor* tens; uint32_t n_t;
     const DevVec* vecs; uint32_t n_v; uint32_t n_groups;
@@ -422,12 +425,17 @@ struct PlanAllArgs {
     uint32_t want_tables;
     uint32_t* below;                   // scratch: per variant and group, width + 1 counts of survivors below a channel
     const uint32_t* cons_prefix; const uint32_t* consumers;
-    uint32_t k_var;
+    uint64_t cap_w, cap_v;
+    PlanTensor* pt; PlanVec* pv; uint32_t* oup; PlanHeader* hdr; uint8_t* pack;
+    uint32_t* ticket;                  // PLAN_TICKET words for each variant, zero before and after
 };
+static_assert(PROP_THREADS >= BLOCK, "plan_variant's shared memory");
 
 __global__ __launch_bounds__(PROP_THREADS) void plan_all_kernel(const PlanAllArgs A) {
     __shared__ uint32_t wave_cnt[PROP_THREADS / 64];
     __shared__ uint32_t s_flag_off[PROP_LDS_PRODUCERS];
+    __shared__ uint64_t smem[PROP_THREADS / 64 + 1];
+    __shared__ uint32_t s_collapse, s_last;
     const uint32_t k = blockIdx.y;
     const uint32_t pos = A.pos.v[k];
     if (blockIdx.x >= A.n_groups) {
@@ -470,6 +478,14 @@ __global__ __launch_bounds__(PROP_THREADS) void plan_all_kernel(const PlanAllArg
             for (uint32_t j = (wid % share) * 64u + lane; j < n_e; j += share * 64u) tab[j] = below[min(j * step, limit)];
         }
     }
+    uint32_t* ticket = A.ticket + k * PLAN_TICKET;
+    if (!last_block(ticket, A.n_groups, &s_last)) return;
+    const uint32_t* widths = A.new_width + k * A.n_groups;
+    plan_variant<PROP_THREADS>(
+        k, A.tens, A.n_t, A.vecs, A.n_v, A.n_groups,
+        [&](int32_t g) { return __hip_atomic_load(widths + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }, A.cap_w, A.cap_v,
+        A.pt, A.pv, A.oup, A.hdr, A.pack, smem, &s_collapse);
+    if (threadIdx.x == 0) *ticket = 0;
 }
 
 // Position of column c of a staged rectangle row in LDS: within each group of 128
@@ -880,18 +896,14 @@ void launch_plan_and_gather(shifter_ctx* ctx, const shifter_model* m, const Port
     A.rowtab_prefix = b.rowtab_prefix; A.coltab_prefix = b.coltab_prefix; A.rowtab = b.rowtab;
     A.coltab = b.coltab; A.want_tables = rect ? 1u : 0u;
     A.below = b.below; A.cons_prefix = b.cons_prefix; A.consumers = b.consumers;
-    A.k_var = a.k_var;
+    A.cap_w = a.cap_w; A.cap_v = a.cap_v;
+    A.pt = b.plan_t; A.pv = b.plan_v; A.oup = b.out_tile_prefix; A.hdr = b.plan_h; A.pack = b.dev_plan;
+    A.ticket = b.plan_ticket;
     const uint64_t mx = std::max<uint64_t>(n_out > n_in ? n_out : n_in, 1);
     const uint32_t expand_blocks = from_levels ? (uint32_t)((mx + PROP_THREADS - 1) / PROP_THREADS) : 0u;
     {
         ProfileScope p(ctx, K_PROPAGATE);
         plan_all_kernel<<<dim3(n_g + expand_blocks, a.k_var), PROP_THREADS, 0, ctx->stream>>>(A);
-    }
-    {
-        ProfileScope p(ctx, K_PLAN);
-        plan_kernel<<<a.k_var, BLOCK, 0, ctx->stream>>>(b.tens, n_t, b.vecs, n_v, b.groups, n_g, a.d_new_width,
-                                                        a.cap_w, a.cap_v, b.plan_t, b.plan_v,
-                                                        b.out_tile_prefix, b.plan_h, b.dev_plan);
     }
     const bool dense_src = rebuild_reads_dense(m, a);
     launch_gather(ctx, m, dense_src ? a.d_w : a.d_w_sparse, dense_src ? 0 : a.w_stride, a.d_vecs, a.d_keep,
