@@ -1024,6 +1024,8 @@ __device__ __forceinline__ void inflate_chunk(
             // on the way: a store wraps inside its sub-chunk's row of the image, offsets only
             // grow, and the end must come out exactly right.
             while (pos < end) {
+                // the window's next dword, on its way while the tokens are looked up
+                const uint32_t w_new = s_seg[min(nextw, SEG_DW - 1u)];
                 const uint32_t x = __builtin_amdgcn_alignbit(w_hi, w_lo, sh_bits);
                 const uint32_t t = sh.tab[x & 511u];
                 const uint32_t nb = t & 31u;
@@ -1063,7 +1065,6 @@ __device__ __forceinline__ void inflate_chunk(
                 i += two ? 1u : 0u;
                 pos += used;
                 sh_bits += used;
-                const uint32_t w_new = s_seg[min(nextw, SEG_DW - 1u)];
                 const bool take = sh_bits >= 32u;
                 w_lo = take ? w_hi : w_lo;
                 w_hi = take ? w_new : w_hi;
