@@ -146,7 +146,7 @@ static void unbind(shifter_model* m) {
                     b.ghist, b.plan_t, b.plan_v, b.plan_h, b.plan_ticket,
                     b.out_tile_prefix, b.rect_prefix, b.rowtab_prefix, b.coltab_prefix, b.rowtab,
                     b.coltab, b.kernel_off, b.fix_prefix, b.cons_prefix, b.consumers, b.fix_alive,
-                    b.fix_produced, b.fix_read, b.fix_out_flags, b.fix_removed, b.fold,
+                    b.fix_produced, b.fix_read, b.fix_removed, b.fold,
                     b.fold_scale, b.levels, b.spec, b.shist, b.spec_cnt, b.partial, b.cand, b.list,
                     b.ranked_ids, b.multi, b.multi_cnt, b.multi_tab, b.below, b.multi_hist,
                     b.multi_list, b.multi_list_cnt, b.multi_rowsum};
@@ -495,7 +495,6 @@ static int bind_tables(shifter_ctx* ctx, shifter_model* m) {
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.fix_alive), std::max<uint64_t>(m->info.sum_group_width, 16)));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.fix_produced), std::max<uint64_t>(m->info.sum_out_ch, 16)));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.fix_read), std::max<uint64_t>(m->info.sum_in_ch, 16)));
-    HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.fix_out_flags), std::max<uint64_t>(m->info.sum_out_ch, 16)));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.fix_removed), sizeof(uint32_t) * FIX_STATE_WORDS));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.fold), sizeof(FoldTensor) * std::max<size_t>(n_t, 1)));
     HIP_TRY(ctx, hipMalloc(reinterpret_cast<void**>(&b.fold_scale),
@@ -1129,10 +1128,10 @@ extern "C" int shifter_propagate_groups_fixpoint(shifter_ctx* ctx, const shifter
     const volatile uint32_t* st = b.host_width;
     const size_t n_g = model->g.size();
     for (uint32_t batch = 0;; ++batch) {
-        // a batch of rounds, the flags of what is alive after it, and the plan from them
+        // a batch of rounds and the plan from what is alive after it
         launch_fix_batch(ctx, model, d_kernel_nz, flags);
-        launch_propagate(ctx, model, b.fix_out_flags, flags & SHIFTER_PAPER_FREEZE_RESIDUAL, d_group_alive,
-                         d_index_map, d_keep, d_new_width, 1);
+        launch_fix_plan(ctx, model, flags & SHIFTER_PAPER_FREEZE_RESIDUAL, d_group_alive, d_index_map, d_keep, d_new_width,
+                        h_new_width != nullptr);
         if ((rc = after_launch(ctx, "propagate_groups_fixpoint"))) return rc;
         if (!wait) {
             // nothing is read back: a fixed number of batches, of which those after the
@@ -1140,7 +1139,6 @@ extern "C" int shifter_propagate_groups_fixpoint(shifter_ctx* ctx, const shifter
             if (batch + 1 == FIX_ENQUEUED_BATCHES) return SHIFTER_OK;
             continue;
         }
-        if (h_new_width) launch_fix_widths(ctx, model, d_new_width);
         HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         if (mirror[1]) break;
         if ((uint64_t)mirror[0] > max_rounds)

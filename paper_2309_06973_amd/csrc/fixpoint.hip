@@ -186,34 +186,6 @@ __global__ __launch_bounds__(BLOCK) void fix_begin_kernel(uint8_t* alive, uint64
     }
 }
 
-// End of a batch of FIX_BATCH rounds.  out_flags[t][o] = alive[out_group(t)][o]: the alive
-// sets in the shape the planner's scan step takes, so that index maps and keep lists come
-// from the same kernel as ever.  The first thread also closes the batch: it adds the rounds
-// that ran to the total, carries removed[FIX_BATCH] to removed[0] for a batch that may
-// follow, clears the other counters and writes (rounds, settled) to the pinned mirror.
-__global__ __launch_bounds__(BLOCK) void fix_finish_kernel(
-    const DevTensor* __restrict__ tens, const DevGroup* __restrict__ groups,
-    const uint8_t* __restrict__ alive, uint8_t* __restrict__ out_flags, uint32_t* __restrict__ st,
-    uint32_t* __restrict__ mirror) {
-    if (blockIdx.x == gridDim.x - 1) {
-        if (threadIdx.x == 0) {
-            uint32_t ran = 0;
-            for (uint32_t j = 1; j <= FIX_BATCH; ++j) ran += st[j - 1] != 0;
-            const uint32_t last = st[FIX_BATCH];
-            const uint32_t rounds = st[FIX_BATCH + 1] + ran;
-            for (uint32_t j = 1; j <= FIX_BATCH; ++j) st[j] = 0;
-            st[0] = last;
-            st[FIX_BATCH + 1] = rounds;
-            mirror[0] = rounds;
-            mirror[1] = last == 0;
-        }
-        return;
-    }
-    const DevTensor& T = tens[blockIdx.x];
-    const uint8_t* a = alive + groups[T.out_group].off;
-    for (uint32_t o = threadIdx.x; o < T.out_ch; o += BLOCK) out_flags[T.out_flag_off + o] = a[o];
-}
-
 void launch_kernel_scan(shifter_ctx* ctx, const shifter_model* m, const float* d_w, uint8_t* d_nz) {
     const auto& b = m->b;
     hipStream_t s = ctx->stream;
@@ -222,17 +194,6 @@ void launch_kernel_scan(shifter_ctx* ctx, const shifter_model* m, const float* d
         auto k = m->info.w_extent * 4 > (192ull << 20) ? kernel_scan_kernel<true> : kernel_scan_kernel<false>;
         k<<<m->n_tiles, BLOCK, 0, s>>>(b.tens, b.tile_prefix, (uint32_t)m->t.size(), b.kernel_off, d_w, d_nz);
     }
-}
-
-__global__ __launch_bounds__(BLOCK) void fix_widths_kernel(const uint32_t* __restrict__ w,
-                                                          uint32_t* __restrict__ mirror, uint32_t n) {
-    for (uint32_t i = threadIdx.x; i < n; i += BLOCK) mirror[i] = w[i];
-}
-
-// The plan's widths into the pinned mirror the host reads after its wait.
-void launch_fix_widths(shifter_ctx* ctx, const shifter_model* m, const uint32_t* d_new_width) {
-    ProfileScope p(ctx, K_FIX_ROUND);
-    fix_widths_kernel<<<1, BLOCK, 0, ctx->stream>>>(d_new_width, m->b.dev_width, (uint32_t)m->g.size());
 }
 
 void launch_fix_begin(shifter_ctx* ctx, const shifter_model* m) {
@@ -245,7 +206,7 @@ void launch_fix_begin(shifter_ctx* ctx, const shifter_model* m) {
                                                         ba, bp, br, b.fix_removed);
 }
 
-// One batch: FIX_BATCH rounds back to back, then the kernel that closes it.
+// One batch: FIX_BATCH rounds back to back; launch_fix_plan closes it.
 void launch_fix_batch(shifter_ctx* ctx, const shifter_model* m, const uint8_t* d_nz, uint32_t flags) {
     const auto& b = m->b;
     hipStream_t s = ctx->stream;
@@ -260,9 +221,6 @@ void launch_fix_batch(shifter_ctx* ctx, const shifter_model* m, const uint8_t* d
                 b.tens, b.groups, b.producers, b.cons_prefix, b.consumers, flags, b.fix_alive,
                 b.fix_produced, b.fix_read, b.fix_removed + j - 1, b.fix_removed + j);
     }
-    fix_finish_kernel<<<(uint32_t)m->t.size() + 1, BLOCK, 0, s>>>(
-        b.tens, b.groups, b.fix_alive, b.fix_out_flags, b.fix_removed,
-        reinterpret_cast<uint32_t*>(b.dev_multi_status) + FIX_MIRROR_WORD);
 }
 
 }  // namespace shifter

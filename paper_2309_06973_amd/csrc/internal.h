@@ -247,7 +247,6 @@ struct shifter_model {
         uint8_t* fix_alive = nullptr;         // sum_group_width
         uint8_t* fix_produced = nullptr;      // sum_out_ch
         uint8_t* fix_read = nullptr;          // sum_in_ch
-        uint8_t* fix_out_flags = nullptr;     // sum_out_ch
         uint32_t* fix_removed = nullptr;      // FIX_STATE_WORDS: per-round counters of a batch, rounds so far
         shifter::FoldTensor* fold = nullptr;  // n_tensors
         std::vector<shifter::FoldTensor> fold_host;   // the layer table the device holds (empty: none yet)
@@ -452,7 +451,8 @@ void launch_copy(shifter_ctx* ctx, const float* src, float* dst, uint64_t n);
 void launch_kernel_scan(shifter_ctx* ctx, const shifter_model* m, const float* d_w, uint8_t* d_nz);
 void launch_fix_begin(shifter_ctx* ctx, const shifter_model* m);
 void launch_fix_batch(shifter_ctx* ctx, const shifter_model* m, const uint8_t* d_nz, uint32_t flags);
-void launch_fix_widths(shifter_ctx* ctx, const shifter_model* m, const uint32_t* d_new_width);
+void launch_fix_plan(shifter_ctx* ctx, const shifter_model* m, uint32_t flags, uint8_t* d_group_alive,
+                     int32_t* d_index_map, uint32_t* d_keep, uint32_t* d_new_width, bool mirror_widths);
 // Status bits of a codec call: the stream is not what the side information says; it does not fit
 // its buffer; a segment's offset did not arrive within the poll limit.
 enum : uint32_t { CODEC_BAD_STREAM = 1u, CODEC_CAPACITY = 2u, CODEC_CHAIN = 4u };
