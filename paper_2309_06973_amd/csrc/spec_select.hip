@@ -29,6 +29,10 @@ namespace shifter {
 constexpr uint32_t FBINS1 = 256;        // round-1 finishing histogram: one bin per thread
 constexpr uint32_t FHIST_COPIES = 4;    // of it in global memory: blocks that meet at one bin take their turns
 constexpr uint32_t FBINS = 4096;        // round-2 finishing histogram (one block, LDS)
+// Up to this many tiles the pass counts the candidates' first histogram itself (its blocks add at most 256 bins each to
+// four copies), beyond it a launch of its own does.  us a step: 24 k weights (9 tiles) 67.0 -> 65.5, 0.13 M 72.4 -> 71.2, 0.9 M
+// (232) 79.8 -> 78.1; with thousands of tiles the pass is bound by memory and the blocks' additions would queue.
+constexpr uint32_t PASS_HIST_TILES = SPEC_SUB;
 constexpr uint32_t FIN_BLOCKS = SPEC_FIN_BLOCKS;  // blocks of the passes over candidates
 // The last one: few blocks, because all draw a ticket of one address at its end (14 ns each), wide ones, because
 // the block that ends last ranks alone; each takes up to FIN_SUBS sub-buffers.
@@ -106,12 +110,14 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void spec_front_kernel(
 // on) and the alive flags of the kept weights outside the candidate interval;
 // spec_fixup_kernel settles the candidates.  A candidate pair holds the weight's full bit
 // pattern (sign included, so a wrongly removed weight can be restored) and its index.
-template <bool FUSED, bool NT>
+// HIST: the candidates' first histogram is counted on the way, in LDS, and added to the global one bin by bin.
+template <bool FUSED, bool NT, bool HIST>
 __global__ __launch_bounds__(BLOCK) void spec_pass_kernel(
     const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix,
     uint32_t n_t, const float* __restrict__ w, SpecState* ss, uint32_t* cnt,
-    uint2* __restrict__ cand, uint32_t cap_sb, float* __restrict__ w_out,
+    uint2* __restrict__ cand, uint32_t cap_sb, uint32_t* __restrict__ hist, float* __restrict__ w_out,
     uint8_t* __restrict__ mask, uint8_t* out_alive, uint8_t* in_alive) {
+    __shared__ uint32_t s_h[HIST ? FBINS1 : 1];
     __shared__ uint8_t rowf[FUSED ? TILE + 16 : 16];
     __shared__ uint8_t colf[FUSED ? TILE + 16 : 16];
     __shared__ uint32_t s_below, s_nan, s_base, s_wtot[BLOCK / 64];
@@ -130,6 +136,8 @@ __global__ __launch_bounds__(BLOCK) void spec_pass_kernel(
     uint2* my_cand = cand + (size_t)sb * cap_sb;
     uint32_t c0 = 0, r0 = 0, nrows = 0, ncols = 0;
     if (threadIdx.x == 0) { s_below = 0; s_nan = 0; s_base = 0; }
+    const uint32_t sh = HIST ? ss->sh : 0u;
+    if (HIST) s_h[threadIdx.x] = 0;
     if (FUSED) {
         c0 = e0 % T.khw;
         r0 = e0 % T.row_len;
@@ -160,13 +168,13 @@ __global__ __launch_bounds__(BLOCK) void spec_pass_kernel(
         return removed ? 0u : bits;
     };
 
+    constexpr uint32_t U = TILE / BLOCK / 4;
+    uint4 v[U];
+    uint32_t cmask = 0;
     if (n == TILE) {
-        constexpr uint32_t U = TILE / BLOCK / 4;
         const float* src4 = src + 4u * threadIdx.x;
-        uint4 v[U];
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(src4 + 4u * BLOCK * u);
-        uint32_t cmask = 0;
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
             const uint32_t j = (threadIdx.x + BLOCK * u) * 4;
@@ -183,6 +191,50 @@ __global__ __launch_bounds__(BLOCK) void spec_pass_kernel(
                 if (mdst) store_mask4<NT>(mdst + 4u * threadIdx.x + 4u * BLOCK * u, k0 | (k1 << 8) | (k2 << 16) | (k3 << 24));
             }
         }
+    } else {
+        // the tensor's last, ragged tile: the same, as far as there are weights
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t j = (threadIdx.x + BLOCK * u) * 4u, here = j < n ? min(n - j, 4u) : 0u;
+            v[u] = make_uint4(0, 0, 0, 0);
+            if (here == 4u) {
+                v[u] = load_u4<NT>(src + j);
+            } else {
+                if (here > 0u) v[u].x = __float_as_uint(src[j]);
+                if (here > 1u) v[u].y = __float_as_uint(src[j + 1u]);
+                if (here > 2u) v[u].z = __float_as_uint(src[j + 2u]);
+            }
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t j = (threadIdx.x + BLOCK * u) * 4u, here = j < n ? min(n - j, 4u) : 0u;
+            const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+            uint32_t o[4] = {0, 0, 0, 0}, k[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) {
+                if (q < here) {
+                    bool is_cand;
+                    o[q] = one(j + q, x[q], k[q], is_cand);
+                    cmask |= (is_cand ? 1u : 0u) << (4u * u + q);
+                }
+            }
+            if (FUSED) {
+                if (here == 4u) {
+                    store_u4<NT>(dst + j, make_uint4(o[0], o[1], o[2], o[3]));
+                    if (mdst) store_mask4<NT>(mdst + j, k[0] | (k[1] << 8) | (k[2] << 16) | (k[3] << 24));
+                } else {
+#pragma unroll
+                    for (uint32_t q = 0; q < 3u; ++q) {
+                        if (q < here) {
+                            dst[j + q] = __uint_as_float(o[q]);
+                            if (mdst) mdst[j + q] = (uint8_t)k[q];
+                        }
+                    }
+                }
+            }
+        }
+    }
+    {
         // append the block's candidates with one global atomic: scan the per-thread
         // counts over the block, reserve a range in this block's sub-buffer, scatter
         const uint32_t c = __popc(cmask);
@@ -212,28 +264,14 @@ __global__ __launch_bounds__(BLOCK) void spec_pass_kernel(
 #pragma unroll
                     for (uint32_t q = 0; q < 4; ++q) {
                         if (cmask & (1u << (4 * u + q))) {
-                            if (pos < cap_sb)
+                            if (pos < cap_sb) {
                                 my_cand[pos] = make_uint2(vv[q], g0 + j + q);
+                                if (HIST) lds_count(s_h, ((vv[q] & 0x7fffffffu) - lo) >> sh, true);
+                            }
                             ++pos;
                         }
                     }
                 }
-            }
-        }
-    } else {
-        // the tensor's last, ragged tile: one atomic per candidate
-        for (uint32_t j = threadIdx.x; j < n; j += BLOCK) {
-            uint32_t k;
-            bool q;
-            const uint32_t bits = __float_as_uint(src[j]);
-            const uint32_t o = one(j, bits, k, q);
-            if (FUSED) {
-                dst[j] = __uint_as_float(o);
-                if (mdst) mdst[j] = (uint8_t)k;
-            }
-            if (q) {
-                const uint32_t pos = atomicAdd(sub_counter(cnt, CNT_CAND, sb), 1u);
-                if (pos < cap_sb) my_cand[pos] = make_uint2(bits, g0 + j);
             }
         }
     }
@@ -249,6 +287,10 @@ __global__ __launch_bounds__(BLOCK) void spec_pass_kernel(
     if (threadIdx.x == 0) {
         if (s_below) atomicAdd(sub_counter(cnt, CNT_BELOW, sb), s_below);
         if (s_nan) atomicOr(&ss->status, 2u);
+    }
+    if (HIST) {
+        const uint32_t c = s_h[threadIdx.x];
+        if (c) atomicAdd(&hist[(blockIdx.x % FHIST_COPIES) * FBINS1 + threadIdx.x], c);
     }
     if (FUSED) {
         const uint32_t row_first = e0 / T.row_len;
@@ -603,6 +645,8 @@ void launch_spec_select(shifter_ctx* ctx, const shifter_model* m, const float* d
     const auto& b = m->b;
     const uint32_t n_t = (uint32_t)m->t.size();
     const bool fused = d_w_out != nullptr;
+    // few tiles: their candidates' histogram costs the pass less than the launch behind it
+    const bool small = m->n_tiles <= PASS_HIST_TILES;
     hipStream_t s = ctx->stream;
     {
         ProfileScope ps(ctx, K_SPEC_SAMPLE);
@@ -613,12 +657,13 @@ void launch_spec_select(shifter_ctx* ctx, const shifter_model* m, const float* d
     {
         ProfileScope ps(ctx, K_SPEC_PASS);
         const bool nt = m->info.w_extent * 4 > (192ull << 20);   // beyond the last-level cache
-        auto k = fused ? (nt ? spec_pass_kernel<true, true> : spec_pass_kernel<true, false>)
-                       : (nt ? spec_pass_kernel<false, true> : spec_pass_kernel<false, false>);
+        auto k = small ? (fused ? spec_pass_kernel<true, false, true> : spec_pass_kernel<false, false, true>)
+                 : fused ? (nt ? spec_pass_kernel<true, true, false> : spec_pass_kernel<true, false, false>)
+                         : (nt ? spec_pass_kernel<false, true, false> : spec_pass_kernel<false, false, false>);
         k<<<m->n_tiles, BLOCK, 0, s>>>(b.tens, b.tile_prefix, n_t, d_w, b.spec, b.spec_cnt, b.cand,
-                                       b.cand_cap_sb, d_w_out, d_mask, d_out_alive, d_in_alive);
+                                       b.cand_cap_sb, b.partial, d_w_out, d_mask, d_out_alive, d_in_alive);
     }
-    {
+    if (!small) {
         ProfileScope ps(ctx, K_SPEC_FINISH);
         spec_hist_kernel<<<FIN_BLOCKS, BLOCK, 0, s>>>(b.spec, b.spec_cnt, b.cand, b.cand_cap_sb,
                                                       b.partial);
