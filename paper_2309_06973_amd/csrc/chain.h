@@ -7,8 +7,9 @@
 
 namespace shifter {
 
-// A chunk's word: 0 nothing yet, bits 62-63 = 1 the size of its segment alone, 2 the size of all
-// segments up to and including it, 3 its wait ran out.
+// A link's word (a link is what one block encodes: one chunk, or two where blocks take pairs; "chunk"
+// below means a link): 0 nothing yet, bits 62-63 = 1 the size of its segments alone, 2 the size of all
+// segments up to and including them, 3 its wait ran out.
 constexpr uint64_t CHAIN_VALUE = (1ull << 62) - 1ull;
 constexpr uint64_t chain_size(uint32_t c, uint64_t size) { return ((c == 0 ? 2ull : 1ull) << 62) | size; }
 constexpr uint64_t CHAIN_BROKEN = 3ull << 62;

@@ -314,8 +314,8 @@ constexpr uint32_t CHAIN_POLLS = 1u << 22;     // seconds: far beyond any wait t
 __device__ __forceinline__ void chain_store(uint64_t* p, uint64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Sum of the sizes before chunk c, by one wavefront.  Chunks are numbered by a ticket that a block
-// draws when it starts, and a block stores its sizes before it waits for anything: every predecessor
+// Sum of the sizes before link c, by one wavefront.  Links (a block's one chunk, or its two) are numbered by
+// a ticket that the block draws when it starts, and a block stores its sizes before it waits for anything: every predecessor
 // is running or done and its size arrives without it waiting for this block.
 __device__ __forceinline__ ChainWalk chain_before(const uint64_t* status, uint32_t c, uint32_t lane) {
     ChainWalk walk(c);
