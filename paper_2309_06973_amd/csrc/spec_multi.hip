@@ -203,18 +203,22 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void ms_front_kernel(
     // because all interval ends are edges of those bins.  Bits 0-5 = #{k : lo_k <= key}, bit 7: the
     // key lies in the interval of the last of those ranks.  Entry 0 is for the bins below the first
     // rank's lower end, entry i for the i-th bin from there on, the last entry for all above it too; where
-    // the intervals span more bins than that, a table of all bins follows it and is used instead.
+    // the intervals span more bins than that, a table of all bins follows it and is used instead.  The last
+    // bin has no upper edge: entries that lie behind it are of its class.
     __syncthreads();
-    auto classes = [&](uint32_t bin0) {      // of four bins from bin0 on, which may start at -1 for bin 0
+    auto classes = [&](uint32_t bin0) {      // of four bins from bin0 on; -1 is bin 0, any behind the last is the last
+        int32_t bin[4];
+#pragma unroll
+        for (uint32_t i = 0; i < 4u; ++i) bin[i] = min(max((int32_t)(bin0 + i), 0), (int32_t)SAMPLE_BINS - 1);
         uint32_t j[4] = {0, 0, 0, 0}, four = 0;
         for (uint32_t k = 0; k < k_var; ++k) {
             const int32_t lo = (int32_t)s_lo_bin[k];
 #pragma unroll
-            for (uint32_t i = 0; i < 4u; ++i) j[i] += lo <= max((int32_t)(bin0 + i), 0) ? 1u : 0u;
+            for (uint32_t i = 0; i < 4u; ++i) j[i] += lo <= bin[i] ? 1u : 0u;
         }
 #pragma unroll
         for (uint32_t i = 0; i < 4u; ++i)
-            four |= (j[i] | (j[i] != 0u && max((int32_t)(bin0 + i), 0) <= (int32_t)s_hi_bin[j[i] - 1u] ? 0x80u : 0u)) << (8u * i);
+            four |= (j[i] | (j[i] != 0u && bin[i] <= (int32_t)s_hi_bin[j[i] - 1u] ? 0x80u : 0u)) << (8u * i);
         return four;
     };
     static_assert(PASS_TAB == 4u * SAMPLE_THREADS, "four entries a thread");

@@ -13,8 +13,10 @@ from paper_2309_06973_amd.pipeline import Pipeline
 pytestmark = pytest.mark.gpu
 
 
-# the first and the last of the ranks lie at 10 % and 97 % of the weights, so 0.87 of the binades apart
-@pytest.mark.parametrize("low,high", [(-3, -2), (-20, -4), (-20, -2), (-20, -1.5), (-20, -1), (-20, 0), (-48, 12), (-75, -30), (10, 16)])
+# the first and the last of the ranks lie at 10 % and 97 % of the weights, so 0.87 of the binades apart; the
+# bins end at 2^14, and the last one holds all that lies above
+@pytest.mark.parametrize("low,high", [(-3, -2), (-20, -4), (-20, -2), (-20, -1.5), (-20, -1), (-20, 0), (-48, 12), (-75, -30), (10, 16),
+                                      (-1, 15), (6, 15), (12, 15)])
 @pytest.mark.parametrize("widths,k", [([37, 91, 64], 2), ([37, 91, 64], 20), ([32, 96, 128, 64], 32)])
 def test_classes(low, high, widths, k):
     spec = synth.chain_spec(widths, in_ch=3)
@@ -31,8 +33,11 @@ def test_classes(low, high, widths, k):
         pl.enable_batch(k)
         recs, (rc, ot, ov, ew, ev) = pl.step(ps)
         torch.cuda.synchronize()
-        if k == 2 and -50 <= low and high <= 14:      # inside the binning the pass decides (of many ranks it may not)
-            assert S.shifter_get_select_stats(pl.ctx)["path"] == 1
+        # The pass decides, whatever the table's form.  But twenty ranks of 84 k weights in one binade share one interval, open
+        # to infinity for the last of them (97 % lie within the margin of 1300 samples' end): its 256 bins are a binade
+        # each, and one of them holds more than the list's 65536 pairs.
+        alone = k == 20 and high - low == 1
+        assert S.shifter_get_select_stats(pl.ctx)["path"] == (2 if alone else 1)
         for i, (rec, ref) in enumerate(zip(recs, refs)):
             t = a[ref.sel.thr_index]
             assert (rec.g_cut, rec.n_less, rec.n_equal) == (ref.sel.thr_index, int((a < t).sum()), int((a == t).sum()))
