@@ -469,6 +469,18 @@ struct PlanAllArgs {
 };
 static_assert(PROP_THREADS >= BLOCK, "plan_variant's shared memory");
 
+// A block's `waves` wavefronts (a power of two) shared out among n tensors: all of them to none or one (a group that
+// only vectors refer to has none), one each to many.
+__host__ __device__ constexpr uint32_t wavefronts_each(uint32_t n, uint32_t waves) {
+    uint32_t share = 1;
+    while (share < waves && share * 2u * n <= waves) share *= 2u;
+    return share;
+}
+static_assert(wavefronts_each(0, 8) == 8 && wavefronts_each(1, 8) == 8 && wavefronts_each(2, 8) == 4 &&
+                  wavefronts_each(3, 8) == 2 && wavefronts_each(4, 8) == 2 && wavefronts_each(5, 8) == 1 &&
+                  wavefronts_each(131070, 8) == 1,
+              "every table has a wavefront, and the search for their number ends");
+
 __global__ __launch_bounds__(PROP_THREADS) void plan_all_kernel(const PlanAllArgs A) {
     __shared__ uint32_t wave_cnt[PROP_THREADS / 64];
     __shared__ uint32_t s_flag_off[PROP_LDS_PRODUCERS];
@@ -501,10 +513,8 @@ __global__ __launch_bounds__(PROP_THREADS) void plan_all_kernel(const PlanAllArg
         const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
         const uint32_t n_prod = G.prod_end - G.prod_begin;
         const uint32_t cons_begin = A.cons_prefix[blockIdx.x], n_cons = A.cons_prefix[blockIdx.x + 1] - cons_begin;
-        // wavefronts per tensor: all sixteen shared out among few tensors, one each for many
         constexpr uint32_t WAVES = PROP_THREADS / 64;
-        uint32_t share = 1;
-        while (share * 2u * (n_prod + n_cons) <= WAVES) share *= 2u;
+        const uint32_t share = wavefronts_each(n_prod + n_cons, WAVES);
         for (uint32_t x = wid / share; x < n_prod + n_cons; x += WAVES / share) {
             const bool writes = x < n_prod;
             const uint32_t t = writes ? A.producers[G.prod_begin + x] : A.consumers[cons_begin + x - n_prod];
