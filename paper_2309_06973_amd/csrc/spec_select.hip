@@ -33,6 +33,11 @@ constexpr uint32_t FBINS = 4096;        // round-2 finishing histogram (one bloc
 // four copies), beyond it a launch of its own does.  us a step: 24 k weights (9 tiles) 67.0 -> 65.5, 0.13 M 72.4 -> 71.2, 0.9 M
 // (232) 79.8 -> 78.1; with thousands of tiles the pass is bound by memory and the blocks' additions would queue.
 constexpr uint32_t PASS_HIST_TILES = SPEC_SUB;
+// A tensor's last tile of up to this many weights goes one weight a thread, with an addition per candidate, a longer one
+// by fours like a full one: there the quads' branches, the block's prefix sum and the barriers around its one
+// addition cost more than they save.  Kernel, us, by fours / singly: 300 tiles of 64 weights 7.2 / 5.4, of 256 6.9 / 5.6, of
+// 400 7.0 / 6.2, of 576 7.4 / 8.1; 4000 of 64 20.3 / 14.5.
+constexpr uint32_t PASS_SINGLES = 2 * BLOCK;
 constexpr uint32_t FIN_BLOCKS = SPEC_FIN_BLOCKS;  // blocks of the passes over candidates
 // The last one: few blocks, because all draw a ticket of one address at its end (14 ns each), wide ones, because
 // the block that ends last ranks alone; each takes up to FIN_SUBS sub-buffers.
@@ -191,12 +196,32 @@ __global__ __launch_bounds__(BLOCK) void spec_pass_kernel(
                 if (mdst) store_mask4<NT>(mdst + 4u * threadIdx.x + 4u * BLOCK * u, k0 | (k1 << 8) | (k2 << 16) | (k3 << 24));
             }
         }
+    } else if (n <= PASS_SINGLES) {
+        // a tensor's last tile with few weights: one a thread and step, one addition per candidate
+        for (uint32_t j = threadIdx.x; j < n; j += BLOCK) {
+            uint32_t k;
+            bool q;
+            const uint32_t bits = __float_as_uint(src[j]);
+            const uint32_t o = one(j, bits, k, q);
+            if (FUSED) {
+                dst[j] = __uint_as_float(o);
+                if (mdst) mdst[j] = (uint8_t)k;
+            }
+            if (q) {
+                const uint32_t pos = atomicAdd(sub_counter(cnt, CNT_CAND, sb), 1u);
+                if (pos < cap_sb) {
+                    my_cand[pos] = make_uint2(bits, g0 + j);
+                    if (HIST) lds_count(s_h, ((bits & 0x7fffffffu) - lo) >> sh, true);
+                }
+            }
+        }
     } else {
-        // the tensor's last, ragged tile: the same, as far as there are weights
+        // the tensor's last, ragged tile: the same as a full one, as far as there are weights
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
             const uint32_t j = (threadIdx.x + BLOCK * u) * 4u, here = j < n ? min(n - j, 4u) : 0u;
             v[u] = make_uint4(0, 0, 0, 0);
+            if (BLOCK * 4u * u >= n) continue;           // the same in every thread
             if (here == 4u) {
                 v[u] = load_u4<NT>(src + j);
             } else {
@@ -210,6 +235,7 @@ __global__ __launch_bounds__(BLOCK) void spec_pass_kernel(
             const uint32_t j = (threadIdx.x + BLOCK * u) * 4u, here = j < n ? min(n - j, 4u) : 0u;
             const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
             uint32_t o[4] = {0, 0, 0, 0}, k[4] = {0, 0, 0, 0};
+            if (BLOCK * 4u * u >= n) continue;
 #pragma unroll
             for (uint32_t q = 0; q < 4u; ++q) {
                 if (q < here) {
@@ -234,7 +260,7 @@ __global__ __launch_bounds__(BLOCK) void spec_pass_kernel(
             }
         }
     }
-    {
+    if (n > PASS_SINGLES) {
         // append the block's candidates with one global atomic: scan the per-thread
         // counts over the block, reserve a range in this block's sub-buffer, scatter
         const uint32_t c = __popc(cmask);

@@ -10,7 +10,7 @@ from test_gpu_single_pass import check_step
 pytestmark = pytest.mark.gpu
 
 
-# 1x1 kernels: tiles of the three layers; 3 and 63 to 65 tiles: fewer blocks than the finish may have, and as many
+# 1x1 kernels: tiles of the three layers (tiles of up to 512 weights go one weight a thread); 3 and 63 to 65 tiles: fewer blocks than the finish may have, and as many
 @pytest.mark.parametrize("widths,tiles", [([8, 40], 3), ([256, 976], 63), ([256, 992], 64), ([256, 1008], 65), ([1024, 1012], 255),
                                           ([1024, 1016], 256), ([1024, 1017], 257), ([1024, 1020], 257)])
 @pytest.mark.parametrize("levels", [0, 2000])
@@ -23,3 +23,16 @@ def test_step(widths, tiles, levels):
         w = (np.round(w * levels) / levels).astype(np.float32)
     v = rng.standard_normal(max(spec.v_elems, 4)).astype(np.float32)
     check_step(spec, w, v, [(9 * spec.n_prunable) // 10], path=1)
+
+
+# short tiles around 512 weights, up to which they go one weight a thread, in networks of up to 256 tiles and of more
+@pytest.mark.parametrize("widths", [[16, 32], [27, 19], [16, 32] * 60, [27, 19] * 60, [16, 32] * 140, [27, 19] * 140, [7, 13] * 140])
+@pytest.mark.parametrize("levels", [0, 2000])
+def test_short_tiles(widths, levels):
+    spec = synth.chain_spec(widths, k=1, in_ch=3)
+    rng = np.random.Generator(np.random.Philox(sum(widths) + levels))
+    w = rng.standard_normal(spec.w_elems, dtype=np.float32)
+    if levels:
+        w = (np.round(w * levels) / levels).astype(np.float32)
+    v = rng.standard_normal(max(spec.v_elems, 4)).astype(np.float32)
+    check_step(spec, w, v, [spec.n_prunable // 3], path=1)
