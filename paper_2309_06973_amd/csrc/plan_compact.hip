@@ -444,10 +444,15 @@ __global__ __launch_bounds__(BLOCK) void rect_tables_kernel(
 // column tables of the tensors around it.  With levels as the source of liveness the blocks
 // from n_groups on expand them into the variant's flag bytes (the outputs of the batched
 // mask pass, which nothing in this launch reads).  The rebuild plan of a variant, which needs every
-// group's new width, is made by that of its group blocks which ends last: widths and tickets go past the L2, so
+// group's new width, is made by that of its group blocks which ends last where the groups are few: widths and tickets go past the L2, so
 // that no block has to write its XCD's back (with a device-wide fence 250 us).  Against a launch of its
 // own (kernels, us): one variant of 24 k weights 3.4 + 3.5 and 7.3, fifteen of 0.86 M 6.8 + 5.6 and 11.4, eight of 10 M
 // 5.1 + 4.8 and 8.8, twenty of 25.5 M 13.9 + 6.1 and 18.3, less a launch and its gap each: the steps are 3 to 7 us shorter.
+// That holds up to this many groups: the tickets of a variant take 14 ns each on their one address, and beyond it a launch
+// of its own costs less.  us a step with tickets / with a launch, networks of 8-channel layers: 200 groups 68 / 68 (one
+// variant), 127 / 136 (ten), 600 88 / 91 and 240 / 240, 800 95 / 98 and 298 / 291, 1000 103 / 102 and 357 / 339, 4000 216 / 207
+// and 1180 / 1120.
+constexpr uint32_t PLAN_LAST_GROUPS = 640;
 struct PlanAllArgs {
     const DevGroup* groups; const uint32_t* producers; const DevTensor* tens; uint32_t n_t;
     const DevVec* vecs; uint32_t n_v; uint32_t n_groups;
@@ -465,7 +470,7 @@ struct PlanAllArgs {
     const uint32_t* cons_prefix; const uint32_t* consumers;
     uint64_t cap_w, cap_v;
     PlanTensor* pt; PlanVec* pv; uint32_t* oup; PlanHeader* hdr; uint8_t* pack;
-    uint32_t* ticket;                  // PLAN_TICKET words for each variant, zero before and after
+    uint32_t* ticket;                  // PLAN_TICKET words for each variant, zero before and after; nullptr: no rebuild plans here
 };
 static_assert(PROP_THREADS >= BLOCK, "plan_variant's shared memory");
 
@@ -526,6 +531,7 @@ __global__ __launch_bounds__(PROP_THREADS) void plan_all_kernel(const PlanAllArg
             for (uint32_t j = (wid % share) * 64u + lane; j < n_e; j += share * 64u) tab[j] = below[min(j * step, limit)];
         }
     }
+    if (!A.ticket) return;               // many groups: plan_kernel follows
     uint32_t* ticket = A.ticket + k * PLAN_TICKET;
     if (!last_block(ticket, A.n_groups, &s_last)) return;
     const uint32_t* widths = A.new_width + k * A.n_groups;
@@ -956,12 +962,17 @@ void launch_plan_and_gather(shifter_ctx* ctx, const shifter_model* m, const Port
     A.below = b.below; A.cons_prefix = b.cons_prefix; A.consumers = b.consumers;
     A.cap_w = a.cap_w; A.cap_v = a.cap_v;
     A.pt = b.plan_t; A.pv = b.plan_v; A.oup = b.out_tile_prefix; A.hdr = b.plan_h; A.pack = b.dev_plan;
-    A.ticket = b.plan_ticket;
+    A.ticket = n_g <= PLAN_LAST_GROUPS ? b.plan_ticket : nullptr;
     const uint64_t mx = std::max<uint64_t>(n_out > n_in ? n_out : n_in, 1);
     const uint32_t expand_blocks = from_levels ? (uint32_t)((mx + PROP_THREADS - 1) / PROP_THREADS) : 0u;
     {
         ProfileScope p(ctx, K_PROPAGATE);
         plan_all_kernel<<<dim3(n_g + expand_blocks, a.k_var), PROP_THREADS, 0, ctx->stream>>>(A);
+    }
+    if (!A.ticket) {
+        ProfileScope p(ctx, K_PLAN);
+        plan_kernel<<<a.k_var, BLOCK, 0, ctx->stream>>>(b.tens, n_t, b.vecs, n_v, b.groups, n_g, a.d_new_width, a.cap_w, a.cap_v,
+                                                        b.plan_t, b.plan_v, b.out_tile_prefix, b.plan_h, b.dev_plan);
     }
     const bool dense_src = rebuild_reads_dense(m, a);
     launch_gather(ctx, m, dense_src ? a.d_w : a.d_w_sparse, dense_src ? 0 : a.w_stride, a.d_vecs, a.d_keep,
