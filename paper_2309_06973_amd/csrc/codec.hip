@@ -144,7 +144,8 @@ constexpr uint32_t CODEC_LOOP_GRID = 1536;                    // blocks of an in
 // one by one, a second instance for the chunks with long segments and a pack pass; 845 with 256
 // threads of this form, 690 with 512, 650 without loops for the matches and with two chunks a
 // block, 570 with the tables and what goes with them (the kernels alone 492 -> 409).  1.3 GB of a model with
-// 5 % of its weights: 4820 us, 1104, 853 now; with 30 % 1209 -> 945; all of its weights 725 -> 725; all zeros 409 -> 420.
+// 5 % of its weights: 4820 us, 1097, 838 now; with 30 % 1196 -> 906; all of its weights 713 -> 708; all zeros 409 -> 414 (64 to
+// 256 MB of zeros 43 -> 46, 61 -> 64, 100 -> 105: the one input that the tables' form is slower for).
 
 // Bits 0-15 of a piece: which bytes differ from the byte before them, and which are >= 144
 // (9-bit literals).  prev: the byte before the piece.
@@ -343,9 +344,10 @@ static_assert(CODEC_SUB == 512u, "258 + 253 + 1");
 
 // DIRECT: the segments go straight to their place in the stream, which cannot overflow (the
 // host checked that it holds the largest possible one).  The tickets take 13.8 ns each on their one
-// address, a bound where chunks hold next to nothing: 1.3 GB of zeros take 540 us a call with a ticket for
-// each chunk, 408 with one for two (GROUPS: 512 threads each, side by side in a block; they are one link of the
-// chain too: dense weights 831 -> 760 us).  Otherwise every segment goes to its
+// address, a bound where chunks hold next to nothing: 1.3 GB of zeros take 538 us a call with a ticket for
+// each chunk, 414 with one for two (GROUPS: 512 threads each, side by side in a block; they are one link of the
+// chain too: dense weights 889 and 708 us; 724 and zeros 421 where a barrier stood between the sizes and
+// their sum).  Otherwise every segment goes to its
 // slot of the workspace, and the two kernels behind this one add up the sizes and, if the
 // stream is large enough, move the segments.
 constexpr uint32_t CODEC_OUT_DW = CODEC_CHUNK / 4 + 8;
@@ -363,7 +365,7 @@ __global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void def
     __shared__ uint32_t g_side[GROUPS][CODEC_NSUB];
     __shared__ CodeTable s_codes;
     __shared__ uint64_t g_off[GROUPS];
-    __shared__ uint32_t s_c, g_size[GROUPS];
+    __shared__ uint32_t s_c, s_sized, g_size[GROUPS];
     constexpr uint32_t STEPS = CODEC_CHUNK / 1024u / (DEF_THREADS / 64u);     // KiB per wavefront
     const uint32_t group = GROUPS == 1 ? 0u : uniform_u32(threadIdx.x / DEF_THREADS), tid = threadIdx.x % DEF_THREADS;
     uint32_t* s_out = g_out[group];
@@ -371,7 +373,10 @@ __global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void def
     uint32_t* s_side = g_side[group];
     const uint32_t lane = threadIdx.x & 63u, wid = uniform_u32(tid >> 6), half = lane >> 5, hl = lane & 31u;
     uint32_t link = blockIdx.x, c = link * GROUPS + group;
-    if (DIRECT && threadIdx.x == 0) s_c = atomicAdd(ticket, 1u);
+    if (DIRECT && threadIdx.x == 0) {
+        s_c = atomicAdd(ticket, 1u);
+        s_sized = 0;
+    }
     // while the first wavefront waits for the ticket
     if (threadIdx.x - 64u < sizeof(CodeTable) / 16u)
         reinterpret_cast<uint4*>(&s_codes)[threadIdx.x - 64u] = reinterpret_cast<const uint4*>(&kCodeTable)[threadIdx.x - 64u];
@@ -471,19 +476,30 @@ __global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void def
                                             &tail_start, &tail_in_block);
     const bool whole = m + 5u <= coded_bytes;           // not shorter than one stored block
     const uint32_t seg_bytes = whole ? m + 5u : coded_bytes;
+    bool walks = false;
     if (DIRECT) {
-        // a block's chunks are one link of the chain
-        if (GROUPS > 1) {
-            if (tid == 0) g_size[group] = alive ? seg_bytes : 0u;
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            uint32_t size = seg_bytes;
+        // a block's chunks are one link of the chain: the wavefront that brings the last size leaves their sum
+        // and, behind its part of the second pass, walks back
+        if (wid == 0u) {
+            uint32_t done = GROUPS - 1u;
             if (GROUPS > 1) {
-                size = 0;
-                for (uint32_t g = 0; g < GROUPS; ++g) size += g_size[g];
+                if (lane == 0u) {
+                    g_size[group] = alive ? seg_bytes : 0u;
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                    done = atomicAdd(&s_sized, 1u);
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                }
+                done = uniform_u32(done);
             }
-            chain_store(status + link, chain_size(link, size));
+            if (done == GROUPS - 1u) {
+                walks = true;
+                uint32_t size = seg_bytes;
+                if (GROUPS > 1) {
+                    size = 0;
+                    for (uint32_t g = 0; g < GROUPS; ++g) size += g_size[g];
+                }
+                if (lane == 0u) chain_store(status + link, chain_size(link, size));
+            }
         }
     } else if (tid == 0 && alive) {
         seg_size[c] = seg_bytes;
@@ -585,17 +601,18 @@ __global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void def
     }
     uint8_t* dst = slots + (uint64_t)c * CODEC_SLOT;
     if (DIRECT) {
-        if (threadIdx.x < 64u) {
+        if (walks) {
+            const uint32_t c0 = link * GROUPS;
             const ChainWalk walk = chain_before(status, link, lane);
             if (lane == 0u) {
                 uint64_t end = walk.sum;
                 for (uint32_t g = 0; g < GROUPS; ++g) {
                     const uint32_t size = GROUPS > 1 ? g_size[g] : seg_bytes;
-                    if (c + g < n_chunks) seg_off[c + g] = end;         // c: the first group's
+                    if (c0 + g < n_chunks) seg_off[c0 + g] = end;
                     g_off[g] = walk.broken ? ~0ull : end;
                     end += size;
                 }
-                const bool ends = c + GROUPS >= n_chunks;
+                const bool ends = c0 + GROUPS >= n_chunks;
                 if (ends) seg_off[n_chunks] = end;
                 chain_leave(walk, link, ends, end - walk.sum, status + link, mirror, chain_store);
             }
@@ -1165,9 +1182,15 @@ static void codec_end(shifter_ctx* ctx) {
 }
 
 // Up to this many chunks, three to each of 256 compute units, a block takes one chunk, beyond it two: they
-// wait for each other at the barriers, which a chip that is not full notices, and share a ticket.  us a
-// call, one / two, 30 % of the weights not zero (none): 4 chunks 27 / 33, 256 32 / 35 (25 / 24), 640 47 / 51 (33 / 30), 769
-// 52 / 53 (35 / 32), 1024 60 / 56 (40 / 34), 4096 123 / 127 (85 / 66), 39347 864 / 929 (539 / 420).
+// wait for each other at the barriers, which a chip that is not full notices, and share a ticket and a link.  us a
+// call, one / two, by the share of weights that are not zero:
+//   chunks    none        0.5 %       5 %         30 %        all
+//   769       34 / 30     42 / 41     48 / 46     51 / 49     44 / 40
+//   1024      41 / 33     49 / 44     53 / 49     56 / 52     52 / 45
+//   4096      82 / 64     97 / 94     110 / 112   118 / 121   112 / 106
+//   39347     538 / 414   617 / 636   745 / 838   815 / 906   889 / 708
+// From 4096 chunks on a partly sparse input would gain up to a tenth from one, an empty or a dense one lose a fifth; which
+// it is nobody knows before the pass.  (4 chunks 27 / 33, 256 32 / 35, 640 47 / 51 before the barrier went, 30 %.)
 constexpr uint32_t DEFLATE_ONE_EACH = 768;
 
 // Room for chunk lists, kept by the context and grown when a longer input comes.
