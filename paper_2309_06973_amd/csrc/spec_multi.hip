@@ -445,10 +445,12 @@ __global__ __launch_bounds__(BLOCK, 8) void ms_pass_kernel(
 constexpr uint32_t MF_THREADS = 1024, MF_DEPTH = 8;
 constexpr uint32_t MF_BINS1 = 256;
 constexpr uint32_t MF_STAGE = 2048;      // pairs of the selected bin that one part may hold
-// Parts that one block of the finish takes at most.  Its registers let a compute unit run one block of 1024
+// Parts that one block of the finish takes at most.  Its 96 registers let a compute unit run one block of 1024
 // threads, so with a block for each of 32 parts nine ranks and more took two rounds or three: a block
-// takes as many parts as make one round.  Kernel, us: fifteen ranks of 0.86 M weights 17.2 -> 12.3, twenty of 25.5 M
-// 20.4 -> 15.4, ten of 14.7 M with ties 33.0 -> 30.0.  (Registers cut to what two blocks need spill: 19.9, 24.2, 37.3.)
+// takes as many parts as make one round, with room in LDS for all of them (90 KB, which alone keeps a second block
+// out now).  Kernel, us: fifteen ranks of 0.86 M weights 17.2 -> 12.3, twenty of 25.5 M
+// 20.4 -> 15.4, ten of 14.7 M with ties 33.0 -> 30.0.  (Registers cut to what two blocks need, with one part's room
+// in LDS, spill: 19.9, 24.2, 37.3.)
 constexpr uint32_t MF_PARTS = 4;
 
 // f(pair) for the n pairs at src, MF_DEPTH loads per thread in flight.
@@ -748,6 +750,9 @@ __global__ __launch_bounds__(MF_THREADS) void ms_finish_kernel(
 // are known, rewrites the candidates written on the wrong side of their rank's cut (the
 // pass decides by the predicted threshold mid of the last rank) and adds their levels.
 // rv[v] = sorted rank of variant v, or -1 for a variant that removes nothing (P = 0).
+// Bound by its stores: ten variants of 322 M weights take 3.42 ms, the same loads and stores without any of the work
+// 3.33.  So the classification by search, an atomic per weight for the levels and ragged tiles weight by weight, which
+// ms_pass_kernel and mask_scan_batch_kernel have left for faster forms, stay here.
 struct VariantRanks {
     int32_t r[MAXK];
 };
