@@ -727,7 +727,7 @@ extern "C" int shifter_global_threshold_static(shifter_ctx* ctx, const float* d_
     uint8_t* base = ctx->static_scratch;   // the array's device address, never its name
     DevTensor* tens = reinterpret_cast<DevTensor*>(base + STATIC_OFF_TENSOR);
     uint32_t* prefix = reinterpret_cast<uint32_t*>(base + STATIC_OFF_PREFIX);
-    const SelectTables tb{tens, prefix, 1u, (uint32_t)n_tiles, n,
+    const SelectTables tb{tens, prefix, nullptr, (uint32_t)n_tiles, n,
                           reinterpret_cast<SelState*>(base + STATIC_OFF_SEL),
                           reinterpret_cast<uint32_t*>(base + STATIC_OFF_GHIST),
                           reinterpret_cast<uint2*>(base + STATIC_OFF_LISTS), STATIC_LIST_PAIRS, tens, prefix};

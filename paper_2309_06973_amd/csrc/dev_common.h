@@ -154,29 +154,46 @@ __device__ __forceinline__ void lds_count(uint32_t* h, uint32_t bin, bool want) 
     if (same && (peers & ((1ull << (threadIdx.x & 63u)) - 1ull)) == 0ull) atomicAdd(&h[first], (uint32_t)__popcll(peers));
 }
 
+// The thread's number, worked out where it is asked for: addresses that follow from it are not kept in registers
+// around a loop (26 of them spilled in the kernel that ranks lists in a loop over the ranks).
+__device__ __forceinline__ uint32_t this_thread() {
+    uint32_t tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    return tid;
+}
+
 // f(valid, pair) for the n pairs at src, which starts on 16 bytes and has room for an even number
 // of them; DEPTH loads of two pairs per thread in flight; every thread of the block makes the same
-// calls.
-template <uint32_t THREADS, uint32_t DEPTH, typename F>
-__device__ __forceinline__ void walk_pairs(const uint2* __restrict__ src, uint32_t n, F&& f) {
-    const uint4* __restrict__ src4 = reinterpret_cast<const uint4*>(src);
-    for (uint32_t i0 = 0; i0 < n; i0 += 2u * THREADS * DEPTH) {
-        uint4 c[DEPTH];
+// calls.  A list that these loads cover is kept in registers from one walk to the next.
+template <uint32_t THREADS, uint32_t DEPTH>
+struct PairWalk {
+    const uint4* __restrict__ src;
+    uint32_t n, tid;
+    uint4 c[DEPTH];
+    __device__ __forceinline__ PairWalk(const uint2* __restrict__ pairs, uint32_t count, uint32_t thread)
+        : src(reinterpret_cast<const uint4*>(pairs)), n(count), tid(thread) { fetch(0); }
+    __device__ __forceinline__ void fetch(uint32_t i0) {
 #pragma unroll
         for (uint32_t u = 0; u < DEPTH; ++u) {
-            const uint32_t i = i0 + 2u * (u * THREADS + threadIdx.x);
-            c[u] = i < n ? src4[i / 2u] : make_uint4(0, 0, 0, 0);
+            const uint32_t i = i0 + 2u * (u * THREADS + tid);
+            c[u] = src[(n ? min(i, n - 1u) : 0u) / 2u];       // behind the end: the last ones again
         }
+    }
+    template <typename F>
+    __device__ __forceinline__ void operator()(F&& f) {
+        for (uint32_t i0 = 0; i0 < n; i0 += 2u * THREADS * DEPTH) {
+            if (n > 2u * THREADS * DEPTH) fetch(i0);
 #pragma unroll
-        for (uint32_t u = 0; u < DEPTH; ++u) {
-            const uint32_t i = i0 + 2u * (u * THREADS + threadIdx.x);
-            if (i0 + 2u * u * THREADS < n) {
-                f(i < n, make_uint2(c[u].x, c[u].y));
-                f(i + 1u < n, make_uint2(c[u].z, c[u].w));
+            for (uint32_t u = 0; u < DEPTH; ++u) {
+                const uint32_t i = i0 + 2u * (u * THREADS + tid);
+                if (i0 + 2u * u * THREADS < n) {
+                    f(i < n, make_uint2(c[u].x, c[u].y));
+                    f(i + 1u < n, make_uint2(c[u].z, c[u].w));
+                }
             }
         }
     }
-}
+};
 
 // The r-th smallest (1-based) of n distinct pairs (bits, global index) in the order (|bits|,
 // index), by one block.  All n lie in the window of 2^width composites (|bits| << 32 | index)
@@ -199,13 +216,15 @@ __device__ bool rank_in_list(const uint2* __restrict__ src, uint32_t n, uint64_t
                              uint64_t r, bool count, RankShared<THREADS>& sh) {
     auto composite = [](uint2 c) { return ((uint64_t)(c.x & 0x7fffffffu) << 32) | c.y; };
     uint32_t in_window = n, below = 0;          // pairs in the window, pairs of the list below it
-    if (threadIdx.x == 0) { sh.sel = 0; sh.nb = 0; sh.lt = 0; sh.eq = 0; }
+    const uint32_t tid = this_thread();
+    PairWalk<THREADS, DEPTH> walk(src, n, tid);
+    if (tid == 0) { sh.sel = 0; sh.nb = 0; sh.lt = 0; sh.eq = 0; }
     while (in_window > RANK_DIRECT) {
         if (width == 0) return false;           // composites are distinct: cannot happen
         const uint32_t shift = width >= 44u ? width - 12u : (width > 32u ? 32u : (width > 12u ? width - 12u : 0u));
-        for (uint32_t i = threadIdx.x; i < RANK_BINS; i += THREADS) sh.h[i] = 0;
+        for (uint32_t i = tid; i < RANK_BINS; i += THREADS) sh.h[i] = 0;
         __syncthreads();
-        walk_pairs<THREADS, DEPTH>(src, n, [&](bool valid, uint2 c) {
+        walk([&](bool valid, uint2 c) {
             const uint64_t d = composite(c) - c_lo;               // wraps for pairs below the window
             lds_count(sh.h, (uint32_t)(d >> shift) & (RANK_BINS - 1u), valid && (d >> width) == 0);
         });
@@ -214,12 +233,12 @@ __device__ bool rank_in_list(const uint2* __restrict__ src, uint32_t n, uint64_t
         uint32_t c[PER];
         uint64_t sum = 0, tot;
 #pragma unroll
-        for (uint32_t i = 0; i < PER; ++i) { c[i] = sh.h[threadIdx.x * PER + i]; sum += c[i]; }
+        for (uint32_t i = 0; i < PER; ++i) { c[i] = sh.h[tid * PER + i]; sum += c[i]; }
         uint64_t base = block_excl_scan_u64<THREADS>(sum, sh.smem, &tot);
         if (tot < r) return false;
 #pragma unroll
         for (uint32_t i = 0; i < PER; ++i) {
-            if (base < r && r <= base + c[i]) { sh.bin = threadIdx.x * PER + i; sh.cnt = c[i]; sh.base = base; }
+            if (base < r && r <= base + c[i]) { sh.bin = tid * PER + i; sh.cnt = c[i]; sh.base = base; }
             base += c[i];
         }
         __syncthreads();
@@ -231,7 +250,7 @@ __device__ bool rank_in_list(const uint2* __restrict__ src, uint32_t n, uint64_t
         __syncthreads();
     }
     __syncthreads();
-    walk_pairs<THREADS, DEPTH>(src, n, [&](bool valid, uint2 c) {
+    walk([&](bool valid, uint2 c) {
         const uint64_t comp = composite(c);
         if (valid && ((comp - c_lo) >> width) == 0) {
             const uint32_t pos = atomicAdd(&sh.nb, 1u);
@@ -240,7 +259,7 @@ __device__ bool rank_in_list(const uint2* __restrict__ src, uint32_t n, uint64_t
     });
     __syncthreads();
     if (sh.nb != in_window || r == 0 || r > in_window) return false;
-    for (uint32_t i = threadIdx.x; i < in_window; i += THREADS) {
+    for (uint32_t i = tid; i < in_window; i += THREADS) {
         const uint64_t c = sh.comp[i];
         uint32_t rank = 0;
         for (uint32_t f = 0; f < in_window; ++f) rank += sh.comp[f] < c;
@@ -251,20 +270,20 @@ __device__ bool rank_in_list(const uint2* __restrict__ src, uint32_t n, uint64_t
     const uint32_t key = (uint32_t)(sh.sel >> 32);
     uint32_t lt = 0, eq = 0;
     if (width >= 32u) {                         // the window holds whole keys
-        for (uint32_t i = threadIdx.x; i < in_window; i += THREADS) {
+        for (uint32_t i = tid; i < in_window; i += THREADS) {
             const uint32_t k = (uint32_t)(sh.comp[i] >> 32);
             lt += k < key;
             eq += k == key;
         }
-        if (threadIdx.x == 0) lt += below;
+        if (tid == 0) lt += below;
     } else {                                    // it is a part of one key's indices
-        walk_pairs<THREADS, DEPTH>(src, n, [&](bool valid, uint2 c) {
+        walk([&](bool valid, uint2 c) {
             const uint32_t k = c.x & 0x7fffffffu;
             lt += valid && k < key;
             eq += valid && k == key;
         });
         for (uint32_t d = 32; d > 0; d >>= 1) { lt += __shfl_down(lt, d, 64); eq += __shfl_down(eq, d, 64); }
-        if ((threadIdx.x & 63u) != 0) lt = eq = 0;
+        if ((tid & 63u) != 0) lt = eq = 0;
     }
     if (lt) atomicAdd(&sh.lt, lt);
     if (eq) atomicAdd(&sh.eq, eq);

@@ -68,6 +68,7 @@ struct SelWindow {
     uint32_t mode;             // of this stage: split by a histogram, listed, or nothing to do
     uint32_t stage;            // whose key_lo, key_hi say what keys it holds; 0: not known
 };
+constexpr uint32_t SEL_GO = 16, SEL_GO_WORDS = 32;   // lines that say that a stage is over
 struct SelState {
     SelWindow win[SEL_STAGES + 1][MAXK];   // by stage; the first is unused
     SelWindow fin[MAXK];                   // the windows that were listed
@@ -77,6 +78,8 @@ struct SelState {
     uint32_t key_lo[SEL_STAGES + 1][MAXK]; // smallest and largest key met in a window, by stage
     uint32_t key_hi[SEL_STAGES + 1][MAXK];
     uint32_t done[SEL_STAGES + 1];         // every rank is listed after this stage
+    uint32_t ticket[SEL_STAGES + 1], arrived[SEL_STAGES + 1];   // parts of a stage handed out and done with (0: ranks)
+    uint32_t go[SEL_STAGES + 1][SEL_GO * SEL_GO_WORDS];         // all parts of a stage have arrived
     uint32_t nan_seen;
     uint32_t n_zero;                       // prunable weights that are zero
 };
@@ -357,7 +360,8 @@ void launch_select(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
 struct SelectTables {
     const DevTensor* tens;
     const uint32_t* tile_prefix;
-    uint32_t n_t, n_tiles;
+    const uint16_t* tile_tensor;   // nullptr: one tensor
+    uint32_t n_tiles;
     uint64_t n_weights;   // prunable weights
     SelState* sel;
     uint32_t* ghist;      // SEL_STAGES * SEL_BINS

@@ -2,33 +2,34 @@
 // magnitude ranking of Sec. II-A / Sec. III-C of the paper in the form that needs no decision
 // on the host, for any number of prune counts, any distribution and any number of ties.
 //
-//   top     one read of the arena: a histogram of all keys on the 16384 bins of sample_bin
-//           (1/256 of a binade where the weights of networks live), zeros counted apart;
+//   top     one read of the arena: a histogram of all keys on 16384 bins (1/512 of a binade where the
+//           weights of networks live), zeros counted apart;
 //   stage   every rank has a window of composites (key << 32 | g) that holds its pair and the
 //           number of weights in it.  A stage reads the arena once: windows of no more pairs
 //           than are good in a list (sel_plan.h) are written out as lists, the others are split by
 //           a further histogram, first by key down to a single key, then by index;
-//   final   one block per rank ranks its list and writes the record.
+//   rest    the stages that are left where the first one has not listed every rank, then one block
+//           per rank ranks its list and writes the record.
 //
 // The first stage lists the ranks whose top bin holds no more than a list: 65536 pairs, in a
-// flat run's scratch 2^19 / K if that is less.  A bin of normally distributed weights holds up to 0.2 % of
-// them, so 10 counts of 25 M weights, or 20 of 13 M, are read three times with no ties at all, fewer twice.
+// flat run's scratch 2^19 / K if that is less.  A bin of normally distributed weights holds up to 0.07 % of
+// them, so 10 counts of up to 75 M weights are read twice where there are no ties.
 //
 // The launches are the same for every input (their number follows from N and K alone), so the
-// calls can be recorded into a graph.  What bounds it: the reads of the arena, and one launch
-// after the other around them (about 5 us each, 2 to 5 for a stage with nothing to do).
+// calls can be recorded into a graph.  What bounds it: the reads of the arena (100 M weights at 5.6 TB/s), and one launch
+// after the other around them: clear, top, stage and rest 5 + 16 + 22 + 11 us on ten counts of 14.7 M.
 // Equal weights are what the rest is built around: zeros take a window of their own from the start,
 // a window that turns out to hold a single key goes on with its index, a lane keeps counts that would meet at
 // one counter, windows that follow each other in one bin are found by halving.  us a call, flat
-// run, the radix select of 11 + 10 + 10 bits with one read per distinct key for the ties that this
-// replaces / lists of up to 2^20 pairs and none of these / now:
-//   counts of weights     normal              half of them zero     all equal             30 levels a sigma
-//    1 of   1 M           85 /   35 /   33    88 / 1336 /   59      92 /  121 /   75      89 /  90 /  48
-//   10 of   1 M          197 /   38 /   35   140 /  132 /   64     140 /  143 /   82     196 /  93 /  54
-//    1 of  14.7 M        174 /   53 /   52   200 /  273 /  122     246 /  331 /  188     181 / 685 /  96
-//   10 of  14.7 M        418 /   71 /   63   258 /  359 /  146     296 /  421 /  213     390 / 165 / 138
-//    1 of 100 M          481 /  175 /  180   723 / 1279 /  508    1210 / 1662 /  857     469 / 617 / 346
-//   10 of 100 M         1276 /  312 /  268   850 / 2287 /  801    1261 / 2781 / 1236    1271 / 693 / 596
+// run, bins of 1/256 of a binade and a launch for each stage, used or not / now:
+//   counts of weights     normal        half of them zero   all equal       30 levels a sigma   half precision
+//    1 of   1 M           32 / 23       33 / 24             78 / 70         49 / 38             41 / 31
+//   10 of   1 M           34 / 25       60 / 56             81 / 78         55 / 44             43 / 33
+//    1 of  14.7 M         56 / 43       55 / 43             178 / 179       113 / 107           76 / 54
+//   10 of  14.7 M         64 / 47       137 / 131           208 / 208       145 / 149           96 / 63
+//    1 of 100 M           249 / 177     246 / 174           850 / 829       399 / 416           273 / 224
+//   10 of 100 M           252 / 265     745 / 718           1214 / 1197     605 / 610           298 / 321
+// (The radix select of 11 + 10 + 10 bits before all this: 85 us for 1 of 1 M, 418 for 10 of 14.7 M.)
 #include <algorithm>
 
 #include "dev_common.h"
@@ -39,6 +40,7 @@ constexpr uint32_t SEL_THREADS = 1024;
 constexpr uint32_t SEL_GROUPS = SEL_THREADS / BLOCK;   // tiles a block walks side by side
 constexpr uint32_t SEL_STAGE_CAP = 4096;               // listed pairs a block collects in LDS
 constexpr uint32_t SEL_QUADS = TILE / BLOCK / 4;        // of a full tile per thread
+constexpr uint32_t SEL_DEPTH = 8;                       // loads of two listed pairs per thread in flight
 constexpr uint32_t NONE8 = 0xffu;
 // What the walk of a stage has to know of a window, in one word: width | shift << 6 | these |
 // leader << 16 | windows in its top bin << 24.
@@ -46,8 +48,23 @@ constexpr uint32_t SEL_ABOUT_SPLIT = 1u << 12;
 constexpr uint32_t SEL_ABOUT_TIES = 1u << 13;     // likely to hold equal weights
 constexpr uint32_t SEL_ABOUT_RUNS = 1u << 14;     // many of a wavefront's lanes meet at one counter
 
+// The top bins: 1/512 of a binade from 2^-25 to 2^7, where thresholds of networks lie; the keys below share the first one
+// with its own, those above the last one.  (1/256 of a binade over 64 of them, as in the sample's histogram: lists twice as
+// long.)
+constexpr uint32_t SEL_BIN_SHIFT = 14, SEL_KEY0 = (127u - 25u) << 23;
+static_assert(SEL_BINS << SEL_BIN_SHIFT == 32u << 23, "2^-25 to 2^7");
+__device__ __forceinline__ uint32_t sel_bin(uint32_t key) {
+    return min(__builtin_elementwise_sub_sat(key, SEL_KEY0) >> SEL_BIN_SHIFT, SEL_BINS - 1u);
+}
+// First key of a bin (zeros are in none), and the bits of a window that is a whole bin: those at both ends span up to 2^30
+// keys.
+__device__ __forceinline__ uint32_t sel_bin_first_key(uint32_t bin) { return bin == 0u ? 1u : SEL_KEY0 + (bin << SEL_BIN_SHIFT); }
+__device__ __forceinline__ uint32_t sel_bin_width(uint32_t bin) {
+    return bin == 0u || bin == SEL_BINS - 1u ? SEL_MAX_WIDTH : 32u + SEL_BIN_SHIFT;
+}
+
 // Where the map of windows is looked up: the key's bin, one more for zero.
-__device__ __forceinline__ uint32_t top_bin(uint32_t key) { return key ? sample_bin(key) : SEL_BINS; }
+__device__ __forceinline__ uint32_t top_bin(uint32_t key) { return key ? sel_bin(key) : SEL_BINS; }
 
 __global__ __launch_bounds__(BLOCK) void sel_clear_kernel(SelState* st, uint32_t* ghist, uint32_t hists,
                                                           PruneCounts pc, MultiPerm perm, uint32_t k,
@@ -66,7 +83,9 @@ __global__ __launch_bounds__(BLOCK) void sel_clear_kernel(SelState* st, uint32_t
         st->perm[tid] = tid < k ? perm.v[tid] : 0;
         st->list_cnt[tid] = 0;
         st->fin[tid].mode = SEL_IDLE;
-        if (tid <= SEL_STAGES) st->done[tid] = 0;
+        if (tid <= SEL_STAGES) st->done[tid] = st->ticket[tid] = st->arrived[tid] = 0;
+        if (tid < SEL_GO)
+            for (uint32_t i = 0; i <= SEL_STAGES; ++i) st->go[i][tid * SEL_GO_WORDS] = 0;
     }
     if (tid == 0) {
         st->nan_seen = 0;
@@ -97,33 +116,72 @@ __global__ __launch_bounds__(BLOCK) void sel_clear_kernel(SelState* st, uint32_t
     }
 }
 
-// whole(bits of a thread's sixteen weights of a full tile, g of the first) and one(bits, g) for the
-// prunable weights; the four quads of the sixteen lie 4 * BLOCK weights apart.  Four tiles at a time per block, one per 256 threads,
-// a thread's 64 bytes in flight together; no barriers, so the wavefronts drift apart and one's
-// loads overlap with another's work.
-template <typename Q, typename F>
-__device__ __forceinline__ void sel_walk(const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix,
-                                         uint32_t n_t, uint32_t n_tiles, const float* __restrict__ w, Q&& whole, F&& one) {
-    const uint32_t tid = threadIdx.x & (BLOCK - 1u);
-    const uint32_t group = uniform_u32(threadIdx.x / BLOCK);
-    for (uint32_t tile = blockIdx.x * SEL_GROUPS + group; tile < n_tiles; tile += gridDim.x * SEL_GROUPS) {
-        const uint32_t t = n_t == 1u ? 0u : find_tensor(tile_prefix, n_t, tile);
-        if (!tens[t].prunable) continue;
-        const uint32_t e0 = (tile - tile_prefix[t]) * TILE;
-        const uint32_t n = min(TILE, tens[t].numel - e0);
-        const uint32_t g0 = (uint32_t)(tens[t].gbase + e0);
-        const float* src = w + tens[t].offset + e0;
+struct SelArena {
+    const DevTensor* __restrict__ tens;
+    const uint32_t* __restrict__ tile_prefix;
+    const uint16_t* __restrict__ tile_tensor;     // nullptr: one tensor
+    uint32_t n_tiles;
+    const float* __restrict__ w;
+};
+
+// The weights of one part of several: four tiles at a time per block, one per 256 threads, a thread's 64 bytes in
+// flight together; no barriers, so the wavefronts drift apart and one's loads overlap with another's work.
+// A tensor's last, ragged tile goes the same way as a full one.
+struct SelWalk {
+    const SelArena& a;
+    uint32_t tile, n, g0;            // the tile at hand: its weights (0: not prunable) and the first one's global index
+    uint4 v[SEL_QUADS];              // sixteen of them: four quads 4 * BLOCK weights apart
+
+    __device__ __forceinline__ explicit SelWalk(const SelArena& arena) : a(arena) {}
+    __device__ __forceinline__ uint32_t thread() const { return threadIdx.x & (BLOCK - 1u); }
+    __device__ __forceinline__ void fetch() {
+        n = 0;
+        const uint32_t t = a.tile_tensor ? a.tile_tensor[tile] : 0u;
+        const DevTensor& T = a.tens[t];
+        if (!T.prunable) return;
+        const uint32_t e0 = (tile - a.tile_prefix[t]) * TILE;
+        n = min(TILE, T.numel - e0);
+        g0 = (uint32_t)(T.gbase + e0);
+        const float* src = a.w + T.offset + e0;
         if (n == TILE) {
-            uint4 v[SEL_QUADS];
-            constexpr uint32_t U = SEL_QUADS;
 #pragma unroll
-            for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<false>(src + 4u * tid + 4u * BLOCK * u);
-            whole(v, g0 + 4u * tid);
+            for (uint32_t u = 0; u < SEL_QUADS; ++u) v[u] = load_u4<false>(src + 4u * thread() + 4u * BLOCK * u);
         } else {
-            for (uint32_t j = tid; j < n; j += BLOCK) one(__float_as_uint(src[j]), g0 + j);
+            // missing ones read as the last one there is
+#pragma unroll
+            for (uint32_t u = 0; u < SEL_QUADS; ++u) {
+                const uint32_t j = (thread() + BLOCK * u) * 4u;
+                auto at = [&](uint32_t q) { return __float_as_uint(src[min(j + q, n - 1u)]); };
+                v[u] = make_uint4(at(0), at(1), at(2), at(3));
+            }
         }
     }
-}
+    template <typename F>
+    __device__ __forceinline__ void run(uint32_t part, uint32_t parts, F&& f) {
+        for (tile = part * SEL_GROUPS + uniform_u32(threadIdx.x / BLOCK); tile < a.n_tiles; tile += parts * SEL_GROUPS) {
+            fetch();
+            if (n) f();
+        }
+    }
+    // bit 4 u + q: weight q of quad u is there (of a ragged tile's)
+    __device__ __forceinline__ uint32_t there() const {
+        uint32_t m = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < SEL_QUADS; ++u) m |= ((1u << min(4u, n - min((thread() + BLOCK * u) * 4u, n))) - 1u) << (4u * u);
+        return m;
+    }
+    // weight j of the sixteen, and its global index
+    __device__ __forceinline__ uint32_t bits(uint32_t j) const {
+        const uint32_t u = j >> 2, q = j & 3u;
+        const uint4 lo = (u & 1u) ? v[1] : v[0], hi = (u & 1u) ? v[3] : v[2], x = (u & 2u) ? hi : lo;
+        const uint32_t a = (q & 1u) ? x.y : x.x, b = (q & 1u) ? x.w : x.z;
+        return (q & 2u) ? b : a;
+    }
+    __device__ __forceinline__ uint32_t index(uint32_t j) const {
+        return g0 + 4u * thread() + 4u * BLOCK * (j >> 2) + (j & 3u);
+    }
+};
+static_assert(SEL_QUADS == 4u, "sixteen weights");
 
 // Counts of one histogram entry that a lane has not added to it yet.  Equal weights would have
 // all lanes meet at one counter, where an LDS atomic takes a turn per lane.
@@ -157,21 +215,28 @@ struct KeyRange {
 
 // Zeros, half of the weights or more in a model that was pruned before, are counted apart, a
 // counter for each lane.  Four neighbours of one bin (weights that are equal or sorted) are counted as a run.
-__global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(
-    const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix, uint32_t n_t, uint32_t n_tiles,
-    const float* __restrict__ w, SelState* st, uint32_t* ghist) {
+__global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(const SelArena arena, SelState* st, uint32_t* ghist) {
     __shared__ uint32_t h[SEL_BINS + 64u];
     const uint32_t lane = threadIdx.x & 63u;
+    SelWalk walk(arena);
     for (uint32_t i = threadIdx.x; i < SEL_BINS + 64u; i += SEL_THREADS) h[i] = 0;
     __syncthreads();
     uint32_t key_max = 0, turn = 0;
     bool runs = false;
     RunCount run;
-    auto bin_of = [&](uint32_t key) { return key ? sample_bin(key) : SEL_BINS + lane; };
-    sel_walk(tens, tile_prefix, n_t, n_tiles, w, [&](const uint4 (&quads)[SEL_QUADS], uint32_t) {
+    auto bin_of = [&](uint32_t key) { return key ? sel_bin(key) : SEL_BINS + lane; };
+    walk.run(blockIdx.x, gridDim.x, [&] {
+        if (walk.n != TILE) {
+            for (uint32_t left = walk.there(); left; left &= left - 1u) {
+                const uint32_t key = walk.bits((uint32_t)__builtin_ctz(left)) & 0x7fffffffu;
+                key_max = max(key_max, key);
+                atomicAdd(&h[bin_of(key)], 1u);
+            }
+            return;
+        }
 #pragma unroll
         for (uint32_t u = 0; u < SEL_QUADS; ++u) {
-            const uint4 v = quads[u];
+            const uint4 v = walk.v[u];
             const uint32_t k0 = v.x & 0x7fffffffu, k1 = v.y & 0x7fffffffu, k2 = v.z & 0x7fffffffu, k3 = v.w & 0x7fffffffu;
             const uint32_t b0 = bin_of(k0), b1 = bin_of(k1), b2 = bin_of(k2), b3 = bin_of(k3);
             key_max = max(max(key_max, max(k0, k1)), max(k2, k3));
@@ -190,10 +255,6 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(
                 atomicAdd(&h[b3], 1u);
             }
         }
-    }, [&](uint32_t bits, uint32_t) {
-        const uint32_t key = bits & 0x7fffffffu;
-        key_max = max(key_max, key);
-        atomicAdd(&h[bin_of(key)], 1u);
     });
     run.flush(h);
     if (key_max > 0x7f800000u) st->nan_seen = 1;
@@ -212,49 +273,76 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(
     }
 }
 
-// Stage `stage` (1 ..): every block first works out the windows from the histograms of the
-// stage before (the same in every block; the first one publishes them), then walks the arena.
-__global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
-    const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix, uint32_t n_t, uint32_t n_tiles,
-    const float* __restrict__ w, SelState* st, uint32_t* ghist, uint2* __restrict__ lists, uint32_t list_cap,
-    uint32_t k, uint32_t n_weights, uint32_t g_bits, uint32_t stage, uint32_t stages) {
+// Stores of what the blocks of one launch leave each other (DEV: past the L2 of their chiplet; the readers drop what theirs
+// holds when they have waited, see sel_rest_kernel), or of what one launch leaves the next.
+template <bool DEV>
+__device__ __forceinline__ void sel_put(uint32_t* p, uint32_t v) {
+    if (DEV) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); else *p = v;
+}
+template <bool DEV>
+__device__ __forceinline__ void sel_put(uint2* p, uint2 v) {
+    if (DEV) store_device(p, v); else *p = v;
+}
+static_assert(sizeof(SelWindow) % 8 == 0, "moved by eight bytes");
+template <bool DEV>
+__device__ __forceinline__ void sel_put(SelWindow* p, const SelWindow& W) {
+    if (!DEV) { *p = W; return; }
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(SelWindow) / 8u; ++i)
+        store_device(reinterpret_cast<uint2*>(p) + i, reinterpret_cast<const uint2*>(&W)[i]);
+}
+
+struct SelShared {
     // bytes of the map: first of the stage's windows, in order, that lies in that top bin
-    __shared__ __align__(16) uint8_t s_map[SEL_BINS + 16u];
-    __shared__ uint32_t s_hist[SEL_BINS];
-    __shared__ __align__(16) uint2 s_pair[SEL_STAGE_CAP];
-    __shared__ uint8_t s_of[SEL_STAGE_CAP];
-    __shared__ SelWindow s_win[MAXK];
-    __shared__ uint64_t s_lo[MAXK];       // of the windows in order: the first composite,
-    __shared__ uint32_t s_about[MAXK];    // what else the walk needs
-    __shared__ uint64_t smem[SEL_THREADS / 64 + 1];
-    __shared__ uint32_t s_cnt[MAXK], s_base[MAXK], s_key_lo[MAXK], s_key_hi[MAXK], s_n, s_left, s_ties;
-    if (stage > 1u && st->done[stage - 1u]) {
-        if (blockIdx.x == 0 && threadIdx.x == 0) st->done[stage] = 1;
-        return;
-    }
+    alignas(16) uint8_t map[SEL_BINS + 16u];
+    uint32_t hist[SEL_BINS];
+    alignas(16) uint2 pair[SEL_STAGE_CAP];
+    uint8_t of[SEL_STAGE_CAP];
+    SelWindow win[MAXK];
+    uint64_t lo[MAXK];       // of the windows in order: the first composite,
+    uint32_t about[MAXK];    // what else the walk needs
+    uint64_t smem[SEL_THREADS / 64 + 1];
+    uint32_t cnt[MAXK], base[MAXK], key_lo[MAXK], key_hi[MAXK], n, left, ties;
+};
+
+// What the stages and the ranking of the lists work on.
+struct SelJob {
+    SelState* st;
+    uint32_t* ghist;
+    uint2* lists;
+    uint32_t list_cap, k, n_weights, g_bits, stages;
+};
+
+// The windows of a stage from the histograms of the stage before: the same in every block, and one of them publishes
+// them.
+template <bool FIRST, bool DEV>
+__device__ __forceinline__ void sel_windows(const SelJob& J, SelShared& S, uint32_t stage, bool publish) {
+    SelState* const st = J.st;
+    const uint32_t* const ghist = J.ghist;
+    const uint32_t k = J.k, g_bits = J.g_bits, list_cap = J.list_cap, stages = J.stages, n_weights = J.n_weights;
     const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
     const uint32_t bits = sel_bits(k);
     if (threadIdx.x < MAXK) {
         SelWindow W;
         W.c_lo = W.r = W.less = W.key_less = W.key_eq = W.cnt = 0;
         W.width = 0; W.leader = threadIdx.x; W.mode = SEL_IDLE; W.stage = 0;
-        s_win[threadIdx.x] = W;
-        s_cnt[threadIdx.x] = 0;
-        s_key_lo[threadIdx.x] = 0xffffffffu;
-        s_key_hi[threadIdx.x] = 0;
+        S.win[threadIdx.x] = W;
+        S.cnt[threadIdx.x] = 0;
+        S.key_lo[threadIdx.x] = 0xffffffffu;
+        S.key_hi[threadIdx.x] = 0;
     }
-    if (threadIdx.x == 0) { s_n = 0; s_left = 0; s_ties = 0; }
-    if (stage == 1u) {
+    if (threadIdx.x == 0) { S.n = 0; S.left = 0; S.ties = 0; }
+    if (FIRST) {
         // sixteen bins per thread, their exclusive prefix over the block (in the room of the
         // pairs), then a search per rank
-        uint64_t* base_of = reinterpret_cast<uint64_t*>(s_pair);
-        static_assert(sizeof(s_pair) >= sizeof(uint64_t) * SEL_THREADS && SEL_BINS == 16u * SEL_THREADS, "prefix");
+        uint64_t* base_of = reinterpret_cast<uint64_t*>(S.pair);
+        static_assert(sizeof(SelShared::pair) >= sizeof(uint64_t) * SEL_THREADS && SEL_BINS == 16u * SEL_THREADS, "prefix");
         const uint4* h4 = reinterpret_cast<const uint4*>(ghist) + threadIdx.x * 4u;
         uint64_t sum = 0, tot;
 #pragma unroll
         for (uint32_t i = 0; i < 4u; ++i) { const uint4 x = h4[i]; sum += (uint64_t)x.x + x.y + x.z + x.w; }
         const uint64_t n_zero = st->n_zero;
-        base_of[threadIdx.x] = n_zero + block_excl_scan_u64<SEL_THREADS>(sum, smem, &tot);
+        base_of[threadIdx.x] = n_zero + block_excl_scan_u64<SEL_THREADS>(sum, S.smem, &tot);
         __syncthreads();
         if (threadIdx.x < k) {
             const uint64_t r = st->p[threadIdx.x];
@@ -267,7 +355,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
                 W.r = r;
                 W.key_eq = W.cnt = n_zero;
                 W.width = 32u;
-                s_win[threadIdx.x] = W;
+                S.win[threadIdx.x] = W;
             } else if (r != 0 && r <= n_zero + tot) {
                 uint32_t a = 0, b = SEL_THREADS;              // last thread whose base is below r
                 while (b - a > 1u) {
@@ -286,13 +374,12 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
                     if (base < r && r <= base + c[i]) { bin = a * 16u + i; cnt = c[i]; below = base; }
                     base += c[i];
                 }
-                // the bins at both ends of the binning span up to 2^30 keys; zeros are not in theirs
-                W.c_lo = (uint64_t)max(sample_bin_first_key(bin), 1u) << 32;
-                W.width = (bin == 0u || bin == SAMPLE_BINS - 1u) ? SEL_MAX_WIDTH : 32u + SAMPLE_BIN_SHIFT;
+                W.c_lo = (uint64_t)sel_bin_first_key(bin) << 32;
+                W.width = sel_bin_width(bin);
                 W.r = r - below;
                 W.less = below;
                 W.cnt = cnt;
-                s_win[threadIdx.x] = W;
+                S.win[threadIdx.x] = W;
             }
         }
     } else {
@@ -300,55 +387,70 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
         __syncthreads();
         const uint32_t nb = 1u << bits, per = nb / 64u;       // 4 .. 64 bins per lane
         for (uint32_t q = wid; q < k; q += SEL_THREADS / 64u) {
-            const SelWindow W = st->win[stage - 1u][q];
-            if (W.mode != SEL_SPLIT) continue;
-            const uint32_t key = st->key_lo[stage - 1u][W.leader];
-            if (W.stage != 0u && W.width > 32u && key == st->key_hi[stage - 1u][W.leader]) {
+            const SelWindow& was = st->win[stage - 1u][q];
+            if (was.mode != SEL_SPLIT) continue;
+            SelWindow& W = S.win[q];
+            const uint32_t leader = was.leader, width = was.width;
+            const uint64_t r = was.r;
+            const uint32_t key = st->key_lo[stage - 1u][leader];
+            if (was.stage != 0u && width > 32u && key == st->key_hi[stage - 1u][leader]) {
                 // all its weights are equal: on with the index
                 if (lane == 0) {
-                    SelWindow V = W;
-                    V.c_lo = (uint64_t)key << 32;
-                    V.width = 32u;
-                    V.key_less = W.less;
-                    V.key_eq = W.cnt;
-                    s_win[q] = V;
+                    W.c_lo = (uint64_t)key << 32;
+                    W.r = r;
+                    W.less = W.key_less = was.less;
+                    W.cnt = W.key_eq = was.cnt;
+                    W.width = 32u;
+                    W.mode = SEL_SPLIT;
                 }
                 continue;
             }
-            const uint32_t* hist = ghist + (size_t)(stage - 1u) * SEL_BINS + W.leader * nb + lane * per;
+            const uint32_t* hist = ghist + (size_t)(stage - 1u) * SEL_BINS + leader * nb;
             uint64_t sum = 0;
-            for (uint32_t i = 0; i < per; ++i) sum += hist[i];
+#pragma unroll 4
+            for (uint32_t i = 0; i < per; i += 2u) {
+                const uint2 c = *reinterpret_cast<const uint2*>(hist + lane * per + i);
+                sum += (uint64_t)c.x + c.y;
+            }
             unsigned long long incl = sum;
             for (uint32_t d = 1; d < 64; d <<= 1) {
                 const unsigned long long y = __shfl_up(incl, d, 64);
                 if (lane >= d) incl += y;
             }
-            uint64_t base = incl - sum;
-            if (base < W.r && W.r <= incl) {
-                uint32_t i = 0, c = hist[0];
-                while (W.r > base + c) { base += c; c = hist[++i]; }
-                const uint32_t shift = sel_shift(W.width, bits, g_bits);
-                SelWindow V = W;
-                V.c_lo = W.c_lo + ((uint64_t)(lane * per + i) << shift);
-                V.r = W.r - base;
-                V.less = W.less + base;
-                V.cnt = c;
-                V.width = shift;
-                if (shift == 32u) { V.key_less = V.less; V.key_eq = c; }
-                s_win[q] = V;
+            const uint64_t at = __ballot(incl - sum < r && r <= incl);
+            if (at == 0ull) continue;
+            // that lane's bins, one to a lane
+            const uint32_t owner = (uint32_t)__ffsll((unsigned long long)at) - 1u;
+            const uint64_t below = __shfl((unsigned long long)(incl - sum), (int)owner, 64);
+            const uint32_t c = lane < per ? hist[owner * per + lane] : 0u;
+            incl = c;
+            for (uint32_t d = 1; d < 64; d <<= 1) {
+                const unsigned long long y = __shfl_up(incl, d, 64);
+                if (lane >= d) incl += y;
+            }
+            const uint64_t base = below + incl - c;
+            if (base < r && r <= base + c) {
+                const uint32_t shift = sel_shift(width, bits, g_bits);
+                W.c_lo = was.c_lo + ((uint64_t)(owner * per + lane) << shift);
+                W.r = r - base;
+                W.less = was.less + base;
+                W.cnt = c;
+                W.width = shift;
+                W.key_less = shift == 32u ? W.less : was.key_less;
+                W.key_eq = shift == 32u ? c : was.key_eq;
+                W.mode = SEL_SPLIT;
             }
         }
     }
     // no window in a top bin yet
     static_assert(SEL_BINS == 16u * SEL_THREADS, "one 16-byte piece of the map per thread");
-    reinterpret_cast<uint4*>(s_map)[threadIdx.x] = make_uint4(~0u, ~0u, ~0u, ~0u);
-    if (threadIdx.x == 0) s_map[SEL_BINS] = (uint8_t)NONE8;
-    for (uint32_t i = threadIdx.x; i < SEL_BINS; i += SEL_THREADS) s_hist[i] = 0;
+    reinterpret_cast<uint4*>(S.map)[threadIdx.x] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    if (threadIdx.x == 0) S.map[SEL_BINS] = (uint8_t)NONE8;
     __syncthreads();
     // the windows in order: the ranks are sorted, so equal windows are neighbours (the first rank
     // leads) and those in one top bin follow each other
     if (wid == 0) {
-        const SelWindow W = s_win[lane];
+        const SelWindow W = S.win[lane];
         const bool live = W.mode == SEL_SPLIT;
         const uint64_t prev_lo = __shfl_up((unsigned long long)W.c_lo, 1, 64);
         const uint32_t prev_live = __shfl_up(live ? 1u : 0u, 1, 64), prev_w = __shfl_up(W.width, 1, 64);
@@ -366,53 +468,75 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
         const uint32_t in_top = (uint32_t)__popcll(open_mask & here & (~0ull << lane));
         if (live) {
             const uint32_t mode = W.cnt <= (stage < stages ? min(list_cap, SEL_LIST_GOOD) : list_cap) ? SEL_LISTED : SEL_SPLIT;
-            s_win[lane].leader = leader;
-            s_win[lane].mode = mode;
+            S.win[lane].leader = leader;
+            S.win[lane].mode = mode;
             // more weights than any spread-out distribution has in 1/256 of a binade, or one key
             const bool ties = W.width <= 32u || W.cnt > (n_weights >> 7);
-            s_win[lane].stage = ties ? stage : 0u;
-            if (ties) s_ties = 1;
+            S.win[lane].stage = ties ? stage : 0u;
+            if (ties) S.ties = 1;
             if (opens) {
                 const uint32_t at = (uint32_t)__popcll(before);
-                s_lo[at] = W.c_lo;
-                s_about[at] = W.width | (sel_shift(W.width, bits, g_bits) << 6) | (mode == SEL_SPLIT ? SEL_ABOUT_SPLIT : 0u) |
-                              (ties ? SEL_ABOUT_TIES : 0u) | (W.cnt > (n_weights >> 4) ? SEL_ABOUT_RUNS : 0u) | (lane << 16) | (in_top << 24);
-                if (first) s_map[top] = (uint8_t)at;
+                S.lo[at] = W.c_lo;
+                S.about[at] = W.width | (sel_shift(W.width, bits, g_bits) << 6) | (mode == SEL_SPLIT ? SEL_ABOUT_SPLIT : 0u) |
+                              (ties ? SEL_ABOUT_TIES : 0u) | (W.cnt > (n_weights >> 4) ? SEL_ABOUT_RUNS : 0u) |
+                              (lane << 16) | (in_top << 24);
+                if (first) S.map[top] = (uint8_t)at;
             }
-            if (mode == SEL_SPLIT) s_left = 1;
+            if (mode == SEL_SPLIT) S.left = 1;
         }
     }
     __syncthreads();
-    if (blockIdx.x == 0) {
+    if (publish) {
         if (threadIdx.x < k) {
-            const SelWindow W = s_win[threadIdx.x];
-            st->win[stage][threadIdx.x] = W;
-            if (W.mode == SEL_LISTED) st->fin[threadIdx.x] = W;
+            const SelWindow W = S.win[threadIdx.x];
+            sel_put<DEV>(&st->win[stage][threadIdx.x], W);
+            if (W.mode == SEL_LISTED) sel_put<DEV>(&st->fin[threadIdx.x], W);
         }
-        if (threadIdx.x == 0) st->done[stage] = s_left ? 0u : 1u;
+        if (threadIdx.x == 0) sel_put<DEV>(&st->done[stage], S.left ? 0u : 1u);
     }
+    if (S.left) {                                 // the same in every thread
+        for (uint32_t i = threadIdx.x; i < (k << bits); i += SEL_THREADS) S.hist[i] = 0;
+        __syncthreads();
+    }
+}
+
+// The weights of a part into the stage's histograms and lists.
+template <bool DEV>
+struct SelCollect {
+    const SelJob& J;
+    SelShared& S;
     RunCount run;
     KeyRange keys;
+    __device__ __forceinline__ SelCollect(const SelJob& job, SelShared& shared) : J(job), S(shared) {}
+    __device__ __forceinline__ void part(const SelArena& arena, uint32_t part, uint32_t parts);
+    __device__ __forceinline__ void leave(uint32_t stage);
+};
+template <bool DEV>
+__device__ __forceinline__ void SelCollect<DEV>::part(const SelArena& arena, uint32_t part, uint32_t parts) {
+    SelWalk walk(arena);
+    SelState* const st = J.st;
+    uint2* const lists = J.lists;
+    const uint32_t lane = threadIdx.x & 63u, bits = sel_bits(J.k), list_cap = J.list_cap;
     auto one = [&](uint32_t wbits, uint32_t g) {
         const uint32_t key = wbits & 0x7fffffffu;
-        uint32_t i = s_map[top_bin(key)];
+        uint32_t i = S.map[top_bin(key)];
         if (i == NONE8) return;
         const uint64_t comp = ((uint64_t)key << 32) | g;
-        uint32_t about = s_about[i];
+        uint32_t about = S.about[i];
         if (about >= 2u << 24) {                    // several windows in this top bin: the last that begins by here
             for (uint32_t n = about >> 24; n > 1u;) {
                 const uint32_t half = n >> 1;
-                if (s_lo[i + half] <= comp) { i += half; n -= half; } else { n = half; }
+                if (S.lo[i + half] <= comp) { i += half; n -= half; } else { n = half; }
             }
-            about = s_about[i];
+            about = S.about[i];
         }
-        const uint64_t d = comp - s_lo[i];
+        const uint64_t d = comp - S.lo[i];
         if ((d >> (about & 63u)) != 0) return;
         const uint32_t s = (about >> 16) & 0xffu;
         if (about & SEL_ABOUT_SPLIT) {
             const uint32_t entry = (s << bits) + (uint32_t)(d >> ((about >> 6) & 63u));
-            if (about & SEL_ABOUT_RUNS) run.add(s_hist, entry, 1u); else atomicAdd(&s_hist[entry], 1u);
-            if (about & SEL_ABOUT_TIES) keys.add(s_key_lo, s_key_hi, s, key);
+            if (about & SEL_ABOUT_RUNS) run.add(S.hist, entry, 1u); else atomicAdd(&S.hist[entry], 1u);
+            if (about & SEL_ABOUT_TIES) keys.add(S.key_lo, S.key_hi, s, key);
             return;
         }
         // one reservation for the lanes that list a pair now, if they are many
@@ -420,17 +544,17 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
         const uint64_t all = __ballot(true);
         if (__popcll(all) > 16) {
             const uint32_t before = (uint32_t)__popcll(all & ((1ull << lane) - 1ull));
-            if (before == 0) pos = atomicAdd(&s_n, (uint32_t)__popcll(all));
+            if (before == 0) pos = atomicAdd(&S.n, (uint32_t)__popcll(all));
             pos = __shfl(pos, (int)__ffsll((unsigned long long)all) - 1, 64) + before;
         } else {
-            pos = atomicAdd(&s_n, 1u);
+            pos = atomicAdd(&S.n, 1u);
         }
         if (pos < SEL_STAGE_CAP) {
-            s_pair[pos] = make_uint2(wbits, g);
-            s_of[pos] = (uint8_t)s;
+            S.pair[pos] = make_uint2(wbits, g);
+            S.of[pos] = (uint8_t)s;
             return;
         }
-        if (about & SEL_ABOUT_TIES) keys.add(s_key_lo, s_key_hi, s, key);
+        if (about & SEL_ABOUT_TIES) keys.add(S.key_lo, S.key_hi, s, key);
         // more than the block's share (weights that are sorted or clustered by size): straight
         // to the list, one reservation for the lanes that meet at it
         // (the base comes to a lane by its own group's leader: the compiler may take the end of
@@ -445,54 +569,60 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
         uint32_t base = 0;
         if (rank == 0) base = atomicAdd(&st->list_cnt[s], (uint32_t)__popcll(peers));
         const uint32_t at = __shfl(base, (int)__ffsll((unsigned long long)peers) - 1, 64) + rank;
-        if (at < list_cap) lists[(size_t)s * list_cap + at] = make_uint2(wbits, g);
+        if (at < list_cap) sel_put<DEV>(&lists[(size_t)s * list_cap + at], make_uint2(wbits, g));
     };
-    sel_walk(tens, tile_prefix, n_t, n_tiles, w, [&](const uint4 (&v)[SEL_QUADS], uint32_t g) {
+    walk.run(part, parts, [&] {
+        const uint4 (&v)[SEL_QUADS] = walk.v;
         // first which of the sixteen are met by a window, without a branch, then those one by one: few are,
         // and the long body stands here once (in line sixteen times: 20 ranks of 14.7 M weights 34 us, 24 so; 30
         // levels a sigma, one rank of 100 M 134 and 92; all 100 M equal 170 and 265)
-        static_assert(SEL_QUADS == 4u, "sixteen weights");
         uint32_t met = 0;
 #pragma unroll
         for (uint32_t u = 0; u < 4u; ++u) {
             const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
-            for (uint32_t q = 0; q < 4u; ++q) met |= (s_map[top_bin(x[q] & 0x7fffffffu)] != NONE8 ? 1u : 0u) << (4u * u + q);
+            for (uint32_t q = 0; q < 4u; ++q) met |= (S.map[top_bin(x[q] & 0x7fffffffu)] != NONE8 ? 1u : 0u) << (4u * u + q);
         }
+        if (walk.n != TILE) met &= walk.there();
         while (met) {
             const uint32_t j = (uint32_t)__builtin_ctz(met);
             met &= met - 1u;
-            const uint32_t u = j >> 2, q = j & 3u;
-            const uint4 lo = (u & 1u) ? v[1] : v[0], hi = (u & 1u) ? v[3] : v[2], x = (u & 2u) ? hi : lo;
-            const uint32_t a = (q & 1u) ? x.y : x.x, b = (q & 1u) ? x.w : x.z;
-            one((q & 2u) ? b : a, g + 4u * BLOCK * u + q);
+            one(walk.bits(j), walk.index(j));
         }
-    }, one);
-    run.flush(s_hist);
-    keys.flush(s_key_lo, s_key_hi);
+    });
+}
+
+// What the block has gathered goes to memory.
+template <bool DEV>
+__device__ __forceinline__ void SelCollect<DEV>::leave(uint32_t stage) {
+    SelState* const st = J.st;
+    uint2* const lists = J.lists;
+    const uint32_t k = J.k, bits = sel_bits(J.k), list_cap = J.list_cap;
+    run.flush(S.hist);
+    keys.flush(S.key_lo, S.key_hi);
     __syncthreads();
     constexpr uint32_t PER = SEL_STAGE_CAP / SEL_THREADS;
-    const uint32_t n = min(s_n, SEL_STAGE_CAP);
-    if (s_ties) {
+    const uint32_t n = min(S.n, SEL_STAGE_CAP);
+    if (S.ties) {
 #pragma unroll
         for (uint32_t u = 0; u < PER; ++u) {
             const uint32_t i = u * SEL_THREADS + threadIdx.x;
             if (i < n) {
-                const uint32_t key = s_pair[i].x & 0x7fffffffu, s = s_of[i];
-                if (key < s_key_lo[s]) atomicMin(&s_key_lo[s], key);
-                if (key > s_key_hi[s]) atomicMax(&s_key_hi[s], key);
+                const uint32_t key = S.pair[i].x & 0x7fffffffu, s = S.of[i];
+                if (key < S.key_lo[s]) atomicMin(&S.key_lo[s], key);
+                if (key > S.key_hi[s]) atomicMax(&S.key_hi[s], key);
             }
         }
         __syncthreads();
-        if (threadIdx.x < k && s_key_lo[threadIdx.x] <= s_key_hi[threadIdx.x]) {
-            atomicMin(&st->key_lo[stage][threadIdx.x], s_key_lo[threadIdx.x]);
-            atomicMax(&st->key_hi[stage][threadIdx.x], s_key_hi[threadIdx.x]);
+        if (threadIdx.x < k && S.key_lo[threadIdx.x] <= S.key_hi[threadIdx.x]) {
+            atomicMin(&st->key_lo[stage][threadIdx.x], S.key_lo[threadIdx.x]);
+            atomicMax(&st->key_hi[stage][threadIdx.x], S.key_hi[threadIdx.x]);
         }
     }
-    if (s_left) {
-        uint32_t* out = ghist + (size_t)stage * SEL_BINS;
+    if (S.left) {
+        uint32_t* out = J.ghist + (size_t)stage * SEL_BINS;
         for (uint32_t i = threadIdx.x; i < (k << bits); i += SEL_THREADS) {
-            const uint32_t c = s_hist[i];
+            const uint32_t c = S.hist[i];
             if (c) atomicAdd(&out[i], c);
         }
     }
@@ -502,27 +632,26 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(
 #pragma unroll
     for (uint32_t u = 0; u < PER; ++u) {
         const uint32_t i = u * SEL_THREADS + threadIdx.x;
-        pos[u] = i < n ? atomicAdd(&s_cnt[s_of[i]], 1u) : 0u;
+        pos[u] = i < n ? atomicAdd(&S.cnt[S.of[i]], 1u) : 0u;
     }
     __syncthreads();
-    if (threadIdx.x < k && s_cnt[threadIdx.x]) s_base[threadIdx.x] = atomicAdd(&st->list_cnt[threadIdx.x], s_cnt[threadIdx.x]);
+    if (threadIdx.x < k && S.cnt[threadIdx.x]) S.base[threadIdx.x] = atomicAdd(&st->list_cnt[threadIdx.x], S.cnt[threadIdx.x]);
     __syncthreads();
 #pragma unroll
     for (uint32_t u = 0; u < PER; ++u) {
         const uint32_t i = u * SEL_THREADS + threadIdx.x;
         if (i < n) {
-            const uint32_t s = s_of[i], at = s_base[s] + pos[u];
-            if (at < list_cap) lists[(size_t)s * list_cap + at] = s_pair[i];
+            const uint32_t s = S.of[i], at = S.base[s] + pos[u];
+            if (at < list_cap) sel_put<DEV>(&lists[(size_t)s * list_cap + at], S.pair[i]);
         }
     }
 }
 
-// One block per rank: the record from its list.
-__global__ __launch_bounds__(SEL_THREADS) void sel_final_kernel(
-    const SelState* __restrict__ st, const uint2* __restrict__ lists, uint32_t list_cap, uint32_t g_bits,
-    shifter_threshold* __restrict__ thr, shifter_threshold* host_rec, uint32_t* host_nan) {
-    __shared__ RankShared<SEL_THREADS> sh;
-    const uint32_t q = blockIdx.x;
+// The record of rank q, by one block, from its list.
+__device__ __forceinline__ void sel_record(const SelJob& J, uint32_t q, RankShared<SEL_THREADS>& sh,
+                                           shifter_threshold* __restrict__ thr, shifter_threshold* host_rec, uint32_t* host_nan) {
+    const SelState* const st = J.st;
+    const uint32_t list_cap = J.list_cap;
     shifter_threshold out;
     out.cut = 0; out.t_key = 0; out.reserved = 0; out.g_cut = ~0ull; out.n_less = 0; out.n_equal = 0;
     out.n_prune = st->p[q];
@@ -540,10 +669,10 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_final_kernel(
                 if (lo == hi) { key_less = W.less; key_eq = W.cnt; }
             }
             const bool one_key = width <= 32u;
-            if (width == 32u) width = g_bits;
+            if (width == 32u) width = J.g_bits;
             // the window's pairs are all in the list: the r-th of them is the pair
-            if (rank_in_list<SEL_THREADS, 4>(lists + (size_t)W.leader * list_cap, min((uint32_t)W.cnt, list_cap), c_lo,
-                                             width, W.r, !one_key, sh)) {
+            if (rank_in_list<SEL_THREADS, SEL_DEPTH>(J.lists + (size_t)W.leader * list_cap, min((uint32_t)W.cnt, list_cap),
+                                                          c_lo, width, W.r, !one_key, sh)) {
                 out.cut = sh.sel + 1;
                 out.t_key = (uint32_t)(sh.sel >> 32);
                 out.g_cut = sh.sel & 0xffffffffull;
@@ -560,12 +689,100 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_final_kernel(
     }
 }
 
+// The first stage, or the second in a launch of its own (see launch_select_tables).
+template <uint32_t STAGE>
+__global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(const SelArena arena, const SelJob J) {
+    __shared__ SelShared S;
+    if (STAGE > 1u && J.st->done[STAGE - 1u]) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) J.st->done[STAGE] = 1;
+        return;
+    }
+    sel_windows<STAGE == 1u, false>(J, S, STAGE, blockIdx.x == 0);
+    SelCollect<false> collect(J, S);
+    collect.part(arena, blockIdx.x, gridDim.x);
+    collect.leave(STAGE);
+}
+
+// The ranking of the lists, a block each, where the first stage certainly lists every rank.
+__global__ __launch_bounds__(SEL_THREADS) void sel_final_kernel(const SelJob J, shifter_threshold* __restrict__ thr,
+                                                                shifter_threshold* host_rec, uint32_t* host_nan) {
+    __shared__ RankShared<SEL_THREADS> sh;
+    sel_record(J, blockIdx.x, sh, thr, host_rec, host_nan);
+}
+
+// The ranking of the lists, a block each.  Where the stages before have not listed every rank (many weights in one bin, equal
+// ones mostly), the further stages come first, in the same launch: with a launch for each, the four that found nothing left
+// took 4 us each of a call that has no ties (ten counts of 14.7 M weights, flat run, 64 us with them, 56 without).  There
+// the parts of a stage are handed out by a ticket, and a block that finds none left waits until all that were taken have
+// arrived.  Every wait ends, however many of the blocks run at a time: a part is only ever held by a block that runs,
+// and that leaves what it has gathered before it waits for its stage; what it may hold then is a part of the next stage,
+// for which nobody waits before this one is over.
+__global__ __launch_bounds__(SEL_THREADS) void sel_rest_kernel(const SelArena arena, const SelJob J, uint32_t before, uint32_t parts,
+                                                               shifter_threshold* __restrict__ thr, shifter_threshold* host_rec,
+                                                               uint32_t* host_nan) {
+    __shared__ SelShared S;
+    __shared__ RankShared<SEL_THREADS> sh;
+    __shared__ uint32_t s_take;
+    SelState* const st = J.st;
+    if (st->done[before]) {
+        if (blockIdx.x < J.k) sel_record(J, blockIdx.x, sh, thr, host_rec, host_nan);
+        return;
+    }
+    // a ticket is drawn while the block still works on what it has, and looked at by all when it is wanted
+    uint32_t drawn = 0;
+    auto draw = [&](uint32_t* ticket) {
+        if (threadIdx.x == 0) drawn = atomicAdd(ticket, 1u);
+    };
+    auto taken = [&]() {
+        __syncthreads();
+        if (threadIdx.x == 0) s_take = drawn;
+        __syncthreads();
+        return uniform_u32(s_take);
+    };
+    draw(&st->ticket[before + 1u]);
+    for (uint32_t stage = before + 1u;; ++stage) {
+        uint32_t part = taken(), mine = 0;
+        if (part < parts) {
+            sel_windows<false, true>(J, S, stage, part == 0);
+            SelCollect<true> collect(J, S);
+            for (; part < parts; part = taken(), ++mine) {
+                draw(&st->ticket[stage]);
+                collect.part(arena, part, parts);
+            }
+            collect.leave(stage);
+            wait_memory();
+            __syncthreads();
+            // the last to arrive says so on several lines: polls at the counter's own would hold up its additions
+            if (threadIdx.x == 0) s_take = atomicAdd(&st->arrived[stage], mine) + mine;
+            __syncthreads();
+            if (s_take == parts && threadIdx.x < SEL_GO) sel_put<true>(&st->go[stage][threadIdx.x * SEL_GO_WORDS], 1u);
+        }
+        const bool last = stage == J.stages;
+        draw(&st->ticket[last ? 0u : stage + 1u]);
+        if (threadIdx.x == 0) {
+            while (!__hip_atomic_load(&st->go[stage][blockIdx.x % SEL_GO * SEL_GO_WORDS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                __builtin_amdgcn_s_sleep(8);
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        __syncthreads();
+        if (last) break;
+        if (st->done[stage]) {               // the same in every thread
+            draw(&st->ticket[0]);
+            break;
+        }
+    }
+    for (uint32_t q = taken(); q < J.k; q = taken()) {
+        sel_record(J, q, sh, thr, host_rec, host_nan);
+        draw(&st->ticket[0]);
+    }
+}
+
 void launch_select(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
                    const PruneCounts& pc, uint32_t k, shifter_threshold* d_thr, bool mirror, uint32_t* zero_ptr,
                    uint32_t zero_n) {
     const auto& b = m->b;
     // the candidate buffer of the single-pass selections is idle here: it holds the lists
-    const SelectTables tb{b.tens, b.tile_prefix, (uint32_t)m->t.size(), m->n_tiles, m->info.n_prunable, b.sel, b.ghist,
+    const SelectTables tb{b.tens, b.tile_prefix, b.tile_tensor, m->n_tiles, m->info.n_prunable, b.sel, b.ghist,
                           b.cand, (uint64_t)b.cand_cap_sb * SPEC_SUB, nullptr, nullptr, zero_ptr, zero_n,
                           mirror ? b.dev_multi_rec : nullptr, mirror ? b.dev_multi_status : nullptr};
     launch_select_tables(ctx, tb, d_w, pc, k, d_thr);
@@ -573,7 +790,7 @@ void launch_select(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
 
 void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float* d_w,
                           const PruneCounts& pc, uint32_t k, shifter_threshold* d_thr) {
-    const uint32_t n_t = tb.n_t, n_tiles = tb.n_tiles;
+    const uint32_t n_tiles = tb.n_tiles;
     hipStream_t s = ctx->stream;
     uint32_t idx[MAXK];
     for (uint32_t i = 0; i < k; ++i) idx[i] = i;
@@ -584,6 +801,11 @@ void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float*
     const uint32_t g_bits = sel_g_bits(tb.n_weights), list_cap = sel_list_cap(tb.list_pairs, k);
     const uint32_t stages = sel_stages(tb.n_weights, k, tb.list_pairs);
     const uint32_t grid = std::max(1u, std::min((n_tiles + SEL_GROUPS - 1) / SEL_GROUPS, ctx->hist_grid));
+    const SelArena arena{tb.tens, tb.tile_prefix, tb.tile_tensor, n_tiles, d_w};
+    const SelJob job{tb.sel, tb.ghist, tb.lists, list_cap, k, (uint32_t)tb.n_weights, g_bits, stages};
+    // At most 1/1536 of spread-out weights lie in one bin: where that is more than a good list, the first stage will hardly list
+    // them all, and a launch costs the second one less than the tickets (ten of 100 M weights 252 us, 268 with them)
+    const uint32_t before = stages > 1u && tb.n_weights / 1536u > std::min(list_cap, SEL_LIST_GOOD) ? 2u : 1u;
     {
         ProfileScope p(ctx, K_SEL_INIT);
         sel_clear_kernel<<<64, BLOCK, 0, s>>>(tb.sel, tb.ghist, stages, sorted, perm, k, tb.flat_tens, tb.flat_prefix,
@@ -591,16 +813,17 @@ void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float*
     }
     {
         ProfileScope p(ctx, K_HIST0);
-        sel_top_kernel<<<grid, SEL_THREADS, 0, s>>>(tb.tens, tb.tile_prefix, n_t, n_tiles, d_w, tb.sel, tb.ghist);
+        sel_top_kernel<<<grid, SEL_THREADS, 0, s>>>(arena, tb.sel, tb.ghist);
     }
-    for (uint32_t stage = 1; stage <= stages; ++stage) {
+    {
         ProfileScope p(ctx, K_SEL_STAGE);
-        sel_stage_kernel<<<grid, SEL_THREADS, 0, s>>>(tb.tens, tb.tile_prefix, n_t, n_tiles, d_w, tb.sel, tb.ghist,
-                                                      tb.lists, list_cap, k, (uint32_t)tb.n_weights, g_bits, stage, stages);
+        sel_stage_kernel<1><<<grid, SEL_THREADS, 0, s>>>(arena, job);
+        if (before == 2u) sel_stage_kernel<2><<<grid, SEL_THREADS, 0, s>>>(arena, job);
     }
     {
         ProfileScope p(ctx, K_SEL_FINAL);
-        sel_final_kernel<<<k, SEL_THREADS, 0, s>>>(tb.sel, tb.lists, list_cap, g_bits, d_thr, tb.host_rec, tb.host_nan);
+        if (stages <= before) sel_final_kernel<<<k, SEL_THREADS, 0, s>>>(job, d_thr, tb.host_rec, tb.host_nan);
+        else sel_rest_kernel<<<std::max(grid, k), SEL_THREADS, 0, s>>>(arena, job, before, grid, d_thr, tb.host_rec, tb.host_nan);
     }
 }
 
