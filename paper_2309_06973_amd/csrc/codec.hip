@@ -768,12 +768,9 @@ __global__ __launch_bounds__(64) void codec_pack_kernel(const uint8_t* __restric
     if (lane < len - done) dst[done + lane] = src[done + lane];
 }
 
-// Dwords of a segment kept in LDS by the three instances of the decoder: 4.5 KiB (with the
-// chunk's image and the token table just under 40 KiB, four blocks per CU), 16 KiB and a
-// whole segment.  The less LDS, the more chunks a CU works on at a time.
+// Dwords of the longest segment that the decoder's instance for chunks of few tokens takes (4.5 KiB): it keeps the segment in
+// LDS, and no image of the chunk.
 constexpr uint32_t CODEC_SEG_SMALL = 1152;
-constexpr uint32_t CODEC_SEG_MEDIUM = 4096;
-constexpr uint32_t CODEC_SEG_LARGE = (CODEC_SLOT + 3) / 4 + 3;
 // n <= 32 bits at bit position pos of the staged segment
 __device__ __forceinline__ uint32_t seg_peek(const uint32_t* s_seg, uint32_t pos, uint32_t n) {
     const uint32_t w = pos >> 5, sh = pos & 31u;
@@ -828,100 +825,187 @@ __device__ __forceinline__ uint32_t img_byte(uint32_t l, uint32_t k) {
     return sub_word(l, k >> 2) * 4u + (k & 3u);
 }
 
-struct InflateShared {
-    uint32_t* img;      // CODEC_CHUNK / 4: the chunk being produced
-    uint32_t* seg;      // SEG_DW: the segment
-    uint32_t* tab;      // 512: token table
-    uint32_t* start;    // CODEC_NSUB: bit 31 = a block is open there
-    uint32_t* misc;     // segment bytes, tail start, tail in block
+// A chunk's segment as the decoder sees it: dwords aligned to the stream's start.  The stream's last dword
+// may be partly beyond stream_bytes: an aligned dword never crosses a page, and what lies beyond the segment is
+// never interpreted.
+struct Segment {
+    const uint32_t* dw;
+    uint64_t s0;
+    uint32_t len;       // bytes; 0: not a segment
+    uint32_t byte0;     // of dw where it begins
+    uint32_t max_w;     // last readable dword
+};
+__device__ __forceinline__ Segment segment_of(const uint8_t* __restrict__ stream, uint64_t stream_bytes, uint64_t s0, uint64_t s1) {
+    Segment g;
+    g.s0 = s0;
+    g.len = s1 < s0 || s1 > stream_bytes || s1 - s0 < 5u || s1 - s0 > CODEC_SLOT ? 0u : (uint32_t)(s1 - s0);
+    g.byte0 = (uint32_t)(s0 & 3u);
+    g.dw = reinterpret_cast<const uint32_t*>(stream + (s0 & ~(uint64_t)3u));
+    g.max_w = (uint32_t)(((stream_bytes + 3u) / 4u) - (s0 >> 2)) - 1u;
+    return g;
+}
+// Dwords of a segment to be staged: two more for the look-ahead.
+__device__ __forceinline__ uint32_t segment_words(uint32_t byte0, uint32_t len) { return (byte0 + len + 3u) / 4u + 2u; }
+
+__device__ __forceinline__ void bad_stream(uint64_t* result) {
+    atomicOr(reinterpret_cast<unsigned long long*>(&result[1]), (unsigned long long)CODEC_BAD_STREAM);
+}
+
+// A chunk in one stored block, copied by the block's threads.
+__device__ __forceinline__ void inflate_whole(const Segment& g, const uint8_t* __restrict__ stream, uint32_t my_side, uint32_t m,
+                                              uint8_t* __restrict__ dst, uint64_t* __restrict__ result) {
+    const uint32_t tid = this_thread();
+    const uint8_t* seg = stream + g.s0;
+    const uint32_t len = seg[1] | ((uint32_t)seg[2] << 8), nlen = seg[3] | ((uint32_t)seg[4] << 8);
+    if (my_side != 0u) bad_stream(result);
+    if (((seg[0] >> 1) & 3u) != 0u || len != m || (len ^ nlen) != 0xffffu || g.len != m + 5u) {
+        if (tid == 0) bad_stream(result);
+        return;
+    }
+    // sixteen bytes a step, from the five dwords they lie in (loads at any byte are slower: 1.3 GB 509 us, 479 so, 466 with two
+    // dwords read for each one written, which takes 124 us for 268 MB, not 115, and 30 for 33 MB, not 26)
+    const uint32_t w0 = (g.byte0 + 5u) >> 2, sh = ((g.byte0 + 5u) & 3u) * 8u;
+    uint4* dst16 = reinterpret_cast<uint4*>(dst);
+    constexpr uint32_t U = 4;
+    for (uint32_t k0 = tid; k0 * 16u + 16u <= m; k0 += U * CODEC_THREADS) {
+        uint4 v[U];
+        uint32_t next[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t k = k0 + u * CODEC_THREADS;
+            if (k * 16u + 16u <= m) {
+                v[u] = load_u4<false>(reinterpret_cast<const float*>(g.dw + w0 + 4u * k));
+                next[u] = g.dw[min(w0 + 4u * k + 4u, g.max_w)];
+            }
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u) {
+            const uint32_t k = k0 + u * CODEC_THREADS;
+            auto join = [&](uint32_t hi, uint32_t lo) { return __builtin_amdgcn_alignbit(hi, lo, sh); };
+            if (k * 16u + 16u <= m)
+                dst16[k] = make_uint4(join(v[u].y, v[u].x), join(v[u].z, v[u].y), join(v[u].w, v[u].z), join(next[u], v[u].w));
+        }
+    }
+    if (tid < (m & 15u)) dst[(m & ~15u) + tid] = seg[5u + (m & ~15u) + tid];
+}
+
+// A lane's part of a sub-chunk from its mark: bits [b_lo, b_hi) of the sub-chunk's tokens make
+// bytes [o_lo, o_hi).
+struct LanePart {
+    uint32_t b_lo, b_hi, o_lo, o_hi;
+    bool ok;
+};
+__device__ __forceinline__ LanePart lane_part(uint64_t mark, uint32_t q, uint32_t side, uint32_t n_l) {
+    LanePart r{0u, side, 0u, n_l, true};
+    uint32_t b_acc = 0;
+#pragma unroll
+    for (uint32_t j = 1; j < CODEC_Q; ++j) {
+        const uint32_t field = (uint32_t)(mark >> (20u * (j - 1u))) & 0xfffffu;
+        b_acc += field & 0x7ffu;
+        const uint32_t o_j = min(j * CODEC_QB, n_l) + (field >> 11);
+        if (j == q) { r.b_lo = b_acc; r.o_lo = o_j; }
+        if (j == q + 1u) { r.b_hi = b_acc; r.o_hi = o_j; }
+    }
+    if ((mark >> 60) != 0ull || r.b_lo > r.b_hi || r.b_hi > side || r.o_lo > r.o_hi || r.o_hi > n_l || r.o_lo < min(q * CODEC_QB, n_l))
+        r.ok = false;
+    return r;
+}
+
+// The state of a lane that decodes: a 64-bit window of the token bits in two registers, sh bits of it used up, and
+// where it writes.
+struct TokenReader {
+    uint32_t pos, end, w_lo, w_hi, sh, i, prev, bad;
+    // Up to two tokens, without branches but for the stores: the table gives
+    // a token's bits, kind and value, and a literal reads as a match of length 1 of
+    // itself; when the token behind it is a literal (three quarters of all tokens are,
+    // in half-empty data) that one is taken in the same turn (a third one gained 1 %).  Offsets are not checked
+    // on the way: a store wraps inside its sub-chunk's row, offsets only
+    // grow, and the end must come out exactly right.  w_new: the dword behind the window; true if it was taken in.
+    // put(offset, byte): only bytes that are not zero.
+    template <typename Put>
+    __device__ __forceinline__ bool turn(const uint32_t* tab, uint32_t w_new, Put&& put) {
+        const uint32_t x = __builtin_amdgcn_alignbit(w_hi, w_lo, sh);
+        const uint32_t t = tab[x & 511u];
+        const uint32_t nb = t & 31u;
+        const uint32_t t2 = tab[(x >> nb) & 511u];                 // at most 18 of the 32 bits are used
+        const uint32_t mm = 0u - ((t >> 5) & 1u);                  // all ones for a match
+        const uint32_t len = ((t >> 7) & 0x1ffu) + __builtin_amdgcn_ubfe(x, (t >> 24) & 15u, t >> 28);
+        const uint32_t byte = ((t >> 16) & 0xffu) | (prev & mm);    // a match repeats the byte before it
+        // not a token of this library's set; a match before any literal of this lane, or
+        // at a distance other than 1
+        bad |= (t & 64u) | ((__builtin_amdgcn_ubfe(x, nb - 5u, 5u) | (prev >> 8)) & mm);
+        if ((byte & 0xffu) != 0u) {                                 // zeros are already there
+            put(i, byte);
+            for (uint32_t u = 1; u < len; ++u) put(i + u, byte);
+        }
+        i += len;
+        // the second token: a literal that starts before the lane's last bit
+        const bool two = (t2 & 0x60u) == 0u && pos + nb < end;
+        const uint32_t byte2 = (t2 >> 16) & 0xffu;
+        if (two && byte2 != 0u) put(i, byte2);
+        const uint32_t used = nb + (two ? t2 & 31u : 0u);          // at most 18 + 9 bits
+        prev = two ? byte2 : byte;
+        i += two ? 1u : 0u;
+        pos += used;
+        sh += used;
+        const bool take = sh >= 32u;
+        w_lo = take ? w_hi : w_lo;
+        w_hi = take ? w_new : w_hi;
+        sh &= 31u;
+        return take;
+    }
 };
 
-// One block of 256 threads per chunk, four lanes per sub-chunk.  A chunk stored as one block
-// is copied.  Otherwise the segment is staged in LDS, every sub-chunk's place follows from
+// The decoder: one block of 256 threads per chunk, four lanes per sub-chunk.  A chunk stored as one block
+// is copied.  Otherwise every sub-chunk's place follows from
 // the side information and every lane's from the sub-chunk's mark: lane q decodes the tokens
-// from bit b_q on (or copies its 128 stored bytes) into a zeroed LDS image of the chunk,
-// which is then written out as whole lines.  Few chunks are all taken by one instance (SEG_MIN 0,
-// room for the longest segment).  Of more, three instances share the chunks by segment
-// size (SEG_DW dwords of LDS for the segment); the smallest visits every chunk and also
-// takes those stored as one block, the other two walk lists.  The segment's size must be
+// from bit b_q on (or copies its 128 stored bytes).  Two instances share the chunks by segment
+// size where there are many; few are all taken by the second.  The segment's size must be
 // what the side information implies, every lane must end exactly where the next one
 // starts, and anything but this library's own token set marks the stream as bad; no access
 // leaves the stream, the staged segment, the image or the output.
-template <uint32_t SEG_DW, uint32_t SEG_MIN>
-__device__ __forceinline__ void inflate_chunk(
-    const InflateShared& sh, uint32_t c, const uint8_t* __restrict__ stream, uint64_t stream_bytes,
-    const uint64_t* __restrict__ seg_off, const uint16_t* __restrict__ side,
-    const uint64_t* __restrict__ marks, uint64_t n_bytes, uint32_t n_chunks, uint8_t* __restrict__ out,
-    uint64_t* __restrict__ result) {
-    constexpr bool FIRST = SEG_MIN == 0;
-    // The instance of the short segments (chunks that are mostly zeros) keeps no image of
-    // the chunk: it writes the chunk's zeros to memory at once, 16 bytes per thread and
-    // store, and after the block's barrier every lane stores its few non-zero bytes one by
-    // one on top.  Without the 32 KiB image many more blocks fit a compute unit, and the
-    // zeros are on their way while the segment is still being fetched.
-    constexpr bool DIRECT = SEG_DW == CODEC_SEG_SMALL;
-    const uint32_t tid = threadIdx.x, l = tid >> 2, q = tid & 3u;
+//
+// The instance of the short segments (chunks that are mostly zeros) visits every chunk and also takes those stored as one
+// block.  It stages the segment in LDS and keeps no image of
+// the chunk: it writes the chunk's zeros to memory at once, 16 bytes per thread and
+// store, and after the block's barrier every lane stores its few non-zero bytes one by
+// one on top.  Without the 32 KiB image many more blocks fit a compute unit, and the
+// zeros are on their way while the segment is still being fetched.
+__global__ __launch_bounds__(CODEC_THREADS, 5) void inflate_sparse_kernel(
+    const uint8_t* __restrict__ stream, uint64_t stream_bytes, const uint64_t* __restrict__ seg_off,
+    const uint16_t* __restrict__ side, const uint64_t* __restrict__ marks, uint64_t n_bytes, uint32_t n_chunks,
+    uint8_t* __restrict__ out, uint64_t* __restrict__ result) {
+    __shared__ uint32_t s_seg[CODEC_SEG_SMALL];
+    __shared__ uint32_t s_tab[512];
+    __shared__ uint32_t s_start[CODEC_NSUB];       // bit 31: a block is open there
+    __shared__ uint32_t s_misc[3];                 // segment bytes, tail start, tail in block
+    const uint32_t c = blockIdx.x, tid = threadIdx.x, l = tid >> 2, q = tid & 3u;
     const uint64_t base = (uint64_t)c * CODEC_CHUNK;
     const uint32_t m = (uint32_t)min((uint64_t)CODEC_CHUNK, n_bytes - min(n_bytes, base));
-    const uint64_t s0 = seg_off[c], s1 = seg_off[c + 1];
-    unsigned long long* status = reinterpret_cast<unsigned long long*>(&result[1]);
-    if (s1 < s0 || s1 > stream_bytes || s1 - s0 < 5u || s1 - s0 > CODEC_SLOT) {
-        if (FIRST && tid == 0) atomicOr(status, (unsigned long long)CODEC_BAD_STREAM);
+    const Segment g = segment_of(stream, stream_bytes, seg_off[c], seg_off[c + 1]);
+    if (g.len == 0u) {
+        if (tid == 0) bad_stream(result);
         return;
     }
     const uint32_t my_side = side[(uint64_t)c * CODEC_NSUB + l];
-    const uint32_t side0 = side[(uint64_t)c * CODEC_NSUB];
-    const uint32_t seg_len = (uint32_t)(s1 - s0);
-    // The segment is read as dwords aligned to the stream's start.  The stream's last dword
-    // may be partly beyond stream_bytes: an aligned dword never crosses a page, and what
-    // lies beyond the segment is never interpreted.
-    const uint32_t byte0 = (uint32_t)(s0 & 3u);
-    const uint32_t* seg32 = reinterpret_cast<const uint32_t*>(stream + (s0 & ~(uint64_t)3u));
-    const uint32_t max_w = (uint32_t)(((stream_bytes + 3u) / 4u) - (s0 >> 2)) - 1u;   // last readable dword
-    const uint32_t seg_w = (byte0 + seg_len + 3u) / 4u + 2u;       // two more for the look-ahead
-    // One stored block iff the first sub-chunk's side information is 0 (the lists of the
-    // other instances are made from it too); every thread then checks that its own
+    // One stored block iff the first sub-chunk's side information is 0 (the list of the
+    // other instance is made from it too); every thread then checks that its own
     // sub-chunk agrees: a coded or stored sub-chunk never has 0, a chunk stored whole has
     // nothing else.
-    const bool whole = side0 == 0u;
-    const uint32_t size_class = whole ? 0u : seg_w;
-    if (size_class < SEG_MIN || size_class > SEG_DW) return;       // another instance's chunk
+    const bool whole = side[(uint64_t)c * CODEC_NSUB] == 0u;
+    const uint32_t seg_w = segment_words(g.byte0, g.len);
+    if (!whole && seg_w > CODEC_SEG_SMALL) return;                 // the other instance's chunk
     uint8_t* dst = out + base;
-    const uint32_t n_l = min(CODEC_SUB, m - min(m, l * CODEC_SUB));
     if (whole) {
-        // the whole chunk in one stored block
-        uint32_t* dst32 = reinterpret_cast<uint32_t*>(dst);
-        const uint8_t* seg = stream + s0;
-        const uint32_t len = seg[1] | ((uint32_t)seg[2] << 8), nlen = seg[3] | ((uint32_t)seg[4] << 8);
-        if (my_side != 0u) atomicOr(status, (unsigned long long)CODEC_BAD_STREAM);
-        if (((seg[0] >> 1) & 3u) != 0u || len != m || (len ^ nlen) != 0xffffu || seg_len != m + 5u) {
-            if (tid == 0) atomicOr(status, (unsigned long long)CODEC_BAD_STREAM);
-            return;
-        }
-        // output dword k = segment bytes 5 + 4k .. 5 + 4k + 3, assembled from two dwords
-        const uint32_t shb = ((byte0 + 5u) & 3u) * 8u, w0 = (byte0 + 5u) >> 2;
-        for (uint32_t k0 = 0; k0 < m / 4u; k0 += CODEC_THREADS * 8u) {
-            uint32_t lo[8], hi[8];
-#pragma unroll
-            for (uint32_t u = 0; u < 8u; ++u) {
-                const uint32_t w = w0 + k0 + u * CODEC_THREADS + tid;
-                lo[u] = w <= max_w ? seg32[w] : 0u;
-                hi[u] = w + 1u <= max_w ? seg32[w + 1u] : 0u;
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < 8u; ++u) {
-                const uint32_t k = k0 + u * CODEC_THREADS + tid;
-                if (k < m / 4u) dst32[k] = shb ? (lo[u] >> shb) | (hi[u] << (32u - shb)) : lo[u];
-            }
-        }
-        if (tid < (m & 3u)) dst[(m & ~3u) + tid] = seg[5u + (m & ~3u) + tid];
+        inflate_whole(g, stream, my_side, m, dst, result);
         return;
     }
+    const uint32_t n_l = min(CODEC_SUB, m - min(m, l * CODEC_SUB));
     const uint64_t mark = marks[(uint64_t)c * CODEC_NSUB + l];
     const bool stored_sub = my_side == CODEC_STORED;
     bool ok = stored_sub ? n_l > 0u : (n_l > 0u ? my_side <= 8u * n_l + CODEC_MARGIN : my_side == 0u);
     // The first wavefront, one lane per sub-chunk, works out where every sub-chunk's part of
-    // the segment starts while the others stage the segment and clear the image: one barrier
+    // the segment starts while the others stage the segment: one barrier
     // before the decoding, one after it.
     if (tid < CODEC_NSUB) {
         const uint32_t n_s = min(CODEC_SUB, m - min(m, tid * CODEC_SUB));
@@ -932,43 +1016,35 @@ __device__ __forceinline__ void inflate_chunk(
         uint32_t start, tail_start;
         bool in_block, tail_in_block;
         const uint32_t sb = place_subs(ok_s ? v : 0u, n_s, tid, &start, &in_block, &tail_start, &tail_in_block);
-        sh.start[tid] = start | (in_block ? 0x80000000u : 0u);
+        s_start[tid] = start | (in_block ? 0x80000000u : 0u);
         if (tid == 0) {
-            sh.misc[0] = all_ok ? sb : 0xffffffffu;      // never a segment's size
-            sh.misc[1] = tail_start;
-            sh.misc[2] = tail_in_block ? 1u : 0u;
+            s_misc[0] = all_ok ? sb : 0xffffffffu;      // never a segment's size
+            s_misc[1] = tail_start;
+            s_misc[2] = tail_in_block ? 1u : 0u;
         }
     }
-    for (uint32_t k = tid; k < seg_w; k += CODEC_THREADS) sh.seg[k] = k <= max_w ? seg32[k] : 0u;
-    sh.tab[tid] = kTokenTable.v[tid];
-    sh.tab[tid + CODEC_THREADS] = kTokenTable.v[tid + CODEC_THREADS];
-    if (DIRECT) {
-        if (m == CODEC_CHUNK) {
-#pragma unroll
-            for (uint32_t j = 0; j < CODEC_CHUNK / 16 / CODEC_THREADS; ++j)
-                *reinterpret_cast<uint4*>(dst + (j * CODEC_THREADS + tid) * 16u) = make_uint4(0, 0, 0, 0);
-        } else {
-            for (uint32_t g = tid; g * 16u < m; g += CODEC_THREADS) {
-                if (g * 16u + 16u <= m) *reinterpret_cast<uint4*>(dst + g * 16u) = make_uint4(0, 0, 0, 0);
-                else for (uint32_t k = g * 16u; k < m; ++k) dst[k] = 0;
-            }
-        }
-    } else {
+    for (uint32_t k = tid; k < seg_w; k += CODEC_THREADS) s_seg[k] = k <= g.max_w ? g.dw[k] : 0u;
+    s_tab[tid] = kTokenTable.v[tid];
+    s_tab[tid + CODEC_THREADS] = kTokenTable.v[tid + CODEC_THREADS];
+    if (m == CODEC_CHUNK) {
 #pragma unroll
         for (uint32_t j = 0; j < CODEC_CHUNK / 16 / CODEC_THREADS; ++j)
-            reinterpret_cast<uint4*>(sh.img)[j * CODEC_THREADS + tid] = make_uint4(0, 0, 0, 0);
+            *reinterpret_cast<uint4*>(dst + (j * CODEC_THREADS + tid) * 16u) = make_uint4(0, 0, 0, 0);
+    } else {
+        for (uint32_t v = tid; v * 16u < m; v += CODEC_THREADS) {
+            if (v * 16u + 16u <= m) *reinterpret_cast<uint4*>(dst + v * 16u) = make_uint4(0, 0, 0, 0);
+            else for (uint32_t k = v * 16u; k < m; ++k) dst[k] = 0;
+        }
     }
-    // orders the block's accesses to the image, and (DIRECT) its zeros in memory before the
-    // bytes its lanes store on top of them
+    // orders the block's zeros in memory before the bytes its lanes store on top of them
     __syncthreads();
-    if (sh.misc[0] != seg_len) {
-        if (tid == 0) atomicOr(status, (unsigned long long)CODEC_BAD_STREAM);
+    if (s_misc[0] != g.len) {
+        if (tid == 0) bad_stream(result);
         return;
     }
-    const uint32_t* s_seg = sh.seg;
-    const uint32_t bit0 = byte0 * 8u;
-    const uint32_t start = sh.start[l] & 0x7fffffffu;
-    const bool in_block = (sh.start[l] >> 31) != 0u;
+    const uint32_t bit0 = g.byte0 * 8u;
+    const uint32_t start = s_start[l] & 0x7fffffffu;
+    const bool in_block = (s_start[l] >> 31) != 0u;
     // the structure around the sub-chunks: block headers, ends of blocks, the closing
     // empty stored block
     if (n_l > 0u && q == 0u) {
@@ -977,8 +1053,8 @@ __device__ __forceinline__ void inflate_chunk(
     }
     if (tid == CODEC_THREADS - 1u) {
         const uint32_t last = c + 1u == n_chunks ? 1u : 0u;
-        uint32_t at = bit0 + sh.misc[1];
-        if (sh.misc[2]) {
+        uint32_t at = bit0 + s_misc[1];
+        if (s_misc[2]) {
             if (seg_peek(s_seg, at, 7u) != 0u) ok = false;
             at += 7u;
         }
@@ -986,174 +1062,238 @@ __device__ __forceinline__ void inflate_chunk(
         at = (at + 3u + 7u) & ~7u;
         if (seg_peek(s_seg, at, 32u) != 0xffff0000u) ok = false;
     }
-    uint8_t* img8 = reinterpret_cast<uint8_t*>(sh.img);
     const uint32_t p_lo = min(q * CODEC_QB, n_l), p_hi = min(p_lo + CODEC_QB, n_l);
     if (stored_sub) {
         // end-of-block of the open block (7 zero bits), header 000, padding, LEN, NLEN, bytes
         const uint32_t at = bit0 + start + (in_block ? 10u : 3u);
-        const uint32_t b0 = ((at + 7u) >> 3);      // byte position of LEN, relative to seg32
+        const uint32_t b0 = ((at + 7u) >> 3);      // byte position of LEN
         const uint32_t len = seg_byte(s_seg, b0) | (seg_byte(s_seg, b0 + 1u) << 8);
         const uint32_t nlen = seg_byte(s_seg, b0 + 2u) | (seg_byte(s_seg, b0 + 3u) << 8);
         if (len != n_l || (len ^ nlen) != 0xffffu || mark != 0ull) ok = false;
         if (ok && p_hi > p_lo) {
             const uint32_t d0 = b0 + 4u + p_lo;    // this lane's first byte
             const uint32_t shb = (d0 & 3u) * 8u, w0 = d0 >> 2, nw = (p_hi - p_lo) / 4u;
-            uint32_t* out32 = reinterpret_cast<uint32_t*>(dst + l * CODEC_SUB + p_lo);   // DIRECT: 128-byte aligned
+            uint32_t* out32 = reinterpret_cast<uint32_t*>(dst + l * CODEC_SUB + p_lo);   // 128-byte aligned
 #pragma unroll 8
             for (uint32_t k = 0; k < nw; ++k) {
                 const uint32_t lo = s_seg[w0 + k];
-                const uint32_t v = shb ? (lo >> shb) | (s_seg[w0 + k + 1u] << (32u - shb)) : lo;
-                if (DIRECT) out32[k] = v;
-                else sh.img[sub_word(l, p_lo / 4u + k)] = v;
+                out32[k] = shb ? (lo >> shb) | (s_seg[w0 + k + 1u] << (32u - shb)) : lo;
             }
-            for (uint32_t k = p_lo + nw * 4u; k < p_hi; ++k) {
-                const uint8_t v = (uint8_t)seg_byte(s_seg, d0 + k - p_lo);
-                if (DIRECT) dst[l * CODEC_SUB + k] = v;
-                else img8[img_byte(l, k)] = v;
-            }
+            for (uint32_t k = p_lo + nw * 4u; k < p_hi; ++k) dst[l * CODEC_SUB + k] = (uint8_t)seg_byte(s_seg, d0 + k - p_lo);
         }
     } else if (n_l > 0u) {
-        // this lane's range from the mark: bits [b_lo, b_hi) of the sub-chunk's tokens make
-        // bytes [o_lo, o_hi)
-        uint32_t b_lo = 0, b_hi = my_side, o_lo = 0, o_hi = n_l, b_acc = 0;
-#pragma unroll
-        for (uint32_t j = 1; j < CODEC_Q; ++j) {
-            const uint32_t field = (uint32_t)(mark >> (20u * (j - 1u))) & 0xfffffu;
-            b_acc += field & 0x7ffu;
-            const uint32_t o_j = min(j * CODEC_QB, n_l) + (field >> 11);
-            if (j == q) { b_lo = b_acc; o_lo = o_j; }
-            if (j == q + 1u) { b_hi = b_acc; o_hi = o_j; }
-        }
-        if ((mark >> 60) != 0ull || b_lo > b_hi || b_hi > my_side || o_lo > o_hi || o_hi > n_l || o_lo < p_lo) ok = false;
+        const LanePart part = lane_part(mark, q, my_side, n_l);
+        if (!part.ok) ok = false;
         if (ok) {
-            uint32_t pos = bit0 + start + (in_block ? 0u : 3u) + b_lo;
-            const uint32_t end = pos + (b_hi - b_lo);
-            uint32_t i = o_lo, prev = 0x100u;      // 0x100: no literal of this lane yet
-            const uint32_t row = l * CODEC_SUB, rot = 16u * l;   // image byte of offset k: row + ((k + rot) & 511)
-            // a 64-bit window of the token bits in two registers, sh bits of it used up
-            uint32_t nextw = (pos >> 5) + 2u, sh_bits = pos & 31u;
-            uint32_t w_lo = s_seg[pos >> 5], w_hi = s_seg[(pos >> 5) + 1u];
-            uint32_t bad_bits = 0;
-            // Up to two tokens per turn, without branches but for the stores: the table gives
-            // a token's bits, kind and value, and a literal reads as a match of length 1 of
-            // itself; when the token behind it is a literal (three quarters of all tokens are,
-            // in half-empty data) that one is taken in the same turn (a third one gained 1 %).  Offsets are not checked
-            // on the way: a store wraps inside its sub-chunk's row of the image, offsets only
-            // grow, and the end must come out exactly right.
-            while (pos < end) {
+            const uint32_t row = l * CODEC_SUB;
+            TokenReader r;
+            r.pos = bit0 + start + (in_block ? 0u : 3u) + part.b_lo;
+            r.end = r.pos + (part.b_hi - part.b_lo);
+            r.i = part.o_lo;
+            r.prev = 0x100u;                       // no literal of this lane yet
+            r.bad = 0;
+            r.sh = r.pos & 31u;
+            r.w_lo = s_seg[r.pos >> 5];
+            r.w_hi = s_seg[(r.pos >> 5) + 1u];
+            uint32_t nextw = (r.pos >> 5) + 2u;
+            while (r.pos < r.end) {
                 // the window's next dword, on its way while the tokens are looked up
-                const uint32_t w_new = s_seg[min(nextw, SEG_DW - 1u)];
-                const uint32_t x = __builtin_amdgcn_alignbit(w_hi, w_lo, sh_bits);
-                const uint32_t t = sh.tab[x & 511u];
-                const uint32_t nb = t & 31u;
-                const uint32_t t2 = sh.tab[(x >> nb) & 511u];              // at most 18 of the 32 bits are used
-                const uint32_t mm = 0u - ((t >> 5) & 1u);                  // all ones for a match
-                const uint32_t len = ((t >> 7) & 0x1ffu) + __builtin_amdgcn_ubfe(x, (t >> 24) & 15u, t >> 28);
-                const uint32_t byte = ((t >> 16) & 0xffu) | (prev & mm);    // a match repeats the byte before it
-                // not a token of this library's set; a match before any literal of this lane, or
-                // at a distance other than 1
-                bad_bits |= (t & 64u) | ((__builtin_amdgcn_ubfe(x, nb - 5u, 5u) | (prev >> 8)) & mm);
-                if ((byte & 0xffu) != 0u) {                                 // zeros are already there
-                    if (DIRECT) {
-                        // no image: straight to memory, inside the sub-chunk and the output
-                        for (uint32_t u = 0; u < len; ++u) {
-                            const uint32_t at = row + ((i + u) & (CODEC_SUB - 1u));
-                            if (at < m) dst[at] = (uint8_t)byte;
-                        }
-                    } else {
-                        img8[row + ((i + rot) & (CODEC_SUB - 1u))] = (uint8_t)byte;
-                        for (uint32_t u = 1; u < len; ++u) img8[row + ((i + u + rot) & (CODEC_SUB - 1u))] = (uint8_t)byte;
-                    }
-                }
-                i += len;
-                // the second token: a literal that starts before the lane's last bit
-                const bool two = (t2 & 0x60u) == 0u && pos + nb < end;
-                const uint32_t byte2 = (t2 >> 16) & 0xffu;
-                if (two && byte2 != 0u) {
-                    if (DIRECT) {
-                        const uint32_t at = row + (i & (CODEC_SUB - 1u));
-                        if (at < m) dst[at] = (uint8_t)byte2;
-                    } else {
-                        img8[row + ((i + rot) & (CODEC_SUB - 1u))] = (uint8_t)byte2;
-                    }
-                }
-                const uint32_t used = nb + (two ? t2 & 31u : 0u);          // at most 18 + 9 bits
-                prev = two ? byte2 : byte;
-                i += two ? 1u : 0u;
-                pos += used;
-                sh_bits += used;
-                const bool take = sh_bits >= 32u;
-                w_lo = take ? w_hi : w_lo;
-                w_hi = take ? w_new : w_hi;
-                nextw += take ? 1u : 0u;
-                sh_bits &= 31u;
+                const uint32_t w_new = s_seg[min(nextw, CODEC_SEG_SMALL - 1u)];
+                // straight to memory, inside the sub-chunk and the output
+                const bool took = r.turn(s_tab, w_new, [&](uint32_t i, uint32_t byte) {
+                    const uint32_t at = row + (i & (CODEC_SUB - 1u));
+                    if (at < m) dst[at] = (uint8_t)byte;
+                });
+                nextw += took ? 1u : 0u;
             }
-            if (bad_bits) ok = false;
-            if (pos != end || i != o_hi) ok = false;
+            if (r.bad || r.pos != r.end || r.i != part.o_hi) ok = false;
+        }
+    } else if (mark != 0ull) {
+        ok = false;
+    }
+    if (__syncthreads_and(ok) == 0 && tid == 0) bad_stream(result);
+}
+
+// The instance of all other segments decodes into a zeroed LDS image of the chunk, which is then written out as whole lines.
+// A lane reads its own part of the segment, 56 bytes on half-full data, from memory: four dwords of it are in LDS, the two
+// behind them in registers or on their way, and every second turn moves on.  What bounds it is vector issue (some 50 of them a
+// turn) and, in one round of chunks, a chunk's chain of latencies.  The whole segment staged in LDS took 68 KB with the
+// image: two blocks to a compute unit, and a second round of chunks beyond 512; with 39 KB four run.  us a call
+// (densities 0.05 / 0.3 / 0.5, before and now): 256 chunks 33 / 36 / 37 and 32 / 35 / 35, 1000 chunks 60 / 70 / 74 and 45 / 49 /
+// 52, 8192 chunks, where a third instance took the segments of up to 16 KiB, 412 / 469 / 514 and 258 / 295 / 319, 39347
+// chunks 1849 / 2192 / 2409 and 1080 / 1243 / 1333; 28 MB of a rebuilt variant, a third of it not zero, 71 and 52.
+constexpr uint32_t INFLATE_RING = 4;
+typedef uint32_t u32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
+__device__ __forceinline__ void inflate_dense(
+    uint32_t* s_img, uint32_t* s_ring, uint32_t* s_tab, uint32_t c, bool all, const uint8_t* __restrict__ stream,
+    uint64_t stream_bytes, const uint64_t* __restrict__ seg_off, const uint16_t* __restrict__ side,
+    const uint64_t* __restrict__ marks, uint64_t n_bytes, uint32_t n_chunks, uint8_t* __restrict__ out, uint64_t* __restrict__ result) {
+    const uint32_t tid = this_thread(), l = tid >> 2, q = tid & 3u, lane = tid & 63u, wid = uniform_u32(tid >> 6);
+    const uint64_t base = (uint64_t)c * CODEC_CHUNK;
+    const uint32_t m = (uint32_t)min((uint64_t)CODEC_CHUNK, n_bytes - min(n_bytes, base));
+    const uint32_t side_s = side[(uint64_t)c * CODEC_NSUB + lane];        // lane = sub-chunk
+    const uint64_t mark = marks[(uint64_t)c * CODEC_NSUB + l];
+    const Segment g = segment_of(stream, stream_bytes, seg_off[c], seg_off[c + 1]);
+    const uint32_t tab0 = kTokenTable.v[tid], tab1 = kTokenTable.v[tid + CODEC_THREADS];
+    if (g.len == 0u) {
+        if (all && tid == 0) bad_stream(result);
+        return;
+    }
+    uint8_t* dst = out + base;
+    const uint32_t my_side = __shfl(side_s, (int)l, 64);
+    if (uniform_u32(side_s) == 0u) {                                     // in one stored block
+        if (all) inflate_whole(g, stream, my_side, m, dst, result);
+        return;
+    }
+    s_tab[tid] = tab0;
+    s_tab[tid + CODEC_THREADS] = tab1;
+    // this wavefront's sixteen rows of the image
+    static_assert(CODEC_CHUNK / 16 == 8u * CODEC_THREADS, "eight pieces a thread");
+#pragma unroll
+    for (uint32_t j = 0; j < 8u; ++j) reinterpret_cast<uint4*>(s_img)[(wid * 8u + j) * 64u + lane] = make_uint4(0, 0, 0, 0);
+    // every wavefront places the sub-chunks for itself, lane = sub-chunk
+    uint32_t start, tail_start, seg_bytes;
+    bool in_block, tail_in_block, ok;
+    {
+        const uint32_t n_s = min(CODEC_SUB, m - min(m, lane * CODEC_SUB));
+        const bool ok_s = side_s == CODEC_STORED ? n_s > 0u : (n_s > 0u ? side_s != 0u && side_s <= 8u * n_s + CODEC_MARGIN : side_s == 0u);
+        uint32_t start_s;
+        bool in_block_s;
+        seg_bytes = place_subs(ok_s ? side_s : 0u, n_s, lane, &start_s, &in_block_s, &tail_start, &tail_in_block);
+        if (__ballot(!ok_s) != 0ull || seg_bytes != g.len) {
+            if (tid == 0) bad_stream(result);
+            return;
+        }
+        const uint32_t both = __shfl(start_s | (in_block_s ? 0x80000000u : 0u), (int)l, 64);
+        start = both & 0x7fffffffu;
+        in_block = (both >> 31) != 0u;
+        ok = true;
+    }
+    __syncthreads();                                                     // the table
+    const uint32_t n_l = min(CODEC_SUB, m - min(m, l * CODEC_SUB));
+    const bool stored_sub = my_side == CODEC_STORED;
+    const uint32_t bit0 = g.byte0 * 8u;
+    // n <= 32 bits at bit position pos of the segment
+    auto peek = [&](uint32_t pos, uint32_t n) {
+        const uint32_t w = pos >> 5;
+        const uint32_t lo = g.dw[min(w, g.max_w)], hi = g.dw[min(w + 1u, g.max_w)];
+        return __builtin_amdgcn_alignbit(hi, lo, pos & 31u) & (n >= 32u ? ~0u : (1u << n) - 1u);
+    };
+    // the structure around the sub-chunks: block headers, ends of blocks, the closing
+    // empty stored block
+    if (n_l > 0u && q == 0u && (stored_sub || !in_block)) {
+        const uint32_t head = peek(bit0 + start, stored_sub && in_block ? 10u : 3u);
+        if (head != (stored_sub ? 0u : 2u)) ok = false;
+    }
+    if (tid == CODEC_THREADS - 1u) {
+        const uint32_t last = c + 1u == n_chunks ? 1u : 0u, at = bit0 + tail_start, eob = tail_in_block ? 7u : 0u;
+        const uint32_t head = peek(at, eob + 3u), lens = peek((at + eob + 3u + 7u) & ~7u, 32u);
+        if (head != last << eob || lens != 0xffff0000u) ok = false;
+    }
+    uint8_t* img8 = reinterpret_cast<uint8_t*>(s_img);
+    const uint32_t p_lo = min(q * CODEC_QB, n_l), p_hi = min(p_lo + CODEC_QB, n_l);
+    if (stored_sub) {
+        // end-of-block of the open block (7 zero bits), header 000, padding, LEN, NLEN, bytes
+        const uint32_t at = bit0 + start + (in_block ? 10u : 3u);
+        const uint32_t b0 = (at + 7u) >> 3;        // byte position of LEN
+        if (peek(8u * b0, 32u) != (n_l | (~n_l << 16)) || mark != 0ull) ok = false;
+        if (ok && p_hi > p_lo) {
+            // this lane's bytes, at any alignment
+            const uint8_t* src = reinterpret_cast<const uint8_t*>(g.dw) + b0 + 4u + p_lo;
+            const uint32_t nw = (p_hi - p_lo) / 4u;
+#pragma unroll 8
+            for (uint32_t k = 0; k < nw; ++k) s_img[sub_word(l, p_lo / 4u + k)] = reinterpret_cast<const u32_a1*>(src)[k];
+            for (uint32_t k = p_lo + nw * 4u; k < p_hi; ++k) img8[img_byte(l, k)] = src[k - p_lo];
+        }
+    } else if (n_l > 0u) {
+        const LanePart part = lane_part(mark, q, my_side, n_l);
+        if (!part.ok) ok = false;
+        if (ok) {
+            const uint32_t row = l * CODEC_SUB, rot = 16u * l;   // image byte of offset k: row + ((k + rot) & 511)
+            TokenReader r;
+            r.pos = bit0 + start + (in_block ? 0u : 3u) + part.b_lo;
+            r.end = r.pos + (part.b_hi - part.b_lo);
+            r.i = part.o_lo;
+            r.prev = 0x100u;                       // no literal of this lane yet
+            r.bad = 0;
+            r.sh = r.pos & 31u;
+            // Dwords at, at + 1.  The tokens end at least four bytes before the segment does, so none lies in the stream's
+            // last dword: what is read again there is not used.
+            auto two = [&](uint32_t at) { return *reinterpret_cast<const u32x2_a4*>(g.dw + min(at, g.max_w - 1u)); };
+            uint32_t nextw = (r.pos >> 5) + 2u, filled = nextw + 2u;     // the ring holds [nextw, filled)
+            const u32x2_a4 first = two(nextw - 2u), second = two(nextw);
+            u32x2_a4 ahead = two(filled);
+            uint32_t* ring = s_ring + tid;
+            auto slot = [&](uint32_t at) { return (at & (INFLATE_RING - 1u)) * CODEC_THREADS; };
+            r.w_lo = first.x;
+            r.w_hi = first.y;
+            ring[slot(nextw)] = second.x;
+            ring[slot(nextw + 1u)] = second.y;
+            auto put = [&](uint32_t i, uint32_t byte) { img8[row + ((i + rot) & (CODEC_SUB - 1u))] = (uint8_t)byte; };
+            while (r.pos < r.end) {
+                // two turns take in two dwords at most
+                if (filled - nextw <= 2u) {
+                    ring[slot(filled)] = ahead.x;
+                    ring[slot(filled + 1u)] = ahead.y;
+                    filled += 2u;
+                    ahead = two(filled);
+                }
+                nextw += r.turn(s_tab, ring[slot(nextw)], put) ? 1u : 0u;
+                if (r.pos < r.end) nextw += r.turn(s_tab, ring[slot(nextw)], put) ? 1u : 0u;
+            }
+            if (r.bad || r.pos != r.end || r.i != part.o_hi) ok = false;
         }
     } else if (mark != 0ull) {
         ok = false;
     }
     const bool fine = __syncthreads_and(ok) != 0;
     if (!fine) {
-        if (tid == 0) atomicOr(status, (unsigned long long)CODEC_BAD_STREAM);
+        if (tid == 0) bad_stream(result);
         return;
     }
-    if (DIRECT) return;
     // write-out: 16 bytes per thread and step, whole lines per wave
     if (m == CODEC_CHUNK) {
 #pragma unroll
         for (uint32_t r = 0; r < CODEC_CHUNK / 16 / CODEC_THREADS; ++r) {
-            const uint32_t g = r * CODEC_THREADS + tid;                 // 16-byte vector of the chunk
-            const uint4 v = *reinterpret_cast<const uint4*>(&sh.img[sub_word(g >> 5, (g & 31u) * 4u)]);
-            *reinterpret_cast<uint4*>(dst + g * 16u) = v;
+            const uint32_t v = r * CODEC_THREADS + tid;                 // 16-byte vector of the chunk
+            *reinterpret_cast<uint4*>(dst + v * 16u) = *reinterpret_cast<const uint4*>(&s_img[sub_word(v >> 5, (v & 31u) * 4u)]);
         }
     } else {
         for (uint32_t r = 0; r < CODEC_CHUNK / 16 / CODEC_THREADS; ++r) {
-            const uint32_t g = r * CODEC_THREADS + tid;
-            if (g * 16u >= m) continue;
-            const uint4 v4 = *reinterpret_cast<const uint4*>(&sh.img[sub_word(g >> 5, (g & 31u) * 4u)]);
-            if (g * 16u + 16u <= m) {
-                *reinterpret_cast<uint4*>(dst + g * 16u) = v4;
+            const uint32_t v = r * CODEC_THREADS + tid;
+            if (v * 16u >= m) continue;
+            const uint4 v4 = *reinterpret_cast<const uint4*>(&s_img[sub_word(v >> 5, (v & 31u) * 4u)]);
+            if (v * 16u + 16u <= m) {
+                *reinterpret_cast<uint4*>(dst + v * 16u) = v4;
             } else {
-                const uint32_t v[4] = {v4.x, v4.y, v4.z, v4.w};
-                for (uint32_t k = 0; g * 16u + k < m; ++k) dst[g * 16u + k] = (uint8_t)(v[k >> 2] >> (8u * (k & 3u)));
+                const uint32_t x[4] = {v4.x, v4.y, v4.z, v4.w};
+                for (uint32_t k = 0; v * 16u + k < m; ++k) dst[v * 16u + k] = (uint8_t)(x[k >> 2] >> (8u * (k & 3u)));
             }
         }
     }
 }
 
-template <uint32_t SEG_DW, uint32_t SEG_MIN>
-__global__ __launch_bounds__(CODEC_THREADS, SEG_DW == CODEC_SEG_SMALL ? 5 : (SEG_DW == CODEC_SEG_MEDIUM ? 3 : 2))
-void inflate_chunk_kernel(
+// list: the chunks to take; nullptr: all, a block each.
+__global__ __launch_bounds__(CODEC_THREADS, 4) void inflate_dense_kernel(
     const uint8_t* __restrict__ stream, uint64_t stream_bytes, const uint64_t* __restrict__ seg_off,
     const uint16_t* __restrict__ side, const uint64_t* __restrict__ marks, uint64_t n_bytes, uint32_t n_chunks,
     uint8_t* __restrict__ out, uint64_t* __restrict__ result, const uint32_t* __restrict__ list,
     const uint32_t* __restrict__ list_count) {
-    __shared__ __align__(16) uint32_t s_img[SEG_DW == CODEC_SEG_SMALL ? 4 : CODEC_CHUNK / 4];   // none for the short segments
-    __shared__ uint32_t s_seg[SEG_DW];
+    __shared__ __align__(16) uint32_t s_img[CODEC_CHUNK / 4];
+    __shared__ uint32_t s_ring[INFLATE_RING * CODEC_THREADS];
     __shared__ uint32_t s_tab[512];
-    __shared__ uint32_t s_start[CODEC_NSUB];
-    __shared__ uint32_t s_misc[4];
-    const InflateShared sh{s_img, s_seg, s_tab, s_start, s_misc};
-    if (!list) {
-        inflate_chunk<SEG_DW, SEG_MIN>(sh, blockIdx.x, stream, stream_bytes, seg_off, side, marks, n_bytes,
-                                       n_chunks, out, result);
-    } else {
-        const uint32_t n_list = *list_count;               // written by the classifying kernel
-        for (uint32_t it = blockIdx.x; it < n_list; it += gridDim.x) {
-            inflate_chunk<SEG_DW, SEG_MIN>(sh, list[it], stream, stream_bytes, seg_off, side, marks, n_bytes,
-                                           n_chunks, out, result);
-            __syncthreads();
-        }
+    const uint32_t n = list ? *list_count : blockIdx.x + 1u;       // written by the classifying kernel
+    for (uint32_t it = blockIdx.x; it < n; it += gridDim.x) {
+        inflate_dense(s_img, s_ring, s_tab, list ? list[it] : it, !list, stream, stream_bytes, seg_off, side, marks, n_bytes,
+                      n_chunks, out, result);
+        __syncthreads();
     }
 }
 
 __global__ void codec_clear_kernel(uint64_t* result) {
     result[0] = 0;
     result[1] = 0;
-    result[2] = 0;      // lengths of the two chunk lists of the decoder, or of the encoder's one
-    result[3] = 0;
+    result[2] = 0;      // length of the decoder's chunk list
 }
 
 // The call's outcome (stream bytes, status bits) into the pinned mirror the host reads after
@@ -1166,7 +1306,6 @@ __global__ void codec_publish_kernel(uint64_t* __restrict__ result, uint64_t* __
     result[0] = 0;
     result[1] = 0;
     result[2] = 0;
-    result[3] = 0;
 }
 
 // The result words are zero when a call starts: the context allocates them cleared and every
@@ -1211,9 +1350,9 @@ static hipError_t codec_ensure_list(shifter_ctx* ctx, uint64_t entries) {
 int launch_deflate(shifter_ctx* ctx, const uint8_t* d_in, uint64_t n_bytes, uint32_t n_chunks,
                    uint8_t* d_work, uint8_t* d_stream, uint64_t stream_cap, uint64_t* d_seg_off,
                    uint16_t* d_sub_bits, uint64_t* d_sub_marks) {
-    // the decoder's lists: a call of either kind makes room for both, so that either may be
+    // the decoder's list: a call of either kind makes room for it, so that either may be
     // recorded into a graph behind it
-    const hipError_t e = codec_ensure_list(ctx, 2ull * n_chunks);
+    const hipError_t e = codec_ensure_list(ctx, n_chunks);
     if (e != hipSuccess) return (int)e;
     if (stream_cap >= n_bytes + 5ull * n_chunks) {
         // the stream holds every segment stored: it cannot overflow, so the segments go straight
@@ -1254,89 +1393,68 @@ int launch_deflate(shifter_ctx* ctx, const uint8_t* d_in, uint64_t n_bytes, uint
     return 0;
 }
 
-// Lists of the chunks whose segments need the medium and the large instance of the decoder
-// (the same rule as inside the instances); counts in result[2] and result[3].  One atomic
-// per block and list (atomics to one address take their turns, about 10 ns each): the
-// wavefronts' counts meet in LDS and share the range the block reserves.
+// The list of the chunks whose segments the second instance of the decoder takes (the same rule as inside the
+// first); its length in result[2].  One atomic per block (atomics to one address take their turns, about 10 ns
+// each): the wavefronts' counts meet in LDS and share the range the block reserves.
 constexpr uint32_t CLASSIFY_THREADS = 1024;
 __global__ __launch_bounds__(CLASSIFY_THREADS) void codec_classify_kernel(
     uint64_t stream_bytes, const uint64_t* __restrict__ seg_off, const uint16_t* __restrict__ side,
-    uint32_t n_chunks, uint32_t* __restrict__ list_medium, uint32_t* __restrict__ list_large,
-    uint64_t* __restrict__ result) {
+    uint32_t n_chunks, uint32_t* __restrict__ list, uint64_t* __restrict__ result) {
     constexpr uint32_t WAVES = CLASSIFY_THREADS / 64u;
-    __shared__ uint32_t s_cnt[2][WAVES], s_base[2];
+    __shared__ uint32_t s_cnt[WAVES], s_base;
     const uint32_t c = blockIdx.x * CLASSIFY_THREADS + threadIdx.x, lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
-    uint32_t seg_w = 0;
+    bool dense = false;
     if (c < n_chunks) {
         const uint64_t s0 = seg_off[c], s1 = seg_off[c + 1];
         // a broken offset is reported by the first instance; one stored block is its chunk too
         if (!(s1 < s0 || s1 > stream_bytes || s1 - s0 < 5u || s1 - s0 > CODEC_SLOT) &&
             side[(uint64_t)c * CODEC_NSUB] != 0u)
-            seg_w = ((uint32_t)(s0 & 3u) + (uint32_t)(s1 - s0) + 3u) / 4u + 2u;
+            dense = segment_words((uint32_t)(s0 & 3u), (uint32_t)(s1 - s0)) > CODEC_SEG_SMALL;
     }
-    const bool large = seg_w > CODEC_SEG_MEDIUM, medium = seg_w > CODEC_SEG_SMALL && !large;
-    const uint64_t votes[2] = {__ballot(medium), __ballot(large)};
-    if (lane == 0) {
-        s_cnt[0][wid] = (uint32_t)__popcll(votes[0]);
-        s_cnt[1][wid] = (uint32_t)__popcll(votes[1]);
-    }
+    const uint64_t votes = __ballot(dense);
+    if (lane == 0) s_cnt[wid] = (uint32_t)__popcll(votes);
     __syncthreads();
-    if (threadIdx.x < 2u) {
+    if (threadIdx.x == 0) {
         uint32_t total = 0;
-        for (uint32_t w = 0; w < WAVES; ++w) total += s_cnt[threadIdx.x][w];
-        s_base[threadIdx.x] = total ? atomicAdd(reinterpret_cast<uint32_t*>(&result[2u + threadIdx.x]), total) : 0u;
+        for (uint32_t w = 0; w < WAVES; ++w) total += s_cnt[w];
+        s_base = total ? atomicAdd(reinterpret_cast<uint32_t*>(&result[2]), total) : 0u;
     }
     __syncthreads();
-    if (medium || large) {
-        const uint32_t x = large ? 1u : 0u;
-        uint32_t at = s_base[x];
-        for (uint32_t w = 0; w < wid; ++w) at += s_cnt[x][w];
-        at += (uint32_t)__popcll(votes[x] & ((1ull << lane) - 1ull));
-        (large ? list_large : list_medium)[at] = c;
+    if (dense) {
+        uint32_t at = s_base;
+        for (uint32_t w = 0; w < wid; ++w) at += s_cnt[w];
+        list[at + (uint32_t)__popcll(votes & ((1ull << lane) - 1ull))] = c;
     }
 }
 
-// Up to this many chunks - two rounds of two blocks on each of 256 compute units - one instance with
-// room for the longest segment takes them all.  An instance's time is then the latency of a
-// chunk or two, and three instances one behind the other cost three; beyond it the room that
-// short segments leave unused costs more than the launches.  Three instances against one, us a
-// call, chunks of one density / of densities from 0 to 1: 128 chunks 26-44 / 74 and 19-37 / 40;
-// 855 29-77 / 87 and 25-70 / 68; 1024 30-79 / 108 and 27-71 / 76; 1280 31-100 / 114 and 31-91 / 89, but at
-// density 0.3 67 and 73; 8192 at density 0.3 285 and 372.
+// Up to this many chunks - one round of four blocks on each of 256 compute units - the second instance takes them all. An
+// instance's time is then the latency of a chunk, and two instances one behind the other cost two; beyond it the
+// chunks of few tokens fare better with their own.  us a call, chunks of one density from 0.05 to 0.5 / of densities from 0
+// to 1: 1000 chunks 45-52 / 52, 1030 58-67 / 65.
 constexpr uint32_t INFLATE_ONE_LAUNCH = 1024;
 
-// Kernels only, nothing waited for: the lists of the two larger instances are made on the
-// device and walked by fixed grids.  Returns a HIP error code (0: fine).
+// Kernels only, nothing waited for: the list of the second instance is made on the
+// device and walked by a fixed grid.  Returns a HIP error code (0: fine).
 int launch_inflate(shifter_ctx* ctx, const uint8_t* d_stream, uint64_t stream_bytes,
                    const uint64_t* d_seg_off, const uint16_t* d_sub_bits, const uint64_t* d_sub_marks,
                    uint64_t n_bytes, uint32_t n_chunks, uint8_t* d_out) {
-    hipError_t e0 = codec_ensure_list(ctx, 2ull * n_chunks);
+    hipError_t e0 = codec_ensure_list(ctx, n_chunks);
     if (e0 != hipSuccess) return (int)e0;
-    uint32_t* list_medium = ctx->d_codec_list;
-    uint32_t* list_large = ctx->d_codec_list + n_chunks;
-    const uint32_t* n_medium = reinterpret_cast<const uint32_t*>(ctx->d_codec + 2);
-    const uint32_t* n_large = reinterpret_cast<const uint32_t*>(ctx->d_codec + 3);
     codec_begin(ctx);
     if (n_chunks <= INFLATE_ONE_LAUNCH) {
         ProfileScope ps(ctx, K_INFLATE_CHUNK);
-        inflate_chunk_kernel<CODEC_SEG_LARGE, 0><<<n_chunks, CODEC_THREADS, 0, ctx->stream>>>(
-            d_stream, stream_bytes, d_seg_off, d_sub_bits, d_sub_marks, n_bytes, n_chunks, d_out, ctx->d_codec,
-            nullptr, nullptr);
+        inflate_dense_kernel<<<n_chunks, CODEC_THREADS, 0, ctx->stream>>>(d_stream, stream_bytes, d_seg_off, d_sub_bits, d_sub_marks,
+                                                                          n_bytes, n_chunks, d_out, ctx->d_codec, nullptr, nullptr);
     } else {
         ProfileScope ps(ctx, K_INFLATE_CHUNK);
         codec_classify_kernel<<<(n_chunks + CLASSIFY_THREADS - 1) / CLASSIFY_THREADS, CLASSIFY_THREADS, 0, ctx->stream>>>(
-            stream_bytes, d_seg_off, d_sub_bits, n_chunks, list_medium, list_large, ctx->d_codec);
-        const uint32_t loop_grid = std::min(n_chunks, CODEC_LOOP_GRID);
+            stream_bytes, d_seg_off, d_sub_bits, n_chunks, ctx->d_codec_list, ctx->d_codec);
         // the long segments first: their blocks run longest
-        inflate_chunk_kernel<CODEC_SEG_LARGE, CODEC_SEG_MEDIUM + 1><<<loop_grid, CODEC_THREADS, 0, ctx->stream>>>(
-            d_stream, stream_bytes, d_seg_off, d_sub_bits, d_sub_marks, n_bytes, n_chunks, d_out, ctx->d_codec,
-            list_large, n_large);
-        inflate_chunk_kernel<CODEC_SEG_MEDIUM, CODEC_SEG_SMALL + 1><<<loop_grid, CODEC_THREADS, 0, ctx->stream>>>(
-            d_stream, stream_bytes, d_seg_off, d_sub_bits, d_sub_marks, n_bytes, n_chunks, d_out, ctx->d_codec,
-            list_medium, n_medium);
-        inflate_chunk_kernel<CODEC_SEG_SMALL, 0><<<n_chunks, CODEC_THREADS, 0, ctx->stream>>>(
-            d_stream, stream_bytes, d_seg_off, d_sub_bits, d_sub_marks, n_bytes, n_chunks, d_out, ctx->d_codec,
-            nullptr, nullptr);
+        inflate_dense_kernel<<<std::min(n_chunks, CODEC_LOOP_GRID), CODEC_THREADS, 0, ctx->stream>>>(
+            d_stream, stream_bytes, d_seg_off, d_sub_bits, d_sub_marks, n_bytes, n_chunks, d_out, ctx->d_codec, ctx->d_codec_list,
+            reinterpret_cast<const uint32_t*>(ctx->d_codec + 2));
+        inflate_sparse_kernel<<<n_chunks, CODEC_THREADS, 0, ctx->stream>>>(d_stream, stream_bytes, d_seg_off, d_sub_bits, d_sub_marks,
+                                                                          n_bytes, n_chunks, d_out, ctx->d_codec);
     }
     codec_end(ctx);
     return 0;

@@ -307,10 +307,10 @@ struct shifter_ctx {
     shifter::SpecState last_spec{};  // outcome of the last single-pass selection
     int last_path = 0;               // 1: single pass decided; 2: multi-pass select ran
     shifter_threshold last_record{};  // record of the last shifter_prune_fused that waited
-    uint64_t* d_codec = nullptr;      // codec: [0] stream bytes, [1] status bits, [2], [3] list lengths (device)
+    uint64_t* d_codec = nullptr;      // codec: [0] stream bytes, [1] status bits, [2] the list's length (device)
     uint64_t* h_codec = nullptr;      // pinned: the call's result words (chain.h), written by its last kernel
     uint64_t* dev_codec_mirror = nullptr;   //   its device address
-    uint32_t* d_codec_list = nullptr; // chunk lists of the instances that take the longer segments
+    uint32_t* d_codec_list = nullptr; // list of the chunks that the decoder's second instance takes
     uint64_t codec_list_cap = 0;      //   its capacity in entries
     bool codec_dirty = true;          // the codec's result words may be non-zero (see codec_begin)
     // a shifter_prune_fused call whose outcome has not been collected yet
