@@ -27,8 +27,8 @@
 //   10 of   1 M           34 / 25       60 / 56             81 / 78         55 / 44             43 / 33
 //    1 of  14.7 M         56 / 43       55 / 43             178 / 179       113 / 107           76 / 54
 //   10 of  14.7 M         64 / 47       137 / 131           208 / 208       145 / 149           96 / 63
-//    1 of 100 M           249 / 177     246 / 174           850 / 829       399 / 416           273 / 224
-//   10 of 100 M           252 / 265     745 / 718           1214 / 1197     605 / 610           298 / 321
+//    1 of 100 M           249 / 159     246 / 159           850 / 835       399 / 395           273 / 206
+//   10 of 100 M           252 / 245     745 / 712           1214 / 1192     605 / 595           298 / 305
 // (The radix select of 11 + 10 + 10 bits before all this: 85 us for 1 of 1 M, 418 for 10 of 14.7 M.)
 #include <algorithm>
 
@@ -129,12 +129,12 @@ struct SelArena {
 // A tensor's last, ragged tile goes the same way as a full one.
 struct SelWalk {
     const SelArena& a;
-    uint32_t tile, n, g0;            // the tile at hand: its weights (0: not prunable) and the first one's global index
+    uint32_t n, g0;                  // the tile at hand: its weights (0: not prunable) and the first one's global index
     uint4 v[SEL_QUADS];              // sixteen of them: four quads 4 * BLOCK weights apart
 
     __device__ __forceinline__ explicit SelWalk(const SelArena& arena) : a(arena) {}
     __device__ __forceinline__ uint32_t thread() const { return threadIdx.x & (BLOCK - 1u); }
-    __device__ __forceinline__ void fetch() {
+    __device__ __forceinline__ void fetch(uint32_t tile) {
         n = 0;
         const uint32_t t = a.tile_tensor ? a.tile_tensor[tile] : 0u;
         const DevTensor& T = a.tens[t];
@@ -156,10 +156,11 @@ struct SelWalk {
             }
         }
     }
+    // down: from the last tile to the first
     template <typename F>
-    __device__ __forceinline__ void run(uint32_t part, uint32_t parts, F&& f) {
-        for (tile = part * SEL_GROUPS + uniform_u32(threadIdx.x / BLOCK); tile < a.n_tiles; tile += parts * SEL_GROUPS) {
-            fetch();
+    __device__ __forceinline__ void run(uint32_t part, uint32_t parts, bool down, F&& f) {
+        for (uint32_t i = part * SEL_GROUPS + uniform_u32(threadIdx.x / BLOCK); i < a.n_tiles; i += parts * SEL_GROUPS) {
+            fetch(down ? a.n_tiles - 1u - i : i);
             if (n) f();
         }
     }
@@ -225,7 +226,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(const SelArena are
     bool runs = false;
     RunCount run;
     auto bin_of = [&](uint32_t key) { return key ? sel_bin(key) : SEL_BINS + lane; };
-    walk.run(blockIdx.x, gridDim.x, [&] {
+    walk.run(blockIdx.x, gridDim.x, false, [&] {
         if (walk.n != TILE) {
             for (uint32_t left = walk.there(); left; left &= left - 1u) {
                 const uint32_t key = walk.bits((uint32_t)__builtin_ctz(left)) & 0x7fffffffu;
@@ -500,6 +501,10 @@ __device__ __forceinline__ void sel_windows(const SelJob& J, SelShared& S, uint3
     }
 }
 
+// The reads of the arena go up and down in turn: what the last-level cache still holds of one larger than itself is the end that was
+// read last.  One count of 100 M weights 176 us a call all the same way, 159 so; ten 265 and 245.
+__device__ __forceinline__ constexpr bool sel_down(uint32_t stage) { return (stage & 1u) != 0u; }
+
 // The weights of a part into the stage's histograms and lists.
 template <bool DEV>
 struct SelCollect {
@@ -508,11 +513,11 @@ struct SelCollect {
     RunCount run;
     KeyRange keys;
     __device__ __forceinline__ SelCollect(const SelJob& job, SelShared& shared) : J(job), S(shared) {}
-    __device__ __forceinline__ void part(const SelArena& arena, uint32_t part, uint32_t parts);
+    __device__ __forceinline__ void part(const SelArena& arena, uint32_t part, uint32_t parts, bool down);
     __device__ __forceinline__ void leave(uint32_t stage);
 };
 template <bool DEV>
-__device__ __forceinline__ void SelCollect<DEV>::part(const SelArena& arena, uint32_t part, uint32_t parts) {
+__device__ __forceinline__ void SelCollect<DEV>::part(const SelArena& arena, uint32_t part, uint32_t parts, bool down) {
     SelWalk walk(arena);
     SelState* const st = J.st;
     uint2* const lists = J.lists;
@@ -571,7 +576,7 @@ __device__ __forceinline__ void SelCollect<DEV>::part(const SelArena& arena, uin
         const uint32_t at = __shfl(base, (int)__ffsll((unsigned long long)peers) - 1, 64) + rank;
         if (at < list_cap) sel_put<DEV>(&lists[(size_t)s * list_cap + at], make_uint2(wbits, g));
     };
-    walk.run(part, parts, [&] {
+    walk.run(part, parts, down, [&] {
         const uint4 (&v)[SEL_QUADS] = walk.v;
         // first which of the sixteen are met by a window, without a branch, then those one by one: few are,
         // and the long body stands here once (in line sixteen times: 20 ranks of 14.7 M weights 34 us, 24 so; 30
@@ -699,7 +704,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(const SelArena a
     }
     sel_windows<STAGE == 1u, false>(J, S, STAGE, blockIdx.x == 0);
     SelCollect<false> collect(J, S);
-    collect.part(arena, blockIdx.x, gridDim.x);
+    collect.part(arena, blockIdx.x, gridDim.x, sel_down(STAGE));
     collect.leave(STAGE);
 }
 
@@ -747,7 +752,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_rest_kernel(const SelArena ar
             SelCollect<true> collect(J, S);
             for (; part < parts; part = taken(), ++mine) {
                 draw(&st->ticket[stage]);
-                collect.part(arena, part, parts);
+                collect.part(arena, part, parts, sel_down(stage));
             }
             collect.leave(stage);
             wait_memory();
@@ -804,7 +809,7 @@ void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float*
     const SelArena arena{tb.tens, tb.tile_prefix, tb.tile_tensor, n_tiles, d_w};
     const SelJob job{tb.sel, tb.ghist, tb.lists, list_cap, k, (uint32_t)tb.n_weights, g_bits, stages};
     // At most 1/1536 of spread-out weights lie in one bin: where that is more than a good list, the first stage will hardly list
-    // them all, and a launch costs the second one less than the tickets (ten of 100 M weights 252 us, 268 with them)
+    // them all, and a launch costs the second one less than the tickets (ten of 100 M weights 252 us, 268 with them, all reads in one direction)
     const uint32_t before = stages > 1u && tb.n_weights / 1536u > std::min(list_cap, SEL_LIST_GOOD) ? 2u : 1u;
     {
         ProfileScope p(ctx, K_SEL_INIT);
