@@ -478,7 +478,7 @@ int shifter_fold_bn(shifter_ctx* ctx, const shifter_model* model,
  *                        the stream was bad (inflate), or did not fit or has a hole because a
  *                        segment's offset never arrived (deflate; a waiting call returns
  *                        SHIFTER_ERR_INTERNAL then); either pointer may be NULL.
- * The codec calls need no model.  They keep chunk lists of 8 bytes per chunk of device
+ * The codec calls need no model.  They keep some 40 bytes per chunk of device
  * memory in the context, allocated when an input with more chunks than before comes (so
  * a call recorded into a HIP graph must follow an eager one of at least that size). */
 #define SHIFTER_CODEC_CHUNK 32768u

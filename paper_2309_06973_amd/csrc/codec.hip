@@ -310,7 +310,12 @@ __device__ __forceinline__ uint32_t incl_sum32(uint32_t x) {
 }
 
 // Chained offsets of the segments (the decoupled look-back of Merrill and Garland's single-pass
-// scan; chain.h has its rules).
+// scan; chain.h has its rules).  Their words belong to the context, two arrays that calls use in turn, all zero to begin with:
+// the block with a call's last link clears the other one, so that no launch has to do it before
+// (us a call: up to 64 chunks 25 -> 23.5, 640 46 -> 43, ten variants of a 14.7 M weight network 568 -> 539).  In the header: the ticket, whose
+// bit 31 says which array is in use, and how many words of either are.
+constexpr uint32_t CHAIN_HEADER = 32, CHAIN_TICKET = 0, CHAIN_USED = 16;
+constexpr uint32_t CHAIN_SIDE = 1u << 31;
 constexpr uint32_t CHAIN_POLLS = 1u << 22;     // seconds: far beyond any wait that ends
 __device__ __forceinline__ void chain_store(uint64_t* p, uint64_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -356,7 +361,7 @@ template <bool DIRECT, uint32_t GROUPS>
 __global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void deflate_kernel(
     const uint8_t* __restrict__ in, uint64_t n_bytes, uint32_t n_chunks, uint16_t* __restrict__ side,
     uint64_t* __restrict__ marks, uint8_t* __restrict__ slots, uint32_t* __restrict__ seg_size,
-    uint64_t* __restrict__ status, uint32_t* __restrict__ ticket, uint64_t* __restrict__ seg_off,
+    uint64_t* chain, uint32_t chain_cap, uint64_t* __restrict__ seg_off,
     uint8_t* __restrict__ stream, uint64_t* __restrict__ mirror) {
     __shared__ __align__(16) uint32_t g_out[GROUPS][CODEC_OUT_DW];
     // of every sub-chunk's quarters the token bits before it (bits 0-15) and how far past its start its first
@@ -374,17 +379,22 @@ __global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void def
     const uint32_t lane = threadIdx.x & 63u, wid = uniform_u32(tid >> 6), half = lane >> 5, hl = lane & 31u;
     uint32_t link = blockIdx.x, c = link * GROUPS + group;
     if (DIRECT && threadIdx.x == 0) {
-        s_c = atomicAdd(ticket, 1u);
+        s_c = atomicAdd(reinterpret_cast<uint32_t*>(chain + CHAIN_TICKET), 1u);
         s_sized = 0;
     }
     // while the first wavefront waits for the ticket
     if (threadIdx.x - 64u < sizeof(CodeTable) / 16u)
         reinterpret_cast<uint4*>(&s_codes)[threadIdx.x - 64u] = reinterpret_cast<const uint4*>(&kCodeTable)[threadIdx.x - 64u];
     __syncthreads();
+    uint32_t side_now = 0;                              // which of the chain's two arrays is this call's
     if (DIRECT) {
         link = uniform_u32(s_c);
+        side_now = link >> 31;
+        link &= CHAIN_SIDE - 1u;
         c = link * GROUPS + group;
+        if (link == 0u && threadIdx.x == 0) chain_store(mirror + CHAIN_BROKE, 0ull);
     }
+    uint64_t* status = chain + CHAIN_HEADER + (uint64_t)side_now * chain_cap;
     const bool alive = c < n_chunks;                    // of the last block's groups maybe the first alone
     const uint64_t base = (uint64_t)c * CODEC_CHUNK;
     const uint32_t m = (uint32_t)min((uint64_t)CODEC_CHUNK, n_bytes - min(n_bytes, base));
@@ -618,6 +628,20 @@ __global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void def
             }
         }
         __syncthreads();
+        if (link == gridDim.x - 1u) {
+            // All tickets are drawn: the next call starts from 0 on the other array, of which this block clears what
+            // the call before left there.  (Nobody reads it now; this call's is left to the next one.)
+            const uint32_t other = side_now ^ 1u;
+            uint64_t* old = chain + CHAIN_HEADER + (uint64_t)other * chain_cap;
+            const uint32_t used = (uint32_t)chain[CHAIN_USED + other];
+            for (uint32_t i = threadIdx.x; i < used; i += DEF_THREADS * GROUPS) old[i] = 0;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                chain[CHAIN_USED + other] = 0;
+                chain[CHAIN_USED + side_now] = gridDim.x;
+                chain_store(chain + CHAIN_TICKET, (uint64_t)other << 31);
+            }
+        }
         const uint64_t off = g_off[group];
         if (!alive || off == ~0ull) return;
         dst = stream + off;
@@ -638,12 +662,8 @@ __global__ __launch_bounds__(DEF_THREADS * GROUPS, GROUPS == 1 ? 6 : 4) void def
     if (tid < seg_bytes - done) dst[done + tid] = out8[done + tid];
 }
 
-// Clears the chain of a call: the status words of its chunks, the ticket behind them and the word
-// that says that a wait ran out.
-__global__ __launch_bounds__(BLOCK) void chain_clear_kernel(uint64_t* status, uint32_t n, uint64_t* mirror) {
-    const uint32_t i = blockIdx.x * BLOCK + threadIdx.x;
-    if (i < n) status[i] = 0;
-    if (i == 0) mirror[CHAIN_BROKE] = 0;
+__global__ __launch_bounds__(BLOCK) void chain_zero_kernel(uint64_t* chain, uint64_t n) {
+    for (uint64_t i = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (uint64_t)gridDim.x * BLOCK) chain[i] = 0;
 }
 
 // Byte offsets of the segments: exclusive prefix sums of their sizes (one block).  A row is
@@ -1346,6 +1366,23 @@ static hipError_t codec_ensure_list(shifter_ctx* ctx, uint64_t entries) {
     return e;
 }
 
+// Words for the chains of up to `links` links.  What they outgrow is kept until the context goes: a recorded graph may
+// still use it.
+static hipError_t codec_ensure_chain(shifter_ctx* ctx, uint32_t links) {
+    if (ctx->codec_chain_cap >= links) return hipSuccess;
+    uint32_t cap = 1024;
+    while (cap < links) cap *= 2u;                       // links < 2^31
+    const uint64_t words = CHAIN_HEADER + 2ull * cap;
+    uint64_t* chain = nullptr;
+    const hipError_t e = hipMalloc(reinterpret_cast<void**>(&chain), words * sizeof(uint64_t));
+    if (e != hipSuccess) return e;
+    chain_zero_kernel<<<64, BLOCK, 0, ctx->stream>>>(chain, words);
+    if (ctx->d_codec_chain) ctx->codec_retired.push_back(ctx->d_codec_chain);
+    ctx->d_codec_chain = chain;
+    ctx->codec_chain_cap = cap;
+    return hipSuccess;
+}
+
 // Kernels only, nothing waited for.  Returns a HIP error code (0: fine).
 int launch_deflate(shifter_ctx* ctx, const uint8_t* d_in, uint64_t n_bytes, uint32_t n_chunks,
                    uint8_t* d_work, uint8_t* d_stream, uint64_t stream_cap, uint64_t* d_seg_off,
@@ -1356,18 +1393,16 @@ int launch_deflate(shifter_ctx* ctx, const uint8_t* d_in, uint64_t n_bytes, uint
     if (e != hipSuccess) return (int)e;
     if (stream_cap >= n_bytes + 5ull * n_chunks) {
         // the stream holds every segment stored: it cannot overflow, so the segments go straight
-        // to their places (the workspace holds the chain)
-        uint64_t* status = reinterpret_cast<uint64_t*>(d_work);
-        {
-            ProfileScope ps(ctx, K_CODEC_SCAN);
-            chain_clear_kernel<<<(n_chunks + BLOCK) / BLOCK, BLOCK, 0, ctx->stream>>>(status, n_chunks + 1u, ctx->dev_codec_mirror);
-        }
-        ProfileScope ps(ctx, K_DEFLATE_CHUNK);
+        // to their places (and the workspace is not needed)
         const bool two = n_chunks > DEFLATE_ONE_EACH;
+        const uint32_t links = two ? (n_chunks + 1u) / 2u : n_chunks;
+        const hipError_t ec = codec_ensure_chain(ctx, links);
+        if (ec != hipSuccess) return (int)ec;
+        ProfileScope ps(ctx, K_DEFLATE_CHUNK);
         const auto kernel = two ? deflate_kernel<true, 2> : deflate_kernel<true, 1>;
-        kernel<<<two ? (n_chunks + 1u) / 2u : n_chunks, two ? 2u * DEF_THREADS : DEF_THREADS, 0, ctx->stream>>>(
-            d_in, n_bytes, n_chunks, d_sub_bits, d_sub_marks, nullptr, nullptr, status,
-            reinterpret_cast<uint32_t*>(status + n_chunks), d_seg_off, d_stream, ctx->dev_codec_mirror);
+        kernel<<<links, two ? 2u * DEF_THREADS : DEF_THREADS, 0, ctx->stream>>>(
+            d_in, n_bytes, n_chunks, d_sub_bits, d_sub_marks, nullptr, nullptr, ctx->d_codec_chain, ctx->codec_chain_cap, d_seg_off,
+            d_stream, ctx->dev_codec_mirror);
         return 0;
     }
     uint32_t* seg_size = reinterpret_cast<uint32_t*>(d_work);
@@ -1376,8 +1411,7 @@ int launch_deflate(shifter_ctx* ctx, const uint8_t* d_in, uint64_t n_bytes, uint
     {
         ProfileScope ps(ctx, K_DEFLATE_CHUNK);
         deflate_kernel<false, 1><<<n_chunks, DEF_THREADS, 0, ctx->stream>>>(
-            d_in, n_bytes, n_chunks, d_sub_bits, d_sub_marks, slots, seg_size, nullptr, nullptr, nullptr, nullptr,
-            nullptr);
+            d_in, n_bytes, n_chunks, d_sub_bits, d_sub_marks, slots, seg_size, nullptr, 0u, nullptr, nullptr, nullptr);
     }
     {
         ProfileScope ps(ctx, K_CODEC_SCAN);
