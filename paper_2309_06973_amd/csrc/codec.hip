@@ -931,49 +931,56 @@ __device__ __forceinline__ LanePart lane_part(uint64_t mark, uint32_t q, uint32_
     return r;
 }
 
-// The state of a lane that decodes: a 64-bit window of the token bits in two registers, sh bits of it used up, and
-// where it writes.
+// The state of a lane that decodes: a 64-bit window of the token bits in two registers, from dword pos / 32 on, and
+// where it writes.  Bytes travel where the table has them, in bits 16-23.
 struct TokenReader {
-    uint32_t pos, end, w_lo, w_hi, sh, i, prev, bad;
+    uint32_t pos, end, w_lo, w_hi, i, prev, seen, dist;
+    // prev stays 0 until there is a literal: a lane starts with one
+    __device__ __forceinline__ void begin(const uint32_t* tab, uint32_t first, uint32_t last, uint32_t lo, uint32_t hi, uint32_t at) {
+        pos = first;
+        end = last;
+        w_lo = lo;
+        w_hi = hi;
+        i = at;
+        prev = dist = 0;
+        seen = pos < end ? (tab[__builtin_amdgcn_alignbit(w_hi, w_lo, pos) & 511u] & 32u) << 1 : 0u;
+    }
     // Up to two tokens, without branches but for the stores: the table gives
     // a token's bits, kind and value, and a literal reads as a match of length 1 of
     // itself; when the token behind it is a literal (three quarters of all tokens are,
     // in half-empty data) that one is taken in the same turn (a third one gained 1 %).  Offsets are not checked
     // on the way: a store wraps inside its sub-chunk's row, offsets only
-    // grow, and the end must come out exactly right.  w_new: the dword behind the window; true if it was taken in.
-    // put(offset, byte): only bytes that are not zero.
+    // grow, and the end must come out exactly right.  w_new: the dword behind the window.
+    // put(offset, byte << 16): only bytes that are not zero.
     template <typename Put>
-    __device__ __forceinline__ bool turn(const uint32_t* tab, uint32_t w_new, Put&& put) {
-        const uint32_t x = __builtin_amdgcn_alignbit(w_hi, w_lo, sh);
+    __device__ __forceinline__ void turn(const uint32_t* tab, uint32_t w_new, Put&& put) {
+        const uint32_t x = __builtin_amdgcn_alignbit(w_hi, w_lo, pos);
         const uint32_t t = tab[x & 511u];
         const uint32_t nb = t & 31u;
-        const uint32_t t2 = tab[(x >> nb) & 511u];                 // at most 18 of the 32 bits are used
+        const uint32_t t2 = tab[__builtin_amdgcn_ubfe(x, nb, 9u)];  // at most 18 of the 32 bits are used
         const uint32_t mm = 0u - ((t >> 5) & 1u);                  // all ones for a match
         const uint32_t len = ((t >> 7) & 0x1ffu) + __builtin_amdgcn_ubfe(x, (t >> 24) & 15u, t >> 28);
-        const uint32_t byte = ((t >> 16) & 0xffu) | (prev & mm);    // a match repeats the byte before it
-        // not a token of this library's set; a match before any literal of this lane, or
-        // at a distance other than 1
-        bad |= (t & 64u) | ((__builtin_amdgcn_ubfe(x, nb - 5u, 5u) | (prev >> 8)) & mm);
-        if ((byte & 0xffu) != 0u) {                                 // zeros are already there
+        const uint32_t byte = (prev & mm) | t;                      // a match repeats the byte before it
+        // not a token of this library's set (bit 6), or a match at a distance other than 1
+        seen |= t;
+        dist |= __builtin_amdgcn_ubfe(x, nb - 5u, 5u) & mm;
+        if ((byte & 0xff0000u) != 0u) {                             // zeros are already there
             put(i, byte);
             for (uint32_t u = 1; u < len; ++u) put(i + u, byte);
         }
         i += len;
         // the second token: a literal that starts before the lane's last bit
         const bool two = (t2 & 0x60u) == 0u && pos + nb < end;
-        const uint32_t byte2 = (t2 >> 16) & 0xffu;
-        if (two && byte2 != 0u) put(i, byte2);
-        const uint32_t used = nb + (two ? t2 & 31u : 0u);          // at most 18 + 9 bits
-        prev = two ? byte2 : byte;
+        if (two && (t2 & 0xff0000u) != 0u) put(i, t2);
+        const uint32_t next = pos + nb + (two ? t2 & 31u : 0u);    // at most 18 + 9 bits on
+        prev = two ? t2 : byte;
         i += two ? 1u : 0u;
-        pos += used;
-        sh += used;
-        const bool take = sh >= 32u;
+        const bool take = ((pos ^ next) & 32u) != 0u;
         w_lo = take ? w_hi : w_lo;
         w_hi = take ? w_new : w_hi;
-        sh &= 31u;
-        return take;
+        pos = next;
     }
+    __device__ __forceinline__ bool fine(uint32_t at) const { return ((seen & 64u) | dist) == 0u && pos == end && i == at; }
 };
 
 // The decoder: one block of 256 threads per chunk, four lanes per sub-chunk.  A chunk stored as one block
@@ -1107,26 +1114,18 @@ __global__ __launch_bounds__(CODEC_THREADS, 5) void inflate_sparse_kernel(
         if (ok) {
             const uint32_t row = l * CODEC_SUB;
             TokenReader r;
-            r.pos = bit0 + start + (in_block ? 0u : 3u) + part.b_lo;
-            r.end = r.pos + (part.b_hi - part.b_lo);
-            r.i = part.o_lo;
-            r.prev = 0x100u;                       // no literal of this lane yet
-            r.bad = 0;
-            r.sh = r.pos & 31u;
-            r.w_lo = s_seg[r.pos >> 5];
-            r.w_hi = s_seg[(r.pos >> 5) + 1u];
-            uint32_t nextw = (r.pos >> 5) + 2u;
+            const uint32_t first = bit0 + start + (in_block ? 0u : 3u) + part.b_lo;
+            r.begin(s_tab, first, first + (part.b_hi - part.b_lo), s_seg[first >> 5], s_seg[(first >> 5) + 1u], part.o_lo);
             while (r.pos < r.end) {
                 // the window's next dword, on its way while the tokens are looked up
-                const uint32_t w_new = s_seg[min(nextw, CODEC_SEG_SMALL - 1u)];
+                const uint32_t w_new = s_seg[min((r.pos >> 5) + 2u, CODEC_SEG_SMALL - 1u)];
                 // straight to memory, inside the sub-chunk and the output
-                const bool took = r.turn(s_tab, w_new, [&](uint32_t i, uint32_t byte) {
+                r.turn(s_tab, w_new, [&](uint32_t i, uint32_t byte) {
                     const uint32_t at = row + (i & (CODEC_SUB - 1u));
-                    if (at < m) dst[at] = (uint8_t)byte;
+                    if (at < m) dst[at] = (uint8_t)(byte >> 16);
                 });
-                nextw += took ? 1u : 0u;
             }
-            if (r.bad || r.pos != r.end || r.i != part.o_hi) ok = false;
+            if (!r.fine(part.o_hi)) ok = false;
         }
     } else if (mark != 0ull) {
         ok = false;
@@ -1136,12 +1135,14 @@ __global__ __launch_bounds__(CODEC_THREADS, 5) void inflate_sparse_kernel(
 
 // The instance of all other segments decodes into a zeroed LDS image of the chunk, which is then written out as whole lines.
 // A lane reads its own part of the segment, 56 bytes on half-full data, from memory: four dwords of it are in LDS, the two
-// behind them in registers or on their way, and every second turn moves on.  What bounds it is vector issue (some 50 of them a
+// behind them in registers or on their way, and every second turn moves on.  What bounds it is vector issue (some 42 instructions a
 // turn) and, in one round of chunks, a chunk's chain of latencies.  The whole segment staged in LDS took 68 KB with the
 // image: two blocks to a compute unit, and a second round of chunks beyond 512; with 39 KB four run.  us a call
 // (densities 0.05 / 0.3 / 0.5, before and now): 256 chunks 33 / 36 / 37 and 32 / 35 / 35, 1000 chunks 60 / 70 / 74 and 45 / 49 /
 // 52, 8192 chunks, where a third instance took the segments of up to 16 KiB, 412 / 469 / 514 and 258 / 295 / 319, 39347
-// chunks 1849 / 2192 / 2409 and 1080 / 1243 / 1333; 28 MB of a rebuilt variant, a third of it not zero, 71 and 52.
+// chunks 1849 / 2192 / 2409 and 1080 / 1243 / 1333; 28 MB of a rebuilt variant, a third of it not zero, 71 and 52.  The turn
+// with ten instructions less (the bit position alone says where the window and the ring are, bytes stay where the table has
+// them, offsets in the image are turned once): 8192 chunks of 30 % 296 -> 276, 39347 1241 -> 1170, the rebuilt variant 51.2 -> 48.4.
 constexpr uint32_t INFLATE_RING = 4;
 typedef uint32_t u32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 __device__ __forceinline__ void inflate_dense(
@@ -1230,38 +1231,33 @@ __device__ __forceinline__ void inflate_dense(
         if (!part.ok) ok = false;
         if (ok) {
             const uint32_t row = l * CODEC_SUB, rot = 16u * l;   // image byte of offset k: row + ((k + rot) & 511)
-            TokenReader r;
-            r.pos = bit0 + start + (in_block ? 0u : 3u) + part.b_lo;
-            r.end = r.pos + (part.b_hi - part.b_lo);
-            r.i = part.o_lo;
-            r.prev = 0x100u;                       // no literal of this lane yet
-            r.bad = 0;
-            r.sh = r.pos & 31u;
+            const uint32_t first = bit0 + start + (in_block ? 0u : 3u) + part.b_lo;
             // Dwords at, at + 1.  The tokens end at least four bytes before the segment does, so none lies in the stream's
             // last dword: what is read again there is not used.
             auto two = [&](uint32_t at) { return *reinterpret_cast<const u32x2_a4*>(g.dw + min(at, g.max_w - 1u)); };
-            uint32_t nextw = (r.pos >> 5) + 2u, filled = nextw + 2u;     // the ring holds [nextw, filled)
-            const u32x2_a4 first = two(nextw - 2u), second = two(nextw);
+            const uint32_t behind = (first >> 5) + 2u;
+            uint32_t filled = behind + 2u;                       // the ring holds the two dwords behind the window, up to this one
+            const u32x2_a4 window = two(behind - 2u), next = two(behind);
             u32x2_a4 ahead = two(filled);
             uint32_t* ring = s_ring + tid;
             auto slot = [&](uint32_t at) { return (at & (INFLATE_RING - 1u)) * CODEC_THREADS; };
-            r.w_lo = first.x;
-            r.w_hi = first.y;
-            ring[slot(nextw)] = second.x;
-            ring[slot(nextw + 1u)] = second.y;
-            auto put = [&](uint32_t i, uint32_t byte) { img8[row + ((i + rot) & (CODEC_SUB - 1u))] = (uint8_t)byte; };
+            ring[slot(behind)] = next.x;
+            ring[slot(behind + 1u)] = next.y;
+            TokenReader r;
+            r.begin(s_tab, first, first + (part.b_hi - part.b_lo), window.x, window.y, part.o_lo + rot);
+            auto put = [&](uint32_t i, uint32_t byte) { img8[row | (i & (CODEC_SUB - 1u))] = (uint8_t)(byte >> 16); };
             while (r.pos < r.end) {
                 // two turns take in two dwords at most
-                if (filled - nextw <= 2u) {
+                if (filled - (r.pos >> 5) <= 4u) {
                     ring[slot(filled)] = ahead.x;
                     ring[slot(filled + 1u)] = ahead.y;
                     filled += 2u;
                     ahead = two(filled);
                 }
-                nextw += r.turn(s_tab, ring[slot(nextw)], put) ? 1u : 0u;
-                if (r.pos < r.end) nextw += r.turn(s_tab, ring[slot(nextw)], put) ? 1u : 0u;
+                r.turn(s_tab, ring[slot((r.pos >> 5) + 2u)], put);
+                if (r.pos < r.end) r.turn(s_tab, ring[slot((r.pos >> 5) + 2u)], put);
             }
-            if (r.bad || r.pos != r.end || r.i != part.o_hi) ok = false;
+            if (!r.fine(part.o_hi + rot)) ok = false;
         }
     } else if (mark != 0ull) {
         ok = false;
