@@ -1,0 +1,43 @@
+"""The rebuild of a portfolio from rectangles of 2048 and of 8192 weights, on networks of either side of the limit between
+them: kernels of 1 to 25 weights, widths that leave ragged bands and chunks, filters that die one by one."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import shifter_oracle as O
+from paper_2309_06973_amd import synth
+from paper_2309_06973_amd.pipeline import Pipeline
+
+pytestmark = pytest.mark.gpu
+
+LIMIT = 524288
+
+
+@pytest.mark.parametrize("kernel,widths,small", [(3, [37, 91, 211, 131], True), (3, [60, 120, 200, 155], False), (1, [130, 515, 700], True),
+                                                 (1, [130, 515, 1100], False), (5, [33, 71, 129, 63], True), (5, [33, 97, 161, 66], False),
+                                                 (3, [1, 700, 3, 900], True), (3, [2, 1300, 47], False)])
+def test_rebuild(kernel, widths, small):
+    spec = synth.chain_spec(widths, k=kernel, in_ch=3)
+    assert (spec.w_elems <= LIMIT) == small
+    rng = np.random.Generator(np.random.Philox(spec.w_elems))
+    w = rng.standard_normal(spec.w_elems, dtype=np.float32)
+    for t in spec.tensors:                    # filters of very different size: some die at every sparsity
+        f = np.exp(rng.standard_normal(t.out_ch) * 3.0).astype(np.float32)
+        w[t.offset:t.offset + t.numel].reshape(t.out_ch, -1)[:] *= f[:, None]
+    v = rng.standard_normal(max(spec.v_elems, 4)).astype(np.float32)
+    n = spec.n_prunable
+    ps = [0, n // 3, (7 * n) // 10, (95 * n) // 100, n // 2]
+    refs = O.prune_and_compact(w, v, spec.tensors, spec.vecs, spec.groups, ps)
+    pl = Pipeline(spec, w, v)
+    try:
+        pl.enable_batch(len(ps))
+        _, (rc, ot, ov, ew, ev) = pl.step(ps)
+        torch.cuda.synchronize()
+        for i, ref in enumerate(refs):
+            assert (ew[i], ev[i]) == (ref.compacted.w.size, ref.compacted.v.size)
+            got = pl.b_w_out[i * pl.cap_w:i * pl.cap_w + ew[i]].cpu().numpy()
+            assert np.array_equal(got.view(np.uint32), ref.compacted.w.view(np.uint32))
+            got = pl.b_vecs_out[i * pl.cap_v:i * pl.cap_v + ev[i]].cpu().numpy()
+            assert np.array_equal(got.view(np.uint32), ref.compacted.v.view(np.uint32))
+    finally:
+        pl.close()
