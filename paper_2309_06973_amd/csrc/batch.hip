@@ -36,13 +36,19 @@ __global__ __launch_bounds__(BLOCK) void zero_u32_kernel(uint32_t* a, uint64_t n
     if (i < n) a[i] = 0;
 }
 
+// Where the ranking could not decide (undecided), the step is made again: of this pass only the filters' levels are read then,
+// by the plan of the rebuild behind it.  No arenas, masks and input features (the maxima of a tile's
+// hundreds of them go past the L2, tile after tile to the same words), and a rank without its cut removes nothing, so
+// only the others' cuts are compared.  Ten variants of 14.7 M weights in half precision, kernel, us: 127 with the
+// stores, 67 with the levels of the input features, 32 without (a set of maxima, those too, for four tiles: 40).
 template <bool NT>
 __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
     const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix, uint32_t n_t,
     const float* __restrict__ w, const shifter_threshold* __restrict__ thr, uint32_t k_var,
     float* __restrict__ w_out, uint64_t w_stride, uint8_t* __restrict__ mask,
     uint64_t mask_stride, uint32_t* out_level, uint32_t* in_level, const uint32_t* __restrict__ undecided) {
-    if (undecided && (*undecided & 1u)) { w_out = nullptr; mask = nullptr; }
+    const bool alone = undecided && (*undecided & 1u);
+    if (alone) { w_out = nullptr; mask = nullptr; }
     __shared__ uint32_t rowmax[TILE + 16];
     __shared__ uint32_t colmax[TILE + 16];
     __shared__ uint64_t s_cut[MAXK];
@@ -57,10 +63,19 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
     const uint32_t g0 = (uint32_t)(T.gbase + e0);
     const uint32_t c0 = e0 % T.khw, r0 = e0 % T.row_len;
     const uint32_t nrows = (r0 + n - 1) / T.row_len + 1;
-    const uint32_t ncols = (c0 + n - 1) / T.khw + 1;
+    const uint32_t ncols = alone ? 0u : (c0 + n - 1) / T.khw + 1;
     for (uint32_t s = threadIdx.x; s < nrows; s += BLOCK) rowmax[s] = 0;
     for (uint32_t s = threadIdx.x; s < ncols; s += BLOCK) colmax[s] = 0;
-    if (threadIdx.x < k_var) s_cut[threadIdx.x] = thr[threadIdx.x].cut;
+    uint32_t n_cut = k_var;                 // cuts to compare with; the other variants keep everything
+    if (alone) {
+        static_assert(MAXK == 64, "a lane for every variant");
+        const uint64_t cut = (threadIdx.x & 63u) < k_var ? thr[threadIdx.x & 63u].cut : 0ull;
+        const uint64_t with_cut = __ballot(cut != 0ull);
+        if (threadIdx.x < 64u && cut) s_cut[__popcll(with_cut & ((1ull << threadIdx.x) - 1ull))] = cut;
+        n_cut = (uint32_t)__popcll(with_cut);
+    } else if (threadIdx.x < k_var) {
+        s_cut[threadIdx.x] = thr[threadIdx.x].cut;
+    }
     __syncthreads();
 
     const float* src = w + T.offset + e0;
@@ -86,6 +101,7 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
 #pragma unroll
             for (uint32_t q = 0; q < 4u; ++q) raise(&rowmax[div_small(r0 + j + q, T.row_len, T.magic_row)], l[q]);
         }
+        if (alone) return;
         if (col == col3) {
             raise(&colmax[col], top);
         } else {
@@ -110,9 +126,9 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
         for (uint32_t u = 0; u < U; ++u) v[u] = load_u4<NT>(src + 4u * q0 + 256u * u);
         uint32_t lvl[U][4];
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) lvl[u][0] = lvl[u][1] = lvl[u][2] = lvl[u][3] = 0;
+        for (uint32_t u = 0; u < U; ++u) lvl[u][0] = lvl[u][1] = lvl[u][2] = lvl[u][3] = k_var - n_cut;
         uint32_t* xm = s_xm + wid * (64u * U);
-        for (uint32_t k = 0; k < k_var; ++k) {
+        for (uint32_t k = 0; k < n_cut; ++k) {
             const uint64_t cut = ranked ? s_cut[k] : 0;
             float* dst = w_out + (uint64_t)k * w_stride + T.offset + e0;
             uint8_t* mdst = want_mask ? mask + (uint64_t)k * mask_stride + T.gbase + e0 : nullptr;
@@ -164,8 +180,9 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
                 if (here > 2u) x.z = __float_as_uint(src[j + 2u]);
             }
             const uint32_t b[4] = {x.x, x.y, x.z, x.w};
-            uint32_t l[4] = {0, 0, 0, 0};
-            for (uint32_t k = 0; k < k_var; ++k) {
+            uint32_t l[4];
+            l[0] = l[1] = l[2] = l[3] = k_var - n_cut;
+            for (uint32_t k = 0; k < n_cut; ++k) {
                 const uint64_t cut = ranked ? s_cut[k] : 0;
                 uint32_t o[4], keep[4];
 #pragma unroll

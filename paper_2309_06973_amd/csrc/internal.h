@@ -451,7 +451,7 @@ void launch_compact(shifter_ctx* ctx, const shifter_model* m, const float* d_w, 
 void launch_plan_and_gather(shifter_ctx* ctx, const shifter_model* m, const PortfolioBuffers& a,
                             bool from_levels, const MultiPerm& pos);
 // The batched mask pass alone, on cleared level arrays.  undecided: bit 0 of that word says that the
-// records are not there yet and the caller will make the step again: levels only (or nullptr).
+// records are not there yet and the caller will make the step again: the levels of the filters only (or nullptr).
 void launch_mask_scan_batch_core(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
                                  const shifter_threshold* d_thr, uint32_t k_var, float* d_w_out,
                                  uint64_t w_stride, uint8_t* d_mask, uint64_t mask_stride,
