@@ -1423,8 +1423,8 @@ extern "C" int shifter_portfolio_begin(shifter_ctx* ctx, const shifter_model* mo
             // Where the ranking could not decide the step is made again (portfolio_end), so this pass leaves the sparse
             // arenas and masks to that one; the filters' levels are what the launches behind it read.  (A rebuild
             // from the sparse arenas has to find some of this model's.)  Ten variants of 14.7 M
-            // weights kept in half precision: this pass 132 us with them, 32 without, the call 593 with its levels of
-            // the input features, 559 without
+            // weights kept in half precision: this pass 132 us with them, 24 without, the call 593 with its levels of
+            // the input features, 552 without
             launch_mask_scan_batch_core(ctx, model, g.d_w, g.d_thr, K, g.d_w_sparse, g.w_stride, g.d_mask,
                                         g.mask_stride, k_eff && rebuild_reads_dense(model, pp.buf) ? &b.multi->status : nullptr);
             launch_plan_and_gather(ctx, model, pp.buf, true, cut_positions(pp.pc, K));

@@ -40,20 +40,15 @@ __global__ __launch_bounds__(BLOCK) void zero_u32_kernel(uint32_t* a, uint64_t n
 // by the plan of the rebuild behind it.  No arenas, masks and input features (the maxima of a tile's
 // hundreds of them go past the L2, tile after tile to the same words), and a rank without its cut removes nothing, so
 // only the others' cuts are compared.  Ten variants of 14.7 M weights in half precision, kernel, us: 127 with the
-// stores, 67 with the levels of the input features, 32 without (a set of maxima, those too, for four tiles: 40).
-template <bool NT>
-__global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
+// stores, 67 with the levels of the input features, 24 without (a set of maxima, those too, for four tiles: 40; 32 where one
+// instance told the cases apart as it ran, and 1 % more on decided steps).
+template <bool NT, bool ALONE>
+__device__ __forceinline__ void mask_scan_batch_tile(
     const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix, uint32_t n_t,
     const float* __restrict__ w, const shifter_threshold* __restrict__ thr, uint32_t k_var,
     float* __restrict__ w_out, uint64_t w_stride, uint8_t* __restrict__ mask,
-    uint64_t mask_stride, uint32_t* out_level, uint32_t* in_level, const uint32_t* __restrict__ undecided) {
-    const bool alone = undecided && (*undecided & 1u);
-    if (alone) { w_out = nullptr; mask = nullptr; }
-    __shared__ uint32_t rowmax[TILE + 16];
-    __shared__ uint32_t colmax[TILE + 16];
-    __shared__ uint64_t s_cut[MAXK];
-    __shared__ __align__(16) uint32_t s_xm[TILE / 4];   // mask words of the tile, per wavefront
-
+    uint64_t mask_stride, uint32_t* out_level, uint32_t* in_level, uint32_t* rowmax, uint32_t* colmax, uint64_t* s_cut,
+    uint32_t* s_xm) {
     const uint32_t tile = blockIdx.x;
     const uint32_t t = find_tensor(tile_prefix, n_t, tile);
     const DevTensor T = tens[t];
@@ -63,11 +58,11 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
     const uint32_t g0 = (uint32_t)(T.gbase + e0);
     const uint32_t c0 = e0 % T.khw, r0 = e0 % T.row_len;
     const uint32_t nrows = (r0 + n - 1) / T.row_len + 1;
-    const uint32_t ncols = alone ? 0u : (c0 + n - 1) / T.khw + 1;
+    const uint32_t ncols = ALONE ? 0u : (c0 + n - 1) / T.khw + 1;
     for (uint32_t s = threadIdx.x; s < nrows; s += BLOCK) rowmax[s] = 0;
     for (uint32_t s = threadIdx.x; s < ncols; s += BLOCK) colmax[s] = 0;
     uint32_t n_cut = k_var;                 // cuts to compare with; the other variants keep everything
-    if (alone) {
+    if (ALONE) {
         static_assert(MAXK == 64, "a lane for every variant");
         const uint64_t cut = (threadIdx.x & 63u) < k_var ? thr[threadIdx.x & 63u].cut : 0ull;
         const uint64_t with_cut = __ballot(cut != 0ull);
@@ -101,7 +96,7 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
 #pragma unroll
             for (uint32_t q = 0; q < 4u; ++q) raise(&rowmax[div_small(r0 + j + q, T.row_len, T.magic_row)], l[q]);
         }
-        if (alone) return;
+        if (ALONE) return;
         if (col == col3) {
             raise(&colmax[col], top);
         } else {
@@ -228,6 +223,24 @@ __global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
             if (*f < l) atomicMax(f, l);
         }
     }
+}
+
+template <bool NT>
+__global__ __launch_bounds__(BLOCK) void mask_scan_batch_kernel(
+    const DevTensor* __restrict__ tens, const uint32_t* __restrict__ tile_prefix, uint32_t n_t,
+    const float* __restrict__ w, const shifter_threshold* __restrict__ thr, uint32_t k_var,
+    float* __restrict__ w_out, uint64_t w_stride, uint8_t* __restrict__ mask,
+    uint64_t mask_stride, uint32_t* out_level, uint32_t* in_level, const uint32_t* __restrict__ undecided) {
+    __shared__ uint32_t rowmax[TILE + 16];
+    __shared__ uint32_t colmax[TILE + 16];
+    __shared__ uint64_t s_cut[MAXK];
+    __shared__ __align__(16) uint32_t s_xm[TILE / 4];   // mask words of the tile, per wavefront
+    if (undecided && (*undecided & 1u))
+        mask_scan_batch_tile<NT, true>(tens, tile_prefix, n_t, w, thr, k_var, nullptr, 0, nullptr, 0, out_level, in_level,
+                                       rowmax, colmax, s_cut, s_xm);
+    else
+        mask_scan_batch_tile<NT, false>(tens, tile_prefix, n_t, w, thr, k_var, w_out, w_stride, mask, mask_stride, out_level,
+                                        in_level, rowmax, colmax, s_cut, s_xm);
 }
 
 // alive[k][i] = level[i] > pos[k], for the out and the in flags of every variant.
