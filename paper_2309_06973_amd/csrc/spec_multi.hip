@@ -517,6 +517,8 @@ __global__ __launch_bounds__(MF_THREADS) void ms_finish_kernel(
     __shared__ uint64_t smem[FIN_THREADS / 64 + 1];
     __shared__ uint64_t s_below, s_inside, s_r2, s_less, s_sel, s_base2;
     __shared__ uint32_t s_over, s_n, s_base, s_bin, s_cnt, s_last, s_why, s_lt, s_eq, s_nb;
+    __shared__ TiedLds s_tied;
+    static_assert(FIN_LIST <= FIN_THREADS && FIN_DIRECT <= TIED_DIRECT, "more than TIED_DIRECT have one key, and a thread each");
     const uint32_t part = blockIdx.x, k = blockIdx.y;     // the block's parts: part, part + gridDim.x, ...
     const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
     const RankIn R = ms->rin[k];
@@ -706,12 +708,22 @@ __global__ __launch_bounds__(MF_THREADS) void ms_finish_kernel(
     });
     __syncthreads();
     if (s_nb != cnt_sel || r == 0 || r > cnt_sel) { give_up(1u); return; }
-    const uint64_t want = r - 1;
-    for (uint32_t i = threadIdx.x; i < cnt_sel; i += FIN_THREADS) {
-        const uint64_t c = comp[i];
-        uint32_t rank = 0;
-        for (uint32_t f = 0; f < cnt_sel; ++f) rank += comp[f] < c;
-        if (rank == want) s_sel = c;        // composites are distinct: exactly one hit
+    uint32_t want = (uint32_t)r - 1u;
+    auto count = [&](const uint64_t* among, uint32_t n_among) {
+        for (uint32_t i = threadIdx.x; i < n_among; i += FIN_THREADS) {
+            const uint64_t c = among[i];
+            uint32_t rank = 0;
+            for (uint32_t f = 0; f < n_among; ++f) rank += among[f] < c;
+            if (rank == want) s_sel = c;        // composites are distinct: exactly one hit
+        }
+    };
+    if (cnt_sel > TIED_DIRECT) {
+        uint64_t* few = reinterpret_cast<uint64_t*>(stage);      // the list has been read
+        const uint2 left = tied_stretch<FIN_THREADS, FIN_BINS>(comp, cnt_sel, want, h, smem, few, &s_tied);
+        want = left.y;
+        count(few, left.x);
+    } else {
+        count(comp, cnt_sel);
     }
     __syncthreads();
     const uint64_t sel = s_sel;

@@ -183,4 +183,48 @@ __device__ __forceinline__ uint32_t sample_bin_of_rank(const uint32_t* prefix, u
     return a;
 }
 
+// The last step of a finish, n distinct composites (at most THREADS of them) of one key: counting for each those below it is
+// quadratic, so more than TIED_DIRECT go by the upper bits of their indices first.  Leaves those that share them with
+// the one of 0-based rank `want` in `few` and returns their number and the rank among them; the caller meets
+// a barrier before.  Ten ranks of 14.7 M weights in half precision, some with hundreds of ties: the finish 30.9 us by counting
+// alone, 17.1 so; one count of 14.7 M 114 -> 103 us a step.
+constexpr uint32_t TIED_DIRECT = 256;
+struct TiedLds {
+    uint64_t base;
+    uint32_t any, bin, n;
+};
+template <uint32_t THREADS, uint32_t BINS>
+__device__ __forceinline__ uint2 tied_stretch(const uint64_t* comp, uint32_t n, uint32_t want, uint32_t* h, uint64_t* smem,
+                                                 uint64_t* few, TiedLds* s) {
+    const uint32_t idx = threadIdx.x < n ? (uint32_t)comp[threadIdx.x] : 0u;
+    uint32_t any = idx;
+    for (uint32_t d = 32; d > 0; d >>= 1) any |= (uint32_t)__shfl_xor((int)any, (int)d, 64);
+    constexpr uint32_t PER = BINS / THREADS;
+    const uint32_t b0 = threadIdx.x * PER;
+#pragma unroll
+    for (uint32_t i = 0; i < PER; ++i) h[b0 + i] = 0;
+    if (threadIdx.x == 0) { s->any = 0; s->n = 0; }
+    __syncthreads();
+    if ((threadIdx.x & 63u) == 0 && any) atomicOr(&s->any, any);
+    __syncthreads();
+    static_assert(BINS == 1u << 12, "twelve bits a bin");
+    const uint32_t bits = 32u - (uint32_t)__clz((int)s->any), sh = bits > 12u ? bits - 12u : 0u;
+    if (threadIdx.x < n) atomicAdd(&h[idx >> sh], 1u);
+    __syncthreads();
+    uint32_t c[PER];
+    uint64_t sum = 0, tot;
+#pragma unroll
+    for (uint32_t i = 0; i < PER; ++i) { c[i] = h[b0 + i]; sum += c[i]; }
+    uint64_t base = block_excl_scan_u64<THREADS>(sum, smem, &tot);
+#pragma unroll
+    for (uint32_t i = 0; i < PER; ++i) {
+        if (base <= want && want < base + c[i]) { s->bin = b0 + i; s->base = base; }
+        base += c[i];
+    }
+    __syncthreads();
+    if (threadIdx.x < n && (idx >> sh) == s->bin) few[atomicAdd(&s->n, 1u)] = comp[threadIdx.x];
+    __syncthreads();
+    return make_uint2(s->n, want - (uint32_t)s->base);
+}
+
 }  // namespace shifter

@@ -409,6 +409,8 @@ __global__ __launch_bounds__(FIN_THREADS) void spec_finish_kernel(
     __shared__ uint32_t s_n, s_base, s_bin, s_cnt1, s_last, s_status, s_sub[FIN_SUBS];
     __shared__ uint64_t s_r2, s_less;
     __shared__ uint32_t s_lt, s_eq, s_bin2, s_cnt2, s_nb;
+    __shared__ TiedLds s_tied;
+    static_assert(SPEC_SMALL_CAP <= FIN_THREADS, "a thread for each");
     const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
     static_assert(SPEC_SUB == BLOCK && FBINS1 == BLOCK, "one split counter and one round-1 bin per thread");
     // the first candidates of the block's sub-buffers, on their way while the P-th pair is located (a sub-buffer has
@@ -488,9 +490,8 @@ __global__ __launch_bounds__(FIN_THREADS) void spec_finish_kernel(
         *thr = out;
         const uint32_t undecided = decided ? 0u : 1u;
         const uint32_t status = atomicOr(&ss->status, undecided) | undecided;
-        SpecState mirror = *ss;
-        mirror.status = status;
-        *host_mirror = mirror;
+        *host_mirror = *ss;               // no copy of it in between, which would be scratch memory
+        host_mirror->status = status;
     };
     if (!reached || bin == 0xffffffffu || s_cnt1 > SPEC_LIST_CAP) {      // the same in every block
         if (blockIdx.x == 0 && threadIdx.x == 0) publish(false);
@@ -589,12 +590,22 @@ __global__ __launch_bounds__(FIN_THREADS) void spec_finish_kernel(
         }
     });
     __syncthreads();
-    const uint64_t want = s_r3 - 1;   // 0-based rank inside the bin
-    for (uint32_t i = threadIdx.x; i < cnt2; i += FIN_THREADS) {
-        const uint64_t c = comp[i];
-        uint32_t rank = 0;
-        for (uint32_t f = 0; f < cnt2; ++f) rank += comp[f] < c;
-        if (rank == want) s_sel = c;    // composites are distinct: exactly one hit
+    uint32_t want = (uint32_t)s_r3 - 1u;         // 0-based rank inside the bin
+    auto count = [&](const uint64_t* among, uint32_t n_among) {
+        for (uint32_t i = threadIdx.x; i < n_among; i += FIN_THREADS) {
+            const uint64_t c = among[i];
+            uint32_t rank = 0;
+            for (uint32_t f = 0; f < n_among; ++f) rank += among[f] < c;
+            if (rank == want) s_sel = c;        // composites are distinct: exactly one hit
+        }
+    };
+    if (cnt2 > TIED_DIRECT && sh2 == 0) {
+        uint64_t* few = reinterpret_cast<uint64_t*>(stage);      // the list has been read
+        const uint2 left = tied_stretch<FIN_THREADS, FBINS>(comp, cnt2, want, h, smem, few, &s_tied);
+        want = left.y;
+        count(few, left.x);
+    } else {
+        count(comp, cnt2);
     }
     __syncthreads();
     const uint64_t sel = s_sel;
