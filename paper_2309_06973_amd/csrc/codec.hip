@@ -1338,7 +1338,7 @@ static void codec_end(shifter_ctx* ctx) {
 
 // Up to this many chunks, three to each of 256 compute units, a block takes one chunk, beyond it two: they
 // wait for each other at the barriers, which a chip that is not full notices, and share a ticket and a link.  us a
-// call, one / two, by the share of weights that are not zero:
+// call, one / two, by the share of weights that are not zero (both with a launch that cleared the chain, 1.5 us, since gone):
 //   chunks    none        0.5 %       5 %         30 %        all
 //   769       34 / 30     42 / 41     48 / 46     51 / 49     44 / 40
 //   1024      41 / 33     49 / 44     53 / 49     56 / 52     52 / 45
