@@ -480,7 +480,8 @@ int shifter_fold_bn(shifter_ctx* ctx, const shifter_model* model,
  *                        SHIFTER_ERR_INTERNAL then); either pointer may be NULL.
  * The codec calls need no model.  They keep some 40 bytes per chunk of device
  * memory in the context, allocated when an input with more chunks than before comes (so
- * a call recorded into a HIP graph must follow an eager one of at least that size). */
+ * a call recorded into a HIP graph must follow an eager one, of either kind, of at least
+ * that size). */
 #define SHIFTER_CODEC_CHUNK 32768u
 #define SHIFTER_CODEC_SUB 512u
 int shifter_codec_layout(uint64_t n_bytes, uint64_t* h_n_chunks, uint64_t* h_work_bytes,

@@ -313,7 +313,8 @@ __device__ __forceinline__ uint32_t incl_sum32(uint32_t x) {
 // scan; chain.h has its rules).  Their words belong to the context, two arrays that calls use in turn, all zero to begin with:
 // the block with a call's last link clears the other one, so that no launch has to do it before
 // (us a call: up to 64 chunks 25 -> 23.5, 640 46 -> 43, ten variants of a 14.7 M weight network 568 -> 539).  In the header: the ticket, whose
-// bit 31 says which array is in use, and how many words of either are.
+// bit 31 says which array is in use, and how many words of either are.  A recorded call has one array, in the caller's
+// workspace, that a launch clears.
 constexpr uint32_t CHAIN_HEADER = 32, CHAIN_TICKET = 0, CHAIN_USED = 16;
 constexpr uint32_t CHAIN_SIDE = 1u << 31;
 constexpr uint32_t CHAIN_POLLS = 1u << 22;     // seconds: far beyond any wait that ends
@@ -1326,14 +1327,15 @@ __global__ void codec_publish_kernel(uint64_t* __restrict__ result, uint64_t* __
 
 // The result words are zero when a call starts: the context allocates them cleared and every
 // call's last kernel leaves them so.  Only a call that could not enqueue all of its kernels
-// leaves them in doubt; the call after it clears them itself.
-static void codec_begin(shifter_ctx* ctx) {
+// leaves them in doubt; the call after it clears them itself.  (What a recorded call enqueues has not run: it says
+// nothing about the words.)
+static void codec_begin(shifter_ctx* ctx, bool recording) {
     if (ctx->codec_dirty) codec_clear_kernel<<<1, 1, 0, ctx->stream>>>(ctx->d_codec);
-    ctx->codec_dirty = true;
+    if (!recording) ctx->codec_dirty = true;
 }
-static void codec_end(shifter_ctx* ctx) {
+static void codec_end(shifter_ctx* ctx, bool recording) {
     codec_publish_kernel<<<1, 1, 0, ctx->stream>>>(ctx->d_codec, ctx->dev_codec_mirror);
-    if (hipPeekAtLastError() == hipSuccess) ctx->codec_dirty = false;
+    if (!recording && hipPeekAtLastError() == hipSuccess) ctx->codec_dirty = false;
 }
 
 // Up to this many chunks, three to each of 256 compute units, a block takes one chunk, beyond it two: they
@@ -1362,9 +1364,23 @@ static hipError_t codec_ensure_list(shifter_ctx* ctx, uint64_t entries) {
     return e;
 }
 
-// Words for the chains of up to `links` links.  What they outgrow is kept until the context goes: a recorded graph may
-// still use it.
-static hipError_t codec_ensure_chain(shifter_ctx* ctx, uint32_t links) {
+// Whether the context's stream is recording (the null stream never is).
+static hipError_t codec_recording(const shifter_ctx* ctx, bool* recording) {
+    *recording = false;
+    if (!ctx->stream) return hipSuccess;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(ctx->stream, &status);
+    *recording = status != hipStreamCaptureStatusNone;
+    return e;
+}
+
+// A block takes one chunk or two (DEFLATE_ONE_EACH).
+static uint32_t deflate_links(uint32_t n_chunks) { return n_chunks > DEFLATE_ONE_EACH ? (n_chunks + 1u) / 2u : n_chunks; }
+
+// Words for the chain of an input of so many chunks.  Every call that is not recorded makes room for it, the decoder's too:
+// nothing is allocated behind a call of that size.  Recorded calls have their chain elsewhere.
+static hipError_t codec_ensure_chain(shifter_ctx* ctx, uint32_t n_chunks) {
+    const uint32_t links = deflate_links(n_chunks);
     if (ctx->codec_chain_cap >= links) return hipSuccess;
     uint32_t cap = 1024;
     while (cap < links) cap *= 2u;                       // links < 2^31
@@ -1373,6 +1389,11 @@ static hipError_t codec_ensure_chain(shifter_ctx* ctx, uint32_t links) {
     const hipError_t e = hipMalloc(reinterpret_cast<void**>(&chain), words * sizeof(uint64_t));
     if (e != hipSuccess) return e;
     chain_zero_kernel<<<64, BLOCK, 0, ctx->stream>>>(chain, words);
+    const hipError_t zeroed = hipPeekAtLastError();
+    if (zeroed != hipSuccess) {
+        (void)hipFree(chain);
+        return zeroed;
+    }
     if (ctx->d_codec_chain) ctx->codec_retired.push_back(ctx->d_codec_chain);
     ctx->d_codec_chain = chain;
     ctx->codec_chain_cap = cap;
@@ -1383,27 +1404,40 @@ static hipError_t codec_ensure_chain(shifter_ctx* ctx, uint32_t links) {
 int launch_deflate(shifter_ctx* ctx, const uint8_t* d_in, uint64_t n_bytes, uint32_t n_chunks,
                    uint8_t* d_work, uint8_t* d_stream, uint64_t stream_cap, uint64_t* d_seg_off,
                    uint16_t* d_sub_bits, uint64_t* d_sub_marks) {
-    // the decoder's list: a call of either kind makes room for it, so that either may be
-    // recorded into a graph behind it
-    const hipError_t e = codec_ensure_list(ctx, n_chunks);
+    // the decoder's list and the encoder's chain: a call of either kind makes room for both, so that
+    // either may be recorded into a graph behind it
+    bool recording;
+    hipError_t e = codec_recording(ctx, &recording);
+    if (e == hipSuccess) e = codec_ensure_list(ctx, n_chunks);
+    if (e == hipSuccess && !recording) e = codec_ensure_chain(ctx, n_chunks);
     if (e != hipSuccess) return (int)e;
     if (stream_cap >= n_bytes + 5ull * n_chunks) {
         // the stream holds every segment stored: it cannot overflow, so the segments go straight
-        // to their places (and the workspace is not needed)
+        // to their places
         const bool two = n_chunks > DEFLATE_ONE_EACH;
-        const uint32_t links = two ? (n_chunks + 1u) / 2u : n_chunks;
-        const hipError_t ec = codec_ensure_chain(ctx, links);
-        if (ec != hipSuccess) return (int)ec;
+        const uint32_t links = deflate_links(n_chunks);
+        uint64_t* chain = ctx->d_codec_chain;
+        uint32_t chain_cap = ctx->codec_chain_cap;
+        if (recording) {
+            // The context's words are its own calls' in turn, and grow: a replay, which may come at any time, has none of
+            // them.  The workspace holds a slot of 32776 bytes a chunk, which this form leaves empty.
+            static_assert((CHAIN_HEADER + 1u) * sizeof(uint64_t) <= CODEC_SLOT, "a header and a word for each chunk");
+            chain = reinterpret_cast<uint64_t*>(d_work);
+            chain_cap = links;
+            const uint32_t words = CHAIN_HEADER + links;
+            ProfileScope ps(ctx, K_CODEC_SCAN);
+            chain_zero_kernel<<<std::min((words + BLOCK - 1u) / BLOCK, 64u), BLOCK, 0, ctx->stream>>>(chain, words);
+        }
         ProfileScope ps(ctx, K_DEFLATE_CHUNK);
         const auto kernel = two ? deflate_kernel<true, 2> : deflate_kernel<true, 1>;
         kernel<<<links, two ? 2u * DEF_THREADS : DEF_THREADS, 0, ctx->stream>>>(
-            d_in, n_bytes, n_chunks, d_sub_bits, d_sub_marks, nullptr, nullptr, ctx->d_codec_chain, ctx->codec_chain_cap, d_seg_off,
+            d_in, n_bytes, n_chunks, d_sub_bits, d_sub_marks, nullptr, nullptr, chain, chain_cap, d_seg_off,
             d_stream, ctx->dev_codec_mirror);
         return 0;
     }
     uint32_t* seg_size = reinterpret_cast<uint32_t*>(d_work);
     uint8_t* slots = d_work + codec_slots_offset(n_chunks);
-    codec_begin(ctx);
+    codec_begin(ctx, recording);
     {
         ProfileScope ps(ctx, K_DEFLATE_CHUNK);
         deflate_kernel<false, 1><<<n_chunks, DEF_THREADS, 0, ctx->stream>>>(
@@ -1419,7 +1453,7 @@ int launch_deflate(shifter_ctx* ctx, const uint8_t* d_in, uint64_t n_bytes, uint
         codec_pack_kernel<<<n_chunks, 64, 0, ctx->stream>>>(slots, seg_size, d_seg_off, ctx->d_codec,
                                                             d_stream);
     }
-    codec_end(ctx);
+    codec_end(ctx, recording);
     return 0;
 }
 
@@ -1468,9 +1502,12 @@ constexpr uint32_t INFLATE_ONE_LAUNCH = 1024;
 int launch_inflate(shifter_ctx* ctx, const uint8_t* d_stream, uint64_t stream_bytes,
                    const uint64_t* d_seg_off, const uint16_t* d_sub_bits, const uint64_t* d_sub_marks,
                    uint64_t n_bytes, uint32_t n_chunks, uint8_t* d_out) {
-    hipError_t e0 = codec_ensure_list(ctx, n_chunks);
+    bool recording;
+    hipError_t e0 = codec_recording(ctx, &recording);
+    if (e0 == hipSuccess) e0 = codec_ensure_list(ctx, n_chunks);
+    if (e0 == hipSuccess && !recording) e0 = codec_ensure_chain(ctx, n_chunks);
     if (e0 != hipSuccess) return (int)e0;
-    codec_begin(ctx);
+    codec_begin(ctx, recording);
     if (n_chunks <= INFLATE_ONE_LAUNCH) {
         ProfileScope ps(ctx, K_INFLATE_CHUNK);
         inflate_dense_kernel<<<n_chunks, CODEC_THREADS, 0, ctx->stream>>>(d_stream, stream_bytes, d_seg_off, d_sub_bits, d_sub_marks,
@@ -1486,7 +1523,7 @@ int launch_inflate(shifter_ctx* ctx, const uint8_t* d_stream, uint64_t stream_by
         inflate_sparse_kernel<<<n_chunks, CODEC_THREADS, 0, ctx->stream>>>(d_stream, stream_bytes, d_seg_off, d_sub_bits, d_sub_marks,
                                                                           n_bytes, n_chunks, d_out, ctx->d_codec);
     }
-    codec_end(ctx);
+    codec_end(ctx, recording);
     return 0;
 }
 

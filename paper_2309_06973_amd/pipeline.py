@@ -281,6 +281,7 @@ class Codec:
         self.own = ctx is None
         self.ctx = ctx or S.shifter_create(device, torch.cuda.current_stream().cuda_stream)
         self.work = None
+        self.recorded = []                 # workspaces that a recorded call holds
 
     def close(self):
         if self.own and self.ctx is not None:
@@ -295,6 +296,8 @@ class Codec:
         n_chunks, work_bytes, bound = S.shifter_codec_layout(n_bytes)
         if self.work is None or self.work.numel() < work_bytes:
             self.work = torch.empty(work_bytes, dtype=torch.uint8, device=self.dev)
+        if not sync and torch.cuda.is_current_stream_capturing() and not any(x is self.work for x in self.recorded):
+            self.recorded.append(self.work)
         if stream is None:
             stream = torch.empty(bound, dtype=torch.uint8, device=self.dev)
         seg_off = torch.empty(n_chunks + 1, dtype=torch.int64, device=self.dev)

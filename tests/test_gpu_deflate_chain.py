@@ -1,5 +1,5 @@
-"""The encoder's chain words stay with the context from call to call: calls of growing and shrinking numbers of links, and a
-recorded call that goes on with words the context has outgrown since.  Streams as from a context of their own."""
+"""The encoder's chain words stay with the context from call to call: calls of growing and shrinking numbers of links, and
+recorded calls, which have words of their own and go on when the context has outgrown its.  Streams as from a context of their own."""
 import pytest
 import torch
 
@@ -56,3 +56,57 @@ def test_recorded_call_and_growth():
             codec.deflate(data([3, 3000, 1, 50][i], i))                  # the second one outgrows the words
         del graph
         stream.synchronize()
+
+
+# An eager call of either kind and of that size makes room for a recorded one (40 chunks: a link each; 900: one to two)
+@pytest.mark.parametrize("chunks", [40, 900])
+@pytest.mark.parametrize("first", ["inflate", "small buffer"])
+def test_recorded_behind_another_call(first, chunks):
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        x = data(chunks, 2)
+        other = Codec()
+        package = other.deflate(x)
+        codec = Codec()
+        codec.work = torch.empty_like(other.work)
+        if first == "inflate":
+            assert torch.equal(codec.inflate(package)[:x.numel()], x)
+        else:
+            codec.deflate(x, stream=torch.empty(package.stream_bytes, dtype=torch.uint8, device="cuda"))
+        check_recorded(codec, other, stream, x, chunks)
+
+
+# A recording of the mode in which it may allocate, in a context that has run nothing: what it leaves to be cleared is not taken
+# for cleared by an eager call before the first replay
+def test_recorded_first():
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        x = data(40, 3)
+        other = Codec()
+        codec = Codec()
+        codec.work = torch.full_like(torch.empty(50 * (CHUNK + 64), dtype=torch.uint8, device="cuda"), 0xEE)
+        check_recorded(codec, other, stream, x, 40, mode="relaxed")
+
+
+def check_recorded(codec, other, stream, x, chunks, mode="global"):
+    out = torch.empty(x.numel() + 5 * chunks, dtype=torch.uint8, device="cuda")
+    back = torch.empty_like(x)
+    stream.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream, capture_error_mode=mode):
+        recorded = codec.deflate(x, stream=out, sync=False)
+        codec.inflate(recorded, out=back, sync=False)
+    for i in range(3):
+        y = data([chunks, 3, 2500][i], 30 + i)                            # eager, before the first replay too
+        got, ref = codec.deflate(y), other.deflate(y)
+        same(got, ref, ref.stream_bytes)
+        assert torch.equal(codec.inflate(got)[:y.numel()], y)
+        x.copy_(data(chunks, 20 + i))
+        out.zero_()
+        graph.replay()
+        stream.synchronize()
+        ref = other.deflate(x)
+        same(recorded, ref, ref.stream_bytes)
+        assert torch.equal(back, x)
+    del graph
+    stream.synchronize()
