@@ -91,7 +91,7 @@ static void destroy_codec_objects(shifter_ctx* c) {
     if (c->h_codec) (void)hipHostFree(c->h_codec);
     if (c->d_codec_list) (void)hipFree(c->d_codec_list);
     if (c->d_codec_chain) (void)hipFree(c->d_codec_chain);
-    for (uint64_t* p : c->codec_retired) (void)hipFree(p);
+    for (void* p : c->codec_retired) (void)hipFree(p);
 }
 
 extern "C" int shifter_create(shifter_ctx** out, int device, void* hip_stream) {

@@ -1350,18 +1350,19 @@ static void codec_end(shifter_ctx* ctx, bool recording) {
 // it is nobody knows before the pass.  (4 chunks 27 / 33, 256 32 / 35, 640 47 / 51 before the barrier went, 30 %.)
 constexpr uint32_t DEFLATE_ONE_EACH = 768;
 
-// Room for chunk lists, kept by the context and grown when a longer input comes.
+// Room for a chunk list, kept by the context and doubled when a longer input comes.  A list that is outgrown goes with the
+// context: a recorded call of the decoder still writes and reads it.
 static hipError_t codec_ensure_list(shifter_ctx* ctx, uint64_t entries) {
     if (ctx->codec_list_cap >= entries) return hipSuccess;
-    if (ctx->d_codec_list) {
-        hipError_t e = hipFree(ctx->d_codec_list);
-        ctx->d_codec_list = nullptr;
-        ctx->codec_list_cap = 0;
-        if (e != hipSuccess) return e;
-    }
-    hipError_t e = hipMalloc(reinterpret_cast<void**>(&ctx->d_codec_list), sizeof(uint32_t) * entries);
-    if (e == hipSuccess) ctx->codec_list_cap = entries;
-    return e;
+    uint64_t cap = 1024;
+    while (cap < entries) cap *= 2u;
+    uint32_t* list = nullptr;
+    const hipError_t e = hipMalloc(reinterpret_cast<void**>(&list), sizeof(uint32_t) * cap);
+    if (e != hipSuccess) return e;
+    if (ctx->d_codec_list) ctx->codec_retired.push_back(ctx->d_codec_list);
+    ctx->d_codec_list = list;
+    ctx->codec_list_cap = cap;
+    return hipSuccess;
 }
 
 // Whether the context's stream is recording (the null stream never is).

@@ -318,7 +318,7 @@ struct shifter_ctx {
     uint64_t codec_list_cap = 0;      //   its capacity in entries
     uint64_t* d_codec_chain = nullptr;       // the encoder's chain (codec.hip): a header and two arrays
     uint32_t codec_chain_cap = 0;            //   of so many words each
-    std::vector<uint64_t*> codec_retired;    // chains it has outgrown, freed with it
+    std::vector<void*> codec_retired;        // lists and chains it has outgrown, freed with it
     bool codec_dirty = true;          // the codec's result words may be non-zero (see codec_begin)
     // a shifter_prune_fused call whose outcome has not been collected yet
     struct Pending {

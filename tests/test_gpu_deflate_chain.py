@@ -88,6 +88,30 @@ def test_recorded_first():
         check_recorded(codec, other, stream, x, 40, mode="relaxed")
 
 
+# More than 1024 chunks: the decoder has a list of those whose segments are long, which a longer input outgrows
+def test_recorded_list_and_growth():
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        x = data(1100, 4)
+        codec, other = Codec(), Codec()
+        package = other.deflate(x)
+        back = torch.empty_like(x)
+        codec.inflate(package, out=back)                                  # makes room
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            codec.inflate(package, out=back, sync=False)
+        for i in range(3):
+            y = data([2100, 4200, 5][i], 40 + i)
+            assert torch.equal(codec.inflate(other.deflate(y))[:y.numel()], y)
+            back.zero_()
+            graph.replay()
+            stream.synchronize()
+            assert torch.equal(back, x)
+        del graph
+        stream.synchronize()
+
+
 def check_recorded(codec, other, stream, x, chunks, mode="global"):
     out = torch.empty(x.numel() + 5 * chunks, dtype=torch.uint8, device="cuda")
     back = torch.empty_like(x)
