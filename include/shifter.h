@@ -195,8 +195,10 @@ int shifter_global_threshold(shifter_ctx* ctx, const shifter_model* model,
  * SHIFTER_STATIC_MAX_TILE_COUNTS, else SHIFTER_ERR_CAPACITY (nothing is enqueued).  (The
  * second is a limit of the call, no longer of its scratch, whose size does not depend on K.)
  * All calls on one GPU share that GPU's array, whatever their context or stream: calls
- * that overlap in time on one GPU race; calls on one stream, or otherwise ordered, are
- * fine.  What must start at zero is cleared by the call's first kernel. */
+ * that overlap in time on one GPU race, their records are then unspecified and a call may
+ * take seconds until it gives up (see shifter_set_select_polls); calls on one stream, or
+ * otherwise ordered, are fine.  What must start at zero is cleared by the call's first
+ * kernel. */
 #define SHIFTER_STATIC_MAX_WEIGHTS (1ull << 28)
 #define SHIFTER_STATIC_MAX_TILE_COUNTS (1ull << 20)
 int shifter_global_threshold_static(shifter_ctx* ctx, const float* d_w, uint64_t n,
@@ -224,6 +226,13 @@ int shifter_set_margin_sigmas(shifter_ctx* ctx, double sigmas);
  * of the grid (default one per compute unit; 1 .. 65536).  A launch shape only: the
  * records, and everything computed from them, are the same bytes for every value. */
 int shifter_set_select_grid(shifter_ctx* ctx, uint32_t blocks);
+
+/* How often a block of the multi-pass select's last launch looks whether the others have
+ * finished a read of the arena before it gives up (default 2^22, which takes seconds; 0: the
+ * default).  Blocks of calls that do not overlap never wait that long.  A rank that is given
+ * up keeps the record that removes nothing (cut 0 although n_prune > 0), and a call that
+ * reads records back returns SHIFTER_ERR_INTERNAL.  For tests of just that. */
+int shifter_set_select_polls(shifter_ctx* ctx, uint32_t polls);
 
 /* Arena size, in bytes, above which shifter_portfolio_begin ranks and masks a portfolio in
  * one fused read of the arena; at or below it the counting pass and the batched mask pass

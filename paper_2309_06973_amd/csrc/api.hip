@@ -639,6 +639,15 @@ static int multi_result(shifter_ctx* ctx, const shifter_model* model, uint32_t k
     return SHIFTER_OK;
 }
 
+// Records of the multi-pass select in which a rank was left out (its last launch gave up waiting) remove
+// nothing although they should.
+static int ranking_ended(shifter_ctx* ctx, const shifter_threshold* rec, uint32_t K, const char* fn) {
+    for (uint32_t k = 0; k < K; ++k)
+        if (rec[k].n_prune != 0 && rec[k].cut == 0)
+            return fail(ctx, SHIFTER_ERR_INTERNAL, std::string(fn) + ": the ranking gave up waiting for its blocks");
+    return SHIFTER_OK;
+}
+
 extern "C" int shifter_global_threshold(shifter_ctx* ctx, const shifter_model* model,
                                         const float* d_w, const uint64_t* h_n_prune, uint32_t K,
                                         shifter_threshold* d_thr, shifter_threshold* h_thr) {
@@ -701,6 +710,7 @@ extern "C" int shifter_global_threshold(shifter_ctx* ctx, const shifter_model* m
         memcpy(&nan_seen, st + sizeof(shifter_threshold) * MAXK, sizeof nan_seen);
         if (nan_seen)
             return fail(ctx, SHIFTER_ERR_NONFINITE, "global_threshold: NaN among the prunable weights");
+        return ranking_ended(ctx, h_thr, K, "global_threshold");
     }
     return SHIFTER_OK;
 }
@@ -819,8 +829,9 @@ extern "C" int shifter_global_threshold_end(shifter_ctx* ctx, shifter_threshold*
     memcpy(&status, st, sizeof status);
     if (status)
         return fail(ctx, SHIFTER_ERR_NONFINITE, "global_threshold_end: NaN among the prunable weights");
-    if (h_thr) memcpy(h_thr, st + MULTI_MIRROR_REC_OFF, sizeof(shifter_threshold) * pr.k);
-    return SHIFTER_OK;
+    const shifter_threshold* rec = reinterpret_cast<const shifter_threshold*>(st + MULTI_MIRROR_REC_OFF);
+    if (h_thr) memcpy(h_thr, rec, sizeof(shifter_threshold) * pr.k);
+    return ranking_ended(ctx, rec, pr.k, "global_threshold_end");
 }
 
 extern "C" int shifter_apply_mask(shifter_ctx* ctx, const shifter_model* model, const float* d_w,
@@ -861,6 +872,7 @@ static int prune_unfused(shifter_ctx* ctx, const shifter_model* model, const flo
     uint32_t nan_seen;
     memcpy(&nan_seen, st + sizeof(shifter_threshold), sizeof nan_seen);
     if (nan_seen) return fail(ctx, SHIFTER_ERR_NONFINITE, "prune_fused: NaN among the prunable weights");
+    if ((rc = ranking_ended(ctx, &ctx->last_record, 1, "prune_fused"))) return rc;
     return SHIFTER_OK;
 }
 
@@ -947,6 +959,12 @@ extern "C" int shifter_set_select_grid(shifter_ctx* ctx, uint32_t blocks) {
     if (!ctx || blocks == 0 || blocks > 65536)
         return fail(ctx, SHIFTER_ERR_INVALID_ARG, "set_select_grid: blocks must be in [1, 65536]");
     ctx->hist_grid = blocks;
+    return SHIFTER_OK;
+}
+
+extern "C" int shifter_set_select_polls(shifter_ctx* ctx, uint32_t polls) {
+    if (!ctx) return fail(nullptr, SHIFTER_ERR_INVALID_ARG, "set_select_polls: ctx is NULL");
+    ctx->select_polls = polls ? polls : SEL_POLLS;
     return SHIFTER_OK;
 }
 
@@ -1466,7 +1484,9 @@ extern "C" int shifter_portfolio_end(shifter_ctx* ctx, shifter_threshold* h_thr,
         memcpy(&nan_seen, st, sizeof nan_seen);
         if (nan_seen)
             return fail(ctx, SHIFTER_ERR_NONFINITE, "portfolio_end: NaN among the prunable weights");
-        if (h_thr) memcpy(h_thr, st + MULTI_MIRROR_REC_OFF, sizeof(shifter_threshold) * K);
+        const shifter_threshold* rec = reinterpret_cast<const shifter_threshold*>(st + MULTI_MIRROR_REC_OFF);
+        if (h_thr) memcpy(h_thr, rec, sizeof(shifter_threshold) * K);
+        if ((rc = ranking_ended(ctx, rec, K, "portfolio_end"))) return rc;
     }
     return plan_readout(ctx, model, K, h_out_tensors, h_out_vecs, h_elems_w, h_elems_v);
 }

@@ -72,6 +72,7 @@ struct SelWindow {
     uint32_t mode;             // of this stage: split by a histogram, listed, or nothing to do
     uint32_t stage;            // whose key_lo, key_hi say what keys it holds; 0: not known
 };
+constexpr uint32_t SEL_POLLS = 1u << 22;       // looks at them: seconds, far beyond any stage
 constexpr uint32_t SEL_GO = 16, SEL_GO_WORDS = 32;   // lines that say that a stage is over
 struct SelState {
     SelWindow win[SEL_STAGES + 1][MAXK];   // by stage; the first is unused
@@ -304,6 +305,7 @@ struct shifter_ctx {
     struct Rec { int id; hipEvent_t a, b; };
     std::vector<Rec> recs;
     std::vector<hipEvent_t> pool;
+    uint32_t select_polls = shifter::SEL_POLLS;
     uint32_t hist_grid = 256;
     int select_path = 0;   // 0: single-pass where it applies; 1: multi-pass select only
     double margin_sigmas = 4.0;   // half-width of the predicted interval, in binomial sigmas

@@ -63,11 +63,19 @@ __device__ __forceinline__ uint32_t sel_bin_width(uint32_t bin) {
     return bin == 0u || bin == SEL_BINS - 1u ? SEL_MAX_WIDTH : 32u + SEL_BIN_SHIFT;
 }
 
+// The record that removes nothing: of a rank of 0, and of one whose wait ran out (see sel_rest_kernel).
+__host__ __device__ __forceinline__ shifter_threshold sel_no_record(uint64_t p) {
+    shifter_threshold r;
+    r.cut = 0; r.t_key = 0; r.reserved = 0; r.g_cut = ~0ull; r.n_less = 0; r.n_equal = 0;
+    r.n_prune = p;
+    return r;
+}
+
 // Where the map of windows is looked up: the key's bin, one more for zero.
 __device__ __forceinline__ uint32_t top_bin(uint32_t key) { return key ? sel_bin(key) : SEL_BINS; }
 
 __global__ __launch_bounds__(BLOCK) void sel_clear_kernel(SelState* st, uint32_t* ghist, uint32_t hists,
-                                                          PruneCounts pc, MultiPerm perm, uint32_t k,
+                                                          PruneCounts pc, MultiPerm perm, uint32_t k, shifter_threshold* thr,
                                                           DevTensor* flat_tens, uint32_t* flat_prefix, uint64_t flat_n,
                                                           uint32_t* zero_ptr, uint32_t zero_n) {
     const uint32_t tid = blockIdx.x * BLOCK + threadIdx.x;
@@ -78,6 +86,7 @@ __global__ __launch_bounds__(BLOCK) void sel_clear_kernel(SelState* st, uint32_t
         (&st->key_lo[0][0])[tid] = 0xffffffffu;
         (&st->key_hi[0][0])[tid] = 0;
     }
+    if (tid < k) thr[perm.v[tid]] = sel_no_record(pc.p[tid]);
     if (tid < MAXK) {
         st->p[tid] = tid < k ? pc.p[tid] : 0;
         st->perm[tid] = tid < k ? perm.v[tid] : 0;
@@ -311,7 +320,7 @@ struct SelJob {
     SelState* st;
     uint32_t* ghist;
     uint2* lists;
-    uint32_t list_cap, k, n_weights, g_bits, stages;
+    uint32_t list_cap, k, n_weights, g_bits, stages, polls;
 };
 
 // The windows of a stage from the histograms of the stage before: the same in every block, and one of them publishes
@@ -657,9 +666,7 @@ __device__ __forceinline__ void sel_record(const SelJob& J, uint32_t q, RankShar
                                            shifter_threshold* __restrict__ thr, shifter_threshold* host_rec, uint32_t* host_nan) {
     const SelState* const st = J.st;
     const uint32_t list_cap = J.list_cap;
-    shifter_threshold out;
-    out.cut = 0; out.t_key = 0; out.reserved = 0; out.g_cut = ~0ull; out.n_less = 0; out.n_equal = 0;
-    out.n_prune = st->p[q];
+    shifter_threshold out = sel_no_record(st->p[q]);
     if (out.n_prune != 0) {
         const SelWindow W = st->fin[q];
         if (W.mode == SEL_LISTED) {
@@ -688,8 +695,10 @@ __device__ __forceinline__ void sel_record(const SelJob& J, uint32_t q, RankShar
         }
     }
     if (threadIdx.x == 0) {
-        thr[st->perm[q]] = out;
-        if (host_rec) host_rec[st->perm[q]] = out;
+        // inside the caller's records also where an overlapping call has left another permutation
+        const uint32_t to = min(st->perm[q], J.k - 1u);
+        thr[to] = out;
+        if (host_rec) host_rec[to] = out;
         if (host_nan && q == 0) *host_nan = st->nan_seen;
     }
 }
@@ -719,15 +728,18 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_final_kernel(const SelJob J, 
 // ones mostly), the further stages come first, in the same launch: with a launch for each, the four that found nothing left
 // took 4 us each of a call that has no ties (ten counts of 14.7 M weights, flat run, 64 us with them, 56 without).  There
 // the parts of a stage are handed out by a ticket, and a block that finds none left waits until all that were taken have
-// arrived.  Every wait ends, however many of the blocks run at a time: a part is only ever held by a block that runs,
-// and that leaves what it has gathered before it waits for its stage; what it may hold then is a part of the next stage,
-// for which nobody waits before this one is over.
+// arrived.  Every wait of calls in order ends, however many of the blocks run at a time: a part is only ever held by a
+// block that runs, and that leaves what it has gathered before it waits for its stage; what it may hold then is a part of
+// the next stage, for which nobody waits before this one is over.  Two flat runs at once, which share their words and
+// may clear each other's, could wait for ever: a wait is given up after J.polls looks.  The block then leaves without another
+// word, the part or rank that it may hold is nobody's, and who waits for it gives up too: records not written stay
+// those that remove nothing, which the first launch wrote.
 __global__ __launch_bounds__(SEL_THREADS) void sel_rest_kernel(const SelArena arena, const SelJob J, uint32_t before, uint32_t parts,
                                                                shifter_threshold* __restrict__ thr, shifter_threshold* host_rec,
                                                                uint32_t* host_nan) {
     __shared__ SelShared S;
     __shared__ RankShared<SEL_THREADS> sh;
-    __shared__ uint32_t s_take;
+    __shared__ uint32_t s_take, s_over;
     SelState* const st = J.st;
     if (st->done[before]) {
         if (blockIdx.x < J.k) sel_record(J, blockIdx.x, sh, thr, host_rec, host_nan);
@@ -760,16 +772,21 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_rest_kernel(const SelArena ar
             // the last to arrive says so on several lines: polls at the counter's own would hold up its additions
             if (threadIdx.x == 0) s_take = atomicAdd(&st->arrived[stage], mine) + mine;
             __syncthreads();
-            if (s_take == parts && threadIdx.x < SEL_GO) sel_put<true>(&st->go[stage][threadIdx.x * SEL_GO_WORDS], 1u);
+            if (s_take >= parts && threadIdx.x < SEL_GO) sel_put<true>(&st->go[stage][threadIdx.x * SEL_GO_WORDS], 1u);
         }
         const bool last = stage == J.stages;
         draw(&st->ticket[last ? 0u : stage + 1u]);
         if (threadIdx.x == 0) {
-            while (!__hip_atomic_load(&st->go[stage][blockIdx.x % SEL_GO * SEL_GO_WORDS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                __builtin_amdgcn_s_sleep(8);
+            uint32_t over = 0;
+            for (uint32_t look = 0; look < J.polls && !over; ++look) {
+                if (look) __builtin_amdgcn_s_sleep(8);
+                over = __hip_atomic_load(&st->go[stage][blockIdx.x % SEL_GO * SEL_GO_WORDS], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            s_over = over;
         }
         __syncthreads();
+        if (!uniform_u32(s_over)) return;
         if (last) break;
         if (st->done[stage]) {               // the same in every thread
             draw(&st->ticket[0]);
@@ -787,6 +804,12 @@ void launch_select(shifter_ctx* ctx, const shifter_model* m, const float* d_w,
                    uint32_t zero_n) {
     const auto& b = m->b;
     // the candidate buffer of the single-pass selections is idle here: it holds the lists
+    if (mirror) {
+        // no call is under way that writes them: what the kernels leave out stays that way
+        shifter_threshold* rec = reinterpret_cast<shifter_threshold*>(b.host_multi + MULTI_MIRROR_REC_OFF);
+        for (uint32_t i = 0; i < k; ++i) rec[i] = sel_no_record(pc.p[i]);
+        *reinterpret_cast<uint32_t*>(b.host_multi) = 0;
+    }
     const SelectTables tb{b.tens, b.tile_prefix, b.tile_tensor, m->n_tiles, m->info.n_prunable, b.sel, b.ghist,
                           b.cand, (uint64_t)b.cand_cap_sb * SPEC_SUB, nullptr, nullptr, zero_ptr, zero_n,
                           mirror ? b.dev_multi_rec : nullptr, mirror ? b.dev_multi_status : nullptr};
@@ -807,13 +830,13 @@ void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float*
     const uint32_t stages = sel_stages(tb.n_weights, k, tb.list_pairs);
     const uint32_t grid = std::max(1u, std::min((n_tiles + SEL_GROUPS - 1) / SEL_GROUPS, ctx->hist_grid));
     const SelArena arena{tb.tens, tb.tile_prefix, tb.tile_tensor, n_tiles, d_w};
-    const SelJob job{tb.sel, tb.ghist, tb.lists, list_cap, k, (uint32_t)tb.n_weights, g_bits, stages};
+    const SelJob job{tb.sel, tb.ghist, tb.lists, list_cap, k, (uint32_t)tb.n_weights, g_bits, stages, ctx->select_polls};
     // At most 1/1536 of spread-out weights lie in one bin: where that is more than a good list, the first stage will hardly list
     // them all, and a launch costs the second one less than the tickets (ten of 100 M weights 252 us, 268 with them, all reads in one direction)
     const uint32_t before = stages > 1u && tb.n_weights / 1536u > std::min(list_cap, SEL_LIST_GOOD) ? 2u : 1u;
     {
         ProfileScope p(ctx, K_SEL_INIT);
-        sel_clear_kernel<<<64, BLOCK, 0, s>>>(tb.sel, tb.ghist, stages, sorted, perm, k, tb.flat_tens, tb.flat_prefix,
+        sel_clear_kernel<<<64, BLOCK, 0, s>>>(tb.sel, tb.ghist, stages, sorted, perm, k, d_thr, tb.flat_tens, tb.flat_prefix,
                                               tb.n_weights, tb.zero_ptr, tb.zero_n);
     }
     {
