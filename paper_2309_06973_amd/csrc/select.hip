@@ -2,8 +2,8 @@
 // magnitude ranking of Sec. II-A / Sec. III-C of the paper in the form that needs no decision
 // on the host, for any number of prune counts, any distribution and any number of ties.
 //
-//   top     one read of the arena: a histogram of all keys on 16384 bins (1/512 of a binade where the
-//           weights of networks live), zeros counted apart;
+//   top     one read of the arena: a histogram of all keys on 16384 bins (sel_plan.h: 1/512 of a binade where the
+//           thresholds of networks lie, 1/128 around), zeros counted apart;
 //   stage   every rank has a window of composites (key << 32 | g) that holds its pair and the
 //           number of weights in it.  A stage reads the arena once: windows of no more pairs
 //           than are good in a list (sel_plan.h) are written out as lists, the others are split by
@@ -12,23 +12,25 @@
 //           per rank ranks its list and writes the record.
 //
 // The first stage lists the ranks whose top bin holds no more than a list: 65536 pairs, in a
-// flat run's scratch 2^19 / K if that is less.  A bin of normally distributed weights holds up to 0.07 % of
-// them, so 10 counts of up to 75 M weights are read twice where there are no ties.
+// flat run's scratch 2^19 / K if that is less.  A fine bin of normally distributed weights holds up to 0.095 % of
+// them, of uniform ones 0.1 %, so 10 counts of up to 50 M weights are read twice where there are no ties.
 //
 // The launches are the same for every input (their number follows from N and K alone), so the
 // calls can be recorded into a graph.  What bounds it: the reads of the arena (100 M weights at 5.6 TB/s), and one launch
-// after the other around them: clear, top, stage and rest 5 + 16 + 22 + 11 us on ten counts of 14.7 M.
+// after the other around them: clear, top, stage and rest 4.5 + 14.5 + 19 + 9.5 us on ten counts of 14.7 M.
 // Equal weights are what the rest is built around: zeros take a window of their own from the start,
 // a window that turns out to hold a single key goes on with its index, a lane keeps counts that would meet at
 // one counter, windows that follow each other in one bin are found by halving.  us a call, flat
-// run, bins of 1/256 of a binade and a launch for each stage, used or not / now:
-//   counts of weights     normal        half of them zero   all equal       30 levels a sigma   half precision
-//    1 of   1 M           32 / 23       33 / 24             78 / 70         49 / 38             41 / 31
-//   10 of   1 M           34 / 25       60 / 56             81 / 78         55 / 44             43 / 33
-//    1 of  14.7 M         56 / 43       55 / 43             178 / 179       113 / 107           76 / 54
-//   10 of  14.7 M         64 / 47       137 / 131           208 / 208       145 / 149           96 / 63
-//    1 of 100 M           249 / 159     246 / 159           850 / 835       399 / 395           273 / 206
-//   10 of 100 M           252 / 245     745 / 712           1214 / 1192     605 / 595           298 / 305
+// run, bins of 1/256 of a binade from 2^-50 to 2^14 and a launch for each stage, used or not / now:
+//   counts of weights     normal        half of them zero   all equal       30 levels a sigma   half precision   times 2^-30   60 % 10^-12
+//    1 of   1 M           32 / 24       33 / 24             78 / 71         49 / 38             41 / 31          33 / 26       34 / 25
+//   10 of   1 M           34 / 25       60 / 57             81 / 79         55 / 44             43 / 33          35 / 29       35 / 28
+//    1 of  14.7 M         56 / 42       55 / 43             178 / 182       113 / 109           76 / 54          56 / 53       59 / 47
+//   10 of  14.7 M         64 / 46       137 / 131           208 / 208       145 / 150           96 / 63          64 / 66       61 / 58
+//    1 of 100 M           249 / 160     246 / 160           850 / 857       399 / 401           273 / 207        245 / 249     198 / 167
+//   10 of 100 M           252 / 247     745 / 722           1214 / 1208     605 / 604           298 / 307        252 / 278     276 / 273
+// (With all bins 1/512 of a binade, which left out what lies below 2^-25 and above 2^7: the first columns 1 % less, the last two
+// 55, 101, 165, 217, 760, 1050 and 29, 72, 59, 203, 255, 960.)
 // (The radix select of 11 + 10 + 10 bits before all this: 85 us for 1 of 1 M, 418 for 10 of 14.7 M.)
 #include <algorithm>
 
@@ -48,21 +50,6 @@ constexpr uint32_t SEL_ABOUT_SPLIT = 1u << 12;
 constexpr uint32_t SEL_ABOUT_TIES = 1u << 13;     // likely to hold equal weights
 constexpr uint32_t SEL_ABOUT_RUNS = 1u << 14;     // many of a wavefront's lanes meet at one counter
 
-// The top bins: 1/512 of a binade from 2^-25 to 2^7, where thresholds of networks lie; the keys below share the first one
-// with its own, those above the last one.  (1/256 of a binade over 64 of them, as in the sample's histogram: lists twice as
-// long.)
-constexpr uint32_t SEL_BIN_SHIFT = 14, SEL_KEY0 = (127u - 25u) << 23;
-static_assert(SEL_BINS << SEL_BIN_SHIFT == 32u << 23, "2^-25 to 2^7");
-__device__ __forceinline__ uint32_t sel_bin(uint32_t key) {
-    return min(__builtin_elementwise_sub_sat(key, SEL_KEY0) >> SEL_BIN_SHIFT, SEL_BINS - 1u);
-}
-// First key of a bin (zeros are in none), and the bits of a window that is a whole bin: those at both ends span up to 2^30
-// keys.
-__device__ __forceinline__ uint32_t sel_bin_first_key(uint32_t bin) { return bin == 0u ? 1u : SEL_KEY0 + (bin << SEL_BIN_SHIFT); }
-__device__ __forceinline__ uint32_t sel_bin_width(uint32_t bin) {
-    return bin == 0u || bin == SEL_BINS - 1u ? SEL_MAX_WIDTH : 32u + SEL_BIN_SHIFT;
-}
-
 // The record that removes nothing: of a rank of 0, and of one whose wait ran out (see sel_rest_kernel).
 __host__ __device__ __forceinline__ shifter_threshold sel_no_record(uint64_t p) {
     shifter_threshold r;
@@ -71,8 +58,8 @@ __host__ __device__ __forceinline__ shifter_threshold sel_no_record(uint64_t p) 
     return r;
 }
 
-// Where the map of windows is looked up: the key's bin, one more for zero.
-__device__ __forceinline__ uint32_t top_bin(uint32_t key) { return key ? sel_bin(key) : SEL_BINS; }
+// A window's place in the map: its bin, one more for those among the zeros.
+__device__ __forceinline__ uint32_t top_bin(uint32_t key) { return key ? sel_top_bin(key) : SEL_BINS; }
 
 __global__ __launch_bounds__(BLOCK) void sel_clear_kernel(SelState* st, uint32_t* ghist, uint32_t hists,
                                                           PruneCounts pc, MultiPerm perm, uint32_t k, shifter_threshold* thr,
@@ -231,25 +218,52 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(const SelArena are
     SelWalk walk(arena);
     for (uint32_t i = threadIdx.x; i < SEL_BINS + 64u; i += SEL_THREADS) h[i] = 0;
     __syncthreads();
-    uint32_t key_max = 0, turn = 0;
+    uint32_t key_max = 0, turn = 0;              // key_max: of those that are in no fine bin
     bool runs = false;
     RunCount run;
-    auto bin_of = [&](uint32_t key) { return key ? sel_bin(key) : SEL_BINS + lane; };
+    // Counters by their distance from the first fine one.  A zero's has two upper bits set, which are shifted out of its address and
+    // tell it from the keys that are in no fine bin: as signed numbers those alone are SEL_FINE_BINS or more.  One look at the
+    // largest of a lane's sixteen finds them, and the wavefront then takes all of its bins from sel_top_bin.  (That for
+    // every weight: 14.7 M 14.7 -> 15.9 us.)
+    const uint32_t zero_at = (3u << 30) + SEL_BINS + lane - SEL_BIN_FINE;
+    auto counter = [&](uint32_t at) { return reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(h) + ((at << 2) + 4u * SEL_BIN_FINE)); };
+    auto any_bin = [&](uint32_t key) {
+        key_max = max(key_max, key);
+        uint32_t at = sel_top_bin(key) - SEL_BIN_FINE;
+        asm("" : "+v"(at));                              // for zeros too: a branch around it takes longer
+        return key ? at : zero_at;
+    };
     walk.run(blockIdx.x, gridDim.x, false, [&] {
         if (walk.n != TILE) {
             for (uint32_t left = walk.there(); left; left &= left - 1u) {
                 const uint32_t key = walk.bits((uint32_t)__builtin_ctz(left)) & 0x7fffffffu;
-                key_max = max(key_max, key);
-                atomicAdd(&h[bin_of(key)], 1u);
+                atomicAdd(counter(any_bin(key)), 1u);
             }
             return;
         }
+        uint32_t at[SEL_QUADS][4];
+        int32_t most = 0;
 #pragma unroll
         for (uint32_t u = 0; u < SEL_QUADS; ++u) {
-            const uint4 v = walk.v[u];
-            const uint32_t k0 = v.x & 0x7fffffffu, k1 = v.y & 0x7fffffffu, k2 = v.z & 0x7fffffffu, k3 = v.w & 0x7fffffffu;
-            const uint32_t b0 = bin_of(k0), b1 = bin_of(k1), b2 = bin_of(k2), b3 = bin_of(k3);
-            key_max = max(max(key_max, max(k0, k1)), max(k2, k3));
+            const uint32_t x[4] = {walk.v[u].x, walk.v[u].y, walk.v[u].z, walk.v[u].w};
+#pragma unroll
+            for (uint32_t q = 0; q < 4u; ++q) {
+                const uint32_t key = x[q] & 0x7fffffffu;
+                at[u][q] = key ? sel_fine_bin(key) : zero_at;
+                most = max(most, (int32_t)at[u][q]);
+            }
+        }
+        if (__builtin_expect(__ballot(most >= (int32_t)SEL_FINE_BINS) != 0ull, 0)) {
+#pragma unroll
+            for (uint32_t u = 0; u < SEL_QUADS; ++u) {
+                const uint32_t x[4] = {walk.v[u].x, walk.v[u].y, walk.v[u].z, walk.v[u].w};
+#pragma unroll
+                for (uint32_t q = 0; q < 4u; ++q) at[u][q] = any_bin(x[q] & 0x7fffffffu);
+            }
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < SEL_QUADS; ++u) {
+            const uint32_t b0 = at[u][0], b1 = at[u][1], b2 = at[u][2], b3 = at[u][3];
             // every fourth time, until some lane has met a run
             bool same = false;
             if (runs || (turn++ & 3u) == 0u) {
@@ -257,12 +271,12 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(const SelArena are
                 runs = __ballot(same) != 0ull;
             }
             if (same) {
-                run.add(h, b0, 4u);
+                run.add(h, (b0 + SEL_BIN_FINE) & ~(3u << 30), 4u);
             } else {
-                atomicAdd(&h[b0], 1u);
-                atomicAdd(&h[b1], 1u);
-                atomicAdd(&h[b2], 1u);
-                atomicAdd(&h[b3], 1u);
+                atomicAdd(counter(b0), 1u);
+                atomicAdd(counter(b1), 1u);
+                atomicAdd(counter(b2), 1u);
+                atomicAdd(counter(b3), 1u);
             }
         }
     });
@@ -312,7 +326,7 @@ struct SelShared {
     uint64_t lo[MAXK];       // of the windows in order: the first composite,
     uint32_t about[MAXK];    // what else the walk needs
     uint64_t smem[SEL_THREADS / 64 + 1];
-    uint32_t cnt[MAXK], base[MAXK], key_lo[MAXK], key_hi[MAXK], n, left, ties;
+    uint32_t cnt[MAXK], base[MAXK], key_lo[MAXK], key_hi[MAXK], n, left, ties, wide;
 };
 
 // What the stages and the ranking of the lists work on.
@@ -341,7 +355,7 @@ __device__ __forceinline__ void sel_windows(const SelJob& J, SelShared& S, uint3
         S.key_lo[threadIdx.x] = 0xffffffffu;
         S.key_hi[threadIdx.x] = 0;
     }
-    if (threadIdx.x == 0) { S.n = 0; S.left = 0; S.ties = 0; }
+    if (threadIdx.x == 0) { S.n = 0; S.left = 0; S.ties = 0; S.wide = 0; }
     if (FIRST) {
         // sixteen bins per thread, their exclusive prefix over the block (in the room of the
         // pairs), then a search per rank
@@ -480,10 +494,11 @@ __device__ __forceinline__ void sel_windows(const SelJob& J, SelShared& S, uint3
             const uint32_t mode = W.cnt <= (stage < stages ? min(list_cap, SEL_LIST_GOOD) : list_cap) ? SEL_LISTED : SEL_SPLIT;
             S.win[lane].leader = leader;
             S.win[lane].mode = mode;
-            // more weights than any spread-out distribution has in 1/256 of a binade, or one key
+            // more weights than any spread-out distribution has in a bin (normal ones 0.38 % in a wide one), or one key
             const bool ties = W.width <= 32u || W.cnt > (n_weights >> 7);
             S.win[lane].stage = ties ? stage : 0u;
             if (ties) S.ties = 1;
+            if ((W.c_lo >> 32) != 0 && !sel_bin_is_fine(top)) S.wide = 1;
             if (opens) {
                 const uint32_t at = (uint32_t)__popcll(before);
                 S.lo[at] = W.c_lo;
@@ -522,18 +537,32 @@ struct SelCollect {
     RunCount run;
     KeyRange keys;
     __device__ __forceinline__ SelCollect(const SelJob& job, SelShared& shared) : J(job), S(shared) {}
-    __device__ __forceinline__ void part(const SelArena& arena, uint32_t part, uint32_t parts, bool down);
+    __device__ __forceinline__ void part(const SelArena& arena, uint32_t part, uint32_t parts, bool down) {
+        if (uniform_u32(S.wide)) part_of<true>(arena, part, parts, down); else part_of<false>(arena, part, parts, down);
+    }
+    template <bool WIDE>
+    __device__ __forceinline__ void part_of(const SelArena& arena, uint32_t part, uint32_t parts, bool down);
     __device__ __forceinline__ void leave(uint32_t stage);
 };
+// Most times all windows, but for zeros', lie in fine bins: the keys of others read the place behind those, where no window is
+// then.  WIDE: some window lies in another bin.
 template <bool DEV>
-__device__ __forceinline__ void SelCollect<DEV>::part(const SelArena& arena, uint32_t part, uint32_t parts, bool down) {
+template <bool WIDE>
+__device__ __forceinline__ void SelCollect<DEV>::part_of(const SelArena& arena, uint32_t part, uint32_t parts, bool down) {
     SelWalk walk(arena);
     SelState* const st = J.st;
     uint2* const lists = J.lists;
     const uint32_t lane = threadIdx.x & 63u, bits = sel_bits(J.k), list_cap = J.list_cap;
+    // where the map is looked up
+    auto place = [](uint32_t key) {
+        if (!WIDE) return SEL_BIN_FINE + (key ? min(sel_fine_bin(key), SEL_FINE_BINS) : SEL_BINS - SEL_BIN_FINE);
+        uint32_t bin = sel_top_bin(key);
+        asm("" : "+v"(bin));                             // for zeros too, without a branch
+        return key ? bin : SEL_BINS;
+    };
     auto one = [&](uint32_t wbits, uint32_t g) {
         const uint32_t key = wbits & 0x7fffffffu;
-        uint32_t i = S.map[top_bin(key)];
+        uint32_t i = S.map[place(key)];
         if (i == NONE8) return;
         const uint64_t comp = ((uint64_t)key << 32) | g;
         uint32_t about = S.about[i];
@@ -595,7 +624,7 @@ __device__ __forceinline__ void SelCollect<DEV>::part(const SelArena& arena, uin
         for (uint32_t u = 0; u < 4u; ++u) {
             const uint32_t x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
 #pragma unroll
-            for (uint32_t q = 0; q < 4u; ++q) met |= (S.map[top_bin(x[q] & 0x7fffffffu)] != NONE8 ? 1u : 0u) << (4u * u + q);
+            for (uint32_t q = 0; q < 4u; ++q) met |= (S.map[place(x[q] & 0x7fffffffu)] != NONE8 ? 1u : 0u) << (4u * u + q);
         }
         if (walk.n != TILE) met &= walk.there();
         while (met) {
@@ -831,8 +860,10 @@ void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float*
     const uint32_t grid = std::max(1u, std::min((n_tiles + SEL_GROUPS - 1) / SEL_GROUPS, ctx->hist_grid));
     const SelArena arena{tb.tens, tb.tile_prefix, tb.tile_tensor, n_tiles, d_w};
     const SelJob job{tb.sel, tb.ghist, tb.lists, list_cap, k, (uint32_t)tb.n_weights, g_bits, stages, ctx->select_polls};
-    // At most 1/1536 of spread-out weights lie in one bin: where that is more than a good list, the first stage will hardly list
-    // them all, and a launch costs the second one less than the tickets (ten of 100 M weights 252 us, 268 with them, all reads in one direction)
+    // Where a bin of spread-out weights is likely to outgrow a good list, the first stage will hardly list them all, and a launch
+    // costs the second one less than the tickets do (ten of 100 M weights 252 us, 268 with them, all reads in one direction).
+    // 1/1536 of the weights is a measured line, not a bound (a bin holds up to 1/1024): with 1/1024 one count of 70 to 90 M normal
+    // weights 2 us more, of 56 to 90 M uniform ones 6 us less.
     const uint32_t before = stages > 1u && tb.n_weights / 1536u > std::min(list_cap, SEL_LIST_GOOD) ? 2u : 1u;
     {
         ProfileScope p(ctx, K_SEL_INIT);

@@ -1,0 +1,73 @@
+"""Multi-pass rankings whose thresholds lie in each kind of the top histogram's bins: fine ones, wide ones below and above, the two
+that all further keys share, and several of them at once, with zeros of both signs, denormals and infinities among the
+weights.  Every record by the counting definition; NaN is found wherever it stands."""
+import pytest
+import torch
+
+from paper_2309_06973_amd import shifter as S
+from paper_2309_06973_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def weights(kind, n):
+    g = torch.Generator(device="cuda").manual_seed(n)
+    w = torch.randn(n, generator=g, device="cuda")
+    at = torch.rand(n, generator=g, device="cuda")
+    if kind.startswith("2^"):
+        e = int(kind[2:])
+        return w * 2.0 ** max(e, -100) * 2.0 ** min(e + 100, 0)
+    if kind == "spread":                                  # from denormals to 2^40
+        return w * torch.exp(torch.randn(n, generator=g, device="cuda") * 22 - 20)
+    if kind == "tiny":                                    # most of them dead
+        return torch.where(at < 0.6, w * 1e-12, w)
+    if kind == "zeros":                                   # and denormals, and tiny ones
+        w = torch.where(at < 0.3, torch.zeros_like(w).copysign(w), torch.where(at < 0.5, w * 2.0 ** -70 * 2.0 ** -70, w))
+        return torch.where((at > 0.5) & (at < 0.6), w * 2.0 ** -60, w)
+    assert kind == "corners"                              # keys on both sides of where the bins' kinds change, and infinities
+    keys = torch.tensor([k + d for b in (-49, -19, 3, 13) for k in [(127 + b) << 23] for d in (-65536, -16384, -1, 0, 1, 16384, 65536)]
+                        + [0, 1, 2, 0x7f7fffff, 0x7f800000], device="cuda", dtype=torch.int32)
+    x = keys[torch.randint(0, keys.numel(), (n,), generator=g, device="cuda")]
+    return torch.where(at < 0.5, x, x | -2 ** 31).view(torch.float32)
+
+
+@pytest.mark.parametrize("kind", ["2^0", "2^-17", "2^-30", "2^-55", "2^-140", "2^4", "2^11", "2^20", "spread", "tiny", "zeros", "corners"])
+@pytest.mark.parametrize("n,k", [(70_001, 1), (300_007, 20), (4_000_003, 7)])
+def test_records(kind, n, k):
+    w = weights(kind, n)
+    key = w.view(torch.int32) & 0x7fffffff
+    ps = [1 + (i * 7919 * 131071) % n for i in range(k)]
+    ctx = S.shifter_create(0, torch.cuda.current_stream().cuda_stream)
+    try:
+        thr = torch.zeros(k * S.THRESHOLD_BYTES, dtype=torch.uint8, device="cuda")
+        S.shifter_global_threshold_static(ctx, w, n, ps, thr)
+        raw = thr.cpu().numpy().tobytes()
+        for i, p in enumerate(ps):
+            rec = S.Threshold.from_buffer_copy(raw, i * S.THRESHOLD_BYTES)
+            at = torch.nonzero(key == rec.t_key).flatten()
+            assert (rec.n_prune, rec.n_less, rec.n_equal) == (p, int((key < rec.t_key).sum()), at.numel())
+            assert 0 < p - rec.n_less <= rec.n_equal and rec.g_cut == int(at[p - rec.n_less - 1])
+            assert rec.cut == ((rec.t_key << 32) | rec.g_cut) + 1
+    finally:
+        S.shifter_destroy(ctx)
+
+
+@pytest.mark.parametrize("where", [0, 4095, 5 * 4096 + 17, 9 * 4096, 9 * 4096 + 99])       # the last tile has 100 weights
+@pytest.mark.parametrize("bits", [0x7f800001, -1])
+def test_nan(where, bits):
+    n = 9 * 4096 + 100
+    model = S.shifter_model_create([synth.TensorDesc(0, 1, n, 1, 1, 1, 1, 0, 1)], [], [synth.GroupDesc(n, 1), synth.GroupDesc(1, 1)])
+    w = torch.randn(n + 12, device="cuda")
+    w[7] = float("inf")
+    ctx = S.shifter_create(0, torch.cuda.current_stream().cuda_stream)
+    try:
+        S.shifter_set_select_path(ctx, 1)
+        thr = torch.zeros(S.THRESHOLD_BYTES, dtype=torch.uint8, device="cuda")
+        S.shifter_global_threshold(ctx, model, w, [n // 2], thr, sync=True)
+        w.view(torch.int32)[where] = bits
+        with pytest.raises(S.ShifterError) as e:
+            S.shifter_global_threshold(ctx, model, w, [n // 2], thr, sync=True)
+        assert e.value.code == S.SHIFTER_ERR_NONFINITE
+    finally:
+        S.shifter_model_destroy(model)
+        S.shifter_destroy(ctx)

@@ -47,9 +47,41 @@ int main() {
 """
 
 
+# The top bins cut all keys above zero into stretches in order, each within its window, and hold no more than 1/128 of a binade
+# between 2^-48 and 2^13.
+BINS = r"""
+#include <initializer_list>
+#include <stdio.h>
+#include "sel_plan.h"
+using namespace shifter;
+int main() {
+    int bad = 0;
+    for (uint32_t bin = 0; bin < SEL_BINS; ++bin) {
+        const uint32_t first = sel_bin_first_key(bin), end = bin + 1 < SEL_BINS ? sel_bin_first_key(bin + 1) : 0x80000000u;
+        const uint32_t width = sel_bin_width(bin);
+        bool ok = first < end && (uint64_t)(end - first) << 32 <= 1ull << width && width <= SEL_MAX_WIDTH;
+        for (uint32_t d : {0u, 1u, (end - first) / 2, end - first - 1}) ok = ok && sel_top_bin(first + d) == bin;
+        const uint32_t from = (127u - 48u) << 23, to = (127u + 13u) << 23;
+        if (first >= from && first < to && bin + 1 < SEL_BINS) ok = ok && end - first <= 1u << 16;
+        if (!ok && ++bad < 20) printf("bin %u: %08x to %08x, width %u\n", bin, first, end, width);
+    }
+    if (sel_top_bin((127u - 48u) << 23) == 0 || sel_top_bin(((127u + 13u) << 23) - (1u << 17)) == SEL_BINS - 1) { ++bad; printf("range\n"); }
+    return bad != 0;
+}
+"""
+
+
+def test_top_bins(tmp_path):
+    run(tmp_path, BINS)
+
+
 def test_stages_fit_the_state(tmp_path):
+    run(tmp_path, PROGRAM)
+
+
+def run(tmp_path, program):
     src = tmp_path / "plan.cpp"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     exe = str(tmp_path / "plan")
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, str(src), "-o", exe], check=True)
     r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
