@@ -233,7 +233,6 @@ extern "C" int shifter_model_create(const shifter_tensor_desc* tensors, uint32_t
     double weights = 0;               // of any descriptors, checked or not
     for (uint32_t i = 0; i < n_tensors; ++i)
         weights += (double)tensors[i].out_ch * tensors[i].in_ch * tensors[i].kh * tensors[i].kw;
-    const uint32_t rect_elems = weights <= RECT_FEW_WEIGHTS ? RECT_ELEMS / 4 : RECT_ELEMS;
     for (uint32_t i = 0; i < n_tensors; ++i) {
         const shifter_tensor_desc& t = tensors[i];
         if (!t.out_ch || !t.in_ch || !t.kh || !t.kw || !t.in_mult) return bad("zero-sized tensor dimension", i);
@@ -277,8 +276,7 @@ extern "C" int shifter_model_create(const shifter_tensor_desc* tensors, uint32_t
             if (d.kk > GATHER_CHUNK) m->rect_ok = false;
             d.chunk_ch = std::min(d.cin, std::max(1u, GATHER_CHUNK / d.kk));
             d.src_chunks = (d.cin + d.chunk_ch - 1) / d.chunk_ch;
-            const uint32_t wp = (d.chunk_ch * d.kk + 127u) & ~127u;
-            d.band_rows = std::max(1u, std::min(64u, rect_elems / std::max(wp, 128u)));
+            d.band_rows = rect_rows(weights, d.chunk_ch * d.kk);
             const uint64_t bands = (t.out_ch + d.band_rows - 1) / d.band_rows;
             if (m->rect_prefix.empty()) {
                 m->rect_prefix.push_back(0);

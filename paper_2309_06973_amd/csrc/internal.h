@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "rect_plan.h"
 #include "sel_plan.h"
 #include "shifter.h"
 
@@ -19,11 +20,6 @@ constexpr uint32_t GATHER_CHUNK = 1024;  // columns of a gather work unit (16 pe
 constexpr uint32_t GATHER_ROWS = 16;
 constexpr uint32_t SAMPLE_BINS = 16384;  // of the sample histogram (sample_bin)
 constexpr uint32_t PLAN_TICKET = 32;     // words of a variant's planning ticket: a line of its own
-constexpr uint32_t RECT_ELEMS = 8192;    // floats of a source rectangle staged in LDS by the portfolio rebuild
-// A network of up to this many weights is cut into rectangles of a quarter of that: whole ones are too few to keep 256
-// compute units busy.  us a step of ten variants, whole / quarters: 12 k weights 82.8 / 82.6, 61 k 91.7 / 87.2, 0.18 M 96.4 / 90.3,
-// 0.24 M 94.0 / 87.7, 0.4 M 100.1 / 91.3, 0.44 M 95.0 / 90.6; 0.93 M 100.0 / 102.5, 3.7 M 144 / 153, 8.1 M 197 / 219.
-constexpr double RECT_FEW_WEIGHTS = 524288.0;
 
 // Device-side view of one weight tensor.
 struct DevTensor {

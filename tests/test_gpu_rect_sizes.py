@@ -15,7 +15,8 @@ LIMIT = 524288
 
 @pytest.mark.parametrize("kernel,widths,small", [(3, [37, 91, 211, 131], True), (3, [60, 120, 200, 155], False), (1, [130, 515, 700], True),
                                                  (1, [130, 515, 1100], False), (5, [33, 71, 129, 63], True), (5, [33, 97, 161, 66], False),
-                                                 (3, [1, 700, 3, 900], True), (3, [2, 1300, 47], False)])
+                                                 (3, [1, 700, 3, 900], True), (3, [2, 1300, 47], False),
+                                                 (1, [1, 2500, 3, 1100, 17, 90], True), (1, [2, 3000, 7, 9000, 50], False)])
 def test_rebuild(kernel, widths, small):
     spec = synth.chain_spec(widths, k=kernel, in_ch=3)
     assert (spec.w_elems <= LIMIT) == small
