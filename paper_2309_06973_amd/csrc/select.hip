@@ -746,7 +746,7 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_stage_kernel(const SelArena a
     collect.leave(STAGE);
 }
 
-// The ranking of the lists, a block each, where the first stage certainly lists every rank.
+// The ranking of the lists, a block each, where there is one stage, which certainly lists every rank.
 __global__ __launch_bounds__(SEL_THREADS) void sel_final_kernel(const SelJob J, shifter_threshold* __restrict__ thr,
                                                                 shifter_threshold* host_rec, uint32_t* host_nan) {
     __shared__ RankShared<SEL_THREADS> sh;
@@ -881,7 +881,7 @@ void launch_select_tables(shifter_ctx* ctx, const SelectTables& tb, const float*
     }
     {
         ProfileScope p(ctx, K_SEL_FINAL);
-        if (stages <= before) sel_final_kernel<<<k, SEL_THREADS, 0, s>>>(job, d_thr, tb.host_rec, tb.host_nan);
+        if (stages == 1u) sel_final_kernel<<<k, SEL_THREADS, 0, s>>>(job, d_thr, tb.host_rec, tb.host_nan);
         else sel_rest_kernel<<<std::max(grid, k), SEL_THREADS, 0, s>>>(arena, job, before, grid, d_thr, tb.host_rec, tb.host_nan);
     }
 }
