@@ -1,6 +1,6 @@
-"""A portfolio step that the sampled ranking cannot decide, because most magnitudes are one: the pass that is made on the records as they
-are leaves levels alone, and what its rebuild wrote stays behind the ends of the variants made again.  That is compared with the
-oracle's rebuild by such levels: kernels of 1 to 25 weights, ragged tiles, tensors within one tile and over many, one of them not ranked."""
+"""A portfolio step that the sampled ranking cannot decide, because most magnitudes are one, and that is made again: its records and
+rebuilt variants, to the ends that the call reports, against the oracle.  Kernels of 1 to 25 weights, ragged tiles, tensors
+within one tile and over many, one of them not ranked, filters that no variant has and such of a weight or two."""
 import numpy as np
 import pytest
 import torch
@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("kernel,widths,ranked", [(3, [37, 91, 211, 131], True), (1, [130, 515, 700], True), (5, [33, 71, 129, 63], True),
                                                   (3, [60, 250, 301], False), (1, [1, 4100, 31, 700], True), (3, [260, 270, 300], True)])
 @pytest.mark.parametrize("by_sampling", [0.2, 0.0])
-def test_first_attempt(kernel, widths, ranked, by_sampling):
+def test_made_again(kernel, widths, ranked, by_sampling):
     spec = synth.chain_spec(widths, k=kernel, in_ch=3)
     if not ranked:
         spec.tensors[1].prunable = 0
@@ -37,31 +37,30 @@ def test_first_attempt(kernel, widths, ranked, by_sampling):
     ps = [zeros + small_n + int(tied * f) for f in (0.9, 0.3, 0.6)]
     if by_sampling:
         ps += [zeros + int(small_n * f) for f in (0.7, 0.4)]
-    K = len(ps)
     refs = O.prune_and_compact(w, v, spec.tensors, spec.vecs, spec.groups, ps)
-    found = [k >= 3 for k in range(K)]
-    kept = [refs[k].w_sparse if found[k] else w for k in range(K)]
-    count = sum((x != 0).astype(np.int32) for x in kept)      # variants that keep a weight; none keeps a zero
-    level = [count[t.offset:t.offset + t.numel].reshape(t.out_ch, -1).max(axis=1) for t in spec.tensors]
-    first = []
-    for k in range(K):
-        pos = sum(p < ps[k] for p in ps)
-        plan = O.propagate_groups(spec.tensors, spec.groups, [(x > pos).astype(np.uint8) for x in level])
-        first.append(O.compact(kept[k], v, spec.tensors, spec.vecs, plan).w)
     pl = Pipeline(spec, w, v)
     try:
-        pl.enable_batch(K)
-        pl.b_w_out.fill_(7.0)
-        _, (rc, ot, ov, ew, ev) = pl.step(ps)
+        pl.enable_batch(len(ps))
+        for x in (pl.b_w_out, pl.b_vecs_out, pl.b_w_sparse):
+            x.fill_(7.0)
+        for x in (pl.b_mask, pl.b_out_alive, pl.b_in_alive):
+            x.fill_(7)
+        recs, (rc, ot, ov, ew, ev) = pl.step(ps)
         torch.cuda.synchronize()
         assert S.shifter_get_select_stats(pl.ctx)["path"] == 2
-        compared = 0
+        bits = lambda x: np.ascontiguousarray(x).view(np.uint32)
+        out_alive, in_alive = pl.b_out_alive.cpu().numpy(), pl.b_in_alive.cpu().numpy()
+        so, si = out_alive.size // len(ps), in_alive.size // len(ps)
+        a = np.abs(O.gather_prunable(w, spec.tensors))
         for k, ref in enumerate(refs):
-            assert ew[k] == ref.compacted.w.size
-            got = pl.b_w_out[k * pl.cap_w:k * pl.cap_w + max(ew[k], first[k].size)].cpu().numpy().view(np.uint32)
-            assert np.array_equal(got[:ew[k]], ref.compacted.w.view(np.uint32))
-            assert np.array_equal(got[ew[k]:], first[k][ew[k]:].view(np.uint32))
-            compared += got.size - ew[k]
-        assert compared > 0
+            t = a[ref.sel.thr_index]
+            assert (recs[k].g_cut, recs[k].n_less, recs[k].n_equal) == (ref.sel.thr_index, int((a < t).sum()), int((a == t).sum()))
+            assert np.array_equal(pl.b_mask[k * pl.m_stride:k * pl.m_stride + n].cpu().numpy(), ref.mask)
+            assert (ew[k], ev[k]) == (ref.compacted.w.size, ref.compacted.v.size)
+            assert np.array_equal(bits(pl.b_w_out[k * pl.cap_w:k * pl.cap_w + ew[k]].cpu().numpy()), bits(ref.compacted.w))
+            assert np.array_equal(bits(pl.b_vecs_out[k * pl.cap_v:k * pl.cap_v + ev[k]].cpu().numpy()), bits(ref.compacted.v))
+            assert np.array_equal(bits(pl.b_w_sparse[k * pl.w_stride:k * pl.w_stride + spec.w_elems].cpu().numpy()), bits(ref.w_sparse))
+            assert np.array_equal(out_alive[k * so:(k + 1) * so], np.concatenate(ref.out_alive))
+            assert np.array_equal(in_alive[k * si:(k + 1) * si], np.concatenate(ref.in_alive))
     finally:
         pl.close()
