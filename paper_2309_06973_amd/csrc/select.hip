@@ -3,7 +3,7 @@
 // on the host, for any number of prune counts, any distribution and any number of ties.
 //
 //   top     one read of the arena: a histogram of all keys on 16384 bins (sel_plan.h: 1/512 of a binade where the
-//           thresholds of networks lie, 1/128 around), zeros counted apart;
+//           thresholds of networks lie, 1/64 below and 1/128 above), zeros counted apart;
 //   stage   every rank has a window of composites (key << 32 | g) that holds its pair and the
 //           number of weights in it.  A stage reads the arena once: windows of no more pairs
 //           than are good in a list (sel_plan.h) are written out as lists, the others are split by
@@ -23,14 +23,15 @@
 // one counter, windows that follow each other in one bin are found by halving.  us a call, flat
 // run, bins of 1/256 of a binade from 2^-50 to 2^14 and a launch for each stage, used or not / now:
 //   counts of weights     normal        half of them zero   all equal       30 levels a sigma   half precision   times 2^-30   60 % 10^-12
-//    1 of   1 M           32 / 24       33 / 24             78 / 71         49 / 38             41 / 31          33 / 26       34 / 25
-//   10 of   1 M           34 / 25       60 / 57             81 / 79         55 / 44             43 / 33          35 / 29       35 / 28
-//    1 of  14.7 M         56 / 42       55 / 43             178 / 182       113 / 109           76 / 54          56 / 53       59 / 47
-//   10 of  14.7 M         64 / 46       137 / 131           208 / 208       145 / 150           96 / 63          64 / 66       61 / 58
-//    1 of 100 M           249 / 160     246 / 160           850 / 857       399 / 401           273 / 207        245 / 249     198 / 167
-//   10 of 100 M           252 / 247     745 / 722           1214 / 1208     605 / 604           298 / 307        252 / 278     276 / 273
+//    1 of   1 M           32 / 24       33 / 24             78 / 71         49 / 38             41 / 31          33 / 26       34 / 26
+//   10 of   1 M           34 / 26       60 / 57             81 / 79         55 / 45             43 / 33          35 / 31       35 / 28
+//    1 of  14.7 M         56 / 42       55 / 43             178 / 183       113 / 109           76 / 54          56 / 62       59 / 45
+//   10 of  14.7 M         64 / 46       137 / 132           208 / 208       145 / 152           96 / 62          64 / 99       61 / 63
+//    1 of 100 M           249 / 159     246 / 159           850 / 841       399 / 400           273 / 206        245 / 260     198 / 170
+//   10 of 100 M           252 / 246     745 / 721           1214 / 1203     605 / 605           298 / 306        252 / 306     276 / 284
 // (With all bins 1/512 of a binade, which left out what lies below 2^-25 and above 2^7: the first columns 1 % less, the last two
-// 55, 101, 165, 217, 760, 1050 and 29, 72, 59, 203, 255, 960.)
+// 55, 101, 165, 217, 760, 1050 and 29, 72, 59, 203, 255, 960.  With the fine ones from 2^-19 to 2^3 and 1/128 below, the last but
+// one 26, 29, 53, 66, 249, 278, but 2 % more on weights of many magnitudes, of which more lie in no fine bin.)
 // (The radix select of 11 + 10 + 10 bits before all this: 85 us for 1 of 1 M, 418 for 10 of 14.7 M.)
 #include <algorithm>
 
@@ -223,8 +224,8 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(const SelArena are
     RunCount run;
     // Counters by their distance from the first fine one.  A zero's has two upper bits set, which are shifted out of its address and
     // tell it from the keys that are in no fine bin: as signed numbers those alone are SEL_FINE_BINS or more.  One look at the
-    // largest of a lane's sixteen finds them, and the wavefront then takes all of its bins from sel_top_bin.  (That for
-    // every weight: 14.7 M 14.7 -> 15.9 us.)
+    // largest of a lane's sixteen finds them, and the wavefront then takes the bins of the quads they are in from sel_top_bin.
+    // (That for every weight: 14.7 M 14.7 -> 15.9 us.)
     const uint32_t zero_at = (3u << 30) + SEL_BINS + lane - SEL_BIN_FINE;
     auto counter = [&](uint32_t at) { return reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(h) + ((at << 2) + 4u * SEL_BIN_FINE)); };
     auto any_bin = [&](uint32_t key) {
@@ -256,6 +257,8 @@ __global__ __launch_bounds__(SEL_THREADS) void sel_top_kernel(const SelArena are
         if (__builtin_expect(__ballot(most >= (int32_t)SEL_FINE_BINS) != 0ull, 0)) {
 #pragma unroll
             for (uint32_t u = 0; u < SEL_QUADS; ++u) {
+                const int32_t of_quad = max(max((int32_t)at[u][0], (int32_t)at[u][1]), max((int32_t)at[u][2], (int32_t)at[u][3]));
+                if (__ballot(of_quad >= (int32_t)SEL_FINE_BINS) == 0ull) continue;
                 const uint32_t x[4] = {walk.v[u].x, walk.v[u].y, walk.v[u].z, walk.v[u].w};
 #pragma unroll
                 for (uint32_t q = 0; q < 4u; ++q) at[u][q] = any_bin(x[q] & 0x7fffffffu);
@@ -494,7 +497,7 @@ __device__ __forceinline__ void sel_windows(const SelJob& J, SelShared& S, uint3
             const uint32_t mode = W.cnt <= (stage < stages ? min(list_cap, SEL_LIST_GOOD) : list_cap) ? SEL_LISTED : SEL_SPLIT;
             S.win[lane].leader = leader;
             S.win[lane].mode = mode;
-            // more weights than any spread-out distribution has in a bin (normal ones 0.38 % in a wide one), or one key
+            // more weights than any spread-out distribution has in a bin (normal ones 0.76 % in a wide one), or one key
             const bool ties = W.width <= 32u || W.cnt > (n_weights >> 7);
             S.win[lane].stage = ties ? stage : 0u;
             if (ties) S.ties = 1;
@@ -538,7 +541,7 @@ struct SelCollect {
     KeyRange keys;
     __device__ __forceinline__ SelCollect(const SelJob& job, SelShared& shared) : J(job), S(shared) {}
     __device__ __forceinline__ void part(const SelArena& arena, uint32_t part, uint32_t parts, bool down) {
-        if (uniform_u32(S.wide)) part_of<true>(arena, part, parts, down); else part_of<false>(arena, part, parts, down);
+        if (__builtin_expect(uniform_u32(S.wide) != 0u, 0)) part_of<true>(arena, part, parts, down); else part_of<false>(arena, part, parts, down);
     }
     template <bool WIDE>
     __device__ __forceinline__ void part_of(const SelArena& arena, uint32_t part, uint32_t parts, bool down);

@@ -47,8 +47,8 @@ int main() {
 """
 
 
-# The top bins cut all keys above zero into stretches in order, each within its window, and hold no more than 1/128 of a binade
-# between 2^-48 and 2^13.
+# The top bins cut all keys above zero into stretches in order, each within its window, and hold no more than 1/64 of a binade
+# from 2^-49 on, 1/512 from 2^-24 on, 1/128 from 2^2 to 2^13.
 BINS = r"""
 #include <initializer_list>
 #include <stdio.h>
@@ -61,11 +61,12 @@ int main() {
         const uint32_t width = sel_bin_width(bin);
         bool ok = first < end && (uint64_t)(end - first) << 32 <= 1ull << width && width <= SEL_MAX_WIDTH;
         for (uint32_t d : {0u, 1u, (end - first) / 2, end - first - 1}) ok = ok && sel_top_bin(first + d) == bin;
-        const uint32_t from = (127u - 48u) << 23, to = (127u + 13u) << 23;
-        if (first >= from && first < to && bin + 1 < SEL_BINS) ok = ok && end - first <= 1u << 16;
+        auto power = [](int e) { return (uint32_t)(127 + e) << 23; };
+        const uint32_t most = first < power(-49) || bin + 1 == SEL_BINS ? 0x40000000u : first < power(-24) ? 1u << 17 : first < power(2) ? 1u << 14 : 1u << 16;
+        ok = ok && end - first <= most;
         if (!ok && ++bad < 20) printf("bin %u: %08x to %08x, width %u\n", bin, first, end, width);
     }
-    if (sel_top_bin((127u - 48u) << 23) == 0 || sel_top_bin(((127u + 13u) << 23) - (1u << 17)) == SEL_BINS - 1) { ++bad; printf("range\n"); }
+    if (sel_top_bin((127u - 49u) << 23) == 0 || sel_top_bin(((127u + 13u) << 23) - (1u << 17)) == SEL_BINS - 1) { ++bad; printf("range\n"); }
     return bad != 0;
 }
 """
