@@ -68,8 +68,8 @@ struct SelWindow {
     uint32_t mode;             // of this stage: split by a histogram, listed, or nothing to do
     uint32_t stage;            // whose key_lo, key_hi say what keys it holds; 0: not known
 };
-constexpr uint32_t SEL_POLLS = 1u << 22;       // looks at them: seconds, far beyond any stage
 constexpr uint32_t SEL_GO = 16, SEL_GO_WORDS = 32;   // lines that say that a stage is over
+constexpr uint32_t SEL_POLLS = 1u << 22;             // looks at one before a block gives up: seconds, far beyond any stage
 struct SelState {
     SelWindow win[SEL_STAGES + 1][MAXK];   // by stage; the first is unused
     SelWindow fin[MAXK];                   // the windows that were listed
