@@ -14,28 +14,28 @@ constexpr uint32_t SEL_MAX_WIDTH = 62;    // of a window: 2^30 keys of the bins 
 // is one.
 constexpr uint32_t SEL_LIST_GOOD = 1u << 16;
 
-// The top bins: 1/512 of a binade from 2^-24 to 2^2, where nearly all thresholds of networks lie, 1/64 below down to 2^-50 and 1/128
-// above up to 2^13; the keys below share the first bin with its own, those above the last one.  Against 1/256 from 2^-50 to 2^14
+// The top bins: 1/512 of a binade from 2^-24 to 2^4, where nearly all thresholds of networks lie, 1/64 below down to 2^-47 and above
+// up to 2^13; the keys below share the first bin with its own, those above the last one.  Against 1/256 from 2^-50 to 2^14
 // lists are half as long, and twice as many bins are added up by the blocks: us a call 10 counts of 14.7 M normal weights 51.6 ->
-// 45.8, half precision 83 -> 62, one of 100 M 225 -> 159, but of 14.7 M weights of many magnitudes 45.8 -> 47.4 (one count 34.2
-// -> 38.5), where nearly all bins hold some.
-constexpr uint32_t SEL_FINE_SHIFT = 14, SEL_BELOW_SHIFT = 17, SEL_ABOVE_SHIFT = 16;
-constexpr uint32_t SEL_KEY_FIRST = (127u - 50u) << 23, SEL_KEY_FINE = (127u - 24u) << 23, SEL_KEY_ABOVE = (127u + 2u) << 23,
+// 45.8, half precision 83 -> 62, one of 100 M 225 -> 159, but of 14.7 M weights of many magnitudes 45.8 -> 47.6 (one count 34.2
+// -> 38.2), where nearly all bins hold some.
+constexpr uint32_t SEL_FINE_SHIFT = 14, SEL_WIDE_SHIFT = 17;
+constexpr uint32_t SEL_KEY_FIRST = (127u - 47u) << 23, SEL_KEY_FINE = (127u - 24u) << 23, SEL_KEY_ABOVE = (127u + 4u) << 23,
                    SEL_KEY_END = (127u + 13u) << 23;
-constexpr uint32_t SEL_BIN_FINE = (SEL_KEY_FINE - SEL_KEY_FIRST) >> SEL_BELOW_SHIFT;           // first fine bin
+constexpr uint32_t SEL_BIN_FINE = (SEL_KEY_FINE - SEL_KEY_FIRST) >> SEL_WIDE_SHIFT;           // first fine bin
 constexpr uint32_t SEL_FINE_BINS = (SEL_KEY_ABOVE - SEL_KEY_FINE) >> SEL_FINE_SHIFT;
 constexpr uint32_t SEL_BIN_ABOVE = SEL_BIN_FINE + SEL_FINE_BINS;
-static_assert(SEL_BIN_ABOVE + ((SEL_KEY_END - SEL_KEY_ABOVE) >> SEL_ABOVE_SHIFT) == SEL_BINS, "all bins are used");
+static_assert(SEL_BIN_ABOVE + ((SEL_KEY_END - SEL_KEY_ABOVE) >> SEL_WIDE_SHIFT) == SEL_BINS, "all bins are used");
 // A key's bin among the fine ones; SEL_FINE_BINS or more where it is in none.
 constexpr uint32_t sel_fine_bin(uint32_t key) { return (key - SEL_KEY_FINE) >> SEL_FINE_SHIFT; }
 // Any key's bin: of three lines through two corners, of which the fine one is the steepest, the middle one.  No branches.
 constexpr uint32_t sel_top_bin(uint32_t key) {
     constexpr uint32_t first = SEL_KEY_FIRST >> SEL_FINE_SHIFT, last = (SEL_KEY_END >> SEL_FINE_SHIFT) - 1u;
     constexpr uint32_t zero = (SEL_KEY_FINE >> SEL_FINE_SHIFT) - SEL_BIN_FINE;
-    constexpr uint32_t below_0 = (SEL_KEY_FINE >> SEL_FINE_SHIFT) - (SEL_KEY_FINE >> SEL_BELOW_SHIFT);
-    constexpr uint32_t above_0 = (SEL_KEY_ABOVE >> SEL_FINE_SHIFT) - (SEL_KEY_ABOVE >> SEL_ABOVE_SHIFT);
+    constexpr uint32_t below_0 = (SEL_KEY_FINE >> SEL_FINE_SHIFT) - (SEL_KEY_FINE >> SEL_WIDE_SHIFT);
+    constexpr uint32_t above_0 = (SEL_KEY_ABOVE >> SEL_FINE_SHIFT) - (SEL_KEY_ABOVE >> SEL_WIDE_SHIFT);
     const uint32_t raised = (key >> SEL_FINE_SHIFT) < first ? first : key >> SEL_FINE_SHIFT, fine = raised < last ? raised : last;
-    const uint32_t below = (fine >> (SEL_BELOW_SHIFT - SEL_FINE_SHIFT)) + below_0, above = (fine >> (SEL_ABOVE_SHIFT - SEL_FINE_SHIFT)) + above_0;
+    const uint32_t wide = fine >> (SEL_WIDE_SHIFT - SEL_FINE_SHIFT), below = wide + below_0, above = wide + above_0;
     const uint32_t low = fine > below ? fine : below;
     return (low < above ? low : above) - zero;
 }
@@ -43,14 +43,14 @@ constexpr uint32_t sel_top_bin(uint32_t key) {
 // keys.
 constexpr uint32_t sel_bin_first_key(uint32_t bin) {
     return bin == 0u ? 1u
-         : bin < SEL_BIN_FINE ? SEL_KEY_FIRST + (bin << SEL_BELOW_SHIFT)
+         : bin < SEL_BIN_FINE ? SEL_KEY_FIRST + (bin << SEL_WIDE_SHIFT)
          : bin < SEL_BIN_ABOVE ? SEL_KEY_FINE + ((bin - SEL_BIN_FINE) << SEL_FINE_SHIFT)
-                               : SEL_KEY_ABOVE + ((bin - SEL_BIN_ABOVE) << SEL_ABOVE_SHIFT);
+                               : SEL_KEY_ABOVE + ((bin - SEL_BIN_ABOVE) << SEL_WIDE_SHIFT);
 }
 constexpr bool sel_bin_is_fine(uint32_t bin) { return bin >= SEL_BIN_FINE && bin < SEL_BIN_ABOVE; }
 constexpr uint32_t sel_bin_width(uint32_t bin) {
     return bin == 0u || bin == SEL_BINS - 1u ? SEL_MAX_WIDTH
-         : 32u + (bin < SEL_BIN_FINE ? SEL_BELOW_SHIFT : bin < SEL_BIN_ABOVE ? SEL_FINE_SHIFT : SEL_ABOVE_SHIFT);
+         : 32u + (sel_bin_is_fine(bin) ? SEL_FINE_SHIFT : SEL_WIDE_SHIFT);
 }
 
 // log2 of the bins of one window's histogram: what k of them may share SEL_BINS counters.

@@ -3,7 +3,7 @@
 // on the host, for any number of prune counts, any distribution and any number of ties.
 //
 //   top     one read of the arena: a histogram of all keys on 16384 bins (sel_plan.h: 1/512 of a binade where the
-//           thresholds of networks lie, 1/64 below and 1/128 above), zeros counted apart;
+//           thresholds of networks lie, 1/64 around), zeros counted apart;
 //   stage   every rank has a window of composites (key << 32 | g) that holds its pair and the
 //           number of weights in it.  A stage reads the arena once: windows of no more pairs
 //           than are good in a list (sel_plan.h) are written out as lists, the others are split by
@@ -23,14 +23,14 @@
 // one counter, windows that follow each other in one bin are found by halving.  us a call, flat
 // run, bins of 1/256 of a binade from 2^-50 to 2^14 and a launch for each stage, used or not / now:
 //   counts of weights     normal        half of them zero   all equal       30 levels a sigma   half precision   times 2^-30   60 % 10^-12
-//    1 of   1 M           32 / 24       33 / 24             78 / 71         49 / 38             41 / 31          33 / 26       34 / 26
-//   10 of   1 M           34 / 26       60 / 57             81 / 79         55 / 45             43 / 33          35 / 31       35 / 28
-//    1 of  14.7 M         56 / 42       55 / 43             178 / 183       113 / 109           76 / 54          56 / 62       59 / 45
-//   10 of  14.7 M         64 / 46       137 / 132           208 / 208       145 / 152           96 / 62          64 / 99       61 / 63
-//    1 of 100 M           249 / 159     246 / 159           850 / 841       399 / 400           273 / 206        245 / 260     198 / 170
-//   10 of 100 M           252 / 246     745 / 721           1214 / 1203     605 / 605           298 / 306        252 / 306     276 / 284
+//    1 of   1 M           32 / 24       33 / 24             78 / 71         49 / 38             41 / 31          33 / 27       34 / 25
+//   10 of   1 M           34 / 25       60 / 57             81 / 79         55 / 45             43 / 33          35 / 31       35 / 28
+//    1 of  14.7 M         56 / 42       55 / 43             178 / 182       113 / 108           76 / 54          56 / 61       59 / 45
+//   10 of  14.7 M         64 / 46       137 / 131           208 / 208       145 / 150           96 / 62          64 / 98       61 / 63
+//    1 of 100 M           249 / 161     246 / 160           850 / 853       399 / 402           273 / 207        245 / 255     198 / 167
+//   10 of 100 M           252 / 248     745 / 722           1214 / 1210     605 / 606           298 / 308        252 / 298     276 / 277
 // (With all bins 1/512 of a binade, which left out what lies below 2^-25 and above 2^7: the first columns 1 % less, the last two
-// 55, 101, 165, 217, 760, 1050 and 29, 72, 59, 203, 255, 960.  With the fine ones from 2^-19 to 2^3 and 1/128 below, the last but
+// 55, 101, 165, 217, 760, 1050 and 29, 72, 59, 203, 255, 960.  With the fine ones from 2^-19 to 2^3 and 1/128 around, the last but
 // one 26, 29, 53, 66, 249, 278, but 2 % more on weights of many magnitudes, of which more lie in no fine bin.)
 // (The radix select of 11 + 10 + 10 bits before all this: 85 us for 1 of 1 M, 418 for 10 of 14.7 M.)
 #include <algorithm>
@@ -401,8 +401,10 @@ __device__ __forceinline__ void sel_windows(const SelJob& J, SelShared& S, uint3
                     if (base < r && r <= base + c[i]) { bin = a * 16u + i; cnt = c[i]; below = base; }
                     base += c[i];
                 }
-                W.c_lo = (uint64_t)sel_bin_first_key(bin) << 32;
-                W.width = sel_bin_width(bin);
+                uint32_t first = SEL_KEY_FINE + ((bin - SEL_BIN_FINE) << SEL_FINE_SHIFT), width = 32u + SEL_FINE_SHIFT;
+                if (!sel_bin_is_fine(bin)) { first = sel_bin_first_key(bin); width = sel_bin_width(bin); }
+                W.c_lo = (uint64_t)first << 32;
+                W.width = width;
                 W.r = r - below;
                 W.less = below;
                 W.cnt = cnt;
@@ -485,7 +487,9 @@ __device__ __forceinline__ void sel_windows(const SelJob& J, SelShared& S, uint3
         const unsigned long long open_mask = __ballot(opens);
         const unsigned long long upto = open_mask & (~0ull >> (63u - lane));
         const uint32_t leader = upto ? 63u - (uint32_t)__clzll(upto) : lane;
-        const uint32_t top = top_bin((uint32_t)(W.c_lo >> 32));
+        const uint32_t key = (uint32_t)(W.c_lo >> 32), fine = sel_fine_bin(key);
+        uint32_t top = SEL_BIN_FINE + fine;
+        if (live && fine >= SEL_FINE_BINS) top = top_bin(key);
         const unsigned long long before = open_mask & ((1ull << lane) - 1ull);
         const uint32_t prev_top = __shfl(top, before ? 63 - __clzll((long long)before) : 0, 64);
         const bool first = opens && !(before && prev_top == top);
@@ -501,7 +505,7 @@ __device__ __forceinline__ void sel_windows(const SelJob& J, SelShared& S, uint3
             const bool ties = W.width <= 32u || W.cnt > (n_weights >> 7);
             S.win[lane].stage = ties ? stage : 0u;
             if (ties) S.ties = 1;
-            if ((W.c_lo >> 32) != 0 && !sel_bin_is_fine(top)) S.wide = 1;
+            if (key != 0u && fine >= SEL_FINE_BINS) S.wide = 1;
             if (opens) {
                 const uint32_t at = (uint32_t)__popcll(before);
                 S.lo[at] = W.c_lo;

@@ -48,7 +48,7 @@ int main() {
 
 
 # The top bins cut all keys above zero into stretches in order, each within its window, and hold no more than 1/64 of a binade
-# from 2^-49 on, 1/512 from 2^-24 on, 1/128 from 2^2 to 2^13.
+# from 2^-46 to 2^13, 1/512 from 2^-24 to 2^4.
 BINS = r"""
 #include <initializer_list>
 #include <stdio.h>
@@ -62,11 +62,11 @@ int main() {
         bool ok = first < end && (uint64_t)(end - first) << 32 <= 1ull << width && width <= SEL_MAX_WIDTH;
         for (uint32_t d : {0u, 1u, (end - first) / 2, end - first - 1}) ok = ok && sel_top_bin(first + d) == bin;
         auto power = [](int e) { return (uint32_t)(127 + e) << 23; };
-        const uint32_t most = first < power(-49) || bin + 1 == SEL_BINS ? 0x40000000u : first < power(-24) ? 1u << 17 : first < power(2) ? 1u << 14 : 1u << 16;
+        const uint32_t most = first < power(-46) || bin + 1 == SEL_BINS ? 0x40000000u : first < power(-24) || first >= power(4) ? 1u << 17 : 1u << 14;
         ok = ok && end - first <= most;
         if (!ok && ++bad < 20) printf("bin %u: %08x to %08x, width %u\n", bin, first, end, width);
     }
-    if (sel_top_bin((127u - 49u) << 23) == 0 || sel_top_bin(((127u + 13u) << 23) - (1u << 17)) == SEL_BINS - 1) { ++bad; printf("range\n"); }
+    if (sel_top_bin((127u - 46u) << 23) == 0 || sel_top_bin(((127u + 13u) << 23) - (1u << 18)) == SEL_BINS - 1) { ++bad; printf("range\n"); }
     return bad != 0;
 }
 """
