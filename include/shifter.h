@@ -458,7 +458,8 @@ int shifter_fold_bn(shifter_ctx* ctx, const shifter_model* model,
  *                        outputs may be NULL)
  * shifter_deflate
  *   d_in, n_bytes        device, 16-byte aligned input (may be NULL when n_bytes = 0)
- *   d_work, work_bytes   device, 256-byte aligned scratch of at least the layout's size
+ *   d_work, work_bytes   device, 256-byte aligned scratch of at least the layout's size (a
+ *                        recorded call uses it at every replay)
  *   d_stream, stream_cap device, 16-byte aligned; capacity in bytes
  *   d_seg_off            device, n_chunks + 1 uint64; the last entry is the stream's size
  *   d_sub_bits           device, n_chunks * (CHUNK / SUB) uint16: the per-sub-chunk side
